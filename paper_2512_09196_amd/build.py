@@ -15,8 +15,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtf_gfx950.so")
-SOURCES = ["tf_gemm_lds.hip", "tf_gemm_stream.hip", "tf_vecmat.hip", "tf_sin.hip", "tf_gemm_simple.hip", "tf_api.hip", "tf_loop.cpp"]
-HEADERS = ["tf_internal.h", "tf_device.h", "tf_loop.h"]
+SOURCES = ["tf_gemm_lds.hip", "tf_gemm_lds_ragged.hip", "tf_gemm_stream.hip", "tf_vecmat.hip", "tf_sin.hip", "tf_gemm_simple.hip", "tf_api.hip", "tf_loop.cpp"]
+HEADERS = ["tf_gemm_lds.h", "tf_internal.h", "tf_device.h", "tf_loop.h"]
 
 # -packed-fp32-ops off: hipcc must not form v_pk_*_f32 from scalar float code on this target.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"),
@@ -56,7 +56,7 @@ def build_library(force: bool = True) -> str:
     if not force and up_to_date():
         return LIB
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs

@@ -30,6 +30,12 @@ tf_status fail(tf_status st, const char* fmt, ...) {
     if (e_ != hipSuccess) return fail(TF_E_LAUNCH, "%s: %s", #call, hipGetErrorString(e_)); \
   } while (0)
 
+// A K that is no multiple of the K tile, on the kernels that stage directly: offered from four K tiles of 64 on, and
+// below for large outputs. What is left out is start-up whichever way the tiles are staged (measured, through
+// registers / directly: 8 x 8192 x 200 7.5 / 7.9 us, 300 x 512 x 104 7.6 / 7.8, 1000 x 1000 x 200 8.5 / 8.4; but
+// 4096 x 4096 x 200 25.7 / 15.9, 4096 x 10000 x 248 72.3 / 45.1).
+bool ragged_k_direct(long M, long N, long K) { return K >= 256 || (K >= 64 && M * N >= (1L << 20)); }
+
 constexpr size_t kStatusBytes = 256;   // tail of the counter area of a workspace: the status word
 
 struct VariantImpl {
@@ -134,7 +140,7 @@ void build_bgemm_family(tf_problem* p) {
   for (int pass = 0; pass < 2; ++pass) {          // 0: transposed staging, 1: separate transposing pass
     for (int i = 0; i < tf::lds_kernel_count(); ++i) {
       const tf::LdsKernelInfo& k = tab[i];
-      if (!k.direct_to_lds || k.a_bypass_lds || k.waves_k != 1 || k.stream_k || k.trans_b || k.bk != 64 || k.bn_tail) continue;
+      if (!k.direct_to_lds || k.a_bypass_lds || k.waves_k != 1 || k.stream_k || k.trans_b || k.bk != 64 || k.bn_tail || k.k_tail) continue;
       if (pass == 0 && !k.trans_a) continue;
       // the persistent kernel: whole tiles, enough K steps to keep its ring busy across a tile's output
       if (k.persistent && (pass == 1 || d.M % k.bm || d.N % k.bn || d.K / 64 < k.stages - 1)) continue;
@@ -248,13 +254,16 @@ void build_family(tf_problem* p) {
     if (pass == 0 && (k.trans_b != 0) != tb) continue;
     if (pass == 1) {
       // a few representative kernels behind the transposing pass
-      const bool pick = !k.trans_b && k.direct_to_lds && !k.a_bypass_lds && !k.stream_k && k.waves_k == 1 && k.bk == 64 && !k.bn_tail &&
+      const bool pick = !k.trans_b && !k.k_tail && k.direct_to_lds && !k.a_bypass_lds && !k.stream_k && k.waves_k == 1 && k.bk == 64 && !k.bn_tail &&
                         ((k.bm == 256 && k.bn == 256) || (k.bm == 128 && k.bn == 128 && k.threads == 512 && k.stages == 3) ||
                          (k.bm == 64 && k.bn == 64) || (k.bm == 32 && k.bn == 64 && k.stages == 4));
       if (!pick) continue;
     }
     const long ktiles = cdivl(d.K, k.bk);
-    if (k.direct_to_lds && d.K % k.bk != 0) continue;      // no zero fill on the direct path
+    // direct staging copies whole K tiles; a K that is no multiple of them has instances of its own
+    const bool k_ragged = d.K % k.bk != 0;
+    if (k.direct_to_lds && k_ragged != (k.k_tail != 0)) continue;
+    if (k.k_tail && !ragged_k_direct(d.M, d.N, d.K)) continue;
     if (k.bn_tail > 0) {
       // a lighter last round: the row panels must take a whole number of CUs each, the leading columns make whole
       // rounds of wide tiles, and what remains is between (bn_tail - 64) and bn_tail columns per CU of a row panel
@@ -327,7 +336,7 @@ void build_family(tf_problem* p) {
         if (s == 1 && fused == 0) continue;
         if (s > 1 && fused != 0 && !k.fused_ok) continue;
         // without split-K also with the K order rotated by XCD (worth it for some shapes, not for others)
-        const int rotations = (s == 1 && k.direct_to_lds && ktiles * k.bk >= 512) ? 2 : 1;
+        const int rotations = (s == 1 && k.direct_to_lds && ktiles * k.bk >= 512 && !k_ragged) ? 2 : 1;
         for (int kr = 0; kr < rotations; ++kr)
         // one row of tiles (a skinny problem, every byte of B read by one work-group only): also with the tiles dealt
         // round-robin over the XCDs instead of a contiguous run each, so that every row of B is pulled through all

@@ -508,3 +508,27 @@ def test_seeded_random_shapes_every_variant_both_layouts():
         total += len(ran)
     print("variants checked:", total, flush=True)
     assert total >= 200
+
+
+@pytest.mark.parametrize("b_as_nk", [0, 1])
+@pytest.mark.parametrize("shape", [(130, 264, 264), (40, 136, 1016), (300, 520, 1864), (16, 512, 2120), (257, 264, 4136)])
+def test_ragged_k_staged_directly(shape, b_as_nk):
+    """K no multiple of the K tile on the kernels that stage directly: the last tile overlaps the one before, whose
+    part of it must count once and, being infinite where the second run says so, must not turn into NaN."""
+    M, N, K = shape
+    A, B, bias = wl.make_custom(M, N, K, seed=700 + K)
+    Bd = np.ascontiguousarray(B.T) if b_as_nk else B
+    direct = lambda v: v.kind == tf.TF_KIND_MFMA_LDS and v.direct_to_lds and K % v.bk
+    ran = check_all_variants(M, N, K, A, Bd, bias, lda=K + 16, ldb=(K if b_as_nk else N) + 8, only=direct, trans_b=b_as_nk)
+    assert len(ran) >= 6
+    # an infinity in the overlap (the k right before the last whole multiple of 64): +-inf results, never NaN
+    A2 = A.copy()
+    A2[0, K // 64 * 64 - 1] = 0x7F80
+    z = wl.bf16_bits_to_f32(A2).astype(np.float64) @ wl.bf16_bits_to_f32(B).astype(np.float64)
+    dA, dB, dbias = gu.to_dev(A2), gu.to_dev(Bd), gu.to_dev(bias)
+    out = gu.OutBuf(M, N, f32=True)
+    with tf.Problem(M, N, K, epi=tf.TF_EPI_NONE_F32, trans_b=b_as_nk) as prob:
+        for v in [v for v in prob.variants() if direct(v)]:
+            print("inf", shape, b_as_nk, v.name.decode(), flush=True)
+            got, intact, _ = gu.run_variant(prob, v.id, dA, dB, dbias, out)
+            assert intact and np.array_equal(got[0], z[0]), v.name.decode()      # row 0: infinities of B's sign
