@@ -74,6 +74,8 @@ typedef enum {
                                per row group)                                                          */
   TF_KIND_BGEMM_TN_NAIVE = 6,/* TF_OP_BATCHED_GEMM_TN baseline: one thread per output element (its tile kernels
                                are TF_KIND_MFMA_LDS, see trans_a)                                       */
+  TF_KIND_MFMA_ANY = 8,      /* rows of A, B and Y at any two-byte address (where the tile kernels' 16-byte pieces do
+                               not fit): bm x bn tiles, the waves_k waves of a work-group share K           */
   TF_KIND_SIN = 7            /* TF_OP_ELEMENTWISE_SIN: one arithmetic, many launch shapes. Descriptor fields: threads,
                                bn = elements per work-group and pass (the paper's BLOCK_SIZE; variant 0 has 4),
                                bk = consecutive elements per thread, stages = passes per work-group,
@@ -147,7 +149,7 @@ typedef struct {
                               only on a device whose work-group placement has been probed, see tf_variant_run);
                               1 = the last slice to arrive reduces inside the GEMM kernel (one launch,
                               arrival counters); 0 = a second kernel sums the slices and applies the epilogue */
-  int32_t direct_to_lds;   /* 1: global_load_lds staging; 0: via registers (allows a ragged K tail) */
+  int32_t direct_to_lds;   /* 1: global_load_lds staging; 0: via registers (zero-fills a ragged K tail) */
   int32_t a_bypass_lds;    /* 1: A fragments are loaded from memory straight into MFMA operand registers, only B is
                               staged in LDS (one wave column per work-group) */
   int32_t trans_a;         /* TF_OP_BATCHED_GEMM_TN, tile kernels: 1 = the A tile is staged as it lies in memory

@@ -209,6 +209,30 @@ void build_sin_family(tf_problem* p) {
   }
 }
 
+// Problems whose rows the 16-byte pieces of the tile kernels do not fit. The last K tile starts at K - 64 and the
+// last column tile of a [K][N] B at N - tile: smaller problems stay with the one-wave kernel. Offsets inside a tile
+// (64 rows) are kept in 32 bits.
+void build_any_family(tf_problem* p) {
+  const tf_problem_desc& d = p->desc;
+  if (d.M <= 0 || d.N <= 0 || d.K < 64 || d.lda >= (1 << 24) || d.ldb >= (1 << 24)) return;
+  const tf::AnyKernelInfo* tab = tf::any_kernel_table();
+  for (int i = 0; i < tf::any_kernel_count(); ++i) {
+    const tf::AnyKernelInfo& k = tab[i];
+    if ((k.trans_b != 0) != (d.trans_b != 0) || (!k.trans_b && d.N < k.tile)) continue;
+    const long tm = cdivl(d.M, k.tile), tn = cdivl(d.N, k.tile);
+    if (tm * tn > 0x7fffffffL / 16) continue;
+    tf_variant_desc v;
+    memset(&v, 0, sizeof(v));
+    v.kind = TF_KIND_MFMA_ANY; v.bm = k.tile; v.bn = k.tile; v.bk = 64; v.waves_m = 1; v.waves_n = 1; v.waves_k = k.waves;
+    v.stages = 2; v.split_k = 1; v.trans_b = k.trans_b; v.xcd_swizzle = 1; v.group_m = (int32_t)std::min<long>(tm, 8);
+    v.threads = k.threads; v.lds_bytes = k.lds_bytes; v.grid = (int32_t)(tm * tn);
+    snprintf(v.name, sizeof(v.name), "any_%dx%dx64_k%d%s", k.tile, k.tile, k.waves, k.trans_b ? "_bnk" : "");
+    VariantImpl im{};
+    im.lds_index = i; im.ktiles_per_split = (int)cdivl(d.K, 64); im.tiles_m = (int)tm; im.tiles_n = (int)tn;
+    add_variant(p, v, im);
+  }
+}
+
 void build_family(tf_problem* p) {
   const tf_problem_desc& d = p->desc;
   p->family.clear();
@@ -242,7 +266,7 @@ void build_family(tf_problem* p) {
                        (double)d.M * (double)d.lda * 2.0 < 4294967296.0 &&
                        (double)(tb ? d.N : d.K) * (double)d.ldb * 2.0 < 4294967296.0 &&
                        (double)d.K * (double)d.N * 2.0 < 4294967296.0;
-  if (!aligned) return;
+  if (!aligned) { build_any_family(p); return; }
   const int cus = p->hw.cus > 0 ? p->hw.cus : 256;
   const tf::LdsKernelInfo* tab = tf::lds_kernel_table();
   // pass 0: kernels compiled for the layout B arrives in; pass 1 (B as [N][K] only): a separate pass writes
@@ -565,6 +589,15 @@ tf_status do_launch(tf_problem* p, int id, const void* A, const void* B, const v
   } else if (v.kind == TF_KIND_MFMA_DIRECT) {
     if (cdivl(d.M, 32) > 65535) return fail(TF_E_UNSUPPORTED, "mfma_direct variant: M too large for the grid");
     tf::launch_mfma_direct(g, stream);
+  } else if (v.kind == TF_KIND_MFMA_ANY) {
+    const tf::AnyKernelInfo& k = tf::any_kernel_table()[im.lds_index];
+    const int slot = tf::lds_kernel_count() + tf::stream_kernel_count() + im.lds_index;
+    if (!p->attr_done[slot]) {
+      TF_HIP(hipFuncSetAttribute(k.func, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds_bytes));
+      p->attr_done[slot] = 1;
+    }
+    g.tiles_m = im.tiles_m; g.tiles_n = im.tiles_n; g.ktiles_per_split = im.ktiles_per_split;
+    k.launch(g, dim3((unsigned)v.grid), stream);
   } else {
     g.tiles_m = im.tiles_m; g.tiles_n = im.tiles_n; g.ktiles_per_split = im.ktiles_per_split;
     if (d.trans_b && v.kind == TF_KIND_MFMA_LDS && !v.trans_b) {
@@ -670,6 +703,7 @@ void fill_static(tf_problem* p, int id, tf_report* r) {
   else if (v.kind == TF_KIND_NAIVE) func = tf::naive_func();
   else if (v.kind == TF_KIND_MFMA_DIRECT) func = tf::mfma_direct_func();
   else if (v.kind == TF_KIND_MFMA_STREAM) { func = tf::stream_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
+  else if (v.kind == TF_KIND_MFMA_ANY) { func = tf::any_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
   else { func = tf::lds_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
   hipFuncAttributes a;
   memset(&a, 0, sizeof(a));
@@ -1133,7 +1167,7 @@ extern "C" tf_status tf_problem_create(const tf_problem_desc* desc, tf_problem**
     ps->own_ws = nullptr; ps->own_ws_bytes = 0; ps->zeroed_ws = nullptr; ps->zeroed_bytes = 0;
     ps->have_hw = tf_hw_query(desc->device, &ps->hw) == TF_OK;
     if (!ps->have_hw) { tf_hw_nominal(&ps->hw); g_err[0] = 0; }
-    ps->attr_done.assign(tf::lds_kernel_count() + tf::stream_kernel_count(), 0);
+    ps->attr_done.assign(tf::lds_kernel_count() + tf::stream_kernel_count() + tf::any_kernel_count(), 0);
     build_family(ps);
     *out = ps;
     return TF_OK;
@@ -1160,7 +1194,7 @@ extern "C" tf_status tf_problem_create(const tf_problem_desc* desc, tf_problem**
   // host-side loop logic work without a GPU; launching does not)
   p->have_hw = tf_hw_query(desc->device, &p->hw) == TF_OK;
   if (!p->have_hw) { tf_hw_nominal(&p->hw); g_err[0] = 0; }
-  p->attr_done.assign(tf::lds_kernel_count() + tf::stream_kernel_count(), 0);
+  p->attr_done.assign(tf::lds_kernel_count() + tf::stream_kernel_count() + tf::any_kernel_count(), 0);
   build_family(p);
   *out = p;
   return TF_OK;
@@ -1189,6 +1223,7 @@ extern "C" int32_t tf_variant_kernel_name(const tf_variant_desc* v, char* buf, i
     case TF_KIND_MFMA_STREAM:
       n = snprintf(buf, cap, "tf_gemm_stream_kernel<tf::StreamCfg<%d, %d, %d, %d>", v->bm / 16, v->waves_k, v->stages, v->bn / 16);
       break;
+    case TF_KIND_MFMA_ANY: n = snprintf(buf, cap, "tf_gemm_any_kernel<tf::AnyCfg<%d, %d, %s>", v->bm / 32, v->waves_k, b(v->trans_b)); break;
     case TF_KIND_VECMAT_NAIVE: n = snprintf(buf, cap, "tf_vecmat_naive_kernel"); break;
     case TF_KIND_BGEMM_TN_NAIVE: n = snprintf(buf, cap, "tf_bgemm_tn_naive_kernel"); break;
     default: buf[0] = 0; return 0;       // kernels whose template arguments the descriptor does not spell out

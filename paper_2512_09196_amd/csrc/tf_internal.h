@@ -71,6 +71,18 @@ struct StreamKernelInfo {
 int stream_kernel_count();
 const StreamKernelInfo* stream_kernel_table();
 
+// One compiled kernel for rows that start at any two-byte address (see tf_gemm_any.hip): K >= 64, and N >= tile
+// where B is [K][N].
+struct AnyKernelInfo {
+  int tile;               // 32 or 64: the tile of Y is tile x tile
+  int waves;              // the waves of a work-group share K
+  int trans_b, threads, lds_bytes;
+  const void* func;
+  void (*launch)(const GemmParams&, dim3 grid, hipStream_t);
+};
+int any_kernel_count();
+const AnyKernelInfo* any_kernel_table();
+
 // One compiled kernel of the streaming family of the batched vector-matrix product.
 // GemmParams: A [M][lda], B [M][N][ldb] (k contiguous), Y fp32 [M][ldy]; group_m unused.
 struct VecmatKernelInfo {

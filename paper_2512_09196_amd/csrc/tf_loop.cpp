@@ -179,6 +179,15 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
   }
   if (v->kind == TF_KIND_NAIVE) return fmax(flops / (0.004 * hw->bf16_tflops_peak * 1e6), hbm_us) + 2.0;
   if (v->kind == TF_KIND_MFMA_DIRECT) return fmax(flops / (0.02 * hw->bf16_tflops_peak * 1e6), hbm_us) + 2.0;
+  if (v->kind == TF_KIND_MFMA_ANY) {
+    // every tile fetches its row and column panel (mostly from L2): 13 TB/s in tiles of 32, 9.5 in tiles of 64 (two
+    // loads in flight per byte of LDS against one); below that a wave takes its share of the K tiles one after the
+    // other, 0.65 and 1.6 us each (measured on thirty shapes from 36 x 61 x 139 to 4096 x 4095 x 4097)
+    const bool t64 = v->bm > 32;
+    const double traffic = (double)v->grid * 2.0 * v->bm * 2.0 * pr->K;
+    const double serial = (double)cdiv(cdiv(pr->K, 64), v->waves_k) * (t64 ? 1.6 : 0.65);
+    return 4.0 + fmax(fmax(traffic / (t64 ? 9.5e6 : 13.0e6), hbm_us), serial);
+  }
   if (v->kind == TF_KIND_MFMA_STREAM) {
     // B is read once at the rate the chip sustains from HBM, if enough waves keep loads in flight
     // (about 96 KB per CU; a wave keeps stages - 1 blocks of 8 KB outstanding)

@@ -532,3 +532,33 @@ def test_ragged_k_staged_directly(shape, b_as_nk):
             print("inf", shape, b_as_nk, v.name.decode(), flush=True)
             got, intact, _ = gu.run_variant(prob, v.id, dA, dB, dbias, out)
             assert intact and np.array_equal(got[0], z[0]), v.name.decode()      # row 0: infinities of B's sign
+
+
+# tiles of 32 and 64: one and two column tiles that overlap, rows past M, K of one tile, a K tail of one value and of 63
+@pytest.mark.parametrize("b_as_nk", [0, 1])
+@pytest.mark.parametrize("shape", [(1, 33, 64), (33, 65, 65), (32, 64, 127), (65, 127, 129), (70, 95, 1023), (257, 1021, 763)])
+def test_rows_at_any_two_byte_address(shape, b_as_nk):
+    M, N, K = shape
+    A, B, bias = wl.make_custom(M, N, K, seed=900 + K)
+    y, z, s = orc.gemm_bias_gelu(A, B, bias)
+    want = {tf.TF_EPI_BIAS_GELU_ERF: y, tf.TF_EPI_NONE_F32: z, tf.TF_EPI_BIAS: z,
+            tf.TF_EPI_BIAS_GELU_TANH: orc.gelu_tanh(z.ravel()).reshape(z.shape)}
+    Bd = np.ascontiguousarray(B.T) if b_as_nk else B
+    lda, ldb, ldy = K + 3, (K if b_as_nk else N) + 5, N + 1
+    odd = lambda bits: gu.to_dev(np.concatenate([[np.uint16(0x7FC1)], bits.ravel()]))[1:]      # NaN in front of, between and (padding) behind the rows
+    dA, dB, dbias = odd(gu.strided(A, lda)), odd(gu.strided(Bd, ldb)), odd(bias)
+    for epi in want:
+        f32 = epi == tf.TF_EPI_NONE_F32
+        out = gu.OutBuf(M, N, ldy=ldy, f32=f32)
+        with tf.Problem(M, N, K, lda=lda, ldb=ldb, ldy=ldy, epi=epi, trans_b=b_as_nk) as prob:
+            vs = [v for v in prob.variants() if v.kind == tf.TF_KIND_MFMA_ANY]
+            assert len(vs) >= 2
+            for v in vs:
+                name = v.name.decode()
+                print("case", shape, b_as_nk, "epi", epi, "variant", name, flush=True)
+                got, intact, _ = gu.run_variant(prob, v.id, dA, dB, dbias, out)
+                assert intact, "%s wrote outside Y" % name
+                assert not np.isnan(got).any(), "%s left elements unwritten or read a padding value" % name
+                err = np.abs(got - want[epi])
+                bound = gu.preact_bound(z, s, K) if f32 else gu.strict_bound(want[epi], z, s, K)
+                assert np.all(err <= bound), "%s: worst excess %g" % (name, (err - bound).max())
