@@ -150,7 +150,9 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
       v1.grid = (int32_t)(((pr->M + v->bm - 1) / v->bm) * (long)((pr->N + v->bn - 1) / v->bn) * (long)items);
       return fmax(0.8 * tf_predict_us(&one, hw, &v1), floor_us + 4.0);
     }
-    double us = fmax(tf_predict_us(&one, hw, &v1), floor_us + 4.0);
+    // (a work-group of the plain kernels reads, multiplies and then writes, and the chip's reads and writes overlap
+    // less for it: 32 x 1024 x 1024 x 256, 168 MB, takes 44.7-52.2 us in their tiles, 34.9 us in the persistent kernel)
+    double us = fmax(tf_predict_us(&one, hw, &v1), 1.4 * floor_us + 4.0);
     // with few K steps per tile a work-group is a short read - multiply - write sequence; alone on its CU
     // it leaves memory idle while it multiplies and the matrix pipes idle while it writes (measured 1.4-1.6x)
     const long slots_one = (long)hw->cus * tf_resident_wgs(hw, v);
@@ -178,7 +180,9 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
     return fmax(floor_us / (0.72 * feed), serial_us) + 3.0;
   }
   if (v->kind == TF_KIND_NAIVE) return fmax(flops / (0.004 * hw->bf16_tflops_peak * 1e6), hbm_us) + 2.0;
-  if (v->kind == TF_KIND_MFMA_DIRECT) return fmax(flops / (0.02 * hw->bf16_tflops_peak * 1e6), hbm_us) + 2.0;
+  // one wave per tile that gathers element by element: each 16 of K are a dependent trip to memory, about 0.75 us,
+  // however few tiles there are (256^3 16.7 us, 6 x 3008 x 1856 98.6 us, 5 x 11008 x 4096 170 us, 19 x 2432 x 3392 225 us)
+  if (v->kind == TF_KIND_MFMA_DIRECT) return fmax(fmax(flops / (0.02 * hw->bf16_tflops_peak * 1e6), hbm_us), 0.75 * (pr->K / 16.0)) + 2.0;
   if (v->kind == TF_KIND_MFMA_ANY) {
     // every tile fetches its row and column panel (mostly from L2): 13 TB/s in tiles of 32, 9.5 in tiles of 64 (two
     // loads in flight per byte of LDS against one); below that a wave takes its share of the K tiles one after the
@@ -316,7 +320,7 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
   // tiles dealt round-robin over the XCDs (offered for one row of tiles): every row of B is then pulled through all
   // eight L2s at once, which streams about a tenth faster than a contiguous run of columns per XCD
   // (and a K tile of 128 streamed 8-10 % slower than one of 64 on 16 x 8192 x 8192: 28.8-29.3 against 26.6-27.1 us)
-  const double spread = (v->xcd_swizzle ? 1.0 : 0.9) * (bk > 64 ? 1.08 : 1.0);
+  const double spread = (v->xcd_swizzle ? 1.0 : 0.9) * (bk > 64 ? 1.12 : 1.0);
   return fmax(us * rot, (hbm_us + ws_us) / (0.75 * inflight) * spread) + 3.6 + reduce_us + fused_tail_us + pretrans_us;
 }
 
