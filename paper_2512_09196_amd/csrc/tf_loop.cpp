@@ -320,7 +320,8 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
   // tiles dealt round-robin over the XCDs (offered for one row of tiles): every row of B is then pulled through all
   // eight L2s at once, which streams about a tenth faster than a contiguous run of columns per XCD
   // (and a K tile of 128 streamed 8-10 % slower than one of 64 on 16 x 8192 x 8192: 28.8-29.3 against 26.6-27.1 us)
-  const double spread = (v->xcd_swizzle ? 1.0 : 0.9) * (bk > 64 ? 1.12 : 1.0);
+  // (not where B is [N][K] and each work-group reads rows of its own: 16 x 8192 x 8192 29.3 us in runs, 29.9 round-robin)
+  const double spread = (v->xcd_swizzle || v->trans_b ? 1.0 : 0.9) * (bk > 64 ? 1.12 : 1.0);
   return fmax(us * rot, (hbm_us + ws_us) / (0.75 * inflight) * spread) + 3.6 + reduce_us + fused_tail_us + pretrans_us;
 }
 
