@@ -110,6 +110,8 @@ static const std::vector<LdsKernelInfo>& all_kernels() {
     int n = 0;
     const LdsKernelInfo* more = lds_ragged_table(&n);
     v.insert(v.end(), more, more + n);
+    more = lds_192_table(&n);
+    v.insert(v.end(), more, more + n);
     return v;
   }();
   return all;

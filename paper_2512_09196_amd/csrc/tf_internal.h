@@ -55,7 +55,8 @@ struct LdsKernelInfo {
   const void* func;       // kernel symbol, for hipFuncGetAttributes / occupancy queries
   void (*launch)(const GemmParams&, dim3 grid, hipStream_t);
 };
-const LdsKernelInfo* lds_ragged_table(int* n);   // the part of the table that tf_gemm_lds_ragged.hip holds
+const LdsKernelInfo* lds_ragged_table(int* n);   // the parts of the table that tf_gemm_lds_ragged.hip and
+const LdsKernelInfo* lds_192_table(int* n);      // tf_gemm_lds_192.hip hold
 int lds_kernel_count();
 const LdsKernelInfo* lds_kernel_table();
 

@@ -562,3 +562,13 @@ def test_rows_at_any_two_byte_address(shape, b_as_nk):
                 err = np.abs(got - want[epi])
                 bound = gu.preact_bound(z, s, K) if f32 else gu.strict_bound(want[epi], z, s, K)
                 assert np.all(err <= bound), "%s: worst excess %g" % (name, (err - bound).max())
+
+
+@pytest.mark.parametrize("b_as_nk", [0, 1])
+@pytest.mark.parametrize("shape", [(193, 264, 64), (385, 520, 320), (191, 256, 576), (200, 776, 1096)])
+def test_tiles_of_192_rows(shape, b_as_nk):
+    # one and two row tiles, a whole and a ragged last column tile, one K tile, K whole and ragged
+    M, N, K = shape
+    A, B, bias = wl.make_custom(M, N, K, seed=800 + M)
+    ran = check_all_variants(M, N, K, A, np.ascontiguousarray(B.T) if b_as_nk else B, bias, only=lambda v: v.bm == 192, trans_b=b_as_nk)
+    assert len(ran) >= 2 and all(n.startswith("lds_192x256") for n in ran)
