@@ -171,7 +171,7 @@ typedef struct {
                               any moment (a different, equally valid, summation order) */
   int32_t persistent;      /* TF_OP_BATCHED_GEMM_TN tile kernels: 1 = one work-group per CU walks through many output
                               tiles and fetches the next tile's K steps while the current one multiplies and
-                              writes out (whole tiles, at least stages - 1 K steps per tile); grid = work-groups */
+                              writes out (M and N at least one tile); grid = work-groups */
   int32_t bn_tail;         /* tile kernels: > 0 = a launch with a lighter last round. Whole rounds of bm x bn tiles (one
                               per CU and round) cover the leading columns; one more round of exactly one work-group
                               per CU shares out the remaining columns of every row panel in tiles of which only

@@ -142,8 +142,9 @@ void build_bgemm_family(tf_problem* p) {
       const tf::LdsKernelInfo& k = tab[i];
       if (!k.direct_to_lds || k.a_bypass_lds || k.waves_k != 1 || k.stream_k || k.trans_b || k.bk != 64 || k.bn_tail || k.k_tail) continue;
       if (pass == 0 && !k.trans_a) continue;
-      // the persistent kernel: whole tiles, enough K steps to keep its ring busy across a tile's output
-      if (k.persistent && (pass == 1 || d.M % k.bm || d.N % k.bn || d.K / 64 < k.stages - 1)) continue;
+      // the persistent kernel (its tiles at a ragged end begin a whole tile before it)
+      if (k.persistent && (k.ragged_mn != 0) != (d.M % k.bm || d.N % k.bn || batch % 8)) continue;
+      if (k.persistent && (pass == 1 || d.M < k.bm || d.N < k.bn || (double)cdivl(d.M, k.bm) * cdivl(d.N, k.bn) * batch * (d.K / 64) >= 2147483648.0)) continue;
       if (pass == 1 && (k.trans_a || k.bm < 64 || k.bn < 64 || (k.bm == 128 && k.bn == 128 && k.waves_m * k.waves_n == 4 && k.stages == 2))) continue;
       if (k.bm > 32 && k.bm / 2 >= d.M) continue;
       if (k.bn > 64 && k.bn / 2 >= d.N) continue;
@@ -159,7 +160,7 @@ void build_bgemm_family(tf_problem* p) {
       v.grid = (int32_t)(tm * tn * batch);
       if (k.persistent) {
         // one work-group per CU, a multiple of 8 (work-group w runs on XCD w mod 8), no more than the busiest XCD has tiles
-        const long busiest = cdivl(batch, 8) * tm * tn;
+        const long busiest = cdivl((long)batch * tm * tn, 8);
         v.persistent = 1;
         v.grid = (int32_t)(8 * std::max<long>(1, std::min<long>(std::max(p->hw.cus, 8) / 8, busiest)));
       }

@@ -1242,13 +1242,20 @@ __global__ void __launch_bounds__(CM::THREADS) tf_gemm_mixed_kernel(const GemmPa
 }
 
 // Persistent kernel for the batched transposed-operand product with few K steps per tile
-// (C[b] = A[b]^T B[b], whole tiles only). With four K steps a work-group spends most of its life waiting for
+// (C[b] = A[b]^T B[b]). With four K steps a work-group spends most of its life waiting for
 // its first tiles and for the end of its stores; here one work-group per CU walks through many output tiles
 // and the ring never drains: the transfers of the next tile's K steps are issued while the current tile still
 // multiplies and writes out. The output goes through a staging area of its own behind the ring, so the ring
 // stays free for those transfers.
 //   * work-group w runs on XCD w mod 8; XCD x takes the batch items x, x + 8, ..., so an item's operands are
 //     fetched into one L2; the work-groups of an XCD deal that XCD's tiles out among themselves in turn.
+//   * RAGGED (M or N no multiple of the tile, but at least one tile; or the batch no multiple of eight): an XCD takes
+//     an eighth of the tiles of all items, in item order, instead; the last tile of a row or column of tiles begins at
+//     M - BM or N - BN, so every transfer stays inside the item, and stores only what its neighbour does not.
+//     An instance of its own: in one kernel for both, 32 x 1024 x 1024 x 256 went from 35.2 to 38.3 us. Against the
+//     one-tile work-groups that had such sizes to themselves, tile picked / best tile / here (us): 32 x 1000 x 1000 x
+//     256 56.3 / 47.2 / 42.2, 48 x 568 x 896 x 128 37.0 / 28.3 / 22.2, 57 x 880 x 288 x 64 26.3 / 21.0 / 14.4,
+//     27 x 320 x 848 x 256 23.2 / 16.6 / 14.1.
 //   * one "flat step" = one K step of one tile. At flat step f the transfers of step f + D (D = STAGES - 1)
 //     are issued into the buffer that step f - 1 has just left. Past the end the last step is fetched again
 //     (into a buffer nobody reads), which keeps the number of transfers in flight, and so the vmcnt waits,
@@ -1261,8 +1268,8 @@ __global__ void __launch_bounds__(CM::THREADS) tf_gemm_mixed_kernel(const GemmPa
 //     during the next tile's first K steps (T2: 48 us against 42 us, also with the waves split as above: the
 //     second barrier in the middle of a step costs more than the overlap gains), and a fourth buffer with
 //     half-size output passes (43 us against 39 us).
-template <class C>
-__global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_kernel(const GemmParams p) {
+template <class C, bool RAGGED>
+__device__ __forceinline__ void bgemm_persist_body(const GemmParams& p) {
   static_assert(C::TRANSA && !C::TRANSB && C::DIRECT && C::WK == 1 && !C::ABYPASS && C::STAGES >= 3, "transposed staging, direct, three buffers or more");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int D = C::STAGES - 1;
@@ -1285,18 +1292,23 @@ __global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_kernel(const Gemm
   // ---- this work-group's tiles
   const int tiles = p.tiles_m * p.tiles_n;                       // per batch item
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, per_xcd = gridDim.x >> 3;
+  const long all = (long)p.batch * tiles;
   const int items_x = (p.batch - xcd + 7) / 8;                   // items x, x + 8, ... < batch
-  const int n_flat = items_x * tiles;
+  const int first = RAGGED ? (int)(xcd * all / 8) : 0;
+  const int n_flat = RAGGED ? (int)((xcd + 1) * all / 8) - first : items_x * tiles;
   const int my_tiles = local < n_flat ? (n_flat - local + per_xcd - 1) / per_xcd : 0;
   const int nkt = p.K / C::BK;
   const int total = my_tiles * nkt;
   if (total <= 0) return;
-  struct Where { const uint16_t* a; const uint16_t* b; char* y; int m0, n0; };
+  struct Where { const uint16_t* a; const uint16_t* b; char* y; int m0, n0, skip_m, skip_n; };    // skip_: leading rows and columns that are the neighbour's
   auto where = [&](int k) -> Where {                               // k-th tile of this work-group
-    const int j = local + k * per_xcd;
-    const int item = xcd + 8 * (j / tiles), tile = j % tiles;
+    const int j = first + local + k * per_xcd;
+    const int item = RAGGED ? j / tiles : xcd + 8 * (j / tiles), tile = j % tiles;
+    const int m_own = (tile % p.tiles_m) * C::BM, n_own = (tile / p.tiles_m) * C::BN;
     Where w;
-    w.m0 = (tile % p.tiles_m) * C::BM; w.n0 = (tile / p.tiles_m) * C::BN;
+    w.m0 = !RAGGED || m_own + C::BM <= p.M ? m_own : p.M - C::BM;
+    w.n0 = !RAGGED || n_own + C::BN <= p.N ? n_own : p.N - C::BN;
+    w.skip_m = m_own - w.m0; w.skip_n = n_own - w.n0;
     w.a = p.A + (size_t)item * p.stride_a + w.m0;                  // A[b] is [K][lda], m contiguous
     w.b = p.B + (size_t)item * p.stride_b + w.n0;
     w.y = (char*)p.Y + (size_t)item * p.stride_y * 4;
@@ -1337,7 +1349,7 @@ __global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_kernel(const Gemm
 
   const bool loader = wave < LW;                 // wave-uniform
   TileLoader<CL> ld;
-  ld.init(p, 0, 0, loader ? wave : 0, lane);     // offsets relative to the tile's corner: whole tiles only
+  ld.init(p, 0, 0, loader ? wave : 0, lane);     // offsets relative to the tile's corner
   const unsigned lds0 = (unsigned)(size_t)smem;
   const size_t a_step = (size_t)C::BK * p.lda, b_step = (size_t)C::BK * p.ldb;
 
@@ -1389,15 +1401,21 @@ __global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_kernel(const Gemm
             *(f32x4*)(wr + (32 * t + 8 * q) * 4) = v;
           }
         barrier_lds();
-        if (!loader) {
+        auto put = [&](bool ragged) {
 #pragma unroll
           for (int j = 0; j < PER_THREAD; ++j) {
             const int c = (tid - LW * 64) + STORE_THREADS * j;
             const int rs = c / CPR, cc = c % CPR;
-            const int m = cw.m0 + (rs >> 5) * C::WTM + 32 * i + (rs & 31);
+            const int r = (rs >> 5) * C::WTM + 32 * i + (rs & 31), m = cw.m0 + r;
             const u32x4 v = *(const u32x4*)(staging + rs * ROWB + cc * 16);
-            __builtin_nontemporal_store(v, (u32x4*)(cw.y + ((size_t)m * p.ldy + cw.n0) * 4 + cc * 16));
+            if (!ragged || (r >= cw.skip_m && 4 * cc >= cw.skip_n))
+              __builtin_nontemporal_store(v, (u32x4*)(cw.y + ((size_t)m * p.ldy + cw.n0) * 4 + cc * 16));
           }
+        };
+        // (a branch of its own for whole tiles: with the test at every store the LDS reads no longer run ahead)
+        if (!loader) {
+          if (!RAGGED || (cw.skip_m == 0 && cw.skip_n == 0)) put(false);
+          else put(true);
         }
       }
 #pragma unroll
@@ -1414,8 +1432,22 @@ __global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_kernel(const Gemm
 }
 
 template <class C>
+__global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_kernel(const GemmParams p) {
+  bgemm_persist_body<C, false>(p);
+}
+template <class C, int RAGGED>
+__global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_kernel(const GemmParams p) {
+  static_assert(RAGGED == 1, "tf_bgemm_persist_kernel<C> is the other one");
+  bgemm_persist_body<C, true>(p);
+}
+
+template <class C>
 static void launch_persist(const GemmParams& p, dim3 grid, hipStream_t stream) {
   hipLaunchKernelGGL(tf_bgemm_persist_kernel<C>, grid, dim3(C::THREADS), C::PERSIST_LDS_BYTES, stream, p);
+}
+template <class C>
+static void launch_persist_ragged(const GemmParams& p, dim3 grid, hipStream_t stream) {
+  hipLaunchKernelGGL((tf_bgemm_persist_kernel<C, 1>), grid, dim3(C::THREADS), C::PERSIST_LDS_BYTES, stream, p);
 }
 
 template <class C>
@@ -1481,6 +1513,15 @@ static LdsKernelInfo make_persist_info() {
   k.lds_bytes = C::PERSIST_LDS_BYTES;
   k.func = (const void*)tf_bgemm_persist_kernel<C>;
   k.launch = launch_persist<C>;
+  return k;
+}
+template <class C>
+static LdsKernelInfo make_persist_ragged_info() {
+  LdsKernelInfo k = describe<C>();
+  k.persistent = 1; k.ragged_mn = 1;
+  k.lds_bytes = C::PERSIST_LDS_BYTES;
+  k.func = (const void*)tf_bgemm_persist_kernel<C, 1>;
+  k.launch = launch_persist_ragged<C>;
   return k;
 }
 

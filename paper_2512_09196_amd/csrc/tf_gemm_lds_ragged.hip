@@ -1,4 +1,4 @@
-// Instances of the LDS-staged kernels (tf_gemm_lds.h) for a K that is no multiple of the K tile.
+// Instances of the LDS-staged kernels (tf_gemm_lds.h) for sizes that are no multiples of the tiles.
 #include "tf_gemm_lds.h"
 
 namespace tf {
@@ -24,11 +24,15 @@ using N32x128  = LdsCfg< 32, 128, 64, 1, 4, 3, true, false, 1, false, true>;
 using N32x64   = LdsCfg< 32,  64, 64, 1, 2, 4, true, false, 1, false, true>;
 using N32x32   = LdsCfg< 32,  32, 64, 1, 1, 4, true, false, 1, false, true>;
 
+// first operand transposed: the persistent kernel for ragged tiles
+using T128x128 = LdsCfg<128, 128, 64, 2, 4, 3, true, false, 1, true>;
+
 static const LdsKernelInfo g_ragged[] = {
     make_ragged_info<K256x256>(), make_ragged_info<K256x128>(), make_ragged_info<K128x256>(), make_ragged_info<K128x128>(),
     make_ragged_info<K64x64>(),   make_ragged_info<K32x128>(),  make_ragged_info<K32x64>(),   make_ragged_info<K32x32>(),
     make_ragged_info<N256x256>(), make_ragged_info<N256x128>(), make_ragged_info<N128x256>(), make_ragged_info<N128x128>(),
     make_ragged_info<N64x64>(),   make_ragged_info<N32x128>(),  make_ragged_info<N32x64>(),   make_ragged_info<N32x32>(),
+    make_persist_ragged_info<T128x128>(),
 };
 
 const LdsKernelInfo* lds_ragged_table(int* n) {

@@ -147,3 +147,13 @@ def test_variant_loop_and_full_size_t2_against_the_whole_oracle():
             assert best != 0 and log[0].t_med_us / rep.t_med_us >= 1.05
             got = Y.double().cpu().numpy()
             assert np.all(np.abs(got - c) <= bound(c, s, w.K))
+
+
+@pytest.mark.parametrize("shape", [(3, 136, 128, 64), (9, 264, 136, 128), (5, 200, 392, 192), (1, 128, 1000, 64), (17, 248, 128, 128),
+                                   (8, 128, 256, 64)])      # the last: whole tiles, one K step
+def test_ragged_tiles_of_the_persistent_kernels(shape):
+    # tiles that begin before their own rows or columns, one K step per tile, items split between XCDs
+    nb, M, N, K = shape
+    A, B = wl.make_bgemm(nb, M, N, K, seed=400 + M)
+    ran = check_all(nb, M, N, K, A, B, lda=M + 8, ldb=N + 16, ldy=N + 4, extra_rows=1)
+    assert any(n.endswith("persist") for n in ran)
