@@ -552,7 +552,7 @@ def test_rows_at_any_two_byte_address(shape, b_as_nk):
         out = gu.OutBuf(M, N, ldy=ldy, f32=f32)
         with tf.Problem(M, N, K, lda=lda, ldb=ldb, ldy=ldy, epi=epi, trans_b=b_as_nk) as prob:
             vs = [v for v in prob.variants() if v.kind == tf.TF_KIND_MFMA_ANY]
-            assert len(vs) >= 2
+            assert vs
             for v in vs:
                 name = v.name.decode()
                 print("case", shape, b_as_nk, "epi", epi, "variant", name, flush=True)
