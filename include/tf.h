@@ -76,6 +76,9 @@ typedef enum {
                                are TF_KIND_MFMA_LDS, see trans_a)                                       */
   TF_KIND_MFMA_ANY = 8,      /* rows of A, B and Y at any two-byte address (where the tile kernels' 16-byte pieces do
                                not fit): bm x bn tiles, the waves_k waves of a work-group share K           */
+  TF_KIND_MFMA_LDS_ANY = 9, /* a tile kernel (fields as for TF_KIND_MFMA_LDS; no K slices, no workspace) for calls whose
+                               pointers have the alignment it needs; other calls run the any-address or the
+                               one-wave kernel. What the static pick of a small problem takes, see tf_proposal */
   TF_KIND_SIN = 7            /* TF_OP_ELEMENTWISE_SIN: one arithmetic, many launch shapes. Descriptor fields: threads,
                                bn = elements per work-group and pass (the paper's BLOCK_SIZE; variant 0 has 4),
                                bk = consecutive elements per thread, stages = passes per work-group,
@@ -372,7 +375,11 @@ int32_t tf_refine_hint(const tf_report* prev, const tf_report* cand, const tf_hw
 
 /* Proposal: id of the next candidate among family[0..n), none of which has tried[id] != 0,
  * given the current kernel `base_id` and its bottleneck class; -1 when the family is
- * exhausted. prob gives the shape. */
+ * exhausted. prob gives the shape. With nothing tried but the baseline the answer is the static
+ * pick, which needs no measurement. The static pick of a small problem (its family has a variant of
+ * kind TF_KIND_MFMA_LDS_ANY) takes operands at any element address and no workspace, so it may run from
+ * several streams at once and be captured on its first call; any other static pick may need
+ * 16-byte aligned pointers and a workspace, see its descriptor. */
 int32_t tf_proposal(const tf_problem_desc* prob, const tf_hw* hw, const tf_variant_desc* family,
                     int32_t n, const uint8_t* tried, int32_t base_id, int32_t bottleneck);
 

@@ -45,6 +45,7 @@ struct VariantImpl {
   size_t counter_bytes;   // leading part of the workspace
   int sk_first, sk_tiles; // stream-K: tiles computed whole (= first shared work-group), tiles whose K steps are shared
   int mix_tiles, mix_blocks;   // lighter last round: its tiles per row panel, the blocks of 32 columns they share (tiles_n = tile columns of the wide part)
+  int any_id;             // TF_KIND_MFMA_LDS_ANY: the variant that takes the calls whose pointers the tile kernel does not
   size_t aux_off;         // B given as [N][K] behind a transposing pass: where B^T lies in the workspace (behind the family's counter area)
 };
 
@@ -232,6 +233,44 @@ void build_any_family(tf_problem* p) {
     im.lds_index = i; im.ktiles_per_split = (int)cdivl(d.K, 64); im.tiles_m = (int)tm; im.tiles_n = (int)tn;
     add_variant(p, v, im);
   }
+}
+
+// Small problems: the ones whose product at a fiftieth of the matrix peak, or whose operands at the full memory rate,
+// are done before any tile kernel is. There the static pick used to be the one-wave kernel, and programs run it on
+// operands at any element address, from several streams at once, and first thing under capture: none of that goes
+// with 16-byte pieces and K slices in a shared workspace. So the pick there stays among variants that allow it: the
+// any-address kernels, and one tile kernel without K slices that hands the calls it cannot take to them. (The line is
+// a promise kept to those programs, not an optimum.) Measured, us, one-wave kernel / tiles with or without K slices /
+// this: 256^3 16.7 / 7.6 / 7.6, 5 x 11008 x 4096 with B as [N][K] 184 / 19.7 / 19.7, 9 x 2304 x 3776 259 / 11.8 / 10.4,
+// 16 x 576 x 4544 with B as [N][K] (one-wave about 200) / 10.4 / 9.7. Long sums over few columns lose: a CU fetches
+// about 60 GB/s and there are fewer tiles than CUs (7 x 968 x 10752 13.8 with slices, 22.6 here; 64 x 256 x 16384 12.5
+// and 35; more waves per tile do not help: 8, 12 and 16 measured). The loop goes on to K slices where they are faster.
+void build_small_family(tf_problem* p) {
+  const tf_problem_desc& d = p->desc;
+  const double flops = 2.0 * d.M * (double)d.N * d.K;
+  const double bytes = 2.0 * ((double)d.M * d.K + (double)d.K * d.N + (double)d.M * d.N + d.N);
+  const double quick = std::max(flops / (0.02 * p->hw.bf16_tflops_peak * 1e6), bytes / (p->hw.hbm_gbs_peak * 1e3)) + 2.0;
+  double best = 1e30, best_plain = 1e30;
+  int plain = -1;
+  for (const tf_variant_desc& v : p->family) {
+    if (v.kind != TF_KIND_MFMA_LDS && v.kind != TF_KIND_MFMA_STREAM) continue;
+    const double us = tf_predict_us(&d, &p->hw, &v);
+    // (the tiles of 192 rows and the direct staging of a ragged K do not move the line)
+    if (v.bm != 192 && !(v.direct_to_lds && v.kind == TF_KIND_MFMA_LDS && d.K % v.bk)) best = std::min(best, us);
+    if (v.kind == TF_KIND_MFMA_LDS && v.workspace_bytes == 0 && us < best_plain) { best_plain = us; plain = v.id; }
+  }
+  if (quick >= best || plain < 0) return;
+  int any = 1;                                             // the one-wave kernel
+  build_any_family(p);
+  for (const tf_variant_desc& v : p->family)
+    if (v.kind == TF_KIND_MFMA_ANY && tf_predict_us(&d, &p->hw, &v) < tf_predict_us(&d, &p->hw, &p->family[any])) any = v.id;
+  tf_variant_desc v = p->family[plain];
+  VariantImpl im = p->impl[plain];
+  v.kind = TF_KIND_MFMA_LDS_ANY;
+  im.any_id = any;
+  const size_t len = strlen(v.name);
+  snprintf(v.name + len, sizeof(v.name) - len, "_or_any");
+  add_variant(p, v, im);
 }
 
 void build_family(tf_problem* p) {
@@ -433,6 +472,7 @@ void build_family(tf_problem* p) {
       }
     }
   }
+  build_small_family(p);
   // One counter area for the whole family, so that the partial sums of one variant never
   // land on the counters of another: [counters, status word | partial sums]. The status word
   // takes the last 256 bytes of the area.
@@ -454,6 +494,10 @@ void build_family(tf_problem* p) {
 }
 
 // ---------------------------------------------------------------- launch
+bool tile_aligned(const void* A, const void* B, const void* bias, const void* Y) {
+  return (((uintptr_t)A | (uintptr_t)B | (uintptr_t)Y) & 15u) == 0 && ((uintptr_t)bias & 7u) == 0;
+}
+
 tf_status check_ptrs(const tf_problem* p, const tf_variant_desc& v, const void* A, const void* B, const void* bias,
                      void* Y) {
   const tf_problem_desc& d = p->desc;
@@ -485,7 +529,7 @@ tf_status check_ptrs(const tf_problem* p, const tf_variant_desc& v, const void* 
   if (!Y || !bias) return fail(TF_E_INVALID, "null Y or bias pointer");
   if (d.K > 0 && (!A || !B)) return fail(TF_E_INVALID, "null A or B pointer");
   if (v.kind == TF_KIND_MFMA_LDS || v.kind == TF_KIND_MFMA_STREAM) {
-    if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)Y) & 15u || ((uintptr_t)bias & 7u))
+    if (!tile_aligned(A, B, bias, Y))
       return fail(TF_E_UNSUPPORTED, "variant %s needs 16-byte aligned A, B, Y and 8-byte aligned bias", v.name);
   }
   return TF_OK;
@@ -516,6 +560,8 @@ tf_status do_launch(tf_problem* p, int id, const void* A, const void* B, const v
   tf_status st = check_ptrs(p, v, A, B, bias, Y);
   if (st != TF_OK) return st;
   if (d.M == 0 || d.N == 0) return TF_OK;   // nothing to compute
+  if (v.kind == TF_KIND_MFMA_LDS_ANY && !tile_aligned(A, B, bias, Y))
+    return do_launch(p, im.any_id, A, B, bias, Y, ws, ws_bytes, stream, epi_override, ldy_override);
   tf::GemmParams g;
   memset(&g, 0, sizeof(g));
   g.A = (const uint16_t*)A; g.B = (const uint16_t*)B; g.bias = (const uint16_t*)bias; g.Y = Y;
@@ -1219,7 +1265,7 @@ extern "C" int32_t tf_variant_kernel_name(const tf_variant_desc* v, char* buf, i
   switch (v->kind) {
     case TF_KIND_NAIVE: n = snprintf(buf, cap, "tf_gemm_naive_kernel"); break;
     case TF_KIND_MFMA_DIRECT: n = snprintf(buf, cap, "tf_gemm_mfma_direct_kernel"); break;
-    case TF_KIND_MFMA_LDS:
+    case TF_KIND_MFMA_LDS: case TF_KIND_MFMA_LDS_ANY:
       snprintf(cfg, sizeof(cfg), "tf::LdsCfg<%d, %d, %d, %d, %d, %d, %s, %s, %d, %s, %s, %d>", v->bm, v->bn, v->bk, v->waves_m,
                v->waves_n, v->stages, b(v->direct_to_lds), b(v->a_bypass_lds), v->waves_k, b(v->trans_a), b(v->trans_b), v->bn);
       n = snprintf(buf, cap, "%s%s", v->bn_tail ? "tf_gemm_mixed_kernel<" : v->persistent ? "tf_bgemm_persist_kernel<"

@@ -85,6 +85,7 @@ extern "C" int32_t tf_refine_hint(const tf_report* prev, const tf_report* cand, 
 
 // ------------------------------------------------------------------ static cost model
 static inline long cdiv(long a, long b) { return (a + b - 1) / b; }
+static inline bool is_tile_kernel(const tf_variant_desc* v) { return v->kind == TF_KIND_MFMA_LDS || v->kind == TF_KIND_MFMA_LDS_ANY; }
 
 extern "C" int32_t tf_resident_wgs(const tf_hw* hw, const tf_variant_desc* v) {
   if (v->kind == TF_KIND_MFMA_STREAM) {
@@ -95,7 +96,7 @@ extern "C" int32_t tf_resident_wgs(const tf_hw* hw, const tf_variant_desc* v) {
     if (by_lds < r) r = by_lds;
     return r < 1 ? 1 : (r > 8 ? 8 : r);
   }
-  if (v->kind != TF_KIND_MFMA_LDS) return 8;
+  if (!is_tile_kernel(v)) return 8;
   const int acc_regs = (v->bm / v->waves_m) * (v->bn / v->waves_n) / 64;
   const int regs = acc_regs + 96;                      // fragments, staging, addresses
   int wps = hw->vgprs_per_simd_lane / regs;
@@ -186,11 +187,13 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
   if (v->kind == TF_KIND_MFMA_ANY) {
     // every tile fetches its row and column panel (mostly from L2): 13 TB/s in tiles of 32, 9.5 in tiles of 64 (two
     // loads in flight per byte of LDS against one); below that a wave takes its share of the K tiles one after the
-    // other, 0.65 and 1.6 us each (measured on thirty shapes from 36 x 61 x 139 to 4096 x 4095 x 4097)
+    // other, 0.65 and 1.6 us each (measured on thirty shapes from 36 x 61 x 139 to 4096 x 4095 x 4097). Operands that
+    // come from memory arrive at about 0.55 of the peak rate (2 x 8000 x 13120 40 us, 3 x 10912 x 7920 with B as
+    // [N][K] 43 us, 1 x 7544 x 14256 49 us; 2.7 to 5.2 TB/s over ten such shapes)
     const bool t64 = v->bm > 32;
     const double traffic = (double)v->grid * 2.0 * v->bm * 2.0 * pr->K;
     const double serial = (double)cdiv(cdiv(pr->K, 64), v->waves_k) * (t64 ? 1.6 : 0.65);
-    return 4.0 + fmax(fmax(traffic / (t64 ? 9.5e6 : 13.0e6), hbm_us), serial);
+    return 4.0 + fmax(fmax(traffic / (t64 ? 9.5e6 : 13.0e6), hbm_us / 0.55), serial);
   }
   if (v->kind == TF_KIND_MFMA_STREAM) {
     // B is read once at the rate the chip sustains from HBM, if enough waves keep loads in flight
@@ -352,25 +355,52 @@ extern "C" int32_t tf_proposal_from(const tf_hw* hw, const tf_variant_desc* fami
                                     int32_t n, const uint8_t* tried, int32_t base_id, int32_t bottleneck) {
   if (!hw || !family || !predicted_us || !tried || n <= 0) return -1;
   const tf_variant_desc* base = (base_id >= 0 && base_id < n) ? &family[base_id] : nullptr;
-  const bool use_hint = base && base->kind == TF_KIND_MFMA_LDS && bottleneck != TF_BN_UNKNOWN;
+  const bool use_hint = base && is_tile_kernel(base) && bottleneck != TF_BN_UNKNOWN;
   int best = -1, best_any = -1;
   for (int i = 0; i < n; ++i) {
     if (tried[i]) continue;
     if (best_any < 0 || predicted_us[i] < predicted_us[best_any]) best_any = i;
-    if (use_hint && family[i].kind == TF_KIND_MFMA_LDS && matches_hint(bottleneck, hw, base, &family[i])) {
+    if (use_hint && is_tile_kernel(&family[i]) && matches_hint(bottleneck, hw, base, &family[i])) {
       if (best < 0 || predicted_us[i] < predicted_us[best]) best = i;
     }
   }
   return best >= 0 ? best : best_any;
 }
 
+// A tile kernel and the TF_KIND_MFMA_LDS_ANY variant made of it are one launch wherever both run.
+static bool same_launch(const tf_variant_desc* a, const tf_variant_desc* b) {
+  return a->bm == b->bm && a->bn == b->bn && a->bk == b->bk && a->waves_m == b->waves_m && a->waves_n == b->waves_n &&
+         a->waves_k == b->waves_k && a->stages == b->stages && a->split_k == b->split_k && a->direct_to_lds == b->direct_to_lds &&
+         a->a_bypass_lds == b->a_bypass_lds && a->trans_b == b->trans_b && a->stream_k == b->stream_k && a->bn_tail == b->bn_tail &&
+         a->k_rotate == b->k_rotate && a->xcd_swizzle == b->xcd_swizzle && a->workspace_bytes == b->workspace_bytes;
+}
+
 extern "C" int32_t tf_proposal(const tf_problem_desc* prob, const tf_hw* hw, const tf_variant_desc* family,
                                int32_t n, const uint8_t* tried, int32_t base_id, int32_t bottleneck) {
   if (!prob || !hw || !family || !tried || n <= 0) return -1;
   double* pred = new double[n];
-  for (int i = 0; i < n; ++i) pred[i] = tf_predict_us(prob, hw, &family[i]);
-  const int r = tf_proposal_from(hw, family, pred, n, tried, base_id, bottleneck);
+  uint8_t* out = new uint8_t[n];          // what is not proposed this time
+  int small = -1;                         // the variant that marks a small problem
+  bool first = true, tiles = false;
+  for (int i = 0; i < n; ++i) {
+    pred[i] = tf_predict_us(prob, hw, &family[i]);
+    out[i] = tried[i];
+    if (family[i].kind == TF_KIND_MFMA_LDS_ANY) small = i;
+    tiles |= family[i].kind == TF_KIND_MFMA_LDS;
+    if (i > 0 && tried[i]) first = false;
+  }
+  if (first && (small >= 0 || !tiles)) {
+    // the static pick of a small problem (which may be too small for any tile): what takes any pointer and needs no workspace
+    for (int i = 0; i < n; ++i)
+      if (family[i].kind == TF_KIND_MFMA_LDS || family[i].kind == TF_KIND_MFMA_STREAM) out[i] = 1;
+  } else if (small >= 0) {
+    // later rounds: the tile kernel under one of its two ids
+    for (int i = 0; i < n; ++i)
+      if (i == small ? !tried[i] : tried[small] && family[i].kind == TF_KIND_MFMA_LDS && same_launch(&family[i], &family[small])) out[i] = 1;
+  }
+  const int r = tf_proposal_from(hw, family, pred, n, out, base_id, bottleneck);
   delete[] pred;
+  delete[] out;
   return r;
 }
 

@@ -1,6 +1,7 @@
 """The library's host-side loop logic (tf_arbiter, tf_refine_hint, tf_proposal_from,
 tf_tune_replay) against the plain-Python loop oracle on synthetic reports, plus sanity of
 the static cost model. No GPU involved."""
+import math
 import os
 import random
 
@@ -249,3 +250,48 @@ def test_case_study3_hint_sequence_through_the_library():
     hints = case_study3_hint_sequence(refine, chain)
     assert hints[:4] == [tf.TF_BN_LATENCY, tf.TF_BN_OCCUPANCY, tf.TF_BN_LATENCY, tf.TF_BN_OCCUPANCY]
     assert (tf.TF_BN_LATENCY, tf.TF_BN_OCCUPANCY) == (lo.LATENCY, lo.OCCUPANCY)
+
+
+def small_problems(n=400):
+    """Aligned problems (whole 16-byte rows) whose product at a fiftieth of the matrix peak, or whose operands at the
+    full memory rate, are done before any tile kernel is predicted to be."""
+    rng = random.Random(31)
+    hw = tf.hw_nominal()
+    size = lambda hi: int(round(math.exp(rng.uniform(0.0, math.log(hi)))))
+    for i in range(n):
+        M, N, K = size(1024), 8 * size(512), 8 * size(1024)
+        if i == 0:
+            M, N, K = 2, 16, 160              # too small for every tile: the streaming kernels are all there is
+        nk = i > 0 and rng.random() < 0.5
+        p = tf.Problem(M, N, K, epi=rng.randrange(4), trans_b=nk)
+        vs = p.variants()
+        tiles = [v for v in vs if v.kind in (tf.TF_KIND_MFMA_LDS, tf.TF_KIND_MFMA_STREAM)]
+        # the instances for a ragged K and the tiles of 192 rows do not count
+        best = min((tf.predict_us(p.desc, hw, v) for v in tiles if v.bm != 192 and not (v.direct_to_lds and K % v.bk)), default=0.0)
+        quick = max(2.0 * M * N * K / (0.02 * hw.bf16_tflops_peak * 1e6), 2.0 * (M * K + K * N + M * N + N) / (hw.hbm_gbs_peak * 1e3))
+        if quick + 2.0 < best:
+            yield p, hw, vs
+
+
+def test_static_pick_of_a_small_problem_takes_any_pointer_and_no_workspace():
+    """The kinds that check no alignment and share no buffer: the call may use any element address, several streams
+    at once, and its first time may be under capture."""
+    anywhere = (tf.TF_KIND_NAIVE, tf.TF_KIND_MFMA_DIRECT, tf.TF_KIND_MFMA_ANY, tf.TF_KIND_MFMA_LDS_ANY)
+    seen = 0
+    for p, hw, vs in small_problems():
+        seen += 1
+        pick = tf.proposal(p.desc, hw, vs, [v.id == 0 for v in vs], 0, tf.TF_BN_UNKNOWN)
+        v = vs[pick]
+        assert v.kind in anywhere and v.workspace_bytes == 0 and v.split_k == 1, (p.desc.M, p.desc.N, p.desc.K, v.name)
+        # the loop's later rounds are free to take anything else, but not the same launch under its other id
+        order, tried = [pick], [u.id == 0 or u.id == pick for u in vs]
+        for _ in range(7):
+            i = tf.proposal(p.desc, hw, vs, tried, 0, tf.TF_BN_UNKNOWN)
+            if i < 0:
+                break
+            order.append(i)
+            tried[i] = True
+        names = [vs[i].name.decode().replace("_or_any", "") for i in order]
+        assert len(set(names)) == len(names), names
+        p.close()
+    assert seen >= 100
