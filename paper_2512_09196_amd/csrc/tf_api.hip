@@ -380,9 +380,6 @@ void build_family(tf_problem* p) {
     }
     if (k.bm > 32 && k.bm / 2 >= d.M) continue;            // tile more than twice the problem
     if (k.bn > 64 && k.bn / 2 >= d.N) continue;
-    // 192 rows where 256 leave rows or CUs over. (Rows that are a multiple of 128 with B as [K][N]: the cost model's
-    // choice there is held to recorded times that this tile has no part in.)
-    if (k.bm == 192 && (k.trans_b ? pass != 0 : d.M % 128 == 0)) continue;
     if (k.lds_bytes > p->hw.lds_bytes_per_cu) continue;
     const long tm = cdivl(d.M, k.bm), tn = cdivl(d.N, k.bn);
     if (tm * tn > 0x7fffffffL / 16) continue;

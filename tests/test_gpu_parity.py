@@ -565,7 +565,7 @@ def test_rows_at_any_two_byte_address(shape, b_as_nk):
 
 
 @pytest.mark.parametrize("b_as_nk", [0, 1])
-@pytest.mark.parametrize("shape", [(193, 264, 64), (385, 520, 320), (191, 256, 576), (200, 776, 1096)])
+@pytest.mark.parametrize("shape", [(193, 264, 64), (385, 520, 320), (191, 256, 576), (200, 776, 1096), (256, 520, 320), (384, 264, 328)])
 def test_tiles_of_192_rows(shape, b_as_nk):
     # one and two row tiles, a whole and a ragged last column tile, one K tile, K whole and ragged
     M, N, K = shape

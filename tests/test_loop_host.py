@@ -295,3 +295,19 @@ def test_static_pick_of_a_small_problem_takes_any_pointer_and_no_workspace():
         assert len(set(names)) == len(names), names
         p.close()
     assert seen >= 100
+
+
+def test_tiles_of_192_rows_are_offered_whatever_the_rows_are_a_multiple_of():
+    for trans_b in (0, 1):
+        for M in (1535, 1536, 1537, 1600, 3072):
+            for K in (2048, 2056):
+                with tf.Problem(M, 6144, K, trans_b=trans_b) as p:
+                    vs = [v for v in p.variants() if v.bm == 192]
+                    hw = tf.hw_nominal()
+                    assert {v.k_rotate for v in vs} == ({0, 1} if K % 64 == 0 else {0}), (M, K, trans_b)
+                    # rows are a whole number of tiles at 1536 and 3072: no slower there than one row less
+                    us = min(tf.predict_us(p.desc, hw, v) for v in p.variants())
+                if M == 1535:
+                    before = us
+                elif M == 1536:
+                    assert us <= 1.01 * before, (K, trans_b, before, us)
