@@ -152,7 +152,8 @@ typedef struct {
                               only on a device whose work-group placement has been probed, see tf_variant_run);
                               1 = the last slice to arrive reduces inside the GEMM kernel (one launch,
                               arrival counters); 0 = a second kernel sums the slices and applies the epilogue */
-  int32_t direct_to_lds;   /* 1: global_load_lds staging; 0: via registers (zero-fills a ragged K tail) */
+  int32_t direct_to_lds;   /* 1: global_load_lds staging; 2: the same in a kernel for a K that is no multiple of bk (its
+                              last K tile overlaps the one before); 0: via registers (zero-fills a ragged K tail) */
   int32_t a_bypass_lds;    /* 1: A fragments are loaded from memory straight into MFMA operand registers, only B is
                               staged in LDS (one wave column per work-group) */
   int32_t trans_a;         /* TF_OP_BATCHED_GEMM_TN, tile kernels: 1 = the A tile is staged as it lies in memory
@@ -174,7 +175,8 @@ typedef struct {
                               any moment (a different, equally valid, summation order) */
   int32_t persistent;      /* TF_OP_BATCHED_GEMM_TN tile kernels: 1 = one work-group per CU walks through many output
                               tiles and fetches the next tile's K steps while the current one multiplies and
-                              writes out (M and N at least one tile); grid = work-groups */
+                              writes out (M and N at least one tile); grid = work-groups; xcd_swizzle 1 = an XCD
+                              takes every eighth item (whole tiles only), 0 = an eighth of the tiles of all items */
   int32_t bn_tail;         /* tile kernels: > 0 = a launch with a lighter last round. Whole rounds of bm x bn tiles (one
                               per CU and round) cover the leading columns; one more round of exactly one work-group
                               per CU shares out the remaining columns of every row panel in tiles of which only

@@ -163,6 +163,7 @@ void build_bgemm_family(tf_problem* p) {
         // one work-group per CU, a multiple of 8 (work-group w runs on XCD w mod 8), no more than the busiest XCD has tiles
         const long busiest = cdivl((long)batch * tm * tn, 8);
         v.persistent = 1;
+        v.xcd_swizzle = k.ragged_mn ? 0 : 1;               // how the tiles are dealt to the XCDs
         v.grid = (int32_t)(8 * std::max<long>(1, std::min<long>(std::max(p->hw.cus, 8) / 8, busiest)));
       }
       v.workspace_bytes = k.trans_a ? 0 : (int64_t)batch * d.M * d.K * 2;
@@ -413,7 +414,7 @@ void build_family(tf_problem* p) {
         v.k_rotate = kr;
         v.kind = TF_KIND_MFMA_LDS; v.bm = k.bm; v.bn = k.bn; v.bk = k.bk; v.waves_m = k.waves_m; v.waves_n = k.waves_n; v.waves_k = k.waves_k;
         v.stages = k.stages; v.split_k = s; v.fused_reduce = (s > 1) ? fused : 0;
-        v.direct_to_lds = k.direct_to_lds; v.a_bypass_lds = k.a_bypass_lds; v.xcd_swizzle = xs;
+        v.direct_to_lds = k.k_tail ? 2 : k.direct_to_lds; v.a_bypass_lds = k.a_bypass_lds; v.xcd_swizzle = xs;
         v.trans_b = k.trans_b;
         v.group_m = (int32_t)std::min<long>(tm, 8);
         v.threads = k.threads; v.lds_bytes = k.lds_bytes;
@@ -1263,9 +1264,12 @@ extern "C" int32_t tf_variant_kernel_name(const tf_variant_desc* v, char* buf, i
     case TF_KIND_NAIVE: n = snprintf(buf, cap, "tf_gemm_naive_kernel"); break;
     case TF_KIND_MFMA_DIRECT: n = snprintf(buf, cap, "tf_gemm_mfma_direct_kernel"); break;
     case TF_KIND_MFMA_LDS: case TF_KIND_MFMA_LDS_ANY:
+      // (a counter file may hold several instances of one configuration: each has a kernel name of its own)
       snprintf(cfg, sizeof(cfg), "tf::LdsCfg<%d, %d, %d, %d, %d, %d, %s, %s, %d, %s, %s, %d>", v->bm, v->bn, v->bk, v->waves_m,
                v->waves_n, v->stages, b(v->direct_to_lds), b(v->a_bypass_lds), v->waves_k, b(v->trans_a), b(v->trans_b), v->bn);
-      n = snprintf(buf, cap, "%s%s", v->bn_tail ? "tf_gemm_mixed_kernel<" : v->persistent ? "tf_bgemm_persist_kernel<"
+      n = snprintf(buf, cap, "%s%s", v->bn_tail ? "tf_gemm_mixed_kernel<"
+                                     : v->persistent ? (v->xcd_swizzle ? "tf_bgemm_persist_kernel<" : "tf_bgemm_persist_ragged_kernel<")
+                                     : v->direct_to_lds == 2 ? "tf_gemm_lds_ktail_kernel<"
                                      : v->stream_k ? "tf_gemm_lds_kernel<tf::StreamKCfg<" : "tf_gemm_lds_kernel<", cfg);
       break;
     case TF_KIND_MFMA_STREAM:

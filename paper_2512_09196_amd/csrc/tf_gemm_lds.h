@@ -1221,9 +1221,8 @@ struct RaggedKCfg : Base {
   static constexpr bool KTAIL = true;
 };
 
-template <class C, int K_TAIL>
-__global__ void __launch_bounds__(C::THREADS) tf_gemm_lds_kernel(const GemmParams p) {
-  static_assert(K_TAIL == 1, "tf_gemm_lds_kernel<C> is the other one");
+template <class C>
+__global__ void __launch_bounds__(C::THREADS) tf_gemm_lds_ktail_kernel(const GemmParams p) {
   gemm_tile_body<RaggedKCfg<C>>(p);
 }
 
@@ -1435,9 +1434,8 @@ template <class C>
 __global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_kernel(const GemmParams p) {
   bgemm_persist_body<C, false>(p);
 }
-template <class C, int RAGGED>
-__global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_kernel(const GemmParams p) {
-  static_assert(RAGGED == 1, "tf_bgemm_persist_kernel<C> is the other one");
+template <class C>
+__global__ void __launch_bounds__(C::THREADS) tf_bgemm_persist_ragged_kernel(const GemmParams p) {
   bgemm_persist_body<C, true>(p);
 }
 
@@ -1447,7 +1445,7 @@ static void launch_persist(const GemmParams& p, dim3 grid, hipStream_t stream) {
 }
 template <class C>
 static void launch_persist_ragged(const GemmParams& p, dim3 grid, hipStream_t stream) {
-  hipLaunchKernelGGL((tf_bgemm_persist_kernel<C, 1>), grid, dim3(C::THREADS), C::PERSIST_LDS_BYTES, stream, p);
+  hipLaunchKernelGGL(tf_bgemm_persist_ragged_kernel<C>, grid, dim3(C::THREADS), C::PERSIST_LDS_BYTES, stream, p);
 }
 
 template <class C>
@@ -1486,13 +1484,13 @@ static LdsKernelInfo make_info() {
 
 template <class C>
 static void launch_lds_ragged(const GemmParams& p, dim3 grid, hipStream_t stream) {
-  hipLaunchKernelGGL((tf_gemm_lds_kernel<C, 1>), grid, dim3(C::THREADS), C::LDS_BYTES, stream, p);
+  hipLaunchKernelGGL(tf_gemm_lds_ktail_kernel<C>, grid, dim3(C::THREADS), C::LDS_BYTES, stream, p);
 }
 template <class C>
 static LdsKernelInfo make_ragged_info() {
   LdsKernelInfo k = describe<C>();
   k.k_tail = 1;
-  k.func = (const void*)tf_gemm_lds_kernel<C, 1>;
+  k.func = (const void*)tf_gemm_lds_ktail_kernel<C>;
   k.launch = launch_lds_ragged<C>;
   return k;
 }
@@ -1520,7 +1518,7 @@ static LdsKernelInfo make_persist_ragged_info() {
   LdsKernelInfo k = describe<C>();
   k.persistent = 1; k.ragged_mn = 1;
   k.lds_bytes = C::PERSIST_LDS_BYTES;
-  k.func = (const void*)tf_bgemm_persist_kernel<C, 1>;
+  k.func = (const void*)tf_bgemm_persist_ragged_kernel<C>;
   k.launch = launch_persist_ragged<C>;
   return k;
 }

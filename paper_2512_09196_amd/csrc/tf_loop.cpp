@@ -148,6 +148,7 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
       // one work-group per CU walks through the tiles and never lets its ring drain: the tile model over all
       // tiles, without the start-up that every work-group of the plain kernels pays
       v1.persistent = 0;
+      v1.xcd_swizzle = 1;
       v1.grid = (int32_t)(((pr->M + v->bm - 1) / v->bm) * (long)((pr->N + v->bn - 1) / v->bn) * (long)items);
       return fmax(0.8 * tf_predict_us(&one, hw, &v1), floor_us + 4.0);
     }
@@ -341,7 +342,7 @@ static bool matches_hint(int bn, const tf_hw* hw, const tf_variant_desc* b, cons
     case TF_BN_MFMA:          // only quantisation and LDS traffic per MFMA are left
       return area_v >= area_b && fill_v >= fill_b - 1e-9;
     case TF_BN_LDS_CONFLICT:  // other staging path or other tile shape
-      return v->direct_to_lds != b->direct_to_lds || v->bn != b->bn;
+      return !v->direct_to_lds != !b->direct_to_lds || v->bn != b->bn;
     case TF_BN_OCCUPANCY:     // fewer registers / less LDS per work-group
       return area_v < area_b || (area_v == area_b && v->lds_bytes < b->lds_bytes);
     case TF_BN_LATENCY:       // deeper staging (more buffers, or a longer K tile: fewer hand-overs), or bigger tiles to amortise it

@@ -165,3 +165,22 @@ def test_counter_files_handed_to_a_problem_are_checked():
         p.set_counter_files([])
         with pytest.raises(tf.TfError):
             p.set_counter_files([os.path.join(G, "no_such_file.csv")])
+
+
+def test_instances_of_one_configuration_are_told_apart(tmp_path):
+    """A whole and a ragged K on one tile, and the batched product's two persistent kernels: one counter file with rows
+    of all four leads every variant to its own."""
+    problems = [(dict(M=512, N=512, K=512), b"lds_128x128x64_w2x4_s3_direct_sk1"), (dict(M=512, N=512, K=520), b"lds_128x128x64_w2x4_s3_direct_sk1"),
+                (dict(M=256, N=256, K=256, op=tf.TF_OP_BATCHED_GEMM_TN, batch=8), b"bgemm_128x128x64_w2x4_s3_persist"),
+                (dict(M=264, N=256, K=256, op=tf.TF_OP_BATCHED_GEMM_TN, batch=8), b"bgemm_128x128x64_w2x4_s3_persist")]
+    subs = []
+    for kw, name in problems:
+        with tf.Problem(**kw) as p:
+            subs.append(tf.kernel_substr([v for v in p.variants() if v.name == name][0]))
+    csv = tmp_path / "c.csv"
+    csv.write_text('"Dispatch_Id","Kernel_Name","Counter_Name","Counter_Value"\n'
+                   + "".join('%d,"void tf::%s >(tf::GemmParams)","WRITE_SIZE",%d\n' % (i + 1, s, 1000 * (i + 1)) for i, s in enumerate(subs)))
+    for i, s in enumerate(subs):
+        r = blank_report(t_med_us=100.0)
+        tf.report_set_counters(r, tf.hw_nominal(), str(csv), s)
+        assert r.hbm_write_gbs == pytest.approx(1000.0 * (i + 1) * 1024 / 100.0 * 1e-3, rel=1e-9), s
