@@ -143,8 +143,13 @@ void build_bgemm_family(tf_problem* p) {
       const tf::LdsKernelInfo& k = tab[i];
       if (!k.direct_to_lds || k.a_bypass_lds || k.waves_k != 1 || k.stream_k || k.trans_b || k.bk != 64 || k.bn_tail || k.k_tail) continue;
       if (pass == 0 && !k.trans_a) continue;
-      // the persistent kernel (its tiles at a ragged end begin a whole tile before it)
-      if (k.persistent && (k.ragged_mn != 0) != (d.M % k.bm || d.N % k.bn || batch % 8)) continue;
+      // the persistent kernels. Whole tiles: the ones that deal out whole items; ragged tiles: the one whose tiles at a
+      // ragged end begin a whole tile before it and which deals out tiles; whole tiles of a number of items that is no
+      // multiple of eight: either, items keep to one L2 and tiles come out even (us, items / tiles: 33 x 512 x 512 x 256
+      // 13.4 / 14.5, 63 x 512 x 512 x 256 19.3 / 19.8; 63 x 1024 x 1024 x 256 88.4 / 85.9, 12 x 1024 x 1024 x 256
+      // 19.6 / 15.5, 3 x 2048 x 2048 x 512 48.7 / 23.4)
+      const bool ragged = d.M % k.bm || d.N % k.bn;
+      if (k.persistent && (k.ragged_mn ? !ragged && batch % 8 == 0 : ragged)) continue;
       if (k.persistent && (pass == 1 || d.M < k.bm || d.N < k.bn || (double)cdivl(d.M, k.bm) * cdivl(d.N, k.bn) * batch * (d.K / 64) >= 2147483648.0)) continue;
       if (pass == 1 && (k.trans_a || k.bm < 64 || k.bn < 64 || (k.bm == 128 && k.bn == 128 && k.waves_m * k.waves_n == 4 && k.stages == 2))) continue;
       if (k.bm > 32 && k.bm / 2 >= d.M) continue;
@@ -161,7 +166,7 @@ void build_bgemm_family(tf_problem* p) {
       v.grid = (int32_t)(tm * tn * batch);
       if (k.persistent) {
         // one work-group per CU, a multiple of 8 (work-group w runs on XCD w mod 8), no more than the busiest XCD has tiles
-        const long busiest = cdivl((long)batch * tm * tn, 8);
+        const long busiest = k.ragged_mn ? cdivl((long)batch * tm * tn, 8) : cdivl(batch, 8) * tm * tn;
         v.persistent = 1;
         v.xcd_swizzle = k.ragged_mn ? 0 : 1;               // how the tiles are dealt to the XCDs
         v.grid = (int32_t)(8 * std::max<long>(1, std::min<long>(std::max(p->hw.cus, 8) / 8, busiest)));
@@ -170,7 +175,7 @@ void build_bgemm_family(tf_problem* p) {
       VariantImpl im{};
       im.lds_index = i; im.ktiles_per_split = (int)cdivl(d.K, 64); im.tiles_m = (int)tm; im.tiles_n = (int)tn; im.counter_bytes = 0;
       snprintf(v.name, sizeof(v.name), "bgemm_%dx%dx%d_w%dx%d_s%d_%s", k.bm, k.bn, k.bk, k.waves_m, k.waves_n, k.stages,
-               k.persistent ? "persist" : k.trans_a ? "ldstrans" : "pretrans");
+               k.persistent ? (k.ragged_mn ? "ragged_persist" : "persist") : k.trans_a ? "ldstrans" : "pretrans");
       add_variant(p, v, im);
     }
   }

@@ -51,7 +51,7 @@ struct LdsKernelInfo {
   int stream_k;           // 1: instance with the loop over (tile, K range) segments compiled in (stream-K variants only)
   int persistent;         // 1: tf_bgemm_persist_kernel (one work-group per CU walks through many tiles; grid.x = work-groups)
   int bn_tail;            // > 0: tf_gemm_mixed_kernel, width of the tiles of its lighter last round
-  int ragged_mn;          // 1: tf_bgemm_persist_kernel for ragged tiles or a batch that is no multiple of eight (and only for those)
+  int ragged_mn;          // 1: tf_bgemm_persist_ragged_kernel, for ragged tiles or a batch that is no multiple of eight (and only for those)
   int k_tail;             // 1: instance for a K that is no multiple of bk (and only for that)
   const void* func;       // kernel symbol, for hipFuncGetAttributes / occupancy queries
   void (*launch)(const GemmParams&, dim3 grid, hipStream_t);

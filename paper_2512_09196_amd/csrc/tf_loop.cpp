@@ -150,7 +150,9 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
       v1.persistent = 0;
       v1.xcd_swizzle = 1;
       v1.grid = (int32_t)(((pr->M + v->bm - 1) / v->bm) * (long)((pr->N + v->bn - 1) / v->bn) * (long)items);
-      return fmax(0.8 * tf_predict_us(&one, hw, &v1), floor_us + 4.0);
+      // (dealt out as whole items, eight XCDs wait for the ones with the most)
+      const double share = v->xcd_swizzle ? 8.0 * cdiv((long)items, 8) / items : 1.0;
+      return fmax(0.8 * tf_predict_us(&one, hw, &v1), floor_us + 4.0) * share;
     }
     // (a work-group of the plain kernels reads, multiplies and then writes, and the chip's reads and writes overlap
     // less for it: 32 x 1024 x 1024 x 256, 168 MB, takes 44.7-52.2 us in their tiles, 34.9 us in the persistent kernel)

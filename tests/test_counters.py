@@ -172,7 +172,7 @@ def test_instances_of_one_configuration_are_told_apart(tmp_path):
     of all four leads every variant to its own."""
     problems = [(dict(M=512, N=512, K=512), b"lds_128x128x64_w2x4_s3_direct_sk1"), (dict(M=512, N=512, K=520), b"lds_128x128x64_w2x4_s3_direct_sk1"),
                 (dict(M=256, N=256, K=256, op=tf.TF_OP_BATCHED_GEMM_TN, batch=8), b"bgemm_128x128x64_w2x4_s3_persist"),
-                (dict(M=264, N=256, K=256, op=tf.TF_OP_BATCHED_GEMM_TN, batch=8), b"bgemm_128x128x64_w2x4_s3_persist")]
+                (dict(M=264, N=256, K=256, op=tf.TF_OP_BATCHED_GEMM_TN, batch=8), b"bgemm_128x128x64_w2x4_s3_ragged_persist")]
     subs = []
     for kw, name in problems:
         with tf.Problem(**kw) as p:

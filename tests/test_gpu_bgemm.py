@@ -157,3 +157,17 @@ def test_ragged_tiles_of_the_persistent_kernels(shape):
     A, B = wl.make_bgemm(nb, M, N, K, seed=400 + M)
     ran = check_all(nb, M, N, K, A, B, lda=M + 8, ldb=N + 16, ldy=N + 4, extra_rows=1)
     assert any(n.endswith("persist") for n in ran)
+
+
+@pytest.mark.parametrize("shape", [(33, 264, 392, 64), (40, 392, 520, 128), (64, 384, 384, 64), (33, 384, 384, 64), (35, 256, 640, 192)])
+def test_persistent_kernels_with_several_tiles_per_work_group(shape):
+    # ragged tiles of one and two K steps, whole tiles of one, whole tiles of a batch that is no multiple of eight: a
+    # work-group goes on to another tile (whole to overlapped and back), and with one K step its ring is two tiles ahead
+    nb, M, N, K = shape
+    A, B = wl.make_bgemm(nb, M, N, K, seed=500 + M)
+    ran = check_all(nb, M, N, K, A, B, only=lambda v: v.persistent)
+    tiles = nb * -(-M // 128) * -(-N // 128)
+    with tf.Problem(M, N, K, op=tf.TF_OP_BATCHED_GEMM_TN, batch=nb) as prob:
+        assert all(tiles > v.grid for v in prob.variants() if v.persistent)
+    whole = M % 128 == 0 and N % 128 == 0
+    assert len(ran) == (1 if not whole else 2 if nb % 8 == 0 else 3)

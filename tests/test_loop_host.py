@@ -311,3 +311,17 @@ def test_tiles_of_192_rows_are_offered_whatever_the_rows_are_a_multiple_of():
                     before = us
                 elif M == 1536:
                     assert us <= 1.01 * before, (K, trans_b, before, us)
+
+
+def test_persistent_batched_kernels_of_every_batch():
+    hw = tf.hw_nominal()
+    for batch in (1, 3, 8, 12, 31, 32, 63):
+        for M in (1024, 1000):
+            with tf.Problem(M, 1024, 256, op=tf.TF_OP_BATCHED_GEMM_TN, batch=batch) as p:
+                vs = p.variants()
+                got = {v.name.decode().split("x64_")[1] for v in vs if v.persistent}
+                whole, ragged = {"w2x4_s3_persist", "w2x2_s3_persist"}, {"w2x4_s3_ragged_persist"}
+                assert got == (ragged if M % 128 else whole if batch % 8 == 0 else whole | ragged), (batch, M, got)
+                # the static pick deals out tiles wherever items do not come out even
+                pick = vs[tf.proposal(p.desc, hw, vs, [v.id == 0 for v in vs], 0, tf.TF_BN_UNKNOWN)]
+                assert not (batch % 8 and pick.persistent and pick.xcd_swizzle), (batch, M, pick.name)
