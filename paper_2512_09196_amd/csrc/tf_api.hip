@@ -151,7 +151,7 @@ void build_bgemm_family(tf_problem* p) {
       const bool ragged = d.M % k.bm || d.N % k.bn;
       if (k.persistent && (k.ragged_mn ? !ragged && batch % 8 == 0 : ragged)) continue;
       if (k.persistent && (pass == 1 || d.M < k.bm || d.N < k.bn || (double)cdivl(d.M, k.bm) * cdivl(d.N, k.bn) * batch * (d.K / 64) >= 2147483648.0)) continue;
-      if (pass == 1 && (k.trans_a || k.bm < 64 || k.bn < 64 || (k.bm == 128 && k.bn == 128 && k.waves_m * k.waves_n == 4 && k.stages == 2))) continue;
+      if (pass == 1 && (k.trans_a || k.bm == 192 || k.bm < 64 || k.bn < 64 || (k.bm == 128 && k.bn == 128 && k.waves_m * k.waves_n == 4 && k.stages == 2))) continue;
       if (k.bm > 32 && k.bm / 2 >= d.M) continue;
       if (k.bn > 64 && k.bn / 2 >= d.N) continue;
       if (k.lds_bytes > p->hw.lds_bytes_per_cu) continue;
