@@ -325,9 +325,13 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
                                  ? 3.0 + 4.0 * (double)pr->K * pr->N / (0.6 * hw->hbm_gbs_peak * 1e3) : 0.0;
   // tiles dealt round-robin over the XCDs (offered for one row of tiles): every row of B is then pulled through all
   // eight L2s at once, which streams about a tenth faster than a contiguous run of columns per XCD
-  // (and a K tile of 128 streamed 8-10 % slower than one of 64 on 16 x 8192 x 8192: 28.8-29.3 against 26.6-27.1 us)
-  // (not where B is [N][K] and each work-group reads rows of its own: 16 x 8192 x 8192 29.3 us in runs, 29.9 round-robin)
-  const double spread = (v->xcd_swizzle || v->trans_b ? 1.0 : 0.9) * (bk > 64 ? 1.12 : 1.0);
+  // (and a K tile of 128 streams 3-13 % slower than one of 64, the same kernel otherwise: 16 x 8192 x 8192 29.6 against
+  // 27.4 us, 1 x 4096 x 11008 21.4 / 18.9, 8 x 4096 x 4096 12.3 / 11.3, 16 x 4096 x 11008 22.0 / 20.5, 4 x 11008 x 4096
+  // 21.6 / 20.8, 32 x 8192 x 4096 18.5 / 17.9. Over 40 skinny problems whose pick the factor moves, the picks were 3.8,
+  // 4.0 and 4.5 % behind the best of them with 1.08, 1.09 and 1.12; 1.08 and 1.09 part on two problems in 900)
+  // (not where B is [N][K] and each work-group reads rows of its own: over 24 skinny problems whose pick that moves,
+  // picks in runs were 10 % faster than the round-robin ones, e.g. 32 x 8576 x 3840 20.1 against 24.2 us)
+  const double spread = (v->xcd_swizzle || v->trans_b ? 1.0 : 0.9) * (bk > 64 ? 1.09 : 1.0);
   return fmax(us * rot, (hbm_us + ws_us) / (0.75 * inflight) * spread) + 3.6 + reduce_us + fused_tail_us + pretrans_us;
 }
 

@@ -325,3 +325,17 @@ def test_persistent_batched_kernels_of_every_batch():
                 # the static pick deals out tiles wherever items do not come out even
                 pick = vs[tf.proposal(p.desc, hw, vs, [v.id == 0 for v in vs], 0, tf.TF_BN_UNKNOWN)]
                 assert not (batch % 8 and pick.persistent and pick.xcd_swizzle), (batch, M, pick.name)
+
+
+def test_a_long_k_tile_streams_slower_by_what_was_measured():
+    """Measured times (us) of two kernels of 32 x 64 tiles that differ in the K tile only, 128 against 64, on 16 x 8192 x
+    8192, 1 x 4096 x 11008, 8 x 4096 x 4096, 16 x 4096 x 11008, 4 x 11008 x 4096 and 32 x 8192 x 4096: on a problem that
+    is bound by memory the model's ratio is no further from their mean than they are."""
+    import statistics
+    ratios = [a / b for a, b in ((29.6, 27.4), (21.4, 18.9), (12.3, 11.3), (22.0, 20.5), (21.6, 20.8), (18.5, 17.9))]
+    hw = tf.hw_nominal()
+    M, N, K = 16, 32768, 4096
+    with tf.Problem(M, N, K) as p:
+        us = [tf.predict_us(p.desc, hw, v) for v in p.variants() if v.name == b"lds_32x64x128_w1x2_s4_direct_rr_sk1"][0]
+    memory = 0.9 * 2.0 * (M * K + K * N + M * N + N) / (0.75 * hw.hbm_gbs_peak * 1e3)      # tiles dealt over the XCDs
+    assert abs((us - 3.6) / memory - statistics.mean(ratios)) <= statistics.stdev(ratios)
