@@ -234,7 +234,7 @@ void build_any_family(tf_problem* p) {
     v.kind = TF_KIND_MFMA_ANY; v.bm = k.tile; v.bn = k.tile; v.bk = 64; v.waves_m = 1; v.waves_n = 1; v.waves_k = k.waves;
     v.stages = 2; v.split_k = 1; v.trans_b = k.trans_b; v.xcd_swizzle = 1; v.group_m = (int32_t)std::min<long>(tm, 8);
     v.threads = k.threads; v.lds_bytes = k.lds_bytes; v.grid = (int32_t)(tm * tn);
-    snprintf(v.name, sizeof(v.name), "any_%dx%dx64_k%d%s", k.tile, k.tile, k.waves, k.trans_b ? "_bnk" : "");
+    snprintf(v.name, sizeof(v.name), "any_%dx%dx64%s_k%d", k.tile, k.tile, k.trans_b ? "_bnk" : "", k.waves);
     VariantImpl im{};
     im.lds_index = i; im.ktiles_per_split = (int)cdivl(d.K, 64); im.tiles_m = (int)tm; im.tiles_n = (int)tn;
     add_variant(p, v, im);
