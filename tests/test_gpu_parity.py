@@ -521,17 +521,35 @@ def test_ragged_k_staged_directly(shape, b_as_nk):
     direct = lambda v: v.kind == tf.TF_KIND_MFMA_LDS and v.direct_to_lds and K % v.bk
     ran = check_all_variants(M, N, K, A, Bd, bias, lda=K + 16, ldb=(K if b_as_nk else N) + 8, only=direct, trans_b=b_as_nk)
     assert len(ran) >= 6
-    # an infinity in the overlap (the k right before the last whole multiple of 64): +-inf results, never NaN
-    A2 = A.copy()
-    A2[0, K // 64 * 64 - 1] = 0x7F80
-    z = wl.bf16_bits_to_f32(A2).astype(np.float64) @ wl.bf16_bits_to_f32(B).astype(np.float64)
-    dA, dB, dbias = gu.to_dev(A2), gu.to_dev(Bd), gu.to_dev(bias)
-    out = gu.OutBuf(M, N, f32=True)
+    check_infinities_in_the_overlap(M, N, K, A, B, bias, b_as_nk, direct)
+
+
+def check_infinities_in_the_overlap(M, N, K, A, B, bias, b_as_nk, only, at=0):
+    """An infinity where the last K tile overlaps the one before (its first and last k), once in A and once in B: that
+    row or column of the fp32 result is infinities of the other operand's sign, never NaN. If the overlap of only one
+    operand were zeroed, the infinity of the other would meet those zeros."""
+    dbias = gu.to_dev(bias)
+    place = lambda bits: gu.to_dev(np.concatenate([np.full(at, 0x7FC1, np.uint16), bits.ravel()]))[at:]
     with tf.Problem(M, N, K, epi=tf.TF_EPI_NONE_F32, trans_b=b_as_nk) as prob:
-        for v in [v for v in prob.variants() if direct(v)]:
-            print("inf", shape, b_as_nk, v.name.decode(), flush=True)
-            got, intact, _ = gu.run_variant(prob, v.id, dA, dB, dbias, out)
-            assert intact and np.array_equal(got[0], z[0]), v.name.decode()      # row 0: infinities of B's sign
+        for k in sorted({K - 64, K // 64 * 64 - 1}):
+            for in_a in (True, False):
+                A2, B2 = A.copy(), B.copy()
+                if in_a:
+                    A2[0, k] = 0x7F80
+                    want = np.where(wl.bf16_bits_to_f32(B)[k] > 0, np.inf, -np.inf)
+                    assert np.all(wl.bf16_bits_to_f32(B)[k] != 0)
+                else:
+                    B2[k, N - 1] = 0x7F80
+                    want = np.where(wl.bf16_bits_to_f32(A)[:, k] > 0, np.inf, -np.inf)
+                    assert np.all(wl.bf16_bits_to_f32(A)[:, k] != 0)
+                dA, dB = place(A2), place(np.ascontiguousarray(B2.T) if b_as_nk else B2)
+                out = gu.OutBuf(M, N, f32=True)
+                for v in [v for v in prob.variants() if only(v)]:
+                    print("inf", (M, N, K), b_as_nk, "k", k, "in", "A" if in_a else "B", v.name.decode(), flush=True)
+                    got, intact, _ = gu.run_variant(prob, v.id, dA, dB, dbias, out)
+                    assert intact and np.array_equal(got[0] if in_a else got[:, N - 1], want), v.name.decode()
+                    rest = np.delete(got, 0, 0) if in_a else np.delete(got, N - 1, 1)
+                    assert np.isfinite(rest).all(), v.name.decode()
 
 
 # tiles of 32 and 64: one and two column tiles that overlap, rows past M, K of one tile, a K tail of one value and of 63
@@ -552,7 +570,7 @@ def test_rows_at_any_two_byte_address(shape, b_as_nk):
         out = gu.OutBuf(M, N, ldy=ldy, f32=f32)
         with tf.Problem(M, N, K, lda=lda, ldb=ldb, ldy=ldy, epi=epi, trans_b=b_as_nk) as prob:
             vs = [v for v in prob.variants() if v.kind == tf.TF_KIND_MFMA_ANY]
-            assert vs
+            assert {v.bm for v in vs} == {t for t in (32, 64) if b_as_nk or N >= t}
             for v in vs:
                 name = v.name.decode()
                 print("case", shape, b_as_nk, "epi", epi, "variant", name, flush=True)
@@ -562,6 +580,14 @@ def test_rows_at_any_two_byte_address(shape, b_as_nk):
                 err = np.abs(got - want[epi])
                 bound = gu.preact_bound(z, s, K) if f32 else gu.strict_bound(want[epi], z, s, K)
                 assert np.all(err <= bound), "%s: worst excess %g" % (name, (err - bound).max())
+
+
+# the overlap of the last K tile: 63 values, one, five (an odd number, half a register at its end)
+@pytest.mark.parametrize("b_as_nk", [0, 1])
+@pytest.mark.parametrize("shape", [(33, 65, 65), (32, 64, 127), (65, 127, 129), (70, 95, 1023), (40, 99, 763)])
+def test_infinities_in_the_overlap_at_any_two_byte_address(shape, b_as_nk):
+    M, N, K = shape
+    check_infinities_in_the_overlap(M, N, K, *wl.make_custom(M, N, K, seed=950 + K), b_as_nk, lambda v: v.kind == tf.TF_KIND_MFMA_ANY, at=1)
 
 
 @pytest.mark.parametrize("b_as_nk", [0, 1])
