@@ -75,7 +75,7 @@ typedef enum {
   TF_KIND_BGEMM_TN_NAIVE = 6,/* TF_OP_BATCHED_GEMM_TN baseline: one thread per output element (its tile kernels
                                are TF_KIND_MFMA_LDS, see trans_a)                                       */
   TF_KIND_MFMA_ANY = 8,      /* rows of A, B and Y at any two-byte address (where the tile kernels' 16-byte pieces do
-                               not fit): bm x bn tiles, the waves_k waves of a work-group share K           */
+                               not fit, and small problems): bm x bn tiles, the waves_k waves of a work-group share K */
   TF_KIND_MFMA_LDS_ANY = 9, /* a tile kernel (fields as for TF_KIND_MFMA_LDS; no K slices, no workspace) for calls whose
                                pointers have the alignment it needs; other calls run the any-address or the
                                one-wave kernel. What the static pick of a small problem takes, see tf_proposal */

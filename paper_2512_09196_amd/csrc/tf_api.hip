@@ -217,7 +217,7 @@ void build_sin_family(tf_problem* p) {
   }
 }
 
-// Problems whose rows the 16-byte pieces of the tile kernels do not fit. The last K tile starts at K - 64 and the
+// Problems whose rows the 16-byte pieces of the tile kernels do not fit, and small ones (build_small_family). The last K tile starts at K - 64 and the
 // last column tile of a [K][N] B at N - tile: smaller problems stay with the one-wave kernel. Offsets inside a tile
 // (64 rows) are kept in 32 bits.
 void build_any_family(tf_problem* p) {

@@ -1252,9 +1252,11 @@ __global__ void __launch_bounds__(CM::THREADS) tf_gemm_mixed_kernel(const GemmPa
 //     an eighth of the tiles of all items, in item order, instead; the last tile of a row or column of tiles begins at
 //     M - BM or N - BN, so every transfer stays inside the item, and stores only what its neighbour does not.
 //     An instance of its own: in one kernel for both, 32 x 1024 x 1024 x 256 went from 35.2 to 38.3 us. Against the
-//     one-tile work-groups that had such sizes to themselves, tile picked / best tile / here (us): 32 x 1000 x 1000 x
-//     256 56.3 / 47.2 / 42.2, 48 x 568 x 896 x 128 37.0 / 28.3 / 22.2, 57 x 880 x 288 x 64 26.3 / 21.0 / 14.4,
-//     27 x 320 x 848 x 256 23.2 / 16.6 / 14.1.
+//     one-tile work-groups that had such sizes to themselves, tile picked / best tile / here (us): 48 x 568 x 896 x
+//     128 37.0 / 28.3 / 22.2, 57 x 880 x 288 x 64 26.3 / 21.0 / 14.4, 27 x 320 x 848 x 256 23.2 / 16.6 / 14.1,
+//     64 x 264 x 392 x 512 30.5 / 22.6 / 22.1. Items of many tiles: 32 x 1000 x 1000 x 192 54.3 / 37.7 / 38.4,
+//     K = 256 56.3 / 39.8 / 41.9, K = 512 93.1 / 54.7 / 71.2, K = 1024 155.0 / 82.8 / 114.9 - tiles of 256 x 256 are
+//     faster there from K = 320 on, and of whole tiles from K = 384 on (tf_predict_us does not see that yet).
 //   * one "flat step" = one K step of one tile. At flat step f the transfers of step f + D (D = STAGES - 1)
 //     are issued into the buffer that step f - 1 has just left. Past the end the last step is fetched again
 //     (into a buffer nobody reads), which keeps the number of transfers in flight, and so the vmcnt waits,
