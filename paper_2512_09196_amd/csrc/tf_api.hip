@@ -217,9 +217,9 @@ void build_sin_family(tf_problem* p) {
   }
 }
 
-// Problems whose rows the 16-byte pieces of the tile kernels do not fit, and small ones (build_small_family). The last K tile starts at K - 64 and the
-// last column tile of a [K][N] B at N - tile: smaller problems stay with the one-wave kernel. Offsets inside a tile
-// (64 rows) are kept in 32 bits.
+// Problems whose rows the 16-byte pieces of the tile kernels do not fit, and small ones (build_small_family). The last
+// K tile starts at K - 64 and the last column tile of a [K][N] B at N - tile: smaller problems stay with the one-wave
+// kernel. Offsets inside a tile (64 rows) are kept in 32 bits.
 void build_any_family(tf_problem* p) {
   const tf_problem_desc& d = p->desc;
   if (d.M <= 0 || d.N <= 0 || d.K < 64 || d.lda >= (1 << 24) || d.ldb >= (1 << 24)) return;
@@ -263,9 +263,10 @@ void build_small_family(tf_problem* p) {
     const double us = tf_predict_us(&d, &p->hw, &v);
     // (the tiles of 192 rows and the direct staging of a ragged K do not move the line)
     if (v.bm != 192 && !(v.direct_to_lds && v.kind == TF_KIND_MFMA_LDS && d.K % v.bk)) best = std::min(best, us);
+    if (quick >= best) return;
     if (v.kind == TF_KIND_MFMA_LDS && v.workspace_bytes == 0 && us < best_plain) { best_plain = us; plain = v.id; }
   }
-  if (quick >= best || plain < 0) return;
+  if (plain < 0) return;
   int any = 1;                                             // the one-wave kernel
   build_any_family(p);
   for (const tf_variant_desc& v : p->family)
