@@ -241,11 +241,54 @@ void build_any_family(tf_problem* p) {
   }
 }
 
+// Few output tiles: the waves of a work-group share K, and where tiles alone leave the chip idle so do work-groups.
+void build_kshare_family(tf_problem* p) {
+  const tf_problem_desc& d = p->desc;
+  if (d.K < 64) return;
+  const int cus = p->hw.cus > 0 ? p->hw.cus : 256;
+  const long nkt = cdivl(d.K, 64);
+  const tf::KshareKernelInfo* tab = tf::kshare_kernel_table();
+  for (int i = 0; i < tf::kshare_kernel_count(); ++i) {
+    const tf::KshareKernelInfo& k = tab[i];
+    if ((k.trans_b != 0) != (d.trans_b != 0) || k.lds_bytes > p->hw.lds_bytes_per_cu) continue;
+    if (k.bm > 32 && k.bm / 2 >= d.M) continue;
+    if (k.bn > 32 && k.bn / 2 >= d.N) continue;
+    const long tm = cdivl(d.M, k.bm), tn = cdivl(d.N, k.bn), tiles = tm * tn;
+    if (tiles > 8L * cus) continue;
+    // slices: an XCD takes one or several, or shares one; every wave has a K tile, and the work-groups one round of the
+    // CUs; of the counts that allows the three largest (of 187 problems timed with every count, none was faster with another)
+    const long round = (long)cus * std::max(1, p->hw.lds_bytes_per_cu / k.lds_bytes);
+    std::vector<int> counts;
+    for (int s : {2, 4, 8, 16})
+      if (cdivl(nkt, s) >= k.waves && cdivl(nkt, s) * (s - 1) < nkt && tiles * s <= round) counts.push_back(s);
+    if (counts.size() > 3) counts.erase(counts.begin());
+    counts.insert(counts.begin(), 1);
+    for (int s : counts) {
+      const long per = cdivl(nkt, s);
+      tf_variant_desc v;
+      memset(&v, 0, sizeof(v));
+      v.kind = TF_KIND_MFMA_KSHARE; v.bm = k.bm; v.bn = k.bn; v.bk = 64; v.waves_m = 1; v.waves_n = 1; v.waves_k = k.waves;
+      v.stages = k.stages; v.split_k = s; v.fused_reduce = s > 1 ? 1 : 0; v.direct_to_lds = 1; v.trans_b = k.trans_b;
+      v.xcd_swizzle = 1; v.group_m = (int32_t)std::min<long>(tm, 8);
+      v.threads = k.threads; v.lds_bytes = k.lds_bytes;
+      v.grid = (int32_t)(s == 1 ? tiles : s <= 8 ? 8 * cdivl(tiles, 8 / s) : tiles * s);
+      VariantImpl im{};
+      im.lds_index = i; im.ktiles_per_split = (int)per; im.tiles_m = (int)tm; im.tiles_n = (int)tn;
+      im.counter_bytes = s > 1 ? (size_t)((tiles * 8 + 255) / 256 * 256) : 0;
+      v.workspace_bytes = s > 1 ? (int64_t)(im.counter_bytes + (size_t)s * d.M * d.N * 4) : 0;
+      snprintf(v.name, sizeof(v.name), "kshare_%dx%dx64_k%d_s%d%s_sk%d%s", k.bm, k.bn, k.waves, k.stages, k.trans_b ? "_bnk" : "", s,
+               s > 1 ? "f" : "");
+      add_variant(p, v, im);
+    }
+  }
+}
+
 // Small problems: the ones whose product at a fiftieth of the matrix peak, or whose operands at the full memory rate,
 // are done before any tile kernel is. There the static pick used to be the one-wave kernel, and programs run it on
 // operands at any element address, from several streams at once, and first thing under capture: none of that goes
 // with 16-byte pieces and K slices in a shared workspace. So the pick there stays among variants that allow it: the
-// any-address kernels, and one tile kernel without K slices that hands the calls it cannot take to them. (The line is
+// any-address kernels, and kernels without K slices that hand the calls they cannot take to them: one tile kernel, and
+// those whose waves share K. (The line is
 // a promise kept to those programs, not an optimum.) Measured, us, one-wave kernel / tiles with or without K slices /
 // this: 256^3 16.7 / 7.6 / 7.6, 5 x 11008 x 4096 with B as [N][K] 184 / 19.7 / 19.7, 9 x 2304 x 3776 259 / 11.8 / 10.4,
 // 16 x 576 x 4544 with B as [N][K] (one-wave about 200) / 10.4 / 9.7. Long sums over few columns lose: a CU fetches
@@ -271,6 +314,14 @@ void build_small_family(tf_problem* p) {
   build_any_family(p);
   for (const tf_variant_desc& v : p->family)
     if (v.kind == TF_KIND_MFMA_ANY && tf_predict_us(&d, &p->hw, &v) < tf_predict_us(&d, &p->hw, &p->family[any])) any = v.id;
+  for (size_t i = 0; i < p->family.size(); ++i) {
+    tf_variant_desc& k = p->family[i];
+    if (k.kind != TF_KIND_MFMA_KSHARE || k.split_k > 1) continue;
+    k.kind = TF_KIND_MFMA_LDS_ANY;
+    p->impl[i].any_id = any;
+    const size_t len = strlen(k.name);
+    snprintf(k.name + len, sizeof(k.name) - len, "_or_any");
+  }
   tf_variant_desc v = p->family[plain];
   VariantImpl im = p->impl[plain];
   v.kind = TF_KIND_MFMA_LDS_ANY;
@@ -441,6 +492,7 @@ void build_family(tf_problem* p) {
       }
     }
   }
+  build_kshare_family(p);
   // Streaming kernels for skinny problems: K in blocks of 32, each wave of a work-group at least one block.
   if (!tb && d.M <= 32 && d.K % 32 == 0 && d.K >= 32) {
     const tf::StreamKernelInfo* stab = tf::stream_kernel_table();
@@ -532,7 +584,7 @@ tf_status check_ptrs(const tf_problem* p, const tf_variant_desc& v, const void* 
   }
   if (!Y || !bias) return fail(TF_E_INVALID, "null Y or bias pointer");
   if (d.K > 0 && (!A || !B)) return fail(TF_E_INVALID, "null A or B pointer");
-  if (v.kind == TF_KIND_MFMA_LDS || v.kind == TF_KIND_MFMA_STREAM) {
+  if (v.kind == TF_KIND_MFMA_LDS || v.kind == TF_KIND_MFMA_STREAM || v.kind == TF_KIND_MFMA_KSHARE) {
     if (!tile_aligned(A, B, bias, Y))
       return fail(TF_E_UNSUPPORTED, "variant %s needs 16-byte aligned A, B, Y and 8-byte aligned bias", v.name);
   }
@@ -731,14 +783,17 @@ tf_status do_launch(tf_problem* p, int id, const void* A, const void* B, const v
         if (own) { p->zeroed_ws = ws; p->zeroed_bytes = im.counter_bytes; }
       }
     }
-    const bool streaming = v.kind == TF_KIND_MFMA_STREAM;
-    const int slot = streaming ? tf::lds_kernel_count() + im.lds_index : im.lds_index;
-    const void* func = streaming ? tf::stream_kernel_table()[im.lds_index].func : tf::lds_kernel_table()[im.lds_index].func;
+    const bool streaming = v.kind == TF_KIND_MFMA_STREAM, kshare = tf::is_kshare(&v);
+    const int slot = kshare ? tf::lds_kernel_count() + tf::stream_kernel_count() + tf::any_kernel_count() + im.lds_index
+                     : streaming ? tf::lds_kernel_count() + im.lds_index : im.lds_index;
+    const void* func = kshare ? tf::kshare_kernel_table()[im.lds_index].func
+                       : streaming ? tf::stream_kernel_table()[im.lds_index].func : tf::lds_kernel_table()[im.lds_index].func;
     if (!p->attr_done[slot]) {
       TF_HIP(hipFuncSetAttribute(func, hipFuncAttributeMaxDynamicSharedMemorySize, v.lds_bytes));
       p->attr_done[slot] = 1;
     }
-    if (streaming) tf::stream_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
+    if (kshare) tf::kshare_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
+    else if (streaming) tf::stream_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
     else tf::lds_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
     if (v.split_k > 1 && !v.fused_reduce) tf::launch_splitk_reduce(g, stream);
   }
@@ -758,6 +813,7 @@ void fill_static(tf_problem* p, int id, tf_report* r) {
   else if (v.kind == TF_KIND_NAIVE) func = tf::naive_func();
   else if (v.kind == TF_KIND_MFMA_DIRECT) func = tf::mfma_direct_func();
   else if (v.kind == TF_KIND_MFMA_STREAM) { func = tf::stream_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
+  else if (tf::is_kshare(&v)) { func = tf::kshare_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
   else if (v.kind == TF_KIND_MFMA_ANY) { func = tf::any_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
   else { func = tf::lds_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
   hipFuncAttributes a;
@@ -1222,7 +1278,7 @@ extern "C" tf_status tf_problem_create(const tf_problem_desc* desc, tf_problem**
     ps->own_ws = nullptr; ps->own_ws_bytes = 0; ps->zeroed_ws = nullptr; ps->zeroed_bytes = 0;
     ps->have_hw = tf_hw_query(desc->device, &ps->hw) == TF_OK;
     if (!ps->have_hw) { tf_hw_nominal(&ps->hw); g_err[0] = 0; }
-    ps->attr_done.assign(tf::lds_kernel_count() + tf::stream_kernel_count() + tf::any_kernel_count(), 0);
+    ps->attr_done.assign(tf::lds_kernel_count() + tf::stream_kernel_count() + tf::any_kernel_count() + tf::kshare_kernel_count(), 0);
     build_family(ps);
     *out = ps;
     return TF_OK;
@@ -1249,7 +1305,7 @@ extern "C" tf_status tf_problem_create(const tf_problem_desc* desc, tf_problem**
   // host-side loop logic work without a GPU; launching does not)
   p->have_hw = tf_hw_query(desc->device, &p->hw) == TF_OK;
   if (!p->have_hw) { tf_hw_nominal(&p->hw); g_err[0] = 0; }
-  p->attr_done.assign(tf::lds_kernel_count() + tf::stream_kernel_count() + tf::any_kernel_count(), 0);
+  p->attr_done.assign(tf::lds_kernel_count() + tf::stream_kernel_count() + tf::any_kernel_count() + tf::kshare_kernel_count(), 0);
   build_family(p);
   *out = p;
   return TF_OK;
@@ -1269,7 +1325,11 @@ extern "C" int32_t tf_variant_kernel_name(const tf_variant_desc* v, char* buf, i
   switch (v->kind) {
     case TF_KIND_NAIVE: n = snprintf(buf, cap, "tf_gemm_naive_kernel"); break;
     case TF_KIND_MFMA_DIRECT: n = snprintf(buf, cap, "tf_gemm_mfma_direct_kernel"); break;
-    case TF_KIND_MFMA_LDS: case TF_KIND_MFMA_LDS_ANY:
+    case TF_KIND_MFMA_LDS: case TF_KIND_MFMA_LDS_ANY: case TF_KIND_MFMA_KSHARE:
+      if (tf::is_kshare(v)) {
+        n = snprintf(buf, cap, "tf_gemm_kshare_kernel<tf::KshareCfg<%d, %d, %d, %d, %s>", v->bm, v->bn, v->waves_k, v->stages, b(v->trans_b));
+        break;
+      }
       // (a counter file may hold several instances of one configuration: each has a kernel name of its own)
       snprintf(cfg, sizeof(cfg), "tf::LdsCfg<%d, %d, %d, %d, %d, %d, %s, %s, %d, %s, %s, %d>", v->bm, v->bn, v->bk, v->waves_m,
                v->waves_n, v->stages, b(v->direct_to_lds), b(v->a_bypass_lds), v->waves_k, b(v->trans_a), b(v->trans_b), v->bn);
@@ -1377,7 +1437,8 @@ extern "C" tf_status tf_workspace_status(tf_problem* p, const void* workspace, v
   int id = -1;
   for (size_t i = 0; i < p->impl.size(); ++i) if (p->impl[i].counter_bytes >= kStatusBytes) { id = (int)i; break; }
   if (id < 0) return TF_OK;                         // no variant of this problem uses a workspace with counters
-  if (!workspace && !p->own_ws) return TF_OK;       // nothing has been launched into the library's own buffer yet
+  // nothing that uses counters has been launched into the library's own buffer yet (a transposing pass may have been)
+  if (!workspace && (!p->own_ws || p->zeroed_ws != p->own_ws)) return TF_OK;
   tf_status st = prepare(p, id);
   if (st != TF_OK) return st;
   unsigned word = 0;

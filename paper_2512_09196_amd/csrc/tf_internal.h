@@ -85,6 +85,16 @@ struct AnyKernelInfo {
 int any_kernel_count();
 const AnyKernelInfo* any_kernel_table();
 
+// One compiled kernel whose waves share K (see tf_gemm_kshare.hip): K >= 64, rows of whole 16-byte pieces.
+struct KshareKernelInfo {
+  int bm, bn, waves, stages;          // stages: K tiles of 64 in each wave's ring
+  int trans_b, threads, lds_bytes;
+  const void* func;
+  void (*launch)(const GemmParams&, dim3 grid, hipStream_t);
+};
+int kshare_kernel_count();
+const KshareKernelInfo* kshare_kernel_table();
+
 // One compiled kernel of the streaming family of the batched vector-matrix product.
 // GemmParams: A [M][lda], B [M][N][ldb] (k contiguous), Y fp32 [M][ldy]; group_m unused.
 struct VecmatKernelInfo {

@@ -85,7 +85,7 @@ extern "C" int32_t tf_refine_hint(const tf_report* prev, const tf_report* cand, 
 
 // ------------------------------------------------------------------ static cost model
 static inline long cdiv(long a, long b) { return (a + b - 1) / b; }
-static inline bool is_tile_kernel(const tf_variant_desc* v) { return v->kind == TF_KIND_MFMA_LDS || v->kind == TF_KIND_MFMA_LDS_ANY; }
+static inline bool is_tile_kernel(const tf_variant_desc* v) { return v->kind == TF_KIND_MFMA_LDS || (v->kind == TF_KIND_MFMA_LDS_ANY && !tf::is_kshare(v)); }
 
 extern "C" int32_t tf_resident_wgs(const tf_hw* hw, const tf_variant_desc* v) {
   if (v->kind == TF_KIND_MFMA_STREAM) {
@@ -94,6 +94,10 @@ extern "C" int32_t tf_resident_wgs(const tf_hw* hw, const tf_variant_desc* v) {
     int r = 4 * hw->simds_per_cu / waves;
     const int by_lds = v->lds_bytes > 0 ? hw->lds_bytes_per_cu / v->lds_bytes : 8;
     if (by_lds < r) r = by_lds;
+    return r < 1 ? 1 : (r > 8 ? 8 : r);
+  }
+  if (tf::is_kshare(v)) {
+    const int r = v->lds_bytes > 0 ? hw->lds_bytes_per_cu / v->lds_bytes : 8;
     return r < 1 ? 1 : (r > 8 ? 8 : r);
   }
   if (!is_tile_kernel(v)) return 8;
@@ -201,6 +205,26 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
     const double traffic = (double)v->grid * 2.0 * v->bm * 2.0 * pr->K;
     const double serial = (double)cdiv(cdiv(pr->K, 64), v->waves_k) * (t64 ? 1.6 : 0.65);
     return 4.0 + fmax(fmax(traffic / (t64 ? 9.5e6 : 13.0e6), hbm_us / 0.55), serial);
+  }
+  if (tf::is_kshare(v)) {
+    // Fitted (log error, 12 % rms) to 893 timings of these kernels on 176 problems from 1 x 4096 x 11008 to 2965 x 1104 x 2224:
+    // a CU fetches the panels of its tiles at 76 to 97 GB/s, the L2s together what their tiles need at 7.4 TB/s (the two
+    // overlap in part), a launch takes 2.9 us and a further round of work-groups costs 2.3 beside its bytes.
+    const int s = v->split_k, res = tf_resident_wgs(hw, v);
+    const long tm = cdiv(pr->M, v->bm), tn = cdiv(pr->N, v->bn), nkt = cdiv(pr->K, 64);
+    const double load = (double)(tm * tn * s) / hw->cus;
+    const double fetch = (v->bm + v->bn) * 128.0 * cdiv(nkt, s) * fmax(1.0, ceil(load - 1e-9)) / (v->bm > 32 ? 76.3e3 : 96.4e3);
+    // an XCD's run of neighbouring tiles (8 / s XCDs share the tiles of a slice), in columns of group_m
+    const double run = (double)(tm * tn) / (s >= 8 ? 1 : 8 / s), gm = v->group_m > 0 ? v->group_m : 1;
+    const double rows = fmin((double)tm, run < gm ? fmax(1.0, run) : gm * fmax(1.0, ceil(run / (gm * tn)))), cols = fmin((double)tn, fmax(1.0, run / gm));
+    const double fabric = fmax(8.0 * (rows * v->bm + cols * v->bn) * 128.0 * nkt / (s < 8 ? s : 8), 2.0 * ((double)pr->M * pr->K + (double)pr->K * pr->N)) / 7.35e6;
+    double us = 2.9 + pow(pow(fetch, 1.55) + pow(fabric, 1.55), 1.0 / 1.55) + 2.3 * fmax(0.0, ceil(load / res - 1e-9) - 1.0);
+    // slices: the acknowledgement of the partial tile, the ticket, the other slices' tiles
+    const double tile_bytes = v->bm * (double)v->bn * 4.0;
+    if (s > 1) us += 1.45 + 1.16e-5 * s * tile_bytes + 6.1e-7 * load * hw->cus * tile_bytes;
+    // (the figures below are up to a quarter high for the tile kernels at these sizes; with 1.15 the picks over 189
+    // problems are 1.9 % behind the fastest variant of either kind, with 1.0 and 1.25 2.6 and 2.7 %)
+    return 1.15 * us;
   }
   if (v->kind == TF_KIND_MFMA_STREAM) {
     // B is read once at the rate the chip sustains from HBM, if enough waves keep loads in flight
@@ -396,14 +420,14 @@ extern "C" int32_t tf_proposal(const tf_problem_desc* prob, const tf_hw* hw, con
   for (int i = 0; i < n; ++i) {
     pred[i] = tf_predict_us(prob, hw, &family[i]);
     out[i] = tried[i];
-    if (family[i].kind == TF_KIND_MFMA_LDS_ANY) small = i;
+    if (family[i].kind == TF_KIND_MFMA_LDS_ANY && !tf::is_kshare(&family[i])) small = i;
     tiles |= family[i].kind == TF_KIND_MFMA_LDS;
     if (i > 0 && tried[i]) first = false;
   }
   if (first && (small >= 0 || !tiles)) {
     // the static pick of a small problem (which may be too small for any tile): what takes any pointer and needs no workspace
     for (int i = 0; i < n; ++i)
-      if (family[i].kind == TF_KIND_MFMA_LDS || family[i].kind == TF_KIND_MFMA_STREAM) out[i] = 1;
+      if (family[i].kind == TF_KIND_MFMA_LDS || family[i].kind == TF_KIND_MFMA_STREAM || family[i].kind == TF_KIND_MFMA_KSHARE) out[i] = 1;
   } else if (small >= 0) {
     // later rounds: the tile kernel under one of its two ids
     for (int i = 0; i < n; ++i)

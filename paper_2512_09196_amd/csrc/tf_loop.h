@@ -4,6 +4,12 @@
 #include "tf.h"
 
 namespace tf {
+// A variant of the kernels whose waves share K: of a small problem, the ones without slices are listed as
+// TF_KIND_MFMA_LDS_ANY (no other tile kernel has a single wave per k group and several groups).
+inline bool is_kshare(const tf_variant_desc* v) {
+  return v->kind == TF_KIND_MFMA_KSHARE || (v->kind == TF_KIND_MFMA_LDS_ANY && v->waves_m == 1 && v->waves_n == 1 && v->waves_k > 1);
+}
+
 // Profile callback: BuildRun + parity gate + Profile of variant `id` into *out.
 typedef tf_status (*profile_fn)(void* user, int32_t id, tf_report* out);
 

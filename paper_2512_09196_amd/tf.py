@@ -17,7 +17,7 @@ TF_OK, TF_E_INVALID, TF_E_UNSUPPORTED, TF_E_LAUNCH, TF_E_NOMEM, TF_E_RANGE, TF_E
 TF_EPI_BIAS_GELU_ERF, TF_EPI_NONE_F32, TF_EPI_BIAS, TF_EPI_BIAS_GELU_TANH = 0, 1, 2, 3
 TF_KIND_NAIVE, TF_KIND_MFMA_DIRECT, TF_KIND_MFMA_LDS, TF_KIND_MFMA_STREAM = 0, 1, 2, 3
 TF_KIND_VECMAT_NAIVE, TF_KIND_VECMAT_STREAM, TF_KIND_BGEMM_TN_NAIVE, TF_KIND_SIN = 4, 5, 6, 7
-TF_KIND_MFMA_ANY, TF_KIND_MFMA_LDS_ANY = 8, 9
+TF_KIND_MFMA_ANY, TF_KIND_MFMA_LDS_ANY, TF_KIND_MFMA_KSHARE = 8, 9, 10
 TF_OP_GEMM_EPILOGUE, TF_OP_BATCHED_VECMAT, TF_OP_BATCHED_GEMM_TN, TF_OP_ELEMENTWISE_SIN = 0, 1, 2, 3
 TF_BN_UNKNOWN, TF_BN_UNDERFILLED, TF_BN_HBM, TF_BN_MFMA, TF_BN_LDS_CONFLICT, TF_BN_OCCUPANCY, TF_BN_LATENCY = range(7)
 TF_DEC_CONTINUE, TF_DEC_ACCEPT, TF_DEC_FINISH = 0, 1, 2
