@@ -8,6 +8,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -15,6 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtf_gfx950.so")
+PYCALL = os.path.join(HERE, "_tfcall.so")        # Python extension module, host code only
 SOURCES = ["tf_gemm_lds.hip", "tf_gemm_lds_ragged.hip", "tf_gemm_lds_192.hip", "tf_gemm_stream.hip", "tf_gemm_any.hip", "tf_gemm_kshare.hip", "tf_vecmat.hip", "tf_sin.hip", "tf_gemm_simple.hip", "tf_api.hip", "tf_loop.cpp"]
 HEADERS = ["tf_gemm_lds.h", "tf_internal.h", "tf_device.h", "tf_loop.h"]
 
@@ -31,12 +33,12 @@ def _hipcc() -> str:
 
 
 def _newest_input() -> float:
-    paths = [os.path.join(CSRC, f) for f in SOURCES + HEADERS] + [os.path.join(ROOT, "include", "tf.h"), __file__]
+    paths = [os.path.join(CSRC, f) for f in SOURCES + HEADERS + ["tf_pycall.cpp"]] + [os.path.join(ROOT, "include", "tf.h"), __file__]
     return max(os.path.getmtime(p) for p in paths)
 
 
 def up_to_date() -> bool:
-    return os.path.exists(LIB) and os.path.getmtime(LIB) >= _newest_input()
+    return all(os.path.exists(f) and os.path.getmtime(f) >= _newest_input() for f in (LIB, PYCALL))
 
 
 def _compile(src: str) -> str:
@@ -51,13 +53,25 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_pycall() -> str:
+    tmp = PYCALL + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "tf_pycall.cpp"), "-o", tmp]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on tf_pycall.cpp:\n" + r.stdout)
+    os.replace(tmp, PYCALL)
+    return PYCALL
+
+
 def build_library(force: bool = True) -> str:
     """Compile every source for gfx950 and link the shared library. Returns its path."""
     if not force and up_to_date():
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
+        pycall = ex.submit(build_pycall)
         objs = list(ex.map(_compile, SOURCES))
+        pycall.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

@@ -8,10 +8,12 @@ for device memory and streams only.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtf_gfx950.so")
+PYCALL_PATH = os.path.join(_HERE, "_tfcall.so")
 
 TF_OK, TF_E_INVALID, TF_E_UNSUPPORTED, TF_E_LAUNCH, TF_E_NOMEM, TF_E_RANGE, TF_E_PROFILER = 0, -1, -2, -3, -4, -5, -6
 TF_EPI_BIAS_GELU_ERF, TF_EPI_NONE_F32, TF_EPI_BIAS, TF_EPI_BIAS_GELU_TANH = 0, 1, 2, 3
@@ -124,6 +126,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_pycall = None
 
 
 class TfError(RuntimeError):
@@ -134,7 +137,7 @@ class TfError(RuntimeError):
 
 def lib():
     """The loaded library. Raises if it has not been built: there is no other code path."""
-    global _lib
+    global _lib, _pycall
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -158,8 +161,22 @@ def lib():
         if list(built) != mine:
             raise RuntimeError("%s was built from another include/tf.h (struct sizes %s, this binding has %s): "
                                "rebuild it with `python -m paper_2512_09196_amd.build`" % (LIB_PATH, list(built), mine))
+        _pycall = _load_pycall(l)
         _lib = l
     return _lib
+
+
+def _load_pycall(l):
+    """The extension module behind Problem.run (csrc/tf_pycall.cpp)."""
+    if not os.path.exists(PYCALL_PATH):
+        raise RuntimeError("%s is missing: build it with `python -m paper_2512_09196_amd.build`" % PYCALL_PATH)
+    spec = importlib.util.spec_from_file_location("_tfcall", PYCALL_PATH)
+    m = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(m)
+    m.bind(C.cast(l.tf_variant_run, C.c_void_p).value, _current_stream)
+    # a forked child must not use its parent's GPU state: it goes through torch.cuda, which says so
+    os.register_at_fork(after_in_child=lambda: m.bind_stream(None, None))
+    return m
 
 
 def _check(st):
@@ -168,20 +185,26 @@ def _check(st):
 
 
 def _ptr(x):
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return C.c_void_p(x)
-    return C.c_void_p(x.data_ptr())   # torch tensor
+    if x is None or isinstance(x, int):
+        return x
+    return x.data_ptr()   # torch tensor
 
 
 def _stream(stream):
     if stream is None:
-        import torch
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return _current_stream()
     if isinstance(stream, int):
-        return C.c_void_p(stream)
-    return C.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
+
+
+def _current_stream():
+    """The handle of torch's current stream on its current device. Once the GPU is in use, tf_pycall.cpp asks torch's
+    C functions for it instead: torch.cuda.current_stream() builds a Stream object, which takes 2.5 us."""
+    import torch
+    if _pycall is not None and torch.cuda.is_initialized():
+        _pycall.bind_stream(getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None))
+    return torch.cuda.current_stream().cuda_stream
 
 
 def theta_default() -> Theta:
@@ -359,8 +382,9 @@ class Problem:
         return [arr[i] for i in range(n2)]
 
     def run(self, variant_id, A, B, bias, Y, workspace=None, workspace_bytes=0, stream=None):
-        _check(lib().tf_variant_run(self._h, variant_id, _ptr(A), _ptr(B), _ptr(bias), _ptr(Y), _ptr(workspace),
-                                    workspace_bytes, _stream(stream)))
+        st = _pycall.run(self._h.value or 0, variant_id, A, B, bias, Y, workspace, workspace_bytes, stream)
+        if st != TF_OK:
+            _check(st)
 
     def run_static(self, variant_id, A, B, bias, Y, stream=None):
         """tf_variant_run on the workspace that is part of the library's device image: allocates nothing."""

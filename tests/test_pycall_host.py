@@ -1,0 +1,61 @@
+"""The native call behind Problem.run: what it hands to tf_variant_run for tensors, addresses, None and streams. A Python
+callback stands in for tf_variant_run; no GPU."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2512_09196_amd import tf
+
+RUN = C.CFUNCTYPE(C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p)
+
+
+@pytest.fixture
+def call():
+    tf.lib()
+    m, seen = tf._pycall, []
+    cb = RUN(lambda *a: seen.append(a) or len(seen))
+    m.bind_stream(None, None)
+    m.bind(C.cast(cb, C.c_void_p).value, lambda: 77)
+    yield m, seen
+    m.bind_stream(None, None)
+    m.bind(C.cast(tf.lib().tf_variant_run, C.c_void_p).value, tf._current_stream)
+
+
+def test_arguments(call):
+    m, seen = call
+    t = torch.zeros(8)
+    big = 2 ** 64 - 16                       # an address with its top bit set stays what it is
+    assert m.run(5, 3, t, big, None, t[1:], 0, 1 << 40, 9) == 1
+    assert m.run(0, -1, None, None, None, None, None, 0, None) == 2
+    assert seen == [(5, 3, t.data_ptr(), big, None, t.data_ptr() + 4, None, 1 << 40, 9), (None, -1, None, None, None, None, None, 0, 77)]
+
+
+def test_stream(call):
+    m, seen = call
+
+    class Stream:
+        cuda_stream = 1234
+    m.run(1, 0, 0, 0, 0, 0, 0, 0, Stream())
+    m.bind_stream(lambda dev: 100 + dev, lambda: 2)
+    m.run(1, 0, 0, 0, 0, 0, 0, 0, None)
+    m.bind_stream(None, None)
+    m.run(1, 0, 0, 0, 0, 0, 0, 0, None)
+    assert [s[-1] for s in seen] == [1234, 102, 77]
+
+
+def test_errors_reach_the_caller_and_nothing_runs(call):
+    m, seen = call
+
+    def broken(*a):
+        raise RuntimeError("no stream")
+    for args, error in (((1, 0, "x", 0, 0, 0, 0, 0, 0), AttributeError), ((1, 0.5, 0, 0, 0, 0, 0, 0, 0), TypeError),
+                        ((1, 0, 0, 0, 0, 0, 0, 0, object()), AttributeError), ((1, 0), TypeError)):
+        with pytest.raises(error):
+            m.run(*args)
+    m.bind_stream(broken, lambda: 0)
+    with pytest.raises(RuntimeError, match="no stream"):
+        m.run(1, 0, 0, 0, 0, 0, 0, 0, None)
+    assert seen == []
+    with tf.Problem(64, 64, 64) as p:
+        assert p.run.__self__ is p           # (run is an ordinary method)
