@@ -520,7 +520,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     p.B += (size_t)item * p.stride_b;
     p.Y = (char*)p.Y + (size_t)item * p.stride_y * (p.epi == TF_EPI_NONE_F32 ? 4 : 2);
   }
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_k = wave / (C::WM * C::WN), wave_mn = wave % (C::WM * C::WN);
   const int wave_m = wave_mn / C::WN, wave_n = wave_mn % C::WN;
 
@@ -597,8 +597,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
   // each: at any moment all work-groups then read inside one narrow band of rows of B, which a streaming read of
   // column strips rewards (134 MB: 21.2 us against 23.2 us with two halves of K; host: direct staging only)
   const bool k_deal = C::DIRECT && p.k_interleave && split && !stream_k;
-  const int nkt = k_deal ? (ktiles_total - tc.ks + p.split_k - 1) / p.split_k
-                         : kt_end - kt_begin;   // may be <= 0 for a trailing empty slice: contributes zeros
+  // (the same for every lane: said so, the K loop keeps its counters and addresses in scalar registers)
+  const int nkt = __builtin_amdgcn_readfirstlane(k_deal ? (ktiles_total - tc.ks + p.split_k - 1) / p.split_k
+                                                        : kt_end - kt_begin);   // may be <= 0 for a trailing empty slice: contributes zeros
 
   // ---- LDS read offsets of this lane (bytes inside a stage)
   int a_off[C::KS];
@@ -738,10 +739,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     }
   };
 
-  // The last tile is peeled off the loop, so the loop body has no branch inside and is
-  // scheduled as one block. Prefetches that would run past the last tile re-fetch the last
-  // tile instead (into a buffer nobody reads any more): the number of transfers in flight is
-  // then the same in every iteration and the vmcnt waits are constants.
+  // The last tile is peeled off the loop, and so are the ones behind which nothing more is fetched: the
+  // loop body has no branch inside and is scheduled as one block, with constant vmcnt waits. (The A-bypass kernel
+  // re-fetches the last tile past the end, into a buffer nobody reads any more. With every kernel doing that, a
+  // work-group fetched STAGES - 1 K tiles more than it has, at the rate that bounds the K loop, and waited for them
+  // before its epilogue.)
   const int last = nkt - 1;
   // Order of the K tiles (a sum: any order is right). Without split-K the work-groups of XCD x start an
   // eighth of the way further into K than those of XCD x - 1 and wrap round: at any moment the eight XCDs
@@ -759,6 +761,30 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
   const int k_over = ktiles_total * C::BK - p.K;
   const int skip = C::KTAIL && k_over > 0 && first_kt + last * (k_deal ? p.split_k : 1) == ktiles_total - 1 ? k_over : 0;
   const long a_back = C::TRANSA ? skip * p.lda : (long)skip, b_back = C::TRANSB ? (long)skip : skip * p.ldb;
+  // Where the next K tile to fetch lies in A and B: moved on a tile at a time, with one wrap (a multiplication per
+  // tile and operand cost the loop some thirty scalar or, where the compiler chose so, vector instructions a step).
+  struct Fetch {
+    unsigned long long a, b;
+    int left;                              // tiles from here to the end of the range
+  } nx;
+  auto uniform = [](const void* x) {
+    const unsigned long long v = (unsigned long long)x;
+    return (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v) |
+           ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32)) << 32);
+  };
+  const unsigned long long a_first = uniform(Ak), b_first = uniform(Bk);
+  const long a_move = 2 * a_step, b_move = 2 * b_step;       // bytes
+  nx.left = nkt - k_rot;
+  nx.a = a_first + (unsigned long long)(k_rot * a_move) - (C::KTAIL && nx.left == 1 ? 2 * a_back : 0);
+  nx.b = b_first + (unsigned long long)(k_rot * b_move) - (C::KTAIL && nx.left == 1 ? 2 * b_back : 0);
+  auto next_tile = [&]() {
+    --nx.left;
+    nx.a = nx.left == 0 ? a_first : nx.a + a_move;
+    nx.b = nx.left == 0 ? b_first : nx.b + b_move;
+    if (C::KTAIL && nx.left == 1) { nx.a -= 2 * a_back; nx.b -= 2 * b_back; }
+  };
+  auto next_a = [&]() { return (const uint16_t*)nx.a; };
+  auto next_b = [&]() { return (const uint16_t*)nx.b; };
   auto zero_skipped = [&](char* stage) {       // every wave calls it; `stage` has landed and is read again behind it
     const u32x4 zero = {0u, 0u, 0u, 0u};
     auto k_contiguous = [&](char* tile, int rows) {
@@ -878,8 +904,6 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     constexpr int PER_TILE = C::A_PER_WAVE + C::B_PER_WAVE;
     static_assert((D - 1) * PER_TILE < 64, "vmcnt range");
     const unsigned lds0 = (unsigned)(size_t)smem;
-    auto tile_a = [&](int t) { return Ak + (long)k_order(t < last ? t : last) * a_step - (C::KTAIL && t >= last ? a_back : 0); };
-    auto tile_b = [&](int t) { return Bk + (long)k_order(t < last ? t : last) * b_step - (C::KTAIL && t >= last ? b_back : 0); };
     bf16x8 fa[2][C::KS][C::TM], fb[2][C::KS][C::TN];
     auto read_tile = [&](const char* stage, bf16x8 (&a)[C::KS][C::TM], bf16x8 (&b)[C::KS][C::TN]) {
 #pragma unroll
@@ -901,20 +925,34 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     };
     if (nkt > 0) {
 #pragma unroll
-      for (int s = 0; s < D; ++s) ld.issue_direct(tile_a(s), tile_b(s), lds0 + s * C::STAGE_BYTES, wave);
-      wait_vmcnt<(D - 1) * PER_TILE>();
+      for (int s = 0; s < D; ++s)
+        if (s < nkt) {
+          ld.issue_direct(next_a(), next_b(), lds0 + s * C::STAGE_BYTES, wave);
+          next_tile();
+        }
+      if (nkt >= D) wait_vmcnt<(D - 1) * PER_TILE>();
+      else wait_vmcnt<0>();
       barrier_lds();
-      ld.issue_direct(tile_a(D), tile_b(D), lds0 + D * C::STAGE_BYTES, wave);
+      if (D < nkt) {
+        ld.issue_direct(next_a(), next_b(), lds0 + D * C::STAGE_BYTES, wave);
+        next_tile();
+      }
       read_tile(smem, fa[0], fb[0]);
       int stage = 0;
-      // one non-final tile t: its fragments are in (ca, cb); (na, nb) receive tile t+1
-      auto step = [&](int t, const bf16x8 (&ca)[C::KS][C::TM], const bf16x8 (&cb)[C::KS][C::TN],
+      // one non-final tile t: its fragments are in (ca, cb); (na, nb) receive tile t+1. FETCH: tile t + 1 + D exists and
+      // is fetched; otherwise what there is
+      auto step = [&](auto fetch, int t, const bf16x8 (&ca)[C::KS][C::TM], const bf16x8 (&cb)[C::KS][C::TN],
                       bf16x8 (&na)[C::KS][C::TM], bf16x8 (&nb)[C::KS][C::TN]) {
+        constexpr bool FETCH = decltype(fetch)::value != 0;
         int nstage = stage + 1;
         if (nstage == C::STAGES) nstage = 0;
-        wait_vmcnt<(D - 1) * PER_TILE>();    // tile t+1 has landed
+        if (FETCH || t + D <= last) wait_vmcnt<(D - 1) * PER_TILE>();    // tile t+1 has landed
+        else wait_vmcnt<0>();
         barrier_lds();                       // ... for every wave; every wave holds tile t in registers
-        ld.issue_direct(tile_a(t + 1 + D), tile_b(t + 1 + D), lds0 + stage * C::STAGE_BYTES, wave);
+        if (FETCH || t + 1 + D <= last) {
+          ld.issue_direct(next_a(), next_b(), lds0 + stage * C::STAGE_BYTES, wave);
+          next_tile();
+        }
         read_tile(smem + nstage * C::STAGE_BYTES, na, nb);
         mfma_tile(ca, cb);
         stage = nstage;
@@ -926,27 +964,29 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
         }
       };
       int kt = 0;
+      for (; kt + 1 < last - D; kt += 2) {
+        step(EpiTag<1>{}, kt, fa[0], fb[0], fa[1], fb[1]);
+        step(EpiTag<1>{}, kt + 1, fa[1], fb[1], fa[0], fb[0]);
+      }
+      kt = __builtin_amdgcn_readfirstlane(kt);   // (the same value: keeps the compiler from making one loop of the two)
       for (; kt + 2 <= last; kt += 2) {
-        step(kt, fa[0], fb[0], fa[1], fb[1]);
-        step(kt + 1, fa[1], fb[1], fa[0], fb[0]);
+        step(EpiTag<0>{}, kt, fa[0], fb[0], fa[1], fb[1]);
+        step(EpiTag<0>{}, kt + 1, fa[1], fb[1], fa[0], fb[0]);
       }
       if (kt < last) {
-        step(kt, fa[0], fb[0], fa[1], fb[1]);
+        step(EpiTag<0>{}, kt, fa[0], fb[0], fa[1], fb[1]);
         reread_skipped(fa[1], fb[1]);
         mfma_tile(fa[1], fb[1]);
       } else {
         reread_skipped(fa[0], fb[0]);
         mfma_tile(fa[0], fb[0]);
       }
-      wait_vmcnt<0>();
     }
   } else if constexpr (C::DIRECT) {
     constexpr int D = C::STAGES - 1;                            // tiles in flight ahead of the one computed
     constexpr int PER_TILE = C::A_PER_WAVE + C::B_PER_WAVE;   // transfers per wave per tile
     static_assert((D - 1) * PER_TILE < 64, "vmcnt range");
     const unsigned lds0 = (unsigned)(size_t)smem;
-    auto tile_a = [&](int t) { return Ak + (long)k_order(t < last ? t : last) * a_step - (C::KTAIL && t >= last ? a_back : 0); };
-    auto tile_b = [&](int t) { return Bk + (long)k_order(t < last ? t : last) * b_step - (C::KTAIL && t >= last ? b_back : 0); };
     // A wave issues in order: a burst of transfers right after the barrier would hold back the
     // MFMAs behind it for as long as the load unit takes to accept the burst (the four waves of a
     // CU share one, at about 16 cycles per transfer). So the transfers of a tile are dealt out
@@ -956,7 +996,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     // MFMAs are spread between them by the scheduling hint.
     auto read_frags_issue = [&](const char* stage, int kk, int set, int which, const uint16_t* src, unsigned dst_lds) {
       constexpr int NR = C::TM + C::TN;                   // fragment reads (A: one b128, B: a tr pair)
-      const int nx = which == 1 ? C::A_PER_WAVE : C::B_PER_WAVE;
+      const int nx = which == 1 ? C::A_PER_WAVE : which == 2 ? C::B_PER_WAVE : 0;
 #pragma unroll
       for (int x = 0; x < (NR > 8 ? NR : 8); ++x) {
         if (x < C::TM) af[set][x] = read_a(stage, kk, x);
@@ -970,20 +1010,34 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     static_assert(C::A_PER_WAVE <= 8 && C::B_PER_WAVE <= 8, "transfers of one part fit between the reads of one step");
     if (nkt > 0) {
 #pragma unroll
-      for (int s = 0; s < D; ++s) ld.issue_direct(tile_a(s), tile_b(s), lds0 + s * C::STAGE_BYTES, wave);
-      wait_vmcnt<(D - 1) * PER_TILE>();      // tile 0 has landed, D-1 younger tiles may still fly
+      for (int s = 0; s < D; ++s)
+        if (s < nkt) {
+          ld.issue_direct(next_a(), next_b(), lds0 + s * C::STAGE_BYTES, wave);
+          next_tile();
+        }
+      if (nkt >= D) wait_vmcnt<(D - 1) * PER_TILE>();      // tile 0 has landed, D-1 younger tiles may still fly
+      else wait_vmcnt<0>();
       barrier_lds();
       // tile D: A part now, B part during the first step of tile 0 (as in the steady state)
-      ld.issue_a_all(tile_a(D), lds0 + D * C::STAGE_BYTES, wave);
+      if (D < nkt) ld.issue_a_all(next_a(), lds0 + D * C::STAGE_BYTES, wave);
       read_frags(smem, 0, 0);
-      int stage = 0;
-      for (int kt = 0; kt < last; ++kt) {
+      int stage = 0, kt = 0;
+      // one tile but the last. FETCH: the B part of tile kt + D and the A part of tile kt + 1 + D are on their way
+      // behind it (there are such tiles); otherwise the B part of the last tile, if that is tile kt + D, and no more
+      auto tile_step = [&](auto fetch) {
+        constexpr bool FETCH = decltype(fetch)::value != 0;
         const char* cur = smem + stage * C::STAGE_BYTES;
         int nstage = stage + 1;
         if (nstage == C::STAGES) nstage = 0;
         int pstage = stage + D;               // buffer of tile kt + D (freed by the barrier before this tile)
         if (pstage >= C::STAGES) pstage -= C::STAGES;
-        read_frags_issue(cur, 1, 1, 2, tile_b(kt + D), lds0 + pstage * C::STAGE_BYTES);
+        const bool last_b = kt + D == last;
+        if (!FETCH && last_b) ld.issue_b_direct(next_b(), lds0 + pstage * C::STAGE_BYTES, wave);
+        if constexpr (FETCH) {
+          read_frags_issue(cur, 1, 1, 2, next_b(), lds0 + pstage * C::STAGE_BYTES);
+          next_tile();
+        }
+        else read_frags(cur, 1, 1);
         mfma_step(0);
         interleave_hint();
 #pragma unroll
@@ -992,23 +1046,25 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
           mfma_step(kk & 1);
           interleave_hint();
         }
-        wait_vmcnt<(D - 1) * PER_TILE>();    // tile kt+1 has landed
+        if (FETCH || last_b) wait_vmcnt<(D - 1) * PER_TILE>();    // tile kt+1 has landed
+        else wait_vmcnt<0>();
         barrier_lds();                       // ... for every wave, and every wave is done reading tile kt
-        read_frags_issue(smem + nstage * C::STAGE_BYTES, 0, 0, 1, tile_a(kt + 1 + D), lds0 + stage * C::STAGE_BYTES);
+        if constexpr (FETCH) read_frags_issue(smem + nstage * C::STAGE_BYTES, 0, 0, 1, next_a(), lds0 + stage * C::STAGE_BYTES);
+        else read_frags(smem + nstage * C::STAGE_BYTES, 0, 0);
         mfma_step(1);                        // the last k16-step of tile kt covers the latencies above
         interleave_hint();
         stage = nstage;
-      }
+      };
+      for (; kt < last - D; ++kt) tile_step(EpiTag<1>{});
+      kt = __builtin_amdgcn_readfirstlane(kt);   // (the same value: keeps the compiler from making one loop of the two)
+      for (; kt < last; ++kt) tile_step(EpiTag<0>{});
       {
         char* cur = smem + stage * C::STAGE_BYTES;
         if (C::KTAIL && skip) {
           zero_skipped(cur);
           read_frags(cur, 0, 0);
         }
-        int pstage = stage + D;
-        if (pstage >= C::STAGES) pstage -= C::STAGES;
-        // (the B part that completes the redundant A part issued at the last hand-over)
-        read_frags_issue(cur, 1, 1, 2, tile_b(last + D), lds0 + pstage * C::STAGE_BYTES);
+        read_frags(cur, 1, 1);
         mfma_step(0);
         interleave_hint();
 #pragma unroll
@@ -1019,7 +1075,6 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
         }
         mfma_step(1);
       }
-      wait_vmcnt<0>();                       // the redundant prefetches must not outlive their LDS
     }
   } else {
     // Register-staged double buffering: the global loads of tile kt+1 fly during tile kt and are
