@@ -297,7 +297,10 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
   // VALU issue slots per output element of the epilogue: erf-GELU 11, tanh-GELU 7, plain conversions 2
   const double epi_valu = pr->epi == TF_EPI_BIAS_GELU_ERF ? 11.0 : pr->epi == TF_EPI_BIAS_GELU_TANH ? 7.0 : 2.0;
   double tile_end = v->bm * (double)v->bn * epi_valu / 64.0;
-  if (v->waves_k > 1) tile_end += v->bm * (double)v->bn * 4.0 * (1.0 / 85.0 + 1.0 / 256.0) / 2.0 * v->waves_k;   // accumulator exchange
+  // accumulator exchange of the k groups (with less, or none behind a second kernel that reduces, the 2 x 2 x 2 waves were
+  // predicted level with the 2 x 4 ones; measured they are 1.0 to 2.0 us slower in 128 x 128 tiles wherever both were
+  // timed, e.g. 477 x 1616 x 4992 20.4 / 18.6, 217 x 4928 x 2368 18.1 / 16.1, 408 x 832 x 10944 21.6 / 20.0)
+  const double exchange = v->waves_k > 1 ? v->bm * (double)v->bn * 0.12 : 0.0;
   double reduce_us = 0.0, fused_tail_us = 0.0;
   const double active = v->grid < hw->cus ? (double)v->grid / hw->cus : 1.0;
   const double mhz = (hw->clock_mhz < 1650.0 ? hw->clock_mhz : 1650.0) * (1.0 + 0.38 * (1.0 - active));
@@ -337,7 +340,7 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
     fused_tail_us = 12.0;
   }
   const double per_cu = rounds * (double)co_resident;            // work-groups one CU works through
-  const double us = per_cu * (ktiles * ktile + fill + tile_end) / mhz;
+  const double us = per_cu * (ktiles * ktile + fill + tile_end + exchange) / mhz;
   const double ws_us = v->split_k > 1 ? 2.0 * v->split_k * 4.0 * pr->M * (double)pr->N / (hw->hbm_gbs_peak * 1e3) : 0.0;
   // HBM floor: about three quarters of the peak rate when at least 32 KB per CU are in flight
   // (prefetched tiles of all co-resident work-groups), in proportion below that
