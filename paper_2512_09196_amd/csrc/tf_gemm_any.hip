@@ -16,8 +16,8 @@
 //    one; the last K tile starts at K - 64 and the k that the tile before holds are zeroed in registers, in
 //    both operands; the last column tile of a [K][N] B starts at N - 32 T and stores only its own columns.
 //    Hence K >= 64, and N >= 32 T where B is [K][N].
-// 509 x 1021 x 763 (fp32 result): 53.8 us a call on the one-wave-per-tile kernel that gathers element by element, 7.7 us
-// here, which is what a call costs; the kernel alone takes 42.7 and 8.4 us there with cold operands. Matrix pipes 2 %
+// 509 x 1021 x 763 (fp32 result): 53.8 us a call on the one-wave-per-tile kernel that gathers element by element, 6.8 us
+// here; the kernel alone takes 42.7 and 8.4 us there with cold operands. Matrix pipes 2 %
 // busy, 92 % of the reads hit in L2: what is left is the trip to memory and back. Where K is long and the tiles are
 // fewer than the CUs, a CU's own rate bounds it (64 x 256 x 16384 35 us, 60 GB/s per CU).
 #include "tf_device.h"
