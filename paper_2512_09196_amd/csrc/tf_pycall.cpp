@@ -33,7 +33,7 @@ bool pointer(PyObject* x, void** out) {
   } else {
     PyObject* r = PyObject_CallMethodNoArgs(x, g_data_ptr);
     if (!r) return false;
-    const bool ok = as_address(r, &v);
+    const bool ok = r == Py_None || as_address(r, &v);      // (no address: null)
     Py_DECREF(r);
     if (!ok) return false;
   }
@@ -61,7 +61,7 @@ bool stream(PyObject* x, void** out) {
   }
   if (!r) return false;
   uintptr_t v = 0;
-  const bool ok = as_address(r, &v);
+  const bool ok = r == Py_None || as_address(r, &v);        // (no handle: the null stream)
   Py_DECREF(r);
   *out = (void*)v;
   return ok;

@@ -382,7 +382,11 @@ class Problem:
         return [arr[i] for i in range(n2)]
 
     def run(self, variant_id, A, B, bias, Y, workspace=None, workspace_bytes=0, stream=None):
-        st = _pycall.run(self._h.value or 0, variant_id, A, B, bias, Y, workspace, workspace_bytes, stream)
+        if type(variant_id) is int and type(workspace_bytes) is int:
+            st = _pycall.run(self._h.value or 0, variant_id, A, B, bias, Y, workspace, workspace_bytes, stream)
+        else:       # integers of other types (numpy's, a tensor's, ctypes' own): ctypes converts them, or says why not
+            st = lib().tf_variant_run(self._h, variant_id, _ptr(A), _ptr(B), _ptr(bias), _ptr(Y), _ptr(workspace),
+                                      workspace_bytes, _stream(stream))
         if st != TF_OK:
             _check(st)
 

@@ -2,6 +2,7 @@
 callback stands in for tf_variant_run; no GPU."""
 import ctypes as C
 
+import numpy as np
 import pytest
 import torch
 
@@ -59,3 +60,36 @@ def test_errors_reach_the_caller_and_nothing_runs(call):
     assert seen == []
     with tf.Problem(64, 64, 64) as p:
         assert p.run.__self__ is p           # (run is an ordinary method)
+
+
+class Data:
+    def __init__(self, p): self.p = p
+    def data_ptr(self): return self.p
+
+
+class Index:
+    def __index__(self): return 3
+
+
+@pytest.mark.parametrize("three", [3, np.int64(3), np.uint8(3), torch.tensor(3), C.c_int32(3), Index(), True], ids=lambda x: type(x).__name__)
+def test_integers_of_any_type_reach_the_library(three):
+    """A variant id straight from numpy's argmin, say. The library sees the number: it knows no such variant."""
+    with tf.Problem(0, 64, 64) as p:
+        n = len(p.variants())
+        assert n == 1
+        with pytest.raises(tf.TfError, match="variant id %d out of range" % int(getattr(three, "value", three))):
+            p.run(three, 16, 16, 16, 16, stream=0)
+        with pytest.raises(tf.TfError, match="variant id 7 out of range"):
+            p.run(7, Data(16), 16, 16, 16, workspace=16, workspace_bytes=C.c_size_t(3) if isinstance(three, C.c_int32) else three, stream=0)
+    for bad in (0.5, "3", None):
+        with tf.Problem(0, 64, 64) as p, pytest.raises(C.ArgumentError):
+            p.run(bad, 16, 16, 16, 16, stream=0)
+
+
+def test_no_address_and_no_handle_are_null(call):
+    m, seen = call
+
+    class Stream:
+        cuda_stream = None
+    m.run(1, 0, Data(None), 0, 0, 0, 0, 0, Stream())
+    assert seen == [(1, 0) + (None,) * 5 + (0, None)]
