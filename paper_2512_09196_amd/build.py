@@ -5,7 +5,9 @@ installed.  ``python -m paper_2512_09196_amd.build`` rebuilds unconditionally.
 """
 from __future__ import annotations
 
+import importlib.machinery
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -16,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtf_gfx950.so")
-PYCALL = os.path.join(HERE, "_tfcall.so")        # Python extension module, host code only
+PYCALL = os.path.join(HERE, "_tfcall" + importlib.machinery.EXTENSION_SUFFIXES[0])   # extension module of this interpreter, host code only
 SOURCES = ["tf_gemm_lds.hip", "tf_gemm_lds_ragged.hip", "tf_gemm_lds_192.hip", "tf_gemm_stream.hip", "tf_gemm_any.hip", "tf_gemm_kshare.hip", "tf_vecmat.hip", "tf_sin.hip", "tf_gemm_simple.hip", "tf_api.hip", "tf_loop.cpp"]
 HEADERS = ["tf_gemm_lds.h", "tf_internal.h", "tf_device.h", "tf_loop.h"]
 
@@ -38,7 +40,8 @@ def _newest_input() -> float:
 
 
 def up_to_date() -> bool:
-    return all(os.path.exists(f) and os.path.getmtime(f) >= _newest_input() for f in (LIB, PYCALL))
+    wanted = (LIB,) if pycall_tools() is None else (LIB, PYCALL)
+    return all(os.path.exists(f) and os.path.getmtime(f) >= _newest_input() for f in wanted)
 
 
 def _compile(src: str) -> str:
@@ -53,12 +56,25 @@ def _compile(src: str) -> str:
     return obj
 
 
-def build_pycall() -> str:
+def pycall_tools():
+    """(C++ compiler, folder of Python.h), or None where one of them is missing. (Not hipcc: it links the HIP runtime.)"""
+    include = sysconfig.get_paths()["include"]
+    cxx = shutil.which("g++") or shutil.which("c++") or shutil.which("clang++")
+    return (cxx, include) if cxx and os.path.exists(os.path.join(include, "Python.h")) else None
+
+
+def build_pycall():
+    """Compile the extension module behind Problem.run for this interpreter. Returns its path, or None without the tools:
+    Problem.run then calls the library through ctypes."""
+    tools = pycall_tools()
+    if tools is None:
+        sys.stderr.write("no C++ compiler or no Python.h: %s is left out\n" % os.path.basename(PYCALL))
+        return None
     tmp = PYCALL + ".tmp.%d" % os.getpid()
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "tf_pycall.cpp"), "-o", tmp]
+    cmd = [tools[0], "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + tools[1], os.path.join(CSRC, "tf_pycall.cpp"), "-o", tmp]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
-        raise RuntimeError("g++ failed on tf_pycall.cpp:\n" + r.stdout)
+        raise RuntimeError("%s failed on tf_pycall.cpp:\n%s" % (tools[0], r.stdout))
     os.replace(tmp, PYCALL)
     return PYCALL
 

@@ -8,12 +8,14 @@ for device memory and streams only.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
 import importlib.util
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtf_gfx950.so")
-PYCALL_PATH = os.path.join(_HERE, "_tfcall.so")
+# (compiled for one interpreter: its name says which, and another interpreter does not see it)
+PYCALL_PATH = os.path.join(_HERE, "_tfcall" + importlib.machinery.EXTENSION_SUFFIXES[0])
 
 TF_OK, TF_E_INVALID, TF_E_UNSUPPORTED, TF_E_LAUNCH, TF_E_NOMEM, TF_E_RANGE, TF_E_PROFILER = 0, -1, -2, -3, -4, -5, -6
 TF_EPI_BIAS_GELU_ERF, TF_EPI_NONE_F32, TF_EPI_BIAS, TF_EPI_BIAS_GELU_TANH = 0, 1, 2, 3
@@ -167,9 +169,10 @@ def lib():
 
 
 def _load_pycall(l):
-    """The extension module behind Problem.run (csrc/tf_pycall.cpp)."""
+    """The extension module behind Problem.run (csrc/tf_pycall.cpp), or None where it was not built for this interpreter:
+    Problem.run then makes the same call of the library through ctypes, which takes 4 us more of host time."""
     if not os.path.exists(PYCALL_PATH):
-        raise RuntimeError("%s is missing: build it with `python -m paper_2512_09196_amd.build`" % PYCALL_PATH)
+        return None
     spec = importlib.util.spec_from_file_location("_tfcall", PYCALL_PATH)
     m = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(m)
@@ -382,7 +385,7 @@ class Problem:
         return [arr[i] for i in range(n2)]
 
     def run(self, variant_id, A, B, bias, Y, workspace=None, workspace_bytes=0, stream=None):
-        if type(variant_id) is int and type(workspace_bytes) is int:
+        if _pycall is not None and type(variant_id) is int and type(workspace_bytes) is int:
             st = _pycall.run(self._h.value or 0, variant_id, A, B, bias, Y, workspace, workspace_bytes, stream)
         else:       # integers of other types (numpy's, a tensor's, ctypes' own): ctypes converts them, or says why not
             st = lib().tf_variant_run(self._h, variant_id, _ptr(A), _ptr(B), _ptr(bias), _ptr(Y), _ptr(workspace),

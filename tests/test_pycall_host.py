@@ -1,12 +1,14 @@
 """The native call behind Problem.run: what it hands to tf_variant_run for tensors, addresses, None and streams. A Python
 callback stands in for tf_variant_run; no GPU."""
 import ctypes as C
+import os
+import sysconfig
 
 import numpy as np
 import pytest
 import torch
 
-from paper_2512_09196_amd import tf
+from paper_2512_09196_amd import build, tf
 
 RUN = C.CFUNCTYPE(C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p)
 
@@ -93,3 +95,19 @@ def test_no_address_and_no_handle_are_null(call):
         cuda_stream = None
     m.run(1, 0, Data(None), 0, 0, 0, 0, 0, Stream())
     assert seen == [(1, 0) + (None,) * 5 + (0, None)]
+
+
+def test_the_module_is_this_interpreters_and_not_needed(monkeypatch, tmp_path):
+    """Its file name carries the interpreter's tag, so that another one does not load it; without it (or without what it is
+    built with) the library loads, and Problem.run reaches it all the same."""
+    assert os.path.basename(tf.PYCALL_PATH) == "_tfcall" + sysconfig.get_config_var("EXT_SUFFIX") == os.path.basename(build.PYCALL)
+    assert tf._pycall.__file__ == tf.PYCALL_PATH
+    monkeypatch.setattr(tf, "_lib", None)
+    monkeypatch.setattr(tf, "_pycall", None)
+    monkeypatch.setattr(tf, "PYCALL_PATH", str(tmp_path / "missing.so"))
+    with tf.Problem(0, 64, 64) as p, pytest.raises(tf.TfError, match="variant id 7 out of range"):
+        assert tf._pycall is None
+        p.run(7, Data(16), 16, 16, 16, stream=0)
+    monkeypatch.setattr(build, "PYCALL", str(tmp_path / "_tfcall.so"))
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_pycall() is None and not os.listdir(tmp_path)
