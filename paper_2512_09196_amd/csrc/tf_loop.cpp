@@ -389,16 +389,19 @@ static bool matches_hint(int bn, const tf_hw* hw, const tf_variant_desc* b, cons
   }
 }
 
+// The kernels that the hints speak of: tiles staged through LDS, with one wave or several to a share of K.
+static bool hinted(const tf_variant_desc* v) { return is_tile_kernel(v) || tf::is_kshare(v); }
+
 extern "C" int32_t tf_proposal_from(const tf_hw* hw, const tf_variant_desc* family, const double* predicted_us,
                                     int32_t n, const uint8_t* tried, int32_t base_id, int32_t bottleneck) {
   if (!hw || !family || !predicted_us || !tried || n <= 0) return -1;
   const tf_variant_desc* base = (base_id >= 0 && base_id < n) ? &family[base_id] : nullptr;
-  const bool use_hint = base && is_tile_kernel(base) && bottleneck != TF_BN_UNKNOWN;
+  const bool use_hint = base && hinted(base) && bottleneck != TF_BN_UNKNOWN;
   int best = -1, best_any = -1;
   for (int i = 0; i < n; ++i) {
     if (tried[i]) continue;
     if (best_any < 0 || predicted_us[i] < predicted_us[best_any]) best_any = i;
-    if (use_hint && is_tile_kernel(&family[i]) && matches_hint(bottleneck, hw, base, &family[i])) {
+    if (use_hint && hinted(&family[i]) && matches_hint(bottleneck, hw, base, &family[i])) {
       if (best < 0 || predicted_us[i] < predicted_us[best]) best = i;
     }
   }
