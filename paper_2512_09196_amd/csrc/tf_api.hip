@@ -591,6 +591,11 @@ tf_status check_ptrs(const tf_problem* p, const tf_variant_desc& v, const void* 
   return TF_OK;
 }
 
+// The variant that runs when `id` is asked for with these pointers.
+int launched(const tf_problem* p, int id, const void* A, const void* B, const void* bias, const void* Y) {
+  return p->family[id].kind == TF_KIND_MFMA_LDS_ANY && !tile_aligned(A, B, bias, Y) ? p->impl[id].any_id : id;
+}
+
 // The placement the L2-local reduction relies on, per device: 0 = not probed yet, 1 = confirmed, -1 = refuted.
 int g_placement[64];
 
@@ -616,8 +621,8 @@ tf_status do_launch(tf_problem* p, int id, const void* A, const void* B, const v
   tf_status st = check_ptrs(p, v, A, B, bias, Y);
   if (st != TF_OK) return st;
   if (d.M == 0 || d.N == 0) return TF_OK;   // nothing to compute
-  if (v.kind == TF_KIND_MFMA_LDS_ANY && !tile_aligned(A, B, bias, Y))
-    return do_launch(p, im.any_id, A, B, bias, Y, ws, ws_bytes, stream, epi_override, ldy_override);
+  const int runs = launched(p, id, A, B, bias, Y);
+  if (runs != id) return do_launch(p, runs, A, B, bias, Y, ws, ws_bytes, stream, epi_override, ldy_override);
   tf::GemmParams g;
   memset(&g, 0, sizeof(g));
   g.A = (const uint16_t*)A; g.B = (const uint16_t*)B; g.bias = (const uint16_t*)bias; g.Y = Y;
@@ -886,7 +891,8 @@ __global__ void gate_sin_kernel(const float* y, const float* ref, size_t n, unsi
 }
 
 // Copies of the operands that the Profile stage cycles through, one set per launch, so that a
-// launch never finds A, B or Y in L2 or the memory-side cache. One allocation holds them all.
+// launch never finds A, B or Y in L2 or the memory-side cache. One allocation holds them all. Each lies as its
+// original does modulo 256 bytes: what is timed is the kernel that runs on the caller's pointers.
 struct Rotation {
   void* base = nullptr;
   std::vector<const void*> A, B;
@@ -1026,7 +1032,7 @@ tf_status tune_profile(void* user, int32_t id, tf_report* out) {
   // hint that follows then reads matrix-pipe, memory and LDS figures instead of rates derived from the time
   if (!p->counter_files.empty() && p->have_hw) {
     char name[192];
-    if (tf_variant_kernel_name(&p->family[id], name, (int32_t)sizeof(name)) > 0)
+    if (tf_variant_kernel_name(&p->family[launched(p, id, c->A, c->B, c->bias, c->Y)], name, (int32_t)sizeof(name)) > 0)
       for (const std::string& f : p->counter_files) (void)tf_report_set_counters(out, &p->hw, f.c_str(), name);   // (a pass without this kernel adds nothing)
   }
   return TF_OK;
@@ -1128,7 +1134,9 @@ tf_status profile_impl(tf_problem* p, int id, const void* A, const void* B, cons
     out->pct_mfma_peak = 100.0 * out->tflops / p->hw.bf16_tflops_peak;
     out->pct_hbm_peak = 100.0 * out->gbytes_per_s / p->hw.hbm_gbs_peak;
   }
-  fill_static(p, id, out);
+  // the figures of the kernel that was timed
+  if (rot && !rot->A.empty()) fill_static(p, launched(p, id, rot->A[0], rot->B[0], bias, rot->Y[0]), out);
+  else fill_static(p, launched(p, id, A, B, bias, Y), out);
   out->parity_ok = 0;
   out->bottleneck = tf_refine_hint(nullptr, out, &p->hw);
   return TF_OK;
@@ -1609,8 +1617,9 @@ extern "C" tf_status tf_tune(tf_problem* p, const void* A, const void* B, const 
       araw = ((size_t)(d.batch - 1) * d.stride_a + (size_t)(d.K - 1) * d.lda + d.M) * 2;
       braw = ((size_t)(d.batch - 1) * d.stride_b + (size_t)(d.K - 1) * d.ldb + d.N) * 2;
     }
-    const size_t abytes = up(araw), bbytes = up(braw);
-    const size_t ybytes = up(c.ybytes), set = abytes + bbytes + ybytes;
+    const size_t aoff = (uintptr_t)A & 255u, boff = (uintptr_t)B & 255u, yoff = (uintptr_t)Y & 255u;
+    const size_t abytes = up(aoff + araw), bbytes = up(boff + braw);
+    const size_t ybytes = up(yoff + c.ybytes), set = abytes + bbytes + ybytes;
     const size_t n = std::min<size_t>((size_t)th.cold_bytes / set + 2, 256);
     if (hipMalloc(&rot.base, n * set) != hipSuccess) {
       (void)hipGetLastError();
@@ -1619,11 +1628,11 @@ extern "C" tf_status tf_tune(tf_problem* p, const void* A, const void* B, const 
       return fail(TF_E_NOMEM, "cannot allocate %zu bytes of rotating operand copies (theta.cold_bytes)", n * set);
     }
     for (size_t i = 0; i < n && st == TF_OK; ++i) {
-      char* a = (char*)rot.base + i * set;
+      char *const base = (char*)rot.base + i * set, *const a = base + aoff, *const b = base + abytes + boff;
       if (hipMemcpyAsync(a, A, araw, hipMemcpyDeviceToDevice, c.stream) != hipSuccess ||
-          (braw > 0 && hipMemcpyAsync(a + abytes, B, braw, hipMemcpyDeviceToDevice, c.stream) != hipSuccess))
+          (braw > 0 && hipMemcpyAsync(b, B, braw, hipMemcpyDeviceToDevice, c.stream) != hipSuccess))
         st = fail(TF_E_LAUNCH, "copying the operands failed");
-      rot.A.push_back(a); rot.B.push_back(a + abytes); rot.Y.push_back(a + abytes + bbytes);
+      rot.A.push_back(a); rot.B.push_back(b); rot.Y.push_back(base + abytes + bbytes + yoff);
     }
     if (st == TF_OK && hipStreamSynchronize(c.stream) != hipSuccess) st = fail(TF_E_LAUNCH, "copying the operands failed");
     c.rot = &rot;
