@@ -433,7 +433,8 @@ int64_t tf_gate_count_bad(const void* Y, int64_t ldy, const float* zref, const f
                           int32_t K, int32_t epi);
 
 /* Algorithm 1. Profiles the baseline (variant 0), then runs at most theta->max_rounds rounds of
- * Proposal -> BuildRun -> parity gate -> Profile -> Arbiter -> RefineHint. round_log (host
+ * Proposal -> BuildRun -> parity gate -> Profile -> Arbiter -> RefineHint, over the variants that run on
+ * the alignment of A, B, bias and Y (one of those that are the same launch there). round_log (host
  * pointer, capacity log_cap >= 1 + max_rounds) receives the baseline report followed by one
  * report per round; *n_log their number. *best_variant / *best get K* and R*. Y is filled with
  * NaN before every candidate's BuildRun, so an element a candidate does not write fails the gate.
@@ -441,7 +442,8 @@ int64_t tf_gate_count_bad(const void* Y, int64_t ldy, const float* zref, const f
  * pre-activation by the rule of tf_gate_count_bad (on the device). Profile here is Sec. 3.4's
  * 3 warm-up + 5 timed iterations, each timed iteration a batch of launches of about 3 ms, after
  * further untimed launches until 60 ms have been spent on the candidate (the clock needs that
- * long to settle after a change of load), on rotating copies of the operands (theta->cold_bytes). */
+ * long to settle after a change of load), on rotating copies of the operands (theta->cold_bytes), which
+ * lie as the originals do modulo 256 bytes. */
 tf_status tf_tune(tf_problem* p, const void* A, const void* B, const void* bias, void* Y,
                   void* workspace, size_t workspace_bytes, void* hip_stream,
                   const tf_theta* theta, tf_parity_fn parity, void* parity_user,

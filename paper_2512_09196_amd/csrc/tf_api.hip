@@ -1637,8 +1637,14 @@ extern "C" tf_status tf_tune(tf_problem* p, const void* A, const void* B, const 
     if (st == TF_OK && hipStreamSynchronize(c.stream) != hipSuccess) st = fail(TF_E_LAUNCH, "copying the operands failed");
     c.rot = &rot;
   }
+  // which variants run on these pointers, and as what (the baseline's refusal is the loop's to report)
+  std::vector<int32_t> launches(p->family.size());
+  for (size_t i = 0; i < launches.size(); ++i) {
+    launches[i] = launched(p, (int)i, A, B, bias, Y);
+    if (i > 0 && check_ptrs(p, p->family[launches[i]], A, B, bias, Y) != TF_OK) launches[i] = -1;
+  }
   if (st == TF_OK)
-    st = tf::run_loop(&p->desc, &p->hw, p->family.data(), (int32_t)p->family.size(), &th, tune_profile, &c, best_variant,
+    st = tf::run_loop(&p->desc, &p->hw, p->family.data(), (int32_t)p->family.size(), launches.data(), &th, tune_profile, &c, best_variant,
                       best, round_log, log_cap, n_log);
   if (rot.base) (void)hipFree(rot.base);
   if (c.yref) (void)hipFree(c.yref);

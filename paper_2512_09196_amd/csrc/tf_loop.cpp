@@ -449,7 +449,7 @@ extern "C" int32_t tf_proposal(const tf_problem_desc* prob, const tf_hw* hw, con
 namespace tf {
 
 tf_status run_loop(const tf_problem_desc* prob, const tf_hw* hw, const tf_variant_desc* family, int32_t n,
-                   const tf_theta* theta, profile_fn profile, void* user, int32_t* best_variant, tf_report* best,
+                   const int32_t* launches, const tf_theta* theta, profile_fn profile, void* user, int32_t* best_variant, tf_report* best,
                    tf_report* round_log, int32_t log_cap, int32_t* n_log) {
   if (!prob || !hw || !family || n <= 0 || !theta || !profile || !best_variant || !best || !round_log || !n_log)
     return TF_E_INVALID;
@@ -467,9 +467,16 @@ tf_status run_loop(const tf_problem_desc* prob, const tf_hw* hw, const tf_varian
   int kstar = 0, kcur = 0, bottleneck = TF_BN_UNKNOWN;   // first proposal: the static one-shot pick
   int stall = 0;
   for (int round = 1; round <= theta->max_rounds; ++round) {
-    const int cand = tf_proposal(prob, hw, family, n, tried, kcur, bottleneck);
+    int cand = tf_proposal(prob, hw, family, n, tried, kcur, bottleneck);
+    while (cand >= 0 && launches && launches[cand] < 0) {        // not on these operands: the next one
+      tried[cand] = 1;
+      cand = tf_proposal(prob, hw, family, n, tried, kcur, bottleneck);
+    }
     if (cand < 0) break;                          // family exhausted
     tried[cand] = 1;
+    if (launches)
+      for (int i = 0; i < n; ++i)
+        if (launches[i] == launches[cand]) tried[i] = 1;
     tf_report Rc;
     st = profile(user, cand, &Rc);                // BuildRun + parity gate + Profile
     if (st != TF_OK) { Rc.status = st; Rc.variant_id = cand; }
@@ -483,6 +490,7 @@ tf_status run_loop(const tf_problem_desc* prob, const tf_hw* hw, const tf_varian
     // starts from; otherwise the next proposal starts again from K*. Either way the newest
     // valid diagnosis gives the direction.
     kcur = (dec == TF_DEC_ACCEPT) ? cand : kstar;
+    if (launches) kcur = launches[kcur];          // (the kernel that the diagnosis is about)
     bottleneck = (Rc.status == TF_OK && Rc.t_med_us > 0.0) ? Rc.bottleneck : Rstar.bottleneck;
     R = Rc;
   }
@@ -512,5 +520,5 @@ extern "C" tf_status tf_tune_replay(const tf_problem_desc* prob, const tf_hw* hw
                                     int32_t log_cap, int32_t* n_log) {
   if (!reports) return TF_E_INVALID;
   SimCtx c{reports, n};
-  return tf::run_loop(prob, hw, family, n, theta, sim_profile, &c, best_variant, best, round_log, log_cap, n_log);
+  return tf::run_loop(prob, hw, family, n, nullptr, theta, sim_profile, &c, best_variant, best, round_log, log_cap, n_log);
 }

@@ -13,7 +13,9 @@ inline bool is_kshare(const tf_variant_desc* v) {
 // Profile callback: BuildRun + parity gate + Profile of variant `id` into *out.
 typedef tf_status (*profile_fn)(void* user, int32_t id, tf_report* out);
 
+// launches: per variant, the variant that runs in its place on the caller's operands, or -1 where those are refused
+// (null: every variant runs as itself). The loop proposes no refused variant and no launch twice.
 tf_status run_loop(const tf_problem_desc* prob, const tf_hw* hw, const tf_variant_desc* family, int32_t n,
-                   const tf_theta* theta, profile_fn profile, void* user, int32_t* best_variant, tf_report* best,
+                   const int32_t* launches, const tf_theta* theta, profile_fn profile, void* user, int32_t* best_variant, tf_report* best,
                    tf_report* round_log, int32_t log_cap, int32_t* n_log);
 }  // namespace tf

@@ -49,3 +49,22 @@ def test_reports_describe_the_kernel_that_ran(shape):
             print("round", shape, vs[r.variant_id].name.decode(), r.status, "%.2f us" % r.t_med_us, flush=True)
             if r.status == tf.TF_OK:
                 assert figures(r) == at_odd[r.variant_id], vs[r.variant_id].name
+
+
+@pytest.mark.parametrize("shape", SHAPES + [(512, 512, 2048, 0)])
+def test_the_loop_spends_its_rounds_on_different_launches(shape):
+    """No variant that refuses the operands, no launch twice: the any-address kernels, then the one-wave kernel, whatever the
+    number of variants that fall back to them (none, for the last shape, which is no small problem)."""
+    ops = odd_operands(*shape)
+    M, N, K, nk = shape
+    with tf.Problem(M, N, K, trans_b=nk) as prob:
+        vs = prob.variants()
+        best, rep, log = prob.tune(*ops)
+        ran = []
+        for r in log:
+            print("round", shape, vs[r.variant_id].name.decode(), r.status, "%.2f us" % r.t_med_us, flush=True)
+            assert r.status == tf.TF_OK
+            ran.append(falls_back_to(prob, vs[r.variant_id]))
+        assert len(set(ran)) == len(ran)
+        assert set(ran) == {v.id for v in vs if v.kind in (tf.TF_KIND_NAIVE, tf.TF_KIND_MFMA_ANY, tf.TF_KIND_MFMA_DIRECT)}
+        assert best != 0
