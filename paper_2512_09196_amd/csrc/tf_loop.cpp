@@ -207,13 +207,16 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
     return 4.0 + fmax(fmax(traffic / (t64 ? 9.5e6 : 13.0e6), hbm_us / 0.55), serial);
   }
   if (tf::is_kshare(v)) {
-    // Fitted (log error, 12 % rms) to 893 timings of these kernels on 176 problems from 1 x 4096 x 11008 to 2965 x 1104 x 2224:
-    // a CU fetches the panels of its tiles at 76 to 97 GB/s, the L2s together what their tiles need at 7.4 TB/s (the two
-    // overlap in part), a launch takes 2.9 us and a further round of work-groups costs 2.3 beside its bytes.
+    // Fitted (log error, 12 % rms) to 893 timings of these kernels on 176 problems from 1 x 4096 x 11008 to 2965 x 1104 x 2224
+    // (13 % rms over three thousand timings on 700 others):
+    // a CU fetches the panels of its tiles at 76 to 101 GB/s (rows of 32 columns of a [K][N] B are half a 128-byte line), the
+    // L2s together what their tiles need at 7.4 TB/s (the two overlap in part), a launch takes 2.9 us and a further round of
+    // work-groups costs 2.3 beside its bytes.
     const int s = v->split_k, res = tf_resident_wgs(hw, v);
     const long tm = cdiv(pr->M, v->bm), tn = cdiv(pr->N, v->bn), nkt = cdiv(pr->K, 64);
     const double load = (double)(tm * tn * s) / hw->cus;
-    const double fetch = (v->bm + v->bn) * 128.0 * cdiv(nkt, s) * fmax(1.0, ceil(load - 1e-9)) / (v->bm > 32 ? 76.3e3 : 96.4e3);
+    const double rate = v->bm > 32 ? 76.3e3 : v->bn > 32 ? 96.4e3 : pr->trans_b ? 101.2e3 : 89.7e3;
+    const double fetch = (v->bm + v->bn) * 128.0 * cdiv(nkt, s) * fmax(1.0, ceil(load - 1e-9)) / rate;
     // an XCD's run of neighbouring tiles (8 / s XCDs share the tiles of a slice), in columns of group_m
     const double run = (double)(tm * tn) / (s >= 8 ? 1 : 8 / s), gm = v->group_m > 0 ? v->group_m : 1;
     const double rows = fmin((double)tm, run < gm ? fmax(1.0, run) : gm * fmax(1.0, ceil(run / (gm * tn)))), cols = fmin((double)tn, fmax(1.0, run / gm));
@@ -222,9 +225,22 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
     // slices: the acknowledgement of the partial tile, the ticket, the other slices' tiles
     const double tile_bytes = v->bm * (double)v->bn * 4.0;
     if (s > 1) us += 1.45 + 1.16e-5 * s * tile_bytes + 6.1e-7 * load * hw->cus * tile_bytes;
-    // (the figures below are up to a quarter high for the tile kernels at these sizes; with 1.15 the picks over 189
-    // problems are 1.9 % behind the fastest variant of either kind, with 1.0 and 1.25 2.6 and 2.7 %)
-    return 1.15 * us;
+    // On the scale of what it is compared with. Small problems, the any-address kernels: a factor. (Where rows start
+    // off 128-byte lines the two are level, 0.9 to 1.1 over 300 problems; on whole lines these lead by 3 to 12 %.)
+    if (v->kind == TF_KIND_MFMA_LDS_ANY) return 1.15 * us;
+    // Otherwise the tile kernels. Operands that no cache holds (three such sets are more than the memory-side cache's 256 MB)
+    // arrive at 3.6 TB/s in half lines of B, at 4.2 in slices (16 x 8192 x 8192 31.8 us, the tile kernels' 26.5), at 4.6 in
+    // whole lines and whole sums (11008 x 5120 24.3).
+    const double opnd_bytes = 2.0 * ((double)pr->M * pr->K + (double)pr->K * pr->N);
+    if (!pr->trans_b && opnd_bytes > 95e6) us = fmax(us, 2.9 + opnd_bytes / (v->bn <= 32 ? 3.6e6 : s > 1 ? 4.25e6 : 4.6e6));
+    // Where K is whole tiles their 64 x 64 tiles, with the K order rotated or a K tile of 128, are 5 to 15 % faster than these
+    // without slices up to a K of about 2000; where it is ragged, 0 to 10 % slower.
+    if (v->bm > 32 && s == 1 && pr->K % 64 == 0) us *= 1.0 + 0.3 * exp(-(double)nkt / 40.0);
+    // The tile kernels' figure below is high by what it counts for start-up: 1.4 us, up to 3.4 where K is short (917 x 640 x
+    // 320 4.0 us measured, 6.7 predicted). With one factor, 1.15, in place of all this, 101 of 1350 picks were 2 to 23 % slower
+    // than the other kernels' (917 x 640 x 320 4.8 / 4.0 us, 1103 x 640 x 448 5.5 / 4.9, 25 x 7808 x 6208 25.5 / 21.5) and the
+    // picks 4.4 % behind the best; now 44 are, and 3.0 %.
+    return (s > 1 ? 0.97 : 1.0) * us + 1.4 + (v->bm > 32 ? 2.0 : 1.2) * exp(-(double)nkt / 12.0);
   }
   if (v->kind == TF_KIND_MFMA_STREAM) {
     // B is read once at the rate the chip sustains from HBM, if enough waves keep loads in flight

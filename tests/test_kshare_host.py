@@ -45,3 +45,29 @@ def test_the_hint_leads_to_a_kernel_whose_waves_share_k():
         other = next(v for v in fam if not tried[v.id] and not follows(tf.TF_BN_UNDERFILLED, base, v))
         pred[want.id], pred[other.id] = 2.0, 1.0
         assert tf.proposal_from(HW, fam, pred, tried, base.id, tf.TF_BN_UNDERFILLED) == want.id
+
+
+# us, operands of three calls in turn: the best of the other kernels and these kernels' best where a wrong scale between the
+# two predictions took, or would take, the slower of them
+MEASURED = [((917, 640, 320, 0), {"lds_64x64x64_w2x2_s3_direct_sk1": 3.93, "kshare_64x64x64_k8_s1_sk1": 4.73}),
+            ((1883, 320, 384, 0), {"lds_64x64x128_w2x2_s3_direct_sk1": 4.23, "kshare_64x64x64_k8_s1_sk1": 4.95}),
+            ((1385, 384, 320, 1), {"lds_64x64x64_w2x2_s3_direct_bnk_sk1": 4.32, "kshare_64x64x64_k8_s1_bnk_sk1": 4.96}),
+            ((2073, 448, 448, 1), {"lds_64x64x64_w2x2_s3_direct_bnk_sk1": 4.80, "kshare_64x64x64_k8_s1_bnk_sk1": 5.55}),
+            ((67, 7552, 256, 0), {"lds_64x64x128_w2x2_s3_direct_sk1": 3.96, "kshare_64x64x64_k8_s1_sk1": 4.58}),
+            ((1103, 640, 448, 0), {"lds_64x64x64_w2x2_s3_direct_sk1": 4.92, "kshare_64x64x64_k8_s1_sk1": 5.46}),
+            ((277, 2368, 1792, 0), {"lds_64x64x128_w2x2_s3_direct_sk1x": 8.76, "kshare_64x64x64_k8_s1_sk1": 9.68}),
+            ((25, 7808, 6208, 0), {"lds_32x128x64_w1x4_s3_direct_rr_sk4r": 21.8, "kshare_32x32x64_k4_s2_sk1": 24.9}),
+            ((16, 8192, 8192, 0), {"lds_32x128x64_w1x4_s3_direct_rr_sk4l": 26.5, "kshare_32x64x64_k8_s1_sk2f": 31.8, "kshare_32x32x64_k4_s2_sk1": 38.1}),
+            ((512, 512, 8192, 0), {"kshare_64x64x64_k8_s1_sk4f": 14.6, "lds_64x64x64_w2x2_s3_direct_sk8r": 17.9}),
+            ((283, 448, 8512, 0), {"kshare_32x64x64_k8_s1_sk4f": 11.4, "lds_64x64x64_w2x2_s3_direct_sk8r": 13.6}),
+            ((333, 640, 8128, 0), {"kshare_32x64x64_k8_s1_sk2f": 15.8, "lds_128x128x64_w2x4_s3_direct_sk16r": 20.6})]
+
+
+@pytest.mark.parametrize("shape,us", MEASURED, ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else "")
+def test_the_static_pick_is_the_faster_kind(shape, us):
+    M, N, K, b_as_nk = shape
+    with tf.Problem(M, N, K, trans_b=b_as_nk) as p:
+        fam = p.variants()
+        pick = fam[tf.proposal(p.desc, HW, fam, [v.id == 0 for v in fam], 0, tf.TF_BN_UNKNOWN)].name.decode()
+        assert set(us) <= {v.name.decode() for v in fam}
+        assert us.get(pick) == min(us.values()), pick
