@@ -33,9 +33,10 @@ struct KshareCfg : LdsCfg<BM_, BN_, 64, 1, 1, S_, true, false, 1, false, TB_> {
   static constexpr int RING = S_ * Base::STAGE_BYTES;
   static constexpr int WG_LDS = NW_ * RING;
   static constexpr int CPR = BN_ / 4, CHUNKS = BM_ * CPR;     // 16-byte pieces of fp32 sums: per row, per tile
-  static constexpr int PER_THREAD = (CHUNKS + WG_THREADS - 1) / WG_THREADS;
+  static constexpr int PER_THREAD = CHUNKS / WG_THREADS;
   static_assert(BM_ * BN_ * 4 <= RING, "the partial sums fit where the tiles were");
-  static_assert((S_ - 1) * PER_TILE < 64, "vmcnt range");
+  static_assert(S_ <= 2 && PER_TILE < 64, "the main loop waits for at most one younger K tile; vmcnt range");
+  static_assert(CHUNKS % WG_THREADS == 0, "the pieces divide over the threads");
   static_assert(WG_LDS <= 160 * 1024, "LDS budget of one CU");
 };
 
@@ -68,7 +69,7 @@ __global__ void __launch_bounds__(C::WG_THREADS) tf_gemm_kshare_kernel(const Gem
     if (j >= base + (sub < rem ? 1 : 0)) return;
     tile = sub * base + (sub < rem ? sub : rem) + j;
   } else {
-    tile = p.xcd_swizzle ? xcd_run(blockIdx.x, tiles) : (int)blockIdx.x;
+    tile = xcd_run(blockIdx.x, tiles);
   }
   const TileCoord tc = tile_at(p, tile);
   const int m0 = tc.tm * C::BM, n0 = tc.tn * C::BN;
@@ -110,11 +111,8 @@ __global__ void __launch_bounds__(C::WG_THREADS) tf_gemm_kshare_kernel(const Gem
 
   int stage = 0;
   for (int i = 0; i < n_own; ++i) {
-    // this tile has landed; up to STAGES - 1 younger ones may still fly
-    const int ahead = n_own - 1 - i;
-    if (C::STAGES > 3 && ahead >= 3) wait_vmcnt<(C::STAGES > 3 ? 3 : 0) * C::PER_TILE>();
-    else if (C::STAGES > 2 && ahead >= 2) wait_vmcnt<(C::STAGES > 2 ? 2 : 0) * C::PER_TILE>();
-    else if (C::STAGES > 1 && ahead >= 1) wait_vmcnt<(C::STAGES > 1 ? 1 : 0) * C::PER_TILE>();
+    // this tile has landed; with two buffers the next one may still fly
+    if (C::STAGES > 1 && i + 1 < n_own) wait_vmcnt<(C::STAGES - 1) * C::PER_TILE>();
     else wait_vmcnt<0>();
     asm volatile("" ::: "memory");
     char* const st = ring + stage * C::STAGE_BYTES;
@@ -183,10 +181,8 @@ __global__ void __launch_bounds__(C::WG_THREADS) tf_gemm_kshare_kernel(const Gem
   for (int y = 0; y < C::PER_THREAD; ++y) {
     const int x = tid + y * C::WG_THREADS, r = x / C::CPR, c = x % C::CPR;
     z[y] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    if (C::CHUNKS % C::WG_THREADS == 0 || x < C::CHUNKS) {
 #pragma unroll
-      for (int w = 0; w < C::NW; ++w) z[y] += *(const f32x4*)(smem + w * C::RING + (r * C::CPR + (c ^ swz(r))) * 16);
-    }
+    for (int w = 0; w < C::NW; ++w) z[y] += *(const f32x4*)(smem + w * C::RING + (r * C::CPR + (c ^ swz(r))) * 16);
   }
 
   if (p.split_k > 1) {
@@ -197,7 +193,7 @@ __global__ void __launch_bounds__(C::WG_THREADS) tf_gemm_kshare_kernel(const Gem
 #pragma unroll
     for (int y = 0; y < C::PER_THREAD; ++y) {
       const int x = tid + y * C::WG_THREADS, r = x / C::CPR;
-      ok[y] = (C::CHUNKS % C::WG_THREADS == 0 || x < C::CHUNKS) && m0 + r < p.M && n_ok;
+      ok[y] = m0 + r < p.M && n_ok;
       if (ok[y]) store_device(corner + ks * slice + (size_t)r * p.N, z[y]);
     }
     // every store of this wave has been acknowledged before the wave reaches the barrier, so the ticket taken behind
@@ -236,7 +232,7 @@ __global__ void __launch_bounds__(C::WG_THREADS) tf_gemm_kshare_kernel(const Gem
 #pragma unroll
   for (int y = 0; y < C::PER_THREAD; ++y) {
     const int x = tid + y * C::WG_THREADS, m = m0 + x / C::CPR;
-    if ((C::CHUNKS % C::WG_THREADS != 0 && x >= C::CHUNKS) || m >= p.M || !n_ok) continue;
+    if (m >= p.M || !n_ok) continue;
     const float z0 = z[y][0] + b0, z1 = z[y][1] + b1, z2 = z[y][2] + b2, z3 = z[y][3] + b3;
     if (p.epi == TF_EPI_NONE_F32) {
       const f32x4 v = {z0, z1, z2, z3};

@@ -84,6 +84,7 @@ struct LdsCfg {
   static_assert(BN == 32 || BN == 64 || BN == 128 || BN == 256, "B row must be 64, 128, 256 or 512 bytes");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of one CU");
   static_assert(WK == 1 || (WK == 2 && TM % 2 == 0 && DIRECT && !ABYPASS), "k groups: two, each keeps half of the row blocks");
+  static_assert(WK == 1 || WM * WN > 1, "one wave per k group and several groups: how a descriptor names the kernels of tf_gemm_kshare.hip");
   static_assert(!TRANSA || (DIRECT && !ABYPASS && (BM == 32 || BM == 64 || BM == 128 || BM == 256)), "transposed A: direct staging, A row of 64 to 512 bytes");
   static_assert(WK == 1 || RING_BYTES >= NWAVES * (TM / 2) * TN * 4096, "the accumulator exchange reuses the tile buffers");
   static constexpr int TM_OUT = TM / WK;                   // row blocks a wave writes out
