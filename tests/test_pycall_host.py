@@ -3,6 +3,7 @@ callback stands in for tf_variant_run; no GPU."""
 import ctypes as C
 import os
 import sysconfig
+import threading
 
 import numpy as np
 import pytest
@@ -111,3 +112,56 @@ def test_the_module_is_this_interpreters_and_not_needed(monkeypatch, tmp_path):
     monkeypatch.setattr(build, "PYCALL", str(tmp_path / "_tfcall.so"))
     monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
     assert build.build_pycall() is None and not os.listdir(tmp_path)
+
+
+def test_a_forked_child_asks_torch_again(call):
+    m, seen = call
+    m.bind_stream(lambda dev: 100 + dev, lambda: 2)
+    pid = os.fork()
+    if pid == 0:
+        ok = False
+        try:
+            m.run(1, 0, 0, 0, 0, 0, 0, 0, None)
+            ok = seen[-1][-1] == 77              # torch.cuda's own way, which refuses a forked child
+        finally:
+            os._exit(0 if ok else 1)
+    assert os.waitpid(pid, 0)[1] == 0
+    m.run(1, 0, 0, 0, 0, 0, 0, 0, None)
+    assert [s[-1] for s in seen] == [102]
+
+
+def test_calls_from_several_threads(call):
+    m, seen = call
+    here = threading.local()
+    m.bind_stream(lambda dev: 1000 * here.n, lambda: 0)
+
+    def work(n):
+        here.n = n
+        for i in range(200):
+            m.run(n, i, n, 2 * n, 3 * n, 4 * n, 0, i, None)
+    ts = [threading.Thread(target=work, args=(n,)) for n in range(1, 5)]
+    [t.start() for t in ts]
+    [t.join() for t in ts]
+    assert sorted(seen) == [(n, i, n, 2 * n, 3 * n, 4 * n, None, i, 1000 * n) for n in range(1, 5) for i in range(200)]
+
+
+@pytest.mark.gpu
+def test_the_current_stream_of_the_calling_thread(call):
+    """Without a stream argument the call goes to torch's current stream: of this thread, and of another."""
+    m, seen = call
+    cb = RUN(lambda *a: seen.append(a) or 0)
+    m.bind(C.cast(cb, C.c_void_p).value, tf._current_stream)
+    torch.zeros(1, device="cuda")
+    got = []
+
+    def work(s):
+        with torch.cuda.stream(s):
+            for _ in range(2):                   # the slow way once, then torch's C functions
+                m.run(1, 0, 0, 0, 0, 0, 0, 0, None)
+                got.append((seen[-1][-1] or 0, s.cuda_stream))
+    for s in (torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream()):
+        work(s)
+        t = threading.Thread(target=work, args=(s,))
+        t.start()
+        t.join()
+    assert len(got) == 12 and all(a == b for a, b in got)
