@@ -129,6 +129,7 @@ SIGNATURES = {
 
 _lib = None
 _pycall = None
+_run = None             # what Problem.run calls
 
 
 class TfError(RuntimeError):
@@ -139,7 +140,7 @@ class TfError(RuntimeError):
 
 def lib():
     """The loaded library. Raises if it has not been built: there is no other code path."""
-    global _lib, _pycall
+    global _lib, _pycall, _run
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -164,6 +165,7 @@ def lib():
             raise RuntimeError("%s was built from another include/tf.h (struct sizes %s, this binding has %s): "
                                "rebuild it with `python -m paper_2512_09196_amd.build`" % (LIB_PATH, list(built), mine))
         _pycall = _load_pycall(l)
+        _run = _ctypes_run if _pycall is None else _pycall.run
         _lib = l
     return _lib
 
@@ -180,6 +182,11 @@ def _load_pycall(l):
     # a forked child must not use its parent's GPU state: it goes through torch.cuda, which says so
     os.register_at_fork(after_in_child=lambda: m.bind_stream(None, None))
     return m
+
+
+def _ctypes_run(handle, variant_id, A, B, bias, Y, workspace, workspace_bytes, stream):
+    return lib().tf_variant_run(handle, variant_id, _ptr(A), _ptr(B), _ptr(bias), _ptr(Y), _ptr(workspace), workspace_bytes,
+                                _stream(stream))
 
 
 def _check(st):
@@ -385,11 +392,10 @@ class Problem:
         return [arr[i] for i in range(n2)]
 
     def run(self, variant_id, A, B, bias, Y, workspace=None, workspace_bytes=0, stream=None):
-        if _pycall is not None and type(variant_id) is int and type(workspace_bytes) is int:
-            st = _pycall.run(self._h.value or 0, variant_id, A, B, bias, Y, workspace, workspace_bytes, stream)
-        else:       # integers of other types (numpy's, a tensor's, ctypes' own): ctypes converts them, or says why not
-            st = lib().tf_variant_run(self._h, variant_id, _ptr(A), _ptr(B), _ptr(bias), _ptr(Y), _ptr(workspace),
-                                      workspace_bytes, _stream(stream))
+        try:
+            st = _run(self._h.value or 0, variant_id, A, B, bias, Y, workspace, workspace_bytes, stream)
+        except TypeError:       # integers of other types (numpy's, a tensor's, ctypes' own): ctypes converts them, or says why not
+            st = _ctypes_run(self._h.value or 0, variant_id, A, B, bias, Y, workspace, workspace_bytes, stream)
         if st != TF_OK:
             _check(st)
 

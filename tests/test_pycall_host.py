@@ -105,6 +105,7 @@ def test_the_module_is_this_interpreters_and_not_needed(monkeypatch, tmp_path):
     assert tf._pycall.__file__ == tf.PYCALL_PATH
     monkeypatch.setattr(tf, "_lib", None)
     monkeypatch.setattr(tf, "_pycall", None)
+    monkeypatch.setattr(tf, "_run", None)
     monkeypatch.setattr(tf, "PYCALL_PATH", str(tmp_path / "missing.so"))
     with tf.Problem(0, 64, 64) as p, pytest.raises(tf.TfError, match="variant id 7 out of range"):
         assert tf._pycall is None
