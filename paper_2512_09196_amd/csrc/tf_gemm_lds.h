@@ -455,7 +455,7 @@ __device__ __forceinline__ void epilogue_staged(const f32x16 (&acc)[C::TM][C::TN
   static_assert(C::ST_ROWS * CPR % C::THREADS == 0, "pieces divide over the threads");
   const char* bias_lds = smem + C::BIAS_OFF + (wave_n * C::WTN + 4 * lane_g) * 2;
   char* wr = smem + ((wave_m * C::WK + wave_k) * 32 + lane_m) * ROWB + (wave_n * C::WTN + 4 * lane_g) * ESZ;
-  wait_vmcnt<0>();          // no transfer into the ring is in flight any more (the clamped tail prefetches)
+  wait_vmcnt<0>();          // no transfer into LDS is in flight any more (the K loops leave none; the bias of a work-group without K tiles may be)
   barrier_lds();            // and nobody reads tile fragments any more
 #pragma unroll
   for (int i = 0; i < C::TM_OUT; ++i) {
@@ -742,9 +742,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
 
   // The last tile is peeled off the loop, and so are the ones behind which nothing more is fetched: the
   // loop body has no branch inside and is scheduled as one block, with constant vmcnt waits. (The A-bypass kernel
-  // re-fetches the last tile past the end, into a buffer nobody reads any more. With every kernel doing that, a
-  // work-group fetched STAGES - 1 K tiles more than it has, at the rate that bounds the K loop, and waited for them
-  // before its epilogue.)
+  // re-fetches the last tile past the end, into a buffer nobody reads any more, and the register-staged kernels into
+  // registers. With every kernel doing that, a work-group fetched STAGES - 1 K tiles more than it has, at the rate that
+  // bounds the K loop, and waited for them before its epilogue.)
   const int last = nkt - 1;
   // Order of the K tiles (a sum: any order is right). Without split-K the work-groups of XCD x start an
   // eighth of the way further into K than those of XCD x - 1 and wrap round: at any moment the eight XCDs
@@ -1268,9 +1268,9 @@ __global__ void __launch_bounds__(C::THREADS) tf_gemm_lds_kernel(const GemmParam
 }
 
 // The same kernel for a K that is no multiple of its K tile (1160 x 3080 x 1864: 34.0 us on the register-staged
-// kernels, 22.7 us on the direct ones). An instance of its own: with the extra address select
-// per transfer and the zeroing in every kernel, 4096 x 11008 x 4096 lost 1.2 %, 2048^3 1.5 % and 1500 x 4096 x 4096
-// with B as [N][K] 2.7 %.
+// kernels, 22.7 us on the direct ones). An instance of its own: where K is whole tiles it costs 1 to 3 % in tiles of 256 x
+// 256, 192 x 256, 128 x 128 and 64 x 64 (us, this / the ordinary kernel: 4096 x 11008 x 4096 310.9 / 305.7, 4096^3 109.8 /
+// 107.1, 2048^3 22.4 / 22.0, 3000 x 3000 x 2048 with B as [N][K] 42.7 / 41.4); tiles of 256 x 128 gain 2 % (4096^3 126.2 / 129.2).
 template <class Base>
 struct RaggedKCfg : Base {
   static_assert(Base::DIRECT && !Base::ABYPASS, "both operands staged directly");
