@@ -2,8 +2,8 @@
 //
 // One work-group computes one BM x BN tile of Y (or one K slice of it). Per K step of
 // BK (32, 64 or 128) it stages an A tile [BM][BK] and a B tile [BK][BN] in LDS, multi-buffered,
-// and each of the WM x WN waves accumulates a (BM/WM) x (BN/WN) sub-tile with
-// v_mfma_f32_32x32x16_bf16 in fp32.
+// and each of the WM x WN waves accumulates a (BM/WM) x (BN/WN) sub-tile in fp32 with
+// v_mfma_f32_16x16x32_bf16 or v_mfma_f32_32x32x16_bf16 (see LdsCfg::MB).
 //
 // LDS layouts (chosen from measured bank behaviour: 64 banks x 4 B, b128 reads are
 // conflict free when 16 consecutive lanes cover 16 distinct 16-byte slots of a 256-byte line):
@@ -12,7 +12,8 @@
 //           (BK = 64: c ^ ((r >> 1) & 7)). MFMA A operands are ds_read_b128.
 //   B tile: row-major as in memory ([k][n], n contiguous), BN*2 bytes per row, split in
 //           64-byte pieces; piece j of row k is stored in slot j ^ f(k) so that four
-//           consecutive k rows fall in four different bank groups. MFMA B operands, which
+//           consecutive k rows fall in four different bank groups (blocks of 16 x 16 also swap the halves of a
+//           piece by bit 3 of k, see b_chunk_swz). MFMA B operands, which
 //           need 8 consecutive k per lane, are read with the transposing
 //           ds_read_b64_tr_b16 (two per operand), so B is never transposed by ALU code.
 // Both tiles are written either by global_load_lds_dwordx4 (memory -> LDS without passing
@@ -46,14 +47,23 @@ struct LdsCfg {
   static constexpr bool TRANSB = TRANSB_;
   // A tile rows (and B tile rows under TRANSB): BK / 8 chunks of 16 bytes; slot = chunk ^ row_swz(row)
   static constexpr int K_ROW_BYTES = BK * 2, K_CHUNKS = BK / 8, K_ROWS_PER_LINE = 16 / K_CHUNKS, K_ROWS_PER_INSTR = 64 / K_CHUNKS;
-  static constexpr int KSTEPS = BK / 16;                   // 16-wide MFMA steps per K tile
+  // The matrix instruction: blocks of MB x MB outputs over KMF of k, 32 x 32 over 16 or 16 x 16 over 32. Both take the
+  // same cycles per flop and the same fragment bytes per wave, but the second reads and writes half as many accumulators
+  // per flop, and under load this board's clock is what its power limit leaves: register-only loops on random operands
+  // sustain 1775 TFLOP/s (1.84 GHz) with the first and 2010 (2.05 GHz) with the second, 2060 in the serpentine order below
+  // (on zeros both 2440, 2.4 GHz). It is used where the matrix pipes set the pace, in wave tiles of 64 rows and more;
+  // smaller ones wait for operands and keep the first, which needs half as many instructions.
+  static constexpr int MB = DIRECT_ && !ABYPASS_ && !TRANSA_ && WK_ == 1 && BK_ >= 64 && WM_ * WN_ > 1 && BM_ / WM_ >= 64 ? 16 : 32;
+  static constexpr int KMF = MB == 16 ? 32 : 16;
+  static constexpr int QN = MB / 16 * (MB / 16);           // runs of four accumulators a lane holds of a block
+  static constexpr int KSTEPS = BK / KMF;                  // MFMA steps per K tile
   // WK: wave groups along k. With WK = 2 a second set of WM x WN waves works on the same
   // BM x BN tile but takes the other half of every 64-wide K step; the two sets add their
   // accumulators through LDS after the main loop. Eight waves then keep the LDS busier than
   // four can (a wave issues one LDS instruction every twenty-odd cycles) without the extra
   // fragment reads that a finer split of the tile along m or n costs.
-  static constexpr int WK = WK_, KS = KSTEPS / WK_;        // k16-steps per wave per K step
-  static_assert(KS >= 2 && KS % 2 == 0, "the pipeline alternates two fragment sets per k16-step");
+  static constexpr int WK = WK_, KS = KSTEPS / WK_;        // MFMA steps per wave per K step
+  static_assert(KS >= 2 && KS % 2 == 0, "the pipeline alternates two fragment sets per MFMA step");
   static constexpr bool DIRECT = DIRECT_;
   // ABYPASS: the A operand never enters LDS. Each wave loads its own A fragments from memory
   // straight into registers (WN must be 1, so no two waves need the same A rows) and only B is
@@ -61,7 +71,22 @@ struct LdsCfg {
   static constexpr bool ABYPASS = ABYPASS_;
   static constexpr int NWAVES = WM * WN * WK, THREADS = NWAVES * 64;
   static constexpr int WTM = BM / WM, WTN = BN_ACT / WN;   // wave tile
-  static constexpr int TM = WTM / 32, TN = WTN / 32;       // 32x32 MFMA blocks per wave
+  static constexpr int TM = WTM / MB, TN = WTN / MB;       // MFMA blocks per wave
+  static constexpr int ACC = TM * TN * MB * MB / 64;       // accumulator registers per lane
+  typedef float Acc __attribute__((ext_vector_type(MB * MB / 64)));
+  // QUAD: the two-buffer eight-wave tiles of 256 columns are staged and multiplied in quadrants. A tile is made of four
+  // units, the first 128 rows of A, its other rows, and the two halves of B's columns, and every wave owns a piece of all
+  // four quadrants (see the main loop: a unit's buffer is free for the tile after next as soon as it has been read).
+  static constexpr bool QUAD = MB == 16 && BK == 64 && STAGES == 2 && WM * WN == 8 && BN == 256 && BM >= 192;
+  static constexpr int TM0 = QUAD ? 128 / (16 * WM) : TM, TN0 = QUAD ? TN / 2 : TN;     // blocks per wave in the first A and B unit
+  static constexpr int B_UNITS = QUAD ? 2 : 1, B_UNIT_COLS = BN / B_UNITS;
+  // first row and column (inside the tile) of a wave's block i, t
+  __device__ __forceinline__ static constexpr int row_off(int i, int wave_m) {
+    return i < TM0 ? wave_m * TM0 * MB + MB * i : WM * TM0 * MB + wave_m * (TM - TM0) * MB + MB * (i - TM0);
+  }
+  __device__ __forceinline__ static constexpr int col_off(int t, int wave_n) {
+    return t < TN0 ? wave_n * TN0 * MB + MB * t : WN * TN0 * MB + wave_n * (TN - TN0) * MB + MB * (t - TN0);
+  }
   static constexpr int A_BYTES = ABYPASS ? 0 : BM * BK * 2, B_BYTES = BK * BN * 2;
   static_assert(!ABYPASS || (WN == 1 && DIRECT && STAGES == 2 && WK_ == 1 && BK == 64 && !TRANSB_), "A bypass: one wave column, direct B staging, two buffers, K tile of 64");
   static_assert(DIRECT || BK == 64, "register staging: K tile of 64");
@@ -75,10 +100,15 @@ struct LdsCfg {
   static constexpr int A_INSTR = A_BYTES / 1024;           // wave-wide 1 KB transfers per tile
   static constexpr int B_INSTR = B_BYTES / 1024;
   static constexpr int A_PER_WAVE = A_INSTR / NWAVES, B_PER_WAVE = B_INSTR / NWAVES;
-  static constexpr int B_ROW_BYTES = TRANSB ? K_ROW_BYTES : BN * 2;
+  static constexpr int B_ROW_BYTES = TRANSB ? K_ROW_BYTES : B_UNIT_COLS * 2;
   static constexpr int B_ROWS_PER_INSTR = 1024 / B_ROW_BYTES;
   static constexpr int B_SLOTS_PER_ROW = B_ROW_BYTES / 16;  // 16-byte slots per B row
   static constexpr int B_PIECES = B_ROW_BYTES / 64;         // 64-byte pieces per B row
+  static constexpr int B_UNIT_BYTES = B_BYTES / B_UNITS;
+  // Ring layout: K tile by K tile, A before B; quadrant tiles all A tiles before all B tiles, so that the 16-bit offset of
+  // an LDS read reaches every buffer from one address register.
+  static constexpr int A_STRIDE = QUAD ? A_BYTES : STAGE_BYTES, B_STRIDE = QUAD ? B_BYTES : STAGE_BYTES;
+  static constexpr int B_BASE = QUAD ? STAGES * A_BYTES : A_BYTES;
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be made of 32x32 blocks");
   static_assert(A_INSTR % NWAVES == 0 && B_INSTR % NWAVES == 0, "tile loads must divide over the waves");
   static_assert(BN == 32 || BN == 64 || BN == 128 || BN == 256, "B row must be 64, 128, 256 or 512 bytes");
@@ -86,12 +116,12 @@ struct LdsCfg {
   static_assert(WK == 1 || (WK == 2 && TM % 2 == 0 && DIRECT && !ABYPASS), "k groups: two, each keeps half of the row blocks");
   static_assert(WK == 1 || WM * WN > 1, "one wave per k group and several groups: how a descriptor names the kernels of tf_gemm_kshare.hip");
   static_assert(!TRANSA || (DIRECT && !ABYPASS && (BM == 32 || BM == 64 || BM == 128 || BM == 256)), "transposed A: direct staging, A row of 64 to 512 bytes");
-  static_assert(WK == 1 || RING_BYTES >= NWAVES * (TM / 2) * TN * 4096, "the accumulator exchange reuses the tile buffers");
+  static_assert(WK == 1 || RING_BYTES >= NWAVES * ACC * 128, "the accumulator exchange reuses the tile buffers");
   static constexpr int TM_OUT = TM / WK;                   // row blocks a wave writes out
   // The in-kernel split-K reduction is only compiled for wave tiles of at most 64 accumulator
   // registers: behind bigger ones its code makes the compiler spill, and the scratch memory
   // that reserves per wave slows every launch of the kernel, split or not.
-  static constexpr bool FUSED_OK = TM * TN <= 4;
+  static constexpr bool FUSED_OK = ACC <= 64;
   static constexpr bool SEGMENTS = false;                  // see StreamKCfg
   static constexpr bool KTAIL = false;                     // see RaggedKCfg
   // Output staging (see epilogue_staged): each pass moves 32 rows per wave row (and k group) through the tile
@@ -100,7 +130,7 @@ struct LdsCfg {
   // (not behind wave tiles of 256 accumulator registers: the extra code makes the compiler spill there)
   // the persistent kernel's fp32 staging area lies behind the ring
   static constexpr int PERSIST_LDS_BYTES = RING_BYTES + ST_ROWS * (BN * 4 + 16);
-  static constexpr bool stage_ok(int esz) { return TM * TN <= 8 && ST_ROWS * (BN_ACT * esz + 16) <= RING_BYTES; }
+  static constexpr bool stage_ok(int esz) { return ACC <= 128 && ST_ROWS * (BN_ACT * esz + 16) <= RING_BYTES; }
   // 32-row tiles serve problems of few rows, where every B element is read by one work-group only: its
   // loads are marked non-temporal
   static constexpr bool B_NT = BM <= 32;
@@ -115,6 +145,13 @@ __device__ __forceinline__ int b_swz(int k) {
   if (PIECES == 2) return (k >> 1) & 1;
   return 0;
 }
+// The same in 16-byte chunks, as TileLoader and the transposing reads of 32-column (MB 32) or 16-column (MB 16) blocks
+// use it. A transposing read of 16 columns takes 32 bytes of the rows 8 g .. 8 g + 3 in lane group g: the half of the
+// 64-byte piece is permuted by bit 3 of k too, so that groups g and g + 1 fall in different banks.
+template <class C>
+__device__ __forceinline__ int b_chunk_swz(int k) {
+  return (b_swz<C::B_PIECES>(k) << 2) | (C::MB == 16 ? ((k >> 3) & 1) << 1 : 0);
+}
 
 template <class C>
 struct TileLoader {
@@ -128,8 +165,23 @@ struct TileLoader {
   int b_k[C::B_PER_WAVE];        // k row of the lane inside the tile
   bool b_ok[C::B_PER_WAVE];      // column chunk inside N
   bool a_ok[NA];                 // row inside M
+  // Quadrant tiles have no registers to spare for an offset per transfer. The transfers of a wave are 64 rows (of a
+  // k-contiguous operand) or 32 k (of a [K][N] one) apart, and a lane's chunk is the same in all of them and in both
+  // operands: the offsets of its first rows and of the chunk are enough, the rest is scalar.
+  unsigned a_first, b_first, chunk;
+  unsigned a_row, b_row, a_last, b_last;     // bytes from one row to the next, to the last row (scalar)
 
   __device__ __forceinline__ void init(const GemmParams& p, int m0, int n0, int wave, int lane) {
+    if constexpr (C::QUAD) {
+      a_row = (unsigned)p.lda * 2u;
+      b_row = (unsigned)p.ldb * 2u;
+      a_last = (unsigned)(p.M - 1) * a_row;
+      b_last = (unsigned)(p.N - 1) * b_row;
+      const int row = C::K_ROWS_PER_INSTR * wave + lane / C::K_CHUNKS;
+      chunk = 16u * ((lane % C::K_CHUNKS) ^ C::row_swz(row));
+      a_first = (unsigned)(m0 + row < p.M ? m0 + row : p.M - 1) * a_row;
+      b_first = (unsigned)(n0 + row < p.N ? n0 + row : p.N - 1) * b_row;
+    }
 #pragma unroll
     for (int q = 0; q < C::A_PER_WAVE; ++q) {
       const int ia = wave + C::NWAVES * q;
@@ -163,17 +215,16 @@ struct TileLoader {
         const int row = C::K_ROWS_PER_INSTR * ib + lane / C::K_CHUNKS;
         const int slot = lane % C::K_CHUNKS;
         const int c = slot ^ C::row_swz(row);
-        int n = n0 + row;
+        int n = n0 + row / C::B_UNIT_COLS * (C::BN_ACT / C::B_UNITS) + row % C::B_UNIT_COLS;
         b_ok[q] = n < p.N;
         if (n >= p.N) n = p.N - 1;
         b_src[q] = ((unsigned)n * (unsigned)p.ldb + 8u * c) * 2u;
         b_k[q] = 8 * c;
       } else {
         constexpr int LPR = 64 / C::B_ROWS_PER_INSTR;          // lanes per row
-        const int krow = C::B_ROWS_PER_INSTR * ib + lane / LPR;
-        const int s16 = lane % LPR;
-        const int piece = (s16 >> 2) ^ b_swz<C::B_PIECES>(krow);
-        int n = n0 + 32 * piece + 8 * (s16 & 3);
+        const int unit = C::B_ROWS_PER_INSTR * ib / C::BK;
+        const int krow = C::B_ROWS_PER_INSTR * ib % C::BK + lane / LPR;
+        int n = n0 + unit * (C::BN_ACT / C::B_UNITS) + 8 * ((lane % LPR) ^ b_chunk_swz<C>(krow));
         b_ok[q] = n < p.N;
         if (n >= p.N) n = 0;
         b_src[q] = ((unsigned)krow * (unsigned)p.ldb + (unsigned)n) * 2u;
@@ -228,13 +279,36 @@ struct TileLoader {
     }
   }
 
+  // min(first + further, last) + chunk, in three instructions where it is needed (the compiler would compute every offset
+  // ahead of the main loop and keep them all)
+  __device__ __forceinline__ unsigned row_chunk(unsigned first, unsigned further, unsigned last) const {
+    unsigned off;
+    asm volatile("v_add_u32 %0, %2, %1\n\tv_min_u32 %0, %3, %0\n\tv_add_u32 %0, %4, %0"
+                 : "=&v"(off) : "v"(first), "s"(further), "s"(last), "v"(chunk));
+    return off;
+  }
   __device__ __forceinline__ void issue_a_one(int q, const uint16_t* Ak, unsigned stage_lds, int wave) const {
     const int ia = wave + C::NWAVES * q;
-    gload_lds16(__builtin_amdgcn_readfirstlane(stage_lds + ia * 1024), a_src[q < NA ? q : 0], Ak);
+    unsigned off = a_src[q < NA ? q : 0];
+    if constexpr (C::QUAD) {
+      off = row_chunk(a_first, (unsigned)q * (64u * a_row), a_last);
+    }
+    gload_lds16(__builtin_amdgcn_readfirstlane(stage_lds + ia * 1024), off, Ak);
   }
   __device__ __forceinline__ void issue_b_one(int q, const uint16_t* Bk, unsigned stage_lds, int wave) const {
     const int ib = wave + C::NWAVES * q;
-    gload_lds16<C::B_NT>(__builtin_amdgcn_readfirstlane(stage_lds + C::A_BYTES + ib * 1024), b_src[q], Bk);
+    unsigned off = b_src[q];
+    if constexpr (C::QUAD) {
+      constexpr int PER_UNIT = C::B_PER_WAVE / C::B_UNITS;
+      const int unit = q / PER_UNIT, x = q % PER_UNIT;
+      if constexpr (C::TRANSB) {
+        off = row_chunk(b_first, (unsigned)(unit * (C::BN_ACT / C::B_UNITS) + 64 * x) * b_row, b_last);
+      } else {
+        off = b_src[unit * PER_UNIT];
+        Bk = (const uint16_t*)((const char*)Bk + (size_t)(32 * x) * b_row);
+      }
+    }
+    gload_lds16<C::B_NT>(__builtin_amdgcn_readfirstlane(stage_lds + C::A_BYTES + ib * 1024), off, Bk);
   }
   __device__ __forceinline__ void issue_a_all(const uint16_t* Ak, unsigned stage_lds, int wave) const {
 #pragma unroll
@@ -316,16 +390,16 @@ __device__ __forceinline__ void wait_through(f32x4& a, f32x4& b, f32x4& c, f32x4
 
 // Split-K: one slice's partial tile -> workspace (fp32, [slice][M][N]).
 template <class C, bool FULL, bool THROUGH>
-__device__ __forceinline__ void store_partial(const f32x16 (&acc)[C::TM][C::TN], float* wsk, const GemmParams& p,
-                                              int wm0, int wn0) {
+__device__ __forceinline__ void store_partial(const typename C::Acc (&acc)[C::TM][C::TN], float* wsk, const GemmParams& p,
+                                              int wm0, int wn0, int wave_m, int wave_n) {
 #pragma unroll
   for (int i = 0; i < C::TM_OUT; ++i) {
-    const int m = wm0 + 32 * i;
+    const int m = wm0 + C::row_off(i, wave_m);
 #pragma unroll
     for (int t = 0; t < C::TN; ++t)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int n = wn0 + 32 * t + 8 * q;
+      for (int q = 0; q < C::QN; ++q) {
+        const int n = wn0 + C::col_off(t, wave_n) + 8 * q;
         if (FULL || (m < p.M && n < p.N)) {
           const f32x4 v = {acc[i][t][4 * q], acc[i][t][4 * q + 1], acc[i][t][4 * q + 2], acc[i][t][4 * q + 3]};
           if (THROUGH) store_through_f32x4(wsk + (size_t)m * p.N + n, v);
@@ -340,21 +414,22 @@ __device__ __forceinline__ void store_partial(const f32x16 (&acc)[C::TM][C::TN],
 // THROUGH: device-scope loads (the slices may have been written through other XCDs' L2s);
 // otherwise plain 16-byte loads, for slices known to sit in this XCD's L2.
 template <class C, bool FULL, bool THROUGH>
-__device__ __forceinline__ void sum_partials(f32x16 (&acc)[C::TM][C::TN], const GemmParams& p, int wm0, int wn0) {
+__device__ __forceinline__ void sum_partials(typename C::Acc (&acc)[C::TM][C::TN], const GemmParams& p, int wm0, int wn0, int wave_m,
+                                             int wave_n) {
   const size_t slice = (size_t)p.M * p.N;
   // 16-byte loads (device scope, or plain ones for slices that sit in this XCD's L2), whole slices in flight at a
   // time: a loop over the slices per element is one long chain of dependent trips to memory, and everything behind
   // the K loop of a memory-bound problem is time in which nothing is streamed. The accumulator registers are free
   // by now: their contents have been published. Pieces outside M or N (ragged tiles) count as zero.
-  constexpr int NV = C::TM_OUT * C::TN * 4;
+  constexpr int NV = C::TM_OUT * C::TN * C::QN;
   static_assert(NV % 4 == 0 && NV <= 16, "register budget of the exchange");
   f32x4 sum[NV];
   bool ok[NV];
 #pragma unroll
   for (int x = 0; x < NV; ++x) {
-    const int i = x / (C::TN * 4), t = (x / 4) % C::TN, q = x % 4;
+    const int i = x / (C::TN * C::QN), t = (x / C::QN) % C::TN, q = x % C::QN;
     sum[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    ok[x] = FULL || (wm0 + 32 * i < p.M && wn0 + 32 * t + 8 * q < p.N);
+    ok[x] = FULL || (wm0 + C::row_off(i, wave_m) < p.M && wn0 + C::col_off(t, wave_n) + 8 * q < p.N);
   }
   // G slices are loaded together (as many as sixteen 16-byte vectors per lane allow: small tiles with two or four
   // slices make one trip to memory in all), then added in slice order
@@ -368,10 +443,10 @@ __device__ __forceinline__ void sum_partials(f32x16 (&acc)[C::TM][C::TN], const 
       const float* base = p.ws + (size_t)sidx * slice;
 #pragma unroll
       for (int x = 0; x < NV; ++x) {
-        const int i = x / (C::TN * 4), t = (x / 4) % C::TN, q = x % 4;
+        const int i = x / (C::TN * C::QN), t = (x / C::QN) % C::TN, q = x % C::QN;
         // (a piece outside the matrix reads the slice's first 16 bytes instead: no branch round the load, whose
         // result only counts after the wait below)
-        const float* src = ok[x] ? base + (size_t)(wm0 + 32 * i) * p.N + (wn0 + 32 * t + 8 * q) : base;
+        const float* src = ok[x] ? base + (size_t)(wm0 + C::row_off(i, wave_m)) * p.N + (wn0 + C::col_off(t, wave_n) + 8 * q) : base;
         if constexpr (THROUGH) load_through_f32x4(v[g][x], src);
         else v[g][x] = *(const f32x4*)src;
       }
@@ -390,30 +465,38 @@ __device__ __forceinline__ void sum_partials(f32x16 (&acc)[C::TM][C::TN], const 
   }
 #pragma unroll
   for (int x = 0; x < NV; ++x) {
-    const int i = x / (C::TN * 4), t = (x / 4) % C::TN, q = x % 4;
+    const int i = x / (C::TN * C::QN), t = (x / C::QN) % C::TN, q = x % C::QN;
     acc[i][t][4 * q] = sum[x][0]; acc[i][t][4 * q + 1] = sum[x][1];
     acc[i][t][4 * q + 2] = sum[x][2]; acc[i][t][4 * q + 3] = sum[x][3];
   }
 }
 
 template <int E> struct EpiTag { static constexpr int value = E; };
+// f(EpiTag<0>{}), ..., f(EpiTag<N - 1>{})
+template <int N, class F>
+__device__ __forceinline__ void static_for(const F& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(EpiTag<N - 1>{});
+  }
+}
 
-// bias_lds: this lane's first four bias values in LDS (columns wn0 .. wn0 + 3 of the tile's copy)
+// wm0, wn0: first row and column of this lane, without the wave's part; bias_lds: the tile's bias from column wn0 on
 template <class C, bool FULL, int EPI>
-__device__ __forceinline__ void epilogue(const f32x16 (&acc)[C::TM][C::TN], const GemmParams& p, int wm0, int wn0,
-                                         const char* bias_lds, int n_end) {
+__device__ __forceinline__ void epilogue(const typename C::Acc (&acc)[C::TM][C::TN], const GemmParams& p, int wm0, int wn0, int wave_m,
+                                         int wave_n, const char* bias_lds, int n_end) {
 #pragma unroll
   for (int t = 0; t < C::TN; ++t) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int n = wn0 + 32 * t + 8 * q;
+    for (int q = 0; q < C::QN; ++q) {
+      const int col = C::col_off(t, wave_n) + 8 * q, n = wn0 + col;
       const bool n_ok = FULL || n < n_end;
-      const u32x2 braw = *(const u32x2*)(bias_lds + (32 * t + 8 * q) * 2);   // (columns past N hold values nobody stores)
+      const u32x2 braw = *(const u32x2*)(bias_lds + col * 2);   // (columns past N hold values nobody stores)
       const float b0 = __builtin_bit_cast(float, braw[0] << 16), b1 = __builtin_bit_cast(float, braw[0] & 0xffff0000u);
       const float b2 = __builtin_bit_cast(float, braw[1] << 16), b3 = __builtin_bit_cast(float, braw[1] & 0xffff0000u);
 #pragma unroll
       for (int i = 0; i < C::TM_OUT; ++i) {
-        const int m = wm0 + 32 * i;
+        const int m = wm0 + C::row_off(i, wave_m);
         if (FULL || (n_ok && m < p.M)) {
           const float z0 = acc[i][t][4 * q] + b0, z1 = acc[i][t][4 * q + 1] + b1;
           const float z2 = acc[i][t][4 * q + 2] + b2, z3 = acc[i][t][4 * q + 3] + b3;
@@ -443,7 +526,7 @@ __device__ __forceinline__ void epilogue(const f32x16 (&acc)[C::TM][C::TN], cons
 // the workspace with rows of `ld` floats, instead of Y.
 // Every wave of the work-group must call it (barriers inside).
 template <class C, int EPI, bool PARTIAL = false>
-__device__ __forceinline__ void epilogue_staged(const f32x16 (&acc)[C::TM][C::TN], const GemmParams& p, char* smem, int m0,
+__device__ __forceinline__ void epilogue_staged(const typename C::Acc (&acc)[C::TM][C::TN], const GemmParams& p, char* smem, int m0,
                                                 int n0, int tid, int wave_m, int wave_n, int wave_k, int lane_m, int lane_g,
                                                 char* dst, size_t ld, int ncols = C::BN_ACT) {
   // ncols: columns of the tile that exist / belong to it (a multiple of 8); pieces past them are not stored
@@ -453,20 +536,24 @@ __device__ __forceinline__ void epilogue_staged(const f32x16 (&acc)[C::TM][C::TN
   constexpr int CPR = C::BN_ACT * ESZ / 16;              // 16-byte pieces per row
   constexpr int PER_THREAD = C::ST_ROWS * CPR / C::THREADS;
   static_assert(C::ST_ROWS * CPR % C::THREADS == 0, "pieces divide over the threads");
-  const char* bias_lds = smem + C::BIAS_OFF + (wave_n * C::WTN + 4 * lane_g) * 2;
-  char* wr = smem + ((wave_m * C::WK + wave_k) * 32 + lane_m) * ROWB + (wave_n * C::WTN + 4 * lane_g) * ESZ;
+  const char* bias_lds = smem + C::BIAS_OFF + 8 * lane_g;
+  char* wr = smem + ((wave_m * C::WK + wave_k) * 32 + lane_m) * ROWB + 4 * lane_g * ESZ;
+  constexpr int RB = 32 / C::MB;                         // row blocks a pass takes
+  static_assert(C::TM0 % RB == 0, "a pass takes consecutive rows of a wave");
   wait_vmcnt<0>();          // no transfer into LDS is in flight any more (the K loops leave none; the bias of a work-group without K tiles may be)
   barrier_lds();            // and nobody reads tile fragments any more
 #pragma unroll
-  for (int i = 0; i < C::TM_OUT; ++i) {
+  for (int i = 0; i < C::TM_OUT / RB; ++i) {
     if (i) barrier_lds();   // the previous pass has been read back
 #pragma unroll
     for (int t = 0; t < C::TN; ++t)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float z0 = acc[i][t][4 * q], z1 = acc[i][t][4 * q + 1], z2 = acc[i][t][4 * q + 2], z3 = acc[i][t][4 * q + 3];
+      for (int q = 0; q < C::QN * RB; ++q) {
+        const int b = i * RB + q / C::QN, e = 4 * (q % C::QN), col = C::col_off(t, wave_n) + 2 * e;
+        char* const at = wr + (q / C::QN) * C::MB * ROWB;
+        float z0 = acc[b][t][e], z1 = acc[b][t][e + 1], z2 = acc[b][t][e + 2], z3 = acc[b][t][e + 3];
         if (!PARTIAL) {
-          const u32x2 braw = *(const u32x2*)(bias_lds + (32 * t + 8 * q) * 2);
+          const u32x2 braw = *(const u32x2*)(bias_lds + col * 2);
           z0 += __builtin_bit_cast(float, braw[0] << 16);
           z1 += __builtin_bit_cast(float, braw[0] & 0xffff0000u);
           z2 += __builtin_bit_cast(float, braw[1] << 16);
@@ -474,12 +561,12 @@ __device__ __forceinline__ void epilogue_staged(const f32x16 (&acc)[C::TM][C::TN
         }
         if (EPI == TF_EPI_NONE_F32) {
           const f32x4 v = {z0, z1, z2, z3};
-          *(f32x4*)(wr + (32 * t + 8 * q) * 4) = v;
+          *(f32x4*)(at + col * 4) = v;
         } else {
           u32x2 o;
           o[0] = pack_bf16x2(activate<EPI>(z0), activate<EPI>(z1));
           o[1] = pack_bf16x2(activate<EPI>(z2), activate<EPI>(z3));
-          *(u32x2*)(wr + (32 * t + 8 * q) * 2) = o;
+          *(u32x2*)(at + col * 2) = o;
         }
       }
     barrier_lds();
@@ -488,7 +575,7 @@ __device__ __forceinline__ void epilogue_staged(const f32x16 (&acc)[C::TM][C::TN
       const int c = tid + C::THREADS * j;
       const int rs = c / CPR, cc = c % CPR;
       const int g = rs >> 5;                               // wave row and k group the staged row came from
-      const int m = m0 + (g / C::WK) * C::WTM + (g % C::WK) * 32 * (C::TM / 2) + 32 * i + (rs & 31);
+      const int m = m0 + C::row_off(RB * i, g / C::WK) + (g % C::WK) * (C::WTM / 2) + (rs & 31);
       const u32x4 v = *(const u32x4*)(smem + rs * ROWB + cc * 16);
       if (cc * 16 < ncols * ESZ) {
         // the output is not read again by this launch: non-temporal; a partial tile is read back at once by the
@@ -605,20 +692,28 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
   // ---- LDS read offsets of this lane (bytes inside a stage)
   int a_off[C::KS];
   {
-    const int r = wave_m * C::WTM + (lane & 31);
-    const int g = lane >> 5;
-    const int sw = C::row_swz(r);          // (the same for the rows 32, 64, ... further down)
+    const int r = C::row_off(0, wave_m) + lane % C::MB;
+    const int g = lane / C::MB;
+    const int sw = C::row_swz(r);          // (the same for the rows MB, 2 MB, ... further down)
 #pragma unroll
-    for (int kk = 0; kk < C::KS; ++kk) a_off[kk] = r * C::K_ROW_BYTES + (((2 * (wave_k * C::KS + kk) + g) ^ sw) << 4);
+    for (int kk = 0; kk < C::KS; ++kk) a_off[kk] = r * C::K_ROW_BYTES + (((C::KMF / 8 * (wave_k * C::KS + kk) + g) ^ sw) << 4);
   }
+  // from a wave's first block of A to block i: the same for every wave but in a tile of unequal units
+  auto a_block = [&](int i) { return (C::row_off(i, wave_m) - C::row_off(0, wave_m)) * C::K_ROW_BYTES; };
+  auto a_block_const = [](int i) { return (C::row_off(i, 0) - C::row_off(0, 0)) * C::K_ROW_BYTES; };
+  constexpr bool EVEN_UNITS = C::TM == C::TM0 || C::TM == 2 * C::TM0;
   // B given as [N][K]: its tile is read like the A tile. Its offsets are derived per read from two values (the
-  // chunk index 2 k + g only differs from g above bit 0, so the swizzled slot of step k is (g ^ sw) ^ 2 k):
+  // chunk index KMF / 8 k + g only differs from g above g's bits, so the swizzled slot of step k is (g ^ sw) ^ (KMF / 8 k)):
   // a table per k16-step as for A costs registers the big tiles do not have.
   int bt_row = 0, bt_c0 = 0;
+  int bt_off[C::QUAD ? C::KS : 1];
   if constexpr (C::TRANSB) {
-    const int r = wave_n * C::WTN + (lane & 31);
-    bt_row = C::A_BYTES + r * C::K_ROW_BYTES;
-    bt_c0 = ((lane >> 5) ^ C::row_swz(r)) << 4;
+    const int r = wave_n * C::TN0 * C::MB + lane % C::MB;
+    bt_row = C::B_BASE + r * C::K_ROW_BYTES;
+    bt_c0 = ((lane / C::MB) ^ C::row_swz(r)) << 4;
+    if constexpr (C::QUAD)
+#pragma unroll
+      for (int kk = 0; kk < C::KS; ++kk) bt_off[kk] = bt_row + (bt_c0 ^ (kk * (C::KMF * 2)));
   }
   int a_toff[C::TRANSA ? C::TM : 1];     // transposed A: offsets for the transposing read, as for B
   if constexpr (C::TRANSA) {
@@ -632,7 +727,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
       a_toff[i] = (krow + wave_k * C::KS * 16) * C::A_ROW_BYTES + piece * 64 + within;
     }
   }
-  // one A operand of k16-step kk (relative to the wave's first step), row block i
+  // one A operand of MFMA step kk (relative to the wave's first step), row block i
   auto read_a = [&](const char* stage, int kk, int i) -> bf16x8 {
     if constexpr (C::TRANSA) {
       const char* ap = stage + a_toff[i] + (16 * kk) * C::A_ROW_BYTES;
@@ -641,41 +736,47 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
       const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
       return __builtin_bit_cast(bf16x8, v);
     } else {
-      return *(const bf16x8*)(stage + a_off[kk] + i * 32 * C::K_ROW_BYTES);
+      return *(const bf16x8*)(stage + a_off[kk] + (EVEN_UNITS ? a_block_const(i) : a_block(i)));
     }
   };
-  int b_off[C::TN];
+  int b_off[C::TN0];                       // the second unit's are B_UNIT_BYTES further
   {
     const int b = lane >> 4, s = lane & 15;
-    const int krow = 8 * (b >> 1) + (s >> 2);                 // + 16 kk + 4 h
-    const int within = (16 * (b & 1) + 4 * (s & 3)) * 2;      // bytes inside the 64-byte piece
+    // a lane group reads four rows of 16 columns, its lanes 4 columns each; MB 32: two groups side by side, then 8 k on
+    const int krow = 8 * (C::MB == 16 ? b : b >> 1) + (s >> 2);      // + KMF kk + 4 h
+    const int col = wave_n * C::TN0 * C::MB + (C::MB == 16 ? 0 : 16 * (b & 1)) + 4 * (s & 3);
 #pragma unroll
-    for (int t = 0; t < C::TN; ++t) {
-      const int j = (wave_n * C::WTN) / 32 + t;
-      const int piece = j ^ b_swz<C::B_PIECES>(krow);
-      b_off[t] = C::A_BYTES + (krow + wave_k * C::KS * 16) * C::B_ROW_BYTES + piece * 64 + within;
+    for (int t = 0; t < C::TN0; ++t) {
+      const int n = col + C::MB * t;
+      b_off[t] = C::B_BASE + (krow + wave_k * C::KS * C::KMF) * C::B_ROW_BYTES + (((n >> 3) ^ b_chunk_swz<C>(krow)) << 4) + (n & 7) * 2;
     }
   }
-  // one B operand of k16-step kk (relative to the wave's first step), column block t
+  // one B operand of MFMA step kk (relative to the wave's first step), column block t
   auto read_b1 = [&](const char* stage, int kk, int t) -> bf16x8 {
-    if constexpr (C::TRANSB) {
-      return *(const bf16x8*)(stage + bt_row + (bt_c0 ^ ((wave_k * C::KS + kk) << 5)) + t * 32 * C::K_ROW_BYTES);
+    if constexpr (C::TRANSB && C::QUAD) {
+      return *(const bf16x8*)(stage + bt_off[kk] + t / C::TN0 * C::B_UNIT_BYTES + t % C::TN0 * C::MB * C::K_ROW_BYTES);
+    } else if constexpr (C::TRANSB) {
+      return *(const bf16x8*)(stage + bt_row + (bt_c0 ^ ((wave_k * C::KS + kk) * (C::KMF * 2))) + t * C::MB * C::K_ROW_BYTES);
     } else {
-      const char* bp = stage + b_off[t] + (16 * kk) * C::B_ROW_BYTES;
+      const char* bp = stage + b_off[t % C::TN0] + t / C::TN0 * C::B_UNIT_BYTES + (C::KMF * kk) * C::B_ROW_BYTES;
       const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(bp));
       const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(bp + 4 * C::B_ROW_BYTES));
       const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
       return __builtin_bit_cast(bf16x8, v);
     }
   };
+  auto mma = [](const bf16x8 b, const bf16x8 a, const typename C::Acc c) -> typename C::Acc {
+    if constexpr (C::MB == 16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0);
+  };
 
-  f32x16 acc[C::TM][C::TN];
+  typename C::Acc acc[C::TM][C::TN];
 #pragma unroll
   for (int i = 0; i < C::TM; ++i)
 #pragma unroll
     for (int t = 0; t < C::TN; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.0f;
+      for (int r = 0; r < 4 * C::QN; ++r) acc[i][t][r] = 0.0f;
 
   TileLoader<C> ld;
   ld.init(p, m0, n0, wave, lane);
@@ -709,11 +810,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
   const uint16_t* Bk = p.B + (long)first_kt * b_tile;
 
   // ---- main loop, software pipelined by hand (one wave per SIMD has nobody to hide behind):
-  //  * fragments are double buffered in registers: the LDS reads of k16-step kk+1 are issued
+  //  * fragments are double buffered in registers: the LDS reads of MFMA step kk+1 are issued
   //    before the MFMAs of step kk;
   //  * the loop is rotated: the barrier that hands over the next tile, the global loads of the
   //    tile after it and the first fragment reads of the next tile are all issued BEFORE the
-  //    last 16-wide step of the current tile, whose MFMAs cover their latency.
+  //    last step of the current tile, whose MFMAs cover their latency.
   bf16x8 af[2][C::TM], bfr[2][C::TN];
   auto read_frags = [&](const char* stage, int kk, int set) {
 #pragma unroll
@@ -722,23 +823,31 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
 #pragma unroll
     for (int t = 0; t < C::TN; ++t) bfr[set][t] = read_b1(stage, kk, t);
   };
+  // (blocks in serpentine order: an MFMA shares one operand with the one before it, which costs less power)
   auto mfma_step = [&](int set) {
 #pragma unroll
     for (int i = 0; i < C::TM; ++i)
 #pragma unroll
-      for (int t = 0; t < C::TN; ++t)
-        acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][t], af[set][i], acc[i][t], 0, 0, 0);
+      for (int u = 0; u < C::TN; ++u) {
+        const int t = i & 1 ? C::TN - 1 - u : u;
+        acc[i][t] = mma(bfr[set][t], af[set][i], acc[i][t]);
+      }
   };
-  // scheduling hint for one pipelined step: alternate one MFMA with one LDS read until the
-  // reads are all issued, so that the matrix pipe never waits for the whole batch of reads
-  constexpr int N_DS = C::TM + (C::TRANSB ? 1 : 2) * C::TN, N_MFMA = C::TM * C::TN;
-  auto interleave_hint = [&]() {
-#pragma unroll
-    for (int x = 0; x < (N_DS < N_MFMA ? N_DS : N_MFMA); ++x) {
+  // Scheduling hint for a step of MFMAs behind which LDS reads go out: one read per MFMA until they are all issued, so that
+  // the matrix pipe never waits for the whole batch and the hand-over at the end of the step finds most of them done (two per
+  // MFMA: 2048^3 20.0 -> 20.8 us). The MFMAs left over are named too: what is not, the compiler moves across steps.
+  constexpr int DS_B = C::TRANSB ? 1 : 2;                  // LDS reads per B operand
+  constexpr int N_DS = C::TM + DS_B * C::TN, N_MFMA = C::TM * C::TN;
+  auto spread = [&](auto reads, auto mfmas) {
+    constexpr int R = decltype(reads)::value, N = decltype(mfmas)::value;
+    static_for<(R < N ? R : N)>([&](auto) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one DS read
-    }
+    });
+    if constexpr (R > N) __builtin_amdgcn_sched_group_barrier(0x100, R - N, 0);
+    if constexpr (N > R) __builtin_amdgcn_sched_group_barrier(0x008, N - R, 0);
   };
+  auto interleave_hint = [&]() { spread(EpiTag<N_DS>{}, EpiTag<N_MFMA>{}); };
 
   // The last tile is peeled off the loop, and so are the ones behind which nothing more is fetched: the
   // loop body has no branch inside and is scheduled as one block, with constant vmcnt waits. (The A-bypass kernel
@@ -751,16 +860,16 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
   // then fetch eight different slabs of A and B, and seven times out of eight a line has already been
   // brought into the memory-side cache by another XCD instead of all eight waiting for it together.
   // (All work-groups of an XCD keep the same order, so they still share panels in its L2.)
-  const int k_rot = (p.k_rotate && nkt > 0) ? (int)(((blockIdx.x & 7u) * (unsigned)nkt) >> 3) : 0;
-  auto k_order = [&](int t) { const int u = t + k_rot; return u >= nkt ? u - nkt : u; };
   // RaggedKCfg (K no multiple of BK; a multiple of 8, at least BK): the last K tile of the problem is fetched from
-  // K - BK on, so that every transfer stays inside the operands, and its first `skip` k, which the tile before has
-  // already multiplied, are zeroed in LDS in BOTH operands (an infinity or NaN among them must not meet a zero)
-  // before its fragments are read. Only the peeled last tile knows of this (the host offers no rotated order here,
-  // so the problem's last tile is the last one a work-group takes). Zeroing fragments in registers instead, with a
-  // second copy of the peeled tile, made the big tiles spill.
+  // K - BK on, so that every transfer stays inside the operands, and its first `skip` k, which the tile before it holds
+  // too, are zeroed in LDS in BOTH operands (an infinity or NaN among them must not meet a zero) before its fragments are
+  // read. The work-group that has this tile takes it first, ahead of the main loop and before there are accumulators
+  // (at the end of the loop the zeroing made the 256 x 256 tiles spill). The host offers no rotated order here.
   const int k_over = ktiles_total * C::BK - p.K;
-  const int skip = C::KTAIL && k_over > 0 && first_kt + last * (k_deal ? p.split_k : 1) == ktiles_total - 1 ? k_over : 0;
+  const int skip = __builtin_amdgcn_readfirstlane(
+      C::KTAIL && k_over > 0 && first_kt + last * (k_deal ? p.split_k : 1) == ktiles_total - 1 ? k_over : 0);
+  const int k_rot = C::KTAIL ? (skip ? last : 0) : (p.k_rotate && nkt > 0) ? (int)(((blockIdx.x & 7u) * (unsigned)nkt) >> 3) : 0;
+  auto k_order = [&](int t) { const int u = t + k_rot; return u >= nkt ? u - nkt : u; };
   const long a_back = C::TRANSA ? skip * p.lda : (long)skip, b_back = C::TRANSB ? (long)skip : skip * p.ldb;
   // Where the next K tile to fetch lies in A and B: moved on a tile at a time, with one wrap (a multiplication per
   // tile and operand cost the loop some thirty scalar or, where the compiler chose so, vector instructions a step).
@@ -776,17 +885,19 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
   const unsigned long long a_first = uniform(Ak), b_first = uniform(Bk);
   const long a_move = 2 * a_step, b_move = 2 * b_step;       // bytes
   nx.left = nkt - k_rot;
-  nx.a = a_first + (unsigned long long)(k_rot * a_move) - (C::KTAIL && nx.left == 1 ? 2 * a_back : 0);
-  nx.b = b_first + (unsigned long long)(k_rot * b_move) - (C::KTAIL && nx.left == 1 ? 2 * b_back : 0);
+  nx.a = uniform((const void*)(a_first + (unsigned long long)(k_rot * a_move) - (C::KTAIL ? 2 * a_back : 0)));
+  nx.b = uniform((const void*)(b_first + (unsigned long long)(k_rot * b_move) - (C::KTAIL ? 2 * b_back : 0)));
   auto next_tile = [&]() {
     --nx.left;
     nx.a = nx.left == 0 ? a_first : nx.a + a_move;
     nx.b = nx.left == 0 ? b_first : nx.b + b_move;
-    if (C::KTAIL && nx.left == 1) { nx.a -= 2 * a_back; nx.b -= 2 * b_back; }
   };
   auto next_a = [&]() { return (const uint16_t*)nx.a; };
   auto next_b = [&]() { return (const uint16_t*)nx.b; };
-  auto zero_skipped = [&](char* stage) {       // every wave calls it; `stage` has landed and is read again behind it
+  auto zero_skipped = [&]() {                  // every wave calls it; the first tile has landed and has not been read
+    if (!C::KTAIL || skip == 0) return;
+    char* const a_tile = smem;
+    char* const b_tile = smem + C::B_BASE;
     const u32x4 zero = {0u, 0u, 0u, 0u};
     auto k_contiguous = [&](char* tile, int rows) {
       for (int c = 0; c < skip / 8; ++c)
@@ -795,8 +906,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     auto k_rows = [&](char* tile, int row_bytes) {
       for (int x = tid * 16; x < skip * row_bytes; x += C::THREADS * 16) *(u32x4*)(tile + x) = zero;
     };
-    if constexpr (C::TRANSA) k_rows(stage, C::A_ROW_BYTES); else k_contiguous(stage, C::BM);
-    if constexpr (C::TRANSB) k_contiguous(stage + C::A_BYTES, C::BN); else k_rows(stage + C::A_BYTES, C::B_ROW_BYTES);
+    if constexpr (C::TRANSA) k_rows(a_tile, C::A_ROW_BYTES); else k_contiguous(a_tile, C::BM);
+    if constexpr (C::TRANSB) k_contiguous(b_tile, C::BN);
+    else
+      for (int u = 0; u < C::B_UNITS; ++u) k_rows(b_tile + u * C::B_UNIT_BYTES, C::B_ROW_BYTES);
     barrier_lds();
   };
   if constexpr (C::ABYPASS) {
@@ -895,8 +1008,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
       }
       wait_vmcnt<0>();
     }
-  } else if constexpr (C::DIRECT && C::TM * C::TN * C::KS <= 8) {
-    // Small wave tiles (skinny problems): a k16-step has only one or two MFMAs, far too few to
+  } else if constexpr (C::DIRECT && C::ACC * C::KS * C::KMF <= 8 * 16 * 16) {
+    // Small wave tiles (skinny problems): an MFMA step has only one or two MFMAs of 32 x 32, far too few to
     // cover an LDS read, so the step-by-step pipeline above would stall four times per tile.
     // Here all fragments of a tile are read at once, into one of two register sets, while the
     // MFMAs of the previous tile run; one wait + barrier per tile. Unrolled by two so that both
@@ -921,8 +1034,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
 #pragma unroll
         for (int i = 0; i < C::TM; ++i)
 #pragma unroll
-          for (int t = 0; t < C::TN; ++t)
-            acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[kk][t], a[kk][i], acc[i][t], 0, 0, 0);
+          for (int u = 0; u < C::TN; ++u) {
+            const int t = i & 1 ? C::TN - 1 - u : u;
+            acc[i][t] = mma(b[kk][t], a[kk][i], acc[i][t]);
+          }
     };
     if (nkt > 0) {
 #pragma unroll
@@ -938,6 +1053,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
         ld.issue_direct(next_a(), next_b(), lds0 + D * C::STAGE_BYTES, wave);
         next_tile();
       }
+      zero_skipped();
       read_tile(smem, fa[0], fb[0]);
       int stage = 0;
       // one non-final tile t: its fragments are in (ca, cb); (na, nb) receive tile t+1. FETCH: tile t + 1 + D exists and
@@ -956,13 +1072,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
         }
         read_tile(smem + nstage * C::STAGE_BYTES, na, nb);
         mfma_tile(ca, cb);
+        if constexpr (C::MB == 16) spread(EpiTag<C::KS * N_DS>{}, EpiTag<C::KS * N_MFMA>{});
+        __builtin_amdgcn_sched_barrier(0);
         stage = nstage;
-      };
-      auto reread_skipped = [&](bf16x8 (&a)[C::KS][C::TM], bf16x8 (&b)[C::KS][C::TN]) {
-        if (C::KTAIL && skip) {
-          zero_skipped(smem + stage * C::STAGE_BYTES);
-          read_tile(smem + stage * C::STAGE_BYTES, a, b);
-        }
       };
       int kt = 0;
       for (; kt + 1 < last - D; kt += 2) {
@@ -976,11 +1088,118 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
       }
       if (kt < last) {
         step(EpiTag<0>{}, kt, fa[0], fb[0], fa[1], fb[1]);
-        reread_skipped(fa[1], fb[1]);
         mfma_tile(fa[1], fb[1]);
       } else {
-        reread_skipped(fa[0], fb[0]);
         mfma_tile(fa[0], fb[0]);
+      }
+    }
+  } else if constexpr (C::QUAD) {
+    // Quadrants. A K tile takes four phases, one quadrant of every wave's tile over the whole 64 of K each: A0 B0, A0 B1,
+    // A1 B1, A1 B0. Behind the MFMAs of a phase the one unit that the next phase needs is read into registers: B1, A1,
+    // then A0 and B0 of the next tile. A unit is read once, so its buffer can take the tile after next as soon as the
+    // two phases that read it and its neighbour are over: the transfers run 1.5 K tiles ahead with the two buffers that
+    // give one tile otherwise, and a wait only ever meets transfers that went out five phases before. Without it the
+    // compiler, or a burst of waves that arrive late, met transfers of half a tile ago. 256 x 256 tiles, us per 64 of K
+    // (random operands / zeros, which leave the clock at 2.4 GHz; 0.85 us of MFMA there): one tile ahead in 32 x 32
+    // blocks 1.49 / 1.44, here 1.35 / 1.07; 192 x 256 1.32 / 1.22 and 1.07 / 0.82. 4096 x 11008 x 4096 306 -> 285 us,
+    // 3072^3 55.0 -> 52.4, 3000 x 5000 x 3000 83.2 -> 76.3 and with B as [N][K] 86.3 -> 77.6.
+    // Two K tiles per pass: the buffers and the register sets (B0 in set t & 1) are then addressed statically.
+    constexpr int PER_TILE = C::A_PER_WAVE + C::B_PER_WAVE;
+    constexpr int TM1 = C::TM - C::TM0, TN1 = C::TN - C::TN0;
+    constexpr int A0_PER_WAVE = 128 * 128 / 1024 / C::NWAVES, B0_PER_WAVE = C::B_PER_WAVE / 2;
+    static_assert(TM1 > 0 && TM1 <= C::TM0 && TN1 == C::TN0 && C::KS == 2 && C::WK == 1, "units of a quadrant tile");
+    const unsigned lds0 = (unsigned)(size_t)smem;
+    bf16x8 qa[2][C::KS][C::TM0], qb[2][C::KS][C::TN0];
+    auto read_au = [&](int buf, auto u) {                     // A unit u of the tile in buffer buf
+#pragma unroll
+      for (int kk = 0; kk < C::KS; ++kk)
+#pragma unroll
+        for (int i = 0; i < (decltype(u)::value ? TM1 : C::TM0); ++i)
+          qa[decltype(u)::value][kk][i] = read_a(smem + buf * C::A_STRIDE, kk, decltype(u)::value * C::TM0 + i);
+    };
+    auto read_bu = [&](int buf, auto u, int set) {
+#pragma unroll
+      for (int kk = 0; kk < C::KS; ++kk)
+#pragma unroll
+        for (int t = 0; t < C::TN0; ++t) qb[set][kk][t] = read_b1(smem + buf * C::B_STRIDE, kk, decltype(u)::value * C::TN0 + t);
+    };
+    auto issue_au = [&](int buf, int u) {
+#pragma unroll
+      for (int q = u ? A0_PER_WAVE : 0; q < (u ? C::A_PER_WAVE : A0_PER_WAVE); ++q) ld.issue_a_one(q, next_a(), lds0 + buf * C::A_STRIDE, wave);
+    };
+    auto issue_bu = [&](int buf, int u) {
+#pragma unroll
+      for (int q = u ? B0_PER_WAVE : 0; q < (u ? C::B_PER_WAVE : B0_PER_WAVE); ++q) ld.issue_b_one(q, next_b(), lds0 + buf * C::B_STRIDE + (C::B_BASE - C::A_BYTES), wave);
+    };
+    // (u, v): the quadrant; B in register set `set`
+    auto quadrant = [&](auto u, auto v, int set) {
+      constexpr int U = decltype(u)::value, V = decltype(v)::value;
+#pragma unroll
+      for (int kk = 0; kk < C::KS; ++kk)
+#pragma unroll
+        for (int i = 0; i < (U ? TM1 : C::TM0); ++i)
+#pragma unroll
+          for (int x = 0; x < C::TN0; ++x) {
+            const int t = (i + kk) & 1 ? C::TN0 - 1 - x : x;
+            acc[U * C::TM0 + i][V * C::TN0 + t] = mma(qb[set][kk][t], qa[U][kk][i], acc[U * C::TM0 + i][V * C::TN0 + t]);
+          }
+    };
+    constexpr int N_B = C::KS * C::TN0 * DS_B, N_A0 = C::KS * C::TM0, N_A1 = C::KS * TM1;
+    // tile t in buffer P = t & 1. STEADY: tile t + 2 exists; otherwise what there is
+    auto tile_quad = [&](auto parity, auto steady, int t) {
+      constexpr int P = decltype(parity)::value, Q = 1 - P;
+      constexpr bool STEADY = decltype(steady)::value != 0;
+      const bool fetch = STEADY || t + 2 <= last;
+      if (fetch) issue_au(P, 0);
+      read_bu(P, EpiTag<1>{}, Q);
+      quadrant(EpiTag<0>{}, EpiTag<0>{}, P);
+      spread(EpiTag<N_B>{}, EpiTag<C::KS * C::TM0 * C::TN0>{});
+      __builtin_amdgcn_sched_barrier(0);           // (a phase keeps its reads: their registers are the last one's)
+      if (fetch) issue_bu(P, 0);
+      read_au(P, EpiTag<1>{});
+      quadrant(EpiTag<0>{}, EpiTag<1>{}, Q);
+      spread(EpiTag<N_A1>{}, EpiTag<C::KS * C::TM0 * C::TN0>{});
+      __builtin_amdgcn_sched_barrier(0);
+      if (fetch) wait_vmcnt<PER_TILE>();           // A0, B0 of tile t + 1 have landed
+      else if (t < last) wait_vmcnt<C::A_PER_WAVE - A0_PER_WAVE + B0_PER_WAVE>();
+      barrier_lds();                               // ... for every wave, and every wave holds B1 and A1 of tile t
+      if (fetch) issue_bu(P, 1);
+      read_au(Q, EpiTag<0>{});                     // (behind the last tile: what the buffer holds, not used)
+      quadrant(EpiTag<1>{}, EpiTag<1>{}, Q);
+      spread(EpiTag<N_A0>{}, EpiTag<C::KS * TM1 * C::TN0>{});
+      __builtin_amdgcn_sched_barrier(0);
+      if (fetch) issue_au(P, 1);
+      read_bu(Q, EpiTag<0>{}, Q);
+      quadrant(EpiTag<1>{}, EpiTag<0>{}, P);
+      spread(EpiTag<N_B>{}, EpiTag<C::KS * TM1 * C::TN0>{});
+      __builtin_amdgcn_sched_barrier(0);
+      if (fetch) { next_tile(); wait_vmcnt<PER_TILE>(); }    // B1, A1 of tile t + 1 have landed
+      else wait_vmcnt<0>();
+      barrier_lds();                               // ... for every wave, and every wave holds A0 and B0 of tile t + 1
+    };
+    if (nkt > 0) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        if (s < nkt) {
+          issue_au(s, 0); issue_bu(s, 0); issue_bu(s, 1); issue_au(s, 1);
+          next_tile();
+        }
+      if (nkt > 1) wait_vmcnt<PER_TILE>();
+      else wait_vmcnt<0>();
+      barrier_lds();
+      zero_skipped();
+      read_au(0, EpiTag<0>{});
+      read_bu(0, EpiTag<0>{}, 0);
+      barrier_lds();
+      int kt = 0;
+      for (; kt + 3 <= last; kt += 2) {
+        tile_quad(EpiTag<0>{}, EpiTag<1>{}, kt);
+        tile_quad(EpiTag<1>{}, EpiTag<1>{}, kt + 1);
+      }
+      kt = __builtin_amdgcn_readfirstlane(kt);   // (the same value: keeps the compiler from making one loop of the two)
+      for (; kt <= last; kt += 2) {
+        tile_quad(EpiTag<0>{}, EpiTag<0>{}, kt);
+        if (kt + 1 <= last) tile_quad(EpiTag<1>{}, EpiTag<0>{}, kt + 1);
       }
     }
   } else if constexpr (C::DIRECT) {
@@ -1021,6 +1240,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
       barrier_lds();
       // tile D: A part now, B part during the first step of tile 0 (as in the steady state)
       if (D < nkt) ld.issue_a_all(next_a(), lds0 + D * C::STAGE_BYTES, wave);
+      zero_skipped();
       read_frags(smem, 0, 0);
       int stage = 0, kt = 0;
       // one tile but the last. FETCH: the B part of tile kt + D and the A part of tile kt + 1 + D are on their way
@@ -1047,12 +1267,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
           mfma_step(kk & 1);
           interleave_hint();
         }
+        __builtin_amdgcn_sched_barrier(0);   // (the MFMAs above stay above)
         if (FETCH || last_b) wait_vmcnt<(D - 1) * PER_TILE>();    // tile kt+1 has landed
         else wait_vmcnt<0>();
         barrier_lds();                       // ... for every wave, and every wave is done reading tile kt
         if constexpr (FETCH) read_frags_issue(smem + nstage * C::STAGE_BYTES, 0, 0, 1, next_a(), lds0 + stage * C::STAGE_BYTES);
         else read_frags(smem + nstage * C::STAGE_BYTES, 0, 0);
-        mfma_step(1);                        // the last k16-step of tile kt covers the latencies above
+        mfma_step(1);                        // the last MFMA step of tile kt covers the latencies above
         interleave_hint();
         stage = nstage;
       };
@@ -1060,11 +1281,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
       kt = __builtin_amdgcn_readfirstlane(kt);   // (the same value: keeps the compiler from making one loop of the two)
       for (; kt < last; ++kt) tile_step(EpiTag<0>{});
       {
-        char* cur = smem + stage * C::STAGE_BYTES;
-        if (C::KTAIL && skip) {
-          zero_skipped(cur);
-          read_frags(cur, 0, 0);
-        }
+        const char* cur = smem + stage * C::STAGE_BYTES;
         read_frags(cur, 1, 1);
         mfma_step(0);
         interleave_hint();
@@ -1122,12 +1339,18 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
   }
 
   // ---- accumulator layout. The MFMA is issued with the B fragment as its first operand and
-  // the A fragment as its second, so each 32x32 block is held transposed: lane l, register r
-  // holds  m = block_m + (l & 31),  n = block_n + 8 (r / 4) + 4 (l / 32) + (r % 4).
+  // the A fragment as its second, so each block is held transposed: lane l, register r
+  // holds  m = block_m + l % MB,  n = block_n + 8 (r / 4) + 4 (l / MB) + (r % 4).
   // A lane therefore owns runs of four consecutive n, which pack into one 8-byte (bf16) or
   // 16-byte (fp32) store without any cross-lane exchange.
-  const int lane_m = lane & 31, lane_g = lane >> 5;
+  int lane_out = lane;
+  if constexpr (C::QUAD) {       // found anew: no register for it (or for tid) has to live through the main loop
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane_out));
+  }
+  const int tid_out = C::QUAD ? wave * 64 + lane_out : tid;
+  const int lane_m = lane_out % C::MB, lane_g = lane_out / C::MB;
   if constexpr (C::WK == 2) {
+    static_assert(C::WK == 1 || C::MB == 32, "the exchange of the k groups: blocks of 32 x 32");
     // The two k groups hold partial sums of the same wave tile. Group 0 keeps its first TM/2 row
     // blocks and hands the others to its partner wave of group 1, which does the reverse;
     // afterwards acc[0 .. TM/2) of every wave holds complete sums of the rows it writes out.
@@ -1162,8 +1385,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
           for (int e = 0; e < 4; ++e) acc[i][t][4 * q + e] += v[e];
         }
   }
-  const int wm0 = m0 + wave_m * C::WTM + lane_m + (C::WK == 2 ? wave_k * 32 * (C::TM / 2) : 0);   // + 32 i
-  const int wn0 = n0 + wave_n * C::WTN + 4 * lane_g;          // + 32 t + 8 q
+  const int wm0 = m0 + lane_m + (C::WK == 2 ? wave_k * (C::WTM / 2) : 0);   // + row_off
+  const int wn0 = n0 + 4 * lane_g;                                          // + col_off + 8 q
   const int ncols = n_end - n0 < C::BN_ACT ? n_end - n0 : C::BN_ACT;     // columns this tile writes (a multiple of 8)
   const bool rows_full = m0 + C::BM <= p.M;
   const bool full = rows_full && ncols == C::BN_ACT;
@@ -1177,9 +1400,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
       // slices in slice order and applies the epilogue (the kernel boundary orders the two)
       if (C::stage_ok(4) && full && p.ws_vec16) {
         if constexpr (C::stage_ok(4))
-          epilogue_staged<C, TF_EPI_NONE_F32, true>(acc, p, smem, m0, n0, tid, wave_m, wave_n, wave_k, lane_m, lane_g, (char*)wsk, (size_t)p.N);
-      } else if (full) store_partial<C, true, false>(acc, wsk, p, wm0, wn0);
-      else store_partial<C, false, false>(acc, wsk, p, wm0, wn0);
+          epilogue_staged<C, TF_EPI_NONE_F32, true>(acc, p, smem, m0, n0, tid_out, wave_m, wave_n, wave_k, lane_m, lane_g, (char*)wsk, (size_t)p.N);
+      } else if (full) store_partial<C, true, false>(acc, wsk, p, wm0, wn0, wave_m, wave_n);
+      else store_partial<C, false, false>(acc, wsk, p, wm0, wn0, wave_m, wave_n);
       continue;
     }
     if constexpr (C::FUSED_OK) {
@@ -1194,11 +1417,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     //    workspace is set (the host probes the placement once per device before it launches this mode).
     const bool local = p.fused_reduce == 2;
     if (local) {
-      if (full) store_partial<C, true, false>(acc, wsk, p, wm0, wn0);
-      else store_partial<C, false, false>(acc, wsk, p, wm0, wn0);
+      if (full) store_partial<C, true, false>(acc, wsk, p, wm0, wn0, wave_m, wave_n);
+      else store_partial<C, false, false>(acc, wsk, p, wm0, wn0, wave_m, wave_n);
     } else {
-      if (full) store_partial<C, true, true>(acc, wsk, p, wm0, wn0);
-      else store_partial<C, false, true>(acc, wsk, p, wm0, wn0);
+      if (full) store_partial<C, true, true>(acc, wsk, p, wm0, wn0, wave_m, wave_n);
+      else store_partial<C, false, true>(acc, wsk, p, wm0, wn0, wave_m, wave_n);
     }
     // every store of this wave has been acknowledged before the wave reaches the barrier, so
     // the ticket taken after it is ordered behind the whole work-group's partials
@@ -1211,28 +1434,28 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     const unsigned long long mine = 1ull + (1ull << (8 + 7 * xcc));
     // (the L2-local mode takes its ticket in this XCD's L2 as well: an atomic of narrower scope is carried out there,
     // one of device scope past it, at several times the latency; all slices of the tile sit on this XCD)
-    if (tid == 0)
+    if (tid_out == 0)
       ticket = (local ? __hip_atomic_fetch_add(ctr, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : atomicAdd(ctr, mine)) + mine;
     __syncthreads();
     const unsigned long long tk = ticket;
     if ((unsigned)(tk & 255u) != (unsigned)p.split_k) continue;
-    if (tid == 0) *ctr = 0ull;        // ready for the next launch
+    if (tid_out == 0) *ctr = 0ull;        // ready for the next launch
     if (local) {
-      if (full) sum_partials<C, true, false>(acc, p, wm0, wn0);
-      else sum_partials<C, false, false>(acc, p, wm0, wn0);
+      if (full) sum_partials<C, true, false>(acc, p, wm0, wn0, wave_m, wave_n);
+      else sum_partials<C, false, false>(acc, p, wm0, wn0, wave_m, wave_n);
       if ((unsigned)((tk >> (8 + 7 * xcc)) & 127u) != (unsigned)p.split_k) {
-        if (tid == 0) atomicOr(p.status, 1u);   // reported by the next synchronous call of the library
+        if (tid_out == 0) atomicOr(p.status, 1u);   // reported by the next synchronous call of the library
         const float nan = __builtin_nanf("");
 #pragma unroll
         for (int i = 0; i < C::TM_OUT; ++i)
 #pragma unroll
           for (int t = 0; t < C::TN; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][t][r] = nan;
+            for (int r = 0; r < 4 * C::QN; ++r) acc[i][t][r] = nan;
       }
     } else {
-      if (full) sum_partials<C, true, true>(acc, p, wm0, wn0);
-      else sum_partials<C, false, true>(acc, p, wm0, wn0);
+      if (full) sum_partials<C, true, true>(acc, p, wm0, wn0, wave_m, wave_n);
+      else sum_partials<C, false, true>(acc, p, wm0, wn0, wave_m, wave_n);
     }
     }
   }
@@ -1242,7 +1465,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     wait_vmcnt<0>();
     __syncthreads();
   }
-  const char* bias_lds = smem + C::BIAS_OFF + (wave_n * C::WTN + 4 * lane_g) * 2;
+  const char* bias_lds = smem + C::BIAS_OFF + 8 * lane_g;
   // whole rows of the tile go out coalesced through LDS, also when the tile's last columns do not exist or belong
   // to its neighbour (their pieces are skipped)
   const bool staged = rows_full && ncols > 0 && p.y_vec16;      // the same for every wave of the work-group
@@ -1251,9 +1474,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     constexpr int ESZ = EPI == TF_EPI_NONE_F32 ? 4 : 2;
     if (C::stage_ok(ESZ) && staged) {
       if constexpr (C::stage_ok(ESZ))
-        epilogue_staged<C, EPI>(acc, p, smem, m0, n0, tid, wave_m, wave_n, wave_k, lane_m, lane_g, (char*)p.Y, (size_t)p.ldy, ncols);
-    } else if (full) epilogue<C, true, EPI>(acc, p, wm0, wn0, bias_lds, n_end);
-    else epilogue<C, false, EPI>(acc, p, wm0, wn0, bias_lds, n_end);
+        epilogue_staged<C, EPI>(acc, p, smem, m0, n0, tid_out, wave_m, wave_n, wave_k, lane_m, lane_g, (char*)p.Y, (size_t)p.ldy, ncols);
+    } else if (full) epilogue<C, true, EPI>(acc, p, wm0, wn0, wave_m, wave_n, bias_lds, n_end);
+    else epilogue<C, false, EPI>(acc, p, wm0, wn0, wave_m, wave_n, bias_lds, n_end);
   };
   if (p.epi == TF_EPI_BIAS_GELU_ERF) finish(EpiTag<TF_EPI_BIAS_GELU_ERF>{});
   else if (p.epi == TF_EPI_NONE_F32) finish(EpiTag<TF_EPI_NONE_F32>{});
