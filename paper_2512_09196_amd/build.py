@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtf_gfx950.so")
 PYCALL = os.path.join(HERE, "_tfcall" + importlib.machinery.EXTENSION_SUFFIXES[0])   # extension module of this interpreter, host code only
-SOURCES = ["tf_gemm_lds.hip", "tf_gemm_lds_ragged.hip", "tf_gemm_lds_192.hip", "tf_gemm_stream.hip", "tf_gemm_any.hip", "tf_gemm_kshare.hip", "tf_vecmat.hip", "tf_sin.hip", "tf_gemm_simple.hip", "tf_api.hip", "tf_loop.cpp"]
+SOURCES = ["tf_gemm_lds.hip", "tf_gemm_lds_ragged.hip", "tf_gemm_lds_192.hip", "tf_gemm_lds_64x128.hip", "tf_gemm_stream.hip", "tf_gemm_any.hip", "tf_gemm_kshare.hip", "tf_vecmat.hip", "tf_sin.hip", "tf_gemm_simple.hip", "tf_api.hip", "tf_loop.cpp"]
 HEADERS = ["tf_gemm_lds.h", "tf_internal.h", "tf_device.h", "tf_loop.h"]
 
 # -packed-fp32-ops off: hipcc must not form v_pk_*_f32 from scalar float code on this target.

@@ -141,7 +141,7 @@ void build_bgemm_family(tf_problem* p) {
   for (int pass = 0; pass < 2; ++pass) {          // 0: transposed staging, 1: separate transposing pass
     for (int i = 0; i < tf::lds_kernel_count(); ++i) {
       const tf::LdsKernelInfo& k = tab[i];
-      if (!k.direct_to_lds || k.a_bypass_lds || k.waves_k != 1 || k.stream_k || k.trans_b || k.bk != 64 || k.bn_tail || k.k_tail) continue;
+      if (!k.direct_to_lds || k.a_bypass_lds || k.waves_k != 1 || k.stream_k || k.trans_b || k.bk != 64 || k.bn_tail || k.k_tail || k.appended) continue;
       if (pass == 0 && !k.trans_a) continue;
       // the persistent kernels. Whole tiles: the ones that deal out whole items; ragged tiles: the one whose tiles at a
       // ragged end begin a whole tile before it and which deals out tiles; whole tiles of a number of items that is no
@@ -303,7 +303,7 @@ void build_small_family(tf_problem* p) {
   int plain = -1;
   for (const tf_variant_desc& v : p->family) {
     if (v.kind != TF_KIND_MFMA_LDS && v.kind != TF_KIND_MFMA_STREAM) continue;
-    const double us = tf_predict_us(&d, &p->hw, &v);
+    const double us = tf::base_predict_us(&d, &p->hw, &v);
     // (the tiles of 192 rows and the direct staging of a ragged K do not move the line)
     if (v.bm != 192 && !(v.direct_to_lds && v.kind == TF_KIND_MFMA_LDS && d.K % v.bk)) best = std::min(best, us);
     if (quick >= best) return;
@@ -313,7 +313,7 @@ void build_small_family(tf_problem* p) {
   int any = 1;                                             // the one-wave kernel
   build_any_family(p);
   for (const tf_variant_desc& v : p->family)
-    if (v.kind == TF_KIND_MFMA_ANY && tf_predict_us(&d, &p->hw, &v) < tf_predict_us(&d, &p->hw, &p->family[any])) any = v.id;
+    if (v.kind == TF_KIND_MFMA_ANY && tf::base_predict_us(&d, &p->hw, &v) < tf::base_predict_us(&d, &p->hw, &p->family[any])) any = v.id;
   for (size_t i = 0; i < p->family.size(); ++i) {
     tf_variant_desc& k = p->family[i];
     if (k.kind != TF_KIND_MFMA_KSHARE || k.split_k > 1) continue;
@@ -369,9 +369,12 @@ void build_family(tf_problem* p) {
   const tf::LdsKernelInfo* tab = tf::lds_kernel_table();
   // pass 0: kernels compiled for the layout B arrives in; pass 1 (B as [N][K] only): a separate pass writes
   // B^T ([K][N]) into the workspace and an ordinary kernel reads that - the alternative the loop measures
+  // (`appended` kernels come behind everything else: the ids of the other variants are those they had before)
+  auto add_tiles = [&](int appended) {
   for (int pass = 0; pass < (tb ? 2 : 1); ++pass)
   for (int i = 0; i < tf::lds_kernel_count(); ++i) {
     const tf::LdsKernelInfo& k = tab[i];
+    if (k.appended != appended) continue;
     if (k.trans_a) continue;                               // kernels of the transposed-operand product
     if (pass == 0 && (k.trans_b != 0) != tb) continue;
     if (pass == 1) {
@@ -492,6 +495,8 @@ void build_family(tf_problem* p) {
       }
     }
   }
+  };
+  add_tiles(0);
   build_kshare_family(p);
   // Streaming kernels for skinny problems: K in blocks of 32, each wave of a work-group at least one block.
   if (!tb && d.M <= 32 && d.K % 32 == 0 && d.K >= 32) {
@@ -529,6 +534,7 @@ void build_family(tf_problem* p) {
     }
   }
   build_small_family(p);
+  add_tiles(1);
   // One counter area for the whole family, so that the partial sums of one variant never
   // land on the counters of another: [counters, status word | partial sums]. The status word
   // takes the last 256 bytes of the area.

@@ -112,6 +112,9 @@ static const std::vector<LdsKernelInfo>& all_kernels() {
     v.insert(v.end(), more, more + n);
     more = lds_192_table(&n);
     v.insert(v.end(), more, more + n);
+    more = lds_64x128_table(&n);
+    v.insert(v.end(), more, more + n);
+    for (size_t i = v.size() - n; i < v.size(); ++i) v[i].appended = 1;
     return v;
   }();
   return all;

@@ -53,11 +53,13 @@ struct LdsKernelInfo {
   int bn_tail;            // > 0: tf_gemm_mixed_kernel, width of the tiles of its lighter last round
   int ragged_mn;          // 1: tf_bgemm_persist_ragged_kernel, for ragged tiles or a batch that is no multiple of eight (and only for those)
   int k_tail;             // 1: instance for a K that is no multiple of bk (and only for that)
+  int appended;           // 1: its variants follow all others of a family
   const void* func;       // kernel symbol, for hipFuncGetAttributes / occupancy queries
   void (*launch)(const GemmParams&, dim3 grid, hipStream_t);
 };
 const LdsKernelInfo* lds_ragged_table(int* n);   // the parts of the table that tf_gemm_lds_ragged.hip and
-const LdsKernelInfo* lds_192_table(int* n);      // tf_gemm_lds_192.hip hold
+const LdsKernelInfo* lds_192_table(int* n);      // tf_gemm_lds_192.hip and
+const LdsKernelInfo* lds_64x128_table(int* n);   // tf_gemm_lds_64x128.hip hold
 int lds_kernel_count();
 const LdsKernelInfo* lds_kernel_table();
 

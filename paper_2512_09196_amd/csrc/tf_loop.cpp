@@ -121,7 +121,7 @@ extern "C" double tf_grid_fill(const tf_hw* hw, const tf_variant_desc* v) {
   return (double)v->grid / (double)(cdiv(v->grid, slots) * slots);
 }
 
-extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
+double tf::base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
   const double flops = 2.0 * pr->M * (double)pr->N * pr->K;
   const double bytes = 2.0 * ((double)pr->M * pr->K + (double)pr->K * pr->N + (double)pr->M * pr->N + pr->N);
   const double hbm_us = bytes / (hw->hbm_gbs_peak * 1e3);
@@ -160,11 +160,11 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
       v1.grid = (int32_t)(((pr->M + v->bm - 1) / v->bm) * (long)((pr->N + v->bn - 1) / v->bn) * (long)items);
       // (dealt out as whole items, eight XCDs wait for the ones with the most)
       const double share = v->xcd_swizzle ? 8.0 * cdiv((long)items, 8) / items : 1.0;
-      return fmax(0.8 * tf_predict_us(&one, hw, &v1), floor_us + 4.0) * share;
+      return fmax(0.8 * tf::base_predict_us(&one, hw, &v1), floor_us + 4.0) * share;
     }
     // (a work-group of the plain kernels reads, multiplies and then writes, and the chip's reads and writes overlap
     // less for it: 32 x 1024 x 1024 x 256, 168 MB, takes 44.7-52.2 us in their tiles, 34.9 us in the persistent kernel)
-    double us = fmax(tf_predict_us(&one, hw, &v1), 1.4 * floor_us + 4.0);
+    double us = fmax(tf::base_predict_us(&one, hw, &v1), 1.4 * floor_us + 4.0);
     // with few K steps per tile a work-group is a short read - multiply - write sequence; alone on its CU
     // it leaves memory idle while it multiplies and the matrix pipes idle while it writes (measured 1.4-1.6x)
     const long slots_one = (long)hw->cus * tf_resident_wgs(hw, v);
@@ -380,6 +380,22 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
   // picks in runs were 10 % faster than the round-robin ones, e.g. 32 x 8576 x 3840 20.1 against 24.2 us)
   const double spread = (v->xcd_swizzle || v->trans_b ? 1.0 : 0.9) * (bk > 64 ? 1.09 : 1.0);
   return fmax(us * rot, (hbm_us + ws_us) / (0.75 * inflight) * spread) + 3.6 + reduce_us + fused_tail_us + pretrans_us;
+}
+
+// What the tile kernels have gained since the constants above were fitted they have gained nearly alike (7 to 15 %), but for:
+//  * eight-wave 128 x 256 tiles, which lead those of 256 x 128, rows of 512 bytes instead of 256 (1500 x 4096 x 4096 with B as
+//    [N][K] 47.4 against 50.8 us, 1559 x 4096 x 3328 42.8 / 47.7, 487 x 10200 x 1688 26.2 / 28.8);
+//  * 64 x 64 tiles where K is short (845 x 5568 x 256 8.8 against 10.0 us, 101 x 7552 x 832 6.9 / 7.8);
+//  * sixteen slices behind a second kernel (300 x 448 x 14016 in 128 x 128 tiles 19.1 us, with eight in 64 x 128 16.4).
+// Over 236 problems the picks were 2.1 % behind the fastest variant without these factors, 1.3 % with them. They are not in
+// what decides which problems are small (base_predict_us).
+extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
+  double us = tf::base_predict_us(pr, hw, v);
+  if (v->kind != TF_KIND_MFMA_LDS || pr->op != TF_OP_GEMM_EPILOGUE) return us;
+  if (v->bm == 128 && v->bn == 256 && v->waves_m * v->waves_n == 8) us *= 0.95;
+  if (v->bm == 64 && v->bn == 64) us *= 1.0 - 0.2 * exp(-(pr->K / 64.0) / 12.0);
+  if (v->split_k >= 16 && !v->fused_reduce) us *= 1.08;
+  return us;
 }
 
 // ------------------------------------------------------------------ Proposal

@@ -18,4 +18,7 @@ typedef tf_status (*profile_fn)(void* user, int32_t id, tf_report* out);
 tf_status run_loop(const tf_problem_desc* prob, const tf_hw* hw, const tf_variant_desc* family, int32_t n,
                    const int32_t* launches, const tf_theta* theta, profile_fn profile, void* user, int32_t* best_variant, tf_report* best,
                    tf_report* round_log, int32_t log_cap, int32_t* n_log);
+// tf_predict_us without the factors that only rank the tile kernels: what decides which problems are small.
+double base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v);
+
 }  // namespace tf
