@@ -124,6 +124,7 @@ struct LdsCfg {
   static constexpr bool FUSED_OK = ACC <= 64;
   static constexpr bool SEGMENTS = false;                  // see StreamKCfg
   static constexpr bool KTAIL = false;                     // see RaggedKCfg
+  static constexpr bool LINES = false;                     // see RaggedKCfg
   // Output staging (see epilogue_staged): each pass moves 32 rows per wave row (and k group) through the tile
   // ring, rows padded by 16 bytes; used for an output type when one pass fits into the ring.
   static constexpr int ST_ROWS = 32 * WM * WK_;
@@ -152,6 +153,29 @@ template <class C>
 __device__ __forceinline__ int b_chunk_swz(int k) {
   return (b_swz<C::B_PIECES>(k) << 2) | (C::MB == 16 ? ((k >> 3) & 1) << 1 : 0);
 }
+
+// An operand whose rows are contiguous along k, staged in whole 128-byte lines. Rows of a length that is no multiple of 128
+// bytes start anywhere in a line, and the 128 bytes a K tile takes of each of them are two requests to the L2, not one. Here
+// buffer w takes line w of every row, counted from the one its first k lies in: chunk j of 16 bytes of K tile t lies in buffer
+// t + (j + shift) / 8, in the slot it would have in a tile's own buffer (with slots in the order of the line the reads conflict:
+// 1160 x 3080 x 1864 24.7 us instead of 23.0; the staging of tiles took 24.3). Rows a multiple of eight apart have the same
+// shift (a row is whole chunks), so a lane has one for all its blocks, and one for all its transfers. Where the ragged last K
+// tile comes first, chunks in front of the range are its (a line shared by the two holds both).
+struct LineRows {
+  int shift;                     // of this lane's rows as it reads them
+  int cs;                        // slot minus shift in its transfers
+  int k0, begin, chunks;         // chunk that slot 0 of buffer 0 stands for where the shift is 0; first chunk of the range; chunks in a row
+  bool wrap;                     // the ragged K tile comes first
+  __device__ __forceinline__ static int shift_of(const uint16_t* base, long ld, int row) {
+    return (int)(((unsigned long long)base >> 4) + (unsigned long long)row * (unsigned long long)(ld >> 3)) & 7;
+  }
+  // chunk to fetch for buffer w, inside the row whatever w is (what no K tile holds is not read)
+  __device__ __forceinline__ int chunk(int w) const {
+    int c = k0 + 8 * w + cs;
+    if (wrap && c < begin) c += chunks - begin;
+    return c < 0 ? 0 : c >= chunks ? chunks - 1 : c;
+  }
+};
 
 template <class C>
 struct TileLoader {
@@ -277,6 +301,18 @@ struct TileLoader {
       const int ib = wave + C::NWAVES * q;
       gload_lds16<C::B_NT>(__builtin_amdgcn_readfirstlane(stage_lds + C::A_BYTES + ib * 1024), b_src[q], Bk);
     }
+  }
+
+  // LINES: buffer w of an operand. EDGE: any w; otherwise one whose lines lie inside the range of every row (offsets that
+  // begin 7 chunks ahead, so that none is negative)
+  template <bool EDGE, bool NT, int PER_WAVE>
+  __device__ __forceinline__ static void issue_lines(const LineRows& r, const unsigned (&src)[PER_WAVE], const uint16_t* base, int w,
+                                                     unsigned lds, int wave) {
+    const int c = EDGE ? r.chunk(w) - (r.cs + 7) : 0;
+    const char* from = (const char*)base + (EDGE ? 0l : 16l * (r.k0 + 8 * w - 7));
+#pragma unroll
+    for (int q = 0; q < PER_WAVE; ++q)
+      gload_lds16<NT>(__builtin_amdgcn_readfirstlane(lds + (wave + C::NWAVES * q) * 1024), src[q] + 16u * (unsigned)c, from);
   }
 
   // min(first + further, last) + chunk, in three instructions where it is needed (the compiler would compute every offset
@@ -765,6 +801,29 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
       return __builtin_bit_cast(bf16x8, v);
     }
   };
+  // LINES: where chunk KMF / 8 kk + g lies, for rows of this lane's shift
+  LineRows la{}, lb{};
+  int la_off[C::LINES ? C::KS : 1], lb_off[C::LINES ? C::KS : 1];
+  bool la_next[C::LINES ? C::KS : 1], lb_next[C::LINES ? C::KS : 1];
+  if constexpr (C::LINES) {
+    const int ra = C::row_off(0, wave_m) + lane % C::MB, rb = wave_n * C::TN0 * C::MB + lane % C::MB;
+    la.shift = LineRows::shift_of(p.A, p.lda, m0 + ra);
+    lb.shift = LineRows::shift_of(p.B, p.ldb, n0 + rb);
+#pragma unroll
+    for (int kk = 0; kk < C::KS; ++kk) {
+      const int ua = C::KMF / 8 * kk + lane / C::MB + la.shift, ub = C::KMF / 8 * kk + lane / C::MB + lb.shift;
+      la_off[kk] = ra * C::K_ROW_BYTES + (((ua - la.shift) ^ C::row_swz(ra)) << 4);
+      la_next[kk] = ua >= 8;
+      lb_off[kk] = C::B_BASE + rb * C::K_ROW_BYTES + (((ub - lb.shift) ^ C::row_swz(rb)) << 4);
+      lb_next[kk] = ub >= 8;
+    }
+  }
+  auto line_a = [&](const char* stage, const char* next, int kk, int i) -> bf16x8 {
+    return *(const bf16x8*)((la_next[kk] ? next : stage) + la_off[kk] + a_block_const(i));
+  };
+  auto line_b = [&](const char* stage, const char* next, int kk, int t) -> bf16x8 {
+    return *(const bf16x8*)((lb_next[kk] ? next : stage) + lb_off[kk] + t * C::MB * C::K_ROW_BYTES);
+  };
   auto mma = [](const bf16x8 b, const bf16x8 a, const typename C::Acc c) -> typename C::Acc {
     if constexpr (C::MB == 16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, c, 0, 0, 0);
     else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0);
@@ -894,6 +953,25 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
   };
   auto next_a = [&]() { return (const uint16_t*)nx.a; };
   auto next_b = [&]() { return (const uint16_t*)nx.b; };
+  if constexpr (C::LINES) {
+    const int row = C::K_ROWS_PER_INSTR * wave + lane / C::K_CHUNKS, c = (lane % C::K_CHUNKS) ^ C::row_swz(row);
+    auto set = [&](LineRows& r, unsigned* src, int per_wave, const uint16_t* base, long ld_elems, int first, int count) {
+      const int s = LineRows::shift_of(base, ld_elems, first + row);
+      r.cs = ((c + s) & 7) - s;
+      r.begin = first_kt * 8;
+      r.k0 = r.begin - (skip ? 8 : 0);
+      r.chunks = p.K / 8;
+      r.wrap = skip != 0;
+      for (int q = 0; q < per_wave; ++q) {
+        int m = first + row + C::K_ROWS_PER_INSTR * C::NWAVES * q;
+        if (m >= count) m = count - 1;
+        src[q] = ((unsigned)m * (unsigned)ld_elems + 8u * (unsigned)(r.cs + 7)) * 2u;
+      }
+    };
+    static_assert(!C::LINES || C::K_ROWS_PER_INSTR * C::NWAVES % 16 == 0, "one slot and one shift for all transfers of a lane");
+    set(la, ld.a_src, C::A_PER_WAVE, p.A, p.lda, m0, p.M);
+    if constexpr (C::TRANSB) set(lb, ld.b_src, C::B_PER_WAVE, p.B, p.ldb, n0, p.N);
+  }
   auto zero_skipped = [&]() {                  // every wave calls it; the first tile has landed and has not been read
     if (!C::KTAIL || skip == 0) return;
     char* const a_tile = smem;
@@ -906,8 +984,18 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     auto k_rows = [&](char* tile, int row_bytes) {
       for (int x = tid * 16; x < skip * row_bytes; x += C::THREADS * 16) *(u32x4*)(tile + x) = zero;
     };
-    if constexpr (C::TRANSA) k_rows(a_tile, C::A_ROW_BYTES); else k_contiguous(a_tile, C::BM);
-    if constexpr (C::TRANSB) k_contiguous(b_tile, C::BN);
+    auto k_lines = [&](char* tile, int rows, const uint16_t* base, long ld_elems, int first) {
+      for (int r = tid; r < rows; r += C::THREADS) {
+        const int s = LineRows::shift_of(base, ld_elems, first + r);
+        for (int c = 0; c < skip / 8; ++c)
+          *(u32x4*)(tile + ((c + s) >> 3) * C::STAGE_BYTES + r * C::K_ROW_BYTES + ((c ^ C::row_swz(r)) << 4)) = zero;
+      }
+    };
+    if constexpr (C::TRANSA) k_rows(a_tile, C::A_ROW_BYTES);
+    else if constexpr (C::LINES) k_lines(a_tile, C::BM, p.A, p.lda, m0);
+    else k_contiguous(a_tile, C::BM);
+    if constexpr (C::TRANSB && C::LINES) k_lines(b_tile, C::BN, p.B, p.ldb, n0);
+    else if constexpr (C::TRANSB) k_contiguous(b_tile, C::BN);
     else
       for (int u = 0; u < C::B_UNITS; ++u) k_rows(b_tile + u * C::B_UNIT_BYTES, C::B_ROW_BYTES);
     barrier_lds();
@@ -1019,15 +1107,44 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     static_assert((D - 1) * PER_TILE < 64, "vmcnt range");
     const unsigned lds0 = (unsigned)(size_t)smem;
     bf16x8 fa[2][C::KS][C::TM], fb[2][C::KS][C::TN];
-    auto read_tile = [&](const char* stage, bf16x8 (&a)[C::KS][C::TM], bf16x8 (&b)[C::KS][C::TN]) {
+    // the K tile in buffer `buf` (LINES: and the next one)
+    auto read_tile = [&](int buf, bf16x8 (&a)[C::KS][C::TM], bf16x8 (&b)[C::KS][C::TN]) {
+      const char* const stage = smem + buf * C::STAGE_BYTES;
+      const char* const next = smem + (buf + 1 == C::STAGES ? 0 : buf + 1) * C::STAGE_BYTES;
 #pragma unroll
       for (int kk = 0; kk < C::KS; ++kk) {
 #pragma unroll
-        for (int i = 0; i < C::TM; ++i) a[kk][i] = read_a(stage, kk, i);
+        for (int i = 0; i < C::TM; ++i) {
+          if constexpr (C::LINES) a[kk][i] = line_a(stage, next, kk, i);
+          else a[kk][i] = read_a(stage, kk, i);
+        }
 #pragma unroll
-        for (int t = 0; t < C::TN; ++t) b[kk][t] = read_b1(stage, kk, t);
+        for (int t = 0; t < C::TN; ++t) {
+          if constexpr (C::LINES && C::TRANSB) b[kk][t] = line_b(stage, next, kk, t);
+          else b[kk][t] = read_b1(stage, kk, t);
+        }
       }
     };
+    // what buffer w takes: K tile w, or the lines of that number, of which there is one more. EDGE: see issue_lines
+    auto fetch_buffer = [&](auto edge, int w, int slot) {
+      constexpr bool EDGE = decltype(edge)::value != 0;
+      const unsigned to = lds0 + slot * C::STAGE_BYTES;
+      if constexpr (!C::LINES) {
+        ld.issue_direct(next_a(), next_b(), to, wave);
+        next_tile();
+      } else {
+        TileLoader<C>::template issue_lines<EDGE, false>(la, ld.a_src, p.A, w, to, wave);
+        if constexpr (C::TRANSB) {
+          TileLoader<C>::template issue_lines<EDGE, C::B_NT>(lb, ld.b_src, p.B, w, to + C::A_BYTES, wave);
+        } else if (!EDGE || w < nkt) {
+          ld.issue_b_direct(next_b(), to, wave);
+          next_tile();
+        }
+      }
+    };
+    constexpr int MORE = C::LINES ? 1 : 0;            // buffers beyond the last K tile
+    // transfers that may still fly when a K tile is about to be read: all behind it, but for the next lines
+    constexpr int FLYING = (D - 1) * PER_TILE - (C::LINES ? (C::TRANSB ? PER_TILE : C::A_PER_WAVE) : 0);
     auto mfma_tile = [&](const bf16x8 (&a)[C::KS][C::TM], const bf16x8 (&b)[C::KS][C::TN]) {
 #pragma unroll
       for (int kk = 0; kk < C::KS; ++kk)
@@ -1042,19 +1159,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     if (nkt > 0) {
 #pragma unroll
       for (int s = 0; s < D; ++s)
-        if (s < nkt) {
-          ld.issue_direct(next_a(), next_b(), lds0 + s * C::STAGE_BYTES, wave);
-          next_tile();
-        }
-      if (nkt >= D) wait_vmcnt<(D - 1) * PER_TILE>();
+        if (s < nkt + MORE) fetch_buffer(EpiTag<1>{}, s, s);
+      if (nkt >= D) wait_vmcnt<FLYING>();
       else wait_vmcnt<0>();
       barrier_lds();
-      if (D < nkt) {
-        ld.issue_direct(next_a(), next_b(), lds0 + D * C::STAGE_BYTES, wave);
-        next_tile();
-      }
+      if (D < nkt + MORE) fetch_buffer(EpiTag<1>{}, D, D);
       zero_skipped();
-      read_tile(smem, fa[0], fb[0]);
+      read_tile(0, fa[0], fb[0]);
       int stage = 0;
       // one non-final tile t: its fragments are in (ca, cb); (na, nb) receive tile t+1. FETCH: tile t + 1 + D exists and
       // is fetched; otherwise what there is
@@ -1063,14 +1174,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
         constexpr bool FETCH = decltype(fetch)::value != 0;
         int nstage = stage + 1;
         if (nstage == C::STAGES) nstage = 0;
-        if (FETCH || t + D <= last) wait_vmcnt<(D - 1) * PER_TILE>();    // tile t+1 has landed
+        if (FETCH || t + D <= last) wait_vmcnt<FLYING>();    // tile t+1 has landed
         else wait_vmcnt<0>();
         barrier_lds();                       // ... for every wave; every wave holds tile t in registers
-        if (FETCH || t + 1 + D <= last) {
-          ld.issue_direct(next_a(), next_b(), lds0 + stage * C::STAGE_BYTES, wave);
-          next_tile();
-        }
-        read_tile(smem + nstage * C::STAGE_BYTES, na, nb);
+        if (FETCH || t + 1 + D < nkt + MORE) fetch_buffer(EpiTag<!FETCH>{}, t + 1 + D, stage);
+        read_tile(nstage, na, nb);
         mfma_tile(ca, cb);
         if constexpr (C::MB == 16) spread(EpiTag<C::KS * N_DS>{}, EpiTag<C::KS * N_MFMA>{});
         __builtin_amdgcn_sched_barrier(0);
@@ -1498,6 +1606,10 @@ template <class Base>
 struct RaggedKCfg : Base {
   static_assert(Base::DIRECT && !Base::ABYPASS, "both operands staged directly");
   static constexpr bool KTAIL = true;
+  // LINES: operands whose rows are contiguous along k are staged in whole 128-byte lines (see LineRows). One buffer more than
+  // the pipeline needs otherwise: a K tile lies in two of them.
+  static constexpr bool LINES = Base::STAGES >= 4 && Base::BM >= 64 && Base::BK == 64 && !Base::TRANSA && Base::WK == 1 && !Base::QUAD &&
+                                Base::ACC * Base::KS * Base::KMF <= 8 * 16 * 16;
 };
 
 template <class C>
@@ -1752,7 +1864,7 @@ static LdsKernelInfo describe() {
   k.stages = C::STAGES; k.direct_to_lds = C::DIRECT ? 1 : 0; k.a_bypass_lds = C::ABYPASS ? 1 : 0; k.trans_a = C::TRANSA ? 1 : 0;
   k.trans_b = C::TRANSB ? 1 : 0;
   k.threads = C::THREADS; k.lds_bytes = C::LDS_BYTES; k.fused_ok = C::FUSED_OK ? 1 : 0;
-  k.persistent = 0; k.stream_k = C::SEGMENTS ? 1 : 0; k.bn_tail = 0; k.k_tail = 0;
+  k.persistent = 0; k.stream_k = C::SEGMENTS ? 1 : 0; k.bn_tail = 0; k.k_tail = 0; k.lines = 0;
   return k;
 }
 template <class C>
@@ -1770,7 +1882,7 @@ static void launch_lds_ragged(const GemmParams& p, dim3 grid, hipStream_t stream
 template <class C>
 static LdsKernelInfo make_ragged_info() {
   LdsKernelInfo k = describe<C>();
-  k.k_tail = 1;
+  k.k_tail = 1; k.lines = RaggedKCfg<C>::LINES ? 1 : 0;
   k.func = (const void*)tf_gemm_lds_ktail_kernel<C>;
   k.launch = launch_lds_ragged<C>;
   return k;

@@ -24,6 +24,12 @@ using N32x128  = LdsCfg< 32, 128, 64, 1, 4, 3, true, false, 1, false, true>;
 using N32x64   = LdsCfg< 32,  64, 64, 1, 2, 4, true, false, 1, false, true>;
 using N32x32   = LdsCfg< 32,  32, 64, 1, 1, 4, true, false, 1, false, true>;
 
+// rows in whole lines (RaggedKCfg::LINES): they take the calls of the instances with three buffers where lds_lines_index says so
+using KL128x128 = LdsCfg<128, 128, 64, 2, 4, 4, true>;
+using KL64x128  = LdsCfg< 64, 128, 64, 2, 4, 4, true>;
+using NL128x128 = LdsCfg<128, 128, 64, 2, 4, 4, true, false, 1, false, true>;
+using NL64x128  = LdsCfg< 64, 128, 64, 2, 4, 4, true, false, 1, false, true>;
+
 // first operand transposed: the persistent kernel for ragged tiles
 using T128x128 = LdsCfg<128, 128, 64, 2, 4, 3, true, false, 1, true>;
 
@@ -33,6 +39,7 @@ static const LdsKernelInfo g_ragged[] = {
     make_ragged_info<N256x256>(), make_ragged_info<N256x128>(), make_ragged_info<N128x256>(), make_ragged_info<N128x128>(),
     make_ragged_info<N64x64>(),   make_ragged_info<N32x128>(),  make_ragged_info<N32x64>(),   make_ragged_info<N32x32>(),
     make_persist_ragged_info<T128x128>(),
+    make_ragged_info<KL128x128>(), make_ragged_info<KL64x128>(), make_ragged_info<NL128x128>(), make_ragged_info<NL64x128>(),
 };
 
 const LdsKernelInfo* lds_ragged_table(int* n) {
