@@ -77,22 +77,18 @@ void add_variant(tf_problem* p, const tf_variant_desc& v, const VariantImpl& im)
   p->impl.push_back(im);
 }
 
-// The instance that runs a variant of kernel i (`per` K tiles a slice, `grid` work-groups): the one that stages rows in whole
-// lines where there is one, rows do not start on lines or half lines anyway, and its fourth buffer and its one line more per row
-// pay. us, without / with, 128 x 128 tiles: 1160 x 3080 x 1864 24.3 / 23.0, with B as [N][K] 25.9 / 22.9; 2038 x 1280 x 3976
-// 33.7 / 30.2; 1500 x 2056 x 1032 [N][K] 15.1 / 13.8; level at 11 to 13 K tiles (1400 x 2000 x 776 12.2 / 12.0, 900 x 904 x 680
-// 10.9 / 11.0), slower below (1000 x 2000 x 520 9.7 / 10.3) and where rows are whole lines (the first with A's rows padded 20.4 /
-// 21.7) or halves (474 x 640 x 14368 in eight slices 21.0 / 21.9). 64 x 128 tiles: 600 x 3000 x 4072 30.4 / 27.1, [N][K]
-// 33.3 / 27.4; 1172 x 928 x 2120 [N][K] 18.8 / 14.6; 551 x 2880 x 1128 10.7 / 10.4, [N][K] 12.2 / 11.0; 900 x 904 x 680 8.4 / 8.5,
-// [N][K] 8.1 / 8.5; only one work-group fits a CU, so not where there are more of them than CUs (1400 x 2000 x 776 13.3 / 17.5).
-// `dealt`: the slices take the K tiles in turn, and a line would belong to two of them.
-int lds_lines_index(const tf_problem_desc& d, const tf::LdsKernelInfo& k, int i, long per, long grid, int cus, bool dealt) {
-  if (!k.k_tail || k.bk != 64 || dealt || !(d.lda % 32 || (k.trans_b && d.ldb % 32))) return i;
-  if (k.bm == 128 ? per < 12 : per < 16 || grid > cus) return i;
-  const tf::LdsKernelInfo* tab = tf::lds_kernel_table();
-  for (int j = 0; j < tf::lds_kernel_count(); ++j)
-    if (tab[j].lines && tab[j].bm == k.bm && tab[j].bn == k.bn && tab[j].trans_b == k.trans_b) return j;
-  return i;
+// Whether an instance that stages rows in whole lines is offered beside the one of the same tile with three buffers (`per` K tiles
+// a slice, `grid` work-groups): where rows do not start on lines or half lines anyway, and its fourth buffer and its one
+// line more per row can pay. us, without / with, 128 x 128 tiles: 1160 x 3080 x 1864 24.3 / 23.0, with B as [N][K] 25.9 / 22.9;
+// 2038 x 1280 x 3976 33.7 / 30.2; 1500 x 2056 x 1032 [N][K] 15.1 / 13.8; level at 11 to 13 K tiles (1400 x 2000 x 776 12.2 / 12.0,
+// 900 x 904 x 680 10.9 / 11.0), slower below (1000 x 2000 x 520 9.7 / 10.3) and where rows are whole lines (the first with A's
+// rows padded 20.4 / 21.7) or halves (474 x 640 x 14368 in eight slices 21.0 / 21.9). 64 x 128 tiles: 600 x 3000 x 4072 30.4 /
+// 27.1, [N][K] 33.3 / 27.4; 1172 x 928 x 2120 [N][K] 18.8 / 14.6; 551 x 2880 x 1128 10.7 / 10.4, [N][K] 12.2 / 11.0; 900 x 904 x 680
+// 8.4 / 8.5, [N][K] 8.1 / 8.5; only one work-group fits a CU, so not where there are more of them than CUs (1400 x 2000 x 776
+// 13.3 / 17.5). `dealt`: the slices take the K tiles in turn, and a line would belong to two of them.
+bool lines_offered(const tf_problem_desc& d, const tf::LdsKernelInfo& k, long per, long grid, int cus, bool dealt) {
+  if (dealt || !(d.lda % 32 || (k.trans_b && d.ldb % 32))) return false;
+  return k.bm == 128 ? per >= 12 : per >= 16 && grid <= cus;
 }
 
 // C[m][n] = sum_k A[m][k] B[m][n][k]: the naive kernel, then the streaming family at several grid sizes.
@@ -401,7 +397,6 @@ void build_family(tf_problem* p) {
     const tf::LdsKernelInfo& k = tab[i];
     if (k.appended != appended) continue;
     if (k.trans_a) continue;                               // kernels of the transposed-operand product
-    if (k.lines) continue;                                 // they take calls of the other instances: lds_lines_index
     if (pass == 0 && (k.trans_b != 0) != tb) continue;
     if (pass == 1) {
       // a few representative kernels behind the transposing pass
@@ -496,27 +491,26 @@ void build_family(tf_problem* p) {
         // eight L2s and their links to memory at once (a streaming read of column strips measured 23.1 us per
         // 134 MB that way, 26.6 us with a contiguous run per XCD)
         for (int xs = 1; xs >= (tm == 1 && pass == 0 ? 0 : 1); --xs) {
-        const int i_run = lds_lines_index(d, k, i, per, tm * tn * s, cus, xs == 0 && s >= 4);
-        const tf::LdsKernelInfo& run = tab[i_run];
+        if (k.lines && !lines_offered(d, k, per, tm * tn * s, cus, xs == 0 && s >= 4)) continue;
         tf_variant_desc v;
         memset(&v, 0, sizeof(v));
         v.k_rotate = kr;
         v.kind = TF_KIND_MFMA_LDS; v.bm = k.bm; v.bn = k.bn; v.bk = k.bk; v.waves_m = k.waves_m; v.waves_n = k.waves_n; v.waves_k = k.waves_k;
-        v.stages = run.stages; v.split_k = s; v.fused_reduce = (s > 1) ? fused : 0;
+        v.stages = k.stages; v.split_k = s; v.fused_reduce = (s > 1) ? fused : 0;
         v.direct_to_lds = k.k_tail ? 2 : k.direct_to_lds; v.a_bypass_lds = k.a_bypass_lds; v.xcd_swizzle = xs;
         v.trans_b = k.trans_b;
         v.group_m = (int32_t)std::min<long>(tm, 8);
-        v.threads = k.threads; v.lds_bytes = run.lds_bytes;
+        v.threads = k.threads; v.lds_bytes = k.lds_bytes;
         v.grid = (int32_t)(tm * tn * s);
         VariantImpl im{};
-        im.lds_index = i_run; im.ktiles_per_split = (int)per; im.tiles_m = (int)tm; im.tiles_n = (int)tn;
+        im.lds_index = i; im.ktiles_per_split = (int)per; im.tiles_m = (int)tm; im.tiles_n = (int)tn;
         im.counter_bytes = s > 1 ? counter_area(tm * tn) : 0;
         v.workspace_bytes = s > 1 ? (int64_t)(im.counter_bytes + (size_t)s * d.M * d.N * 4) : 0;
         if (pass == 1) v.workspace_bytes = (int64_t)(((size_t)d.K * d.N * 2 + 255) / 256 * 256);     // B^T
         char wk[8] = "";
         if (k.waves_k > 1) snprintf(wk, sizeof(wk), "x%d", k.waves_k);
         snprintf(v.name, sizeof(v.name), "lds_%dx%dx%d_w%dx%d%s_s%d_%s%s%s_sk%d%s", k.bm, k.bn, k.bk, k.waves_m, k.waves_n,
-                 wk, run.stages, k.a_bypass_lds ? "areg" : (k.direct_to_lds ? "direct" : "regs"),
+                 wk, k.stages, k.a_bypass_lds ? "areg" : (k.direct_to_lds ? "direct" : "regs"),
                  pass == 1 ? "_pretransB" : (k.trans_b ? "_bnk" : ""), xs ? "" : "_rr", s,
                  s > 1 ? (fused == 2 ? "l" : (fused ? "f" : "r")) : (kr ? "x" : ""));
         add_variant(p, v, im);
@@ -564,6 +558,7 @@ void build_family(tf_problem* p) {
   }
   build_small_family(p);
   add_tiles(1);
+  add_tiles(2);
   // One counter area for the whole family, so that the partial sums of one variant never
   // land on the counters of another: [counters, status word | partial sums]. The status word
   // takes the last 256 bytes of the area.

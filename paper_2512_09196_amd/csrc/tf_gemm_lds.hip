@@ -115,6 +115,8 @@ static const std::vector<LdsKernelInfo>& all_kernels() {
     more = lds_64x128_table(&n);
     v.insert(v.end(), more, more + n);
     for (size_t i = v.size() - n; i < v.size(); ++i) v[i].appended = 1;
+    for (LdsKernelInfo& k : v)
+      if (k.lines) k.appended = 2;
     return v;
   }();
   return all;

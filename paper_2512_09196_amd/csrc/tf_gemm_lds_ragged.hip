@@ -24,7 +24,7 @@ using N32x128  = LdsCfg< 32, 128, 64, 1, 4, 3, true, false, 1, false, true>;
 using N32x64   = LdsCfg< 32,  64, 64, 1, 2, 4, true, false, 1, false, true>;
 using N32x32   = LdsCfg< 32,  32, 64, 1, 1, 4, true, false, 1, false, true>;
 
-// rows in whole lines (RaggedKCfg::LINES): they take the calls of the instances with three buffers where lds_lines_index says so
+// rows in whole lines (RaggedKCfg::LINES): beside the instances with three buffers, where lines_offered says so
 using KL128x128 = LdsCfg<128, 128, 64, 2, 4, 4, true>;
 using KL64x128  = LdsCfg< 64, 128, 64, 2, 4, 4, true>;
 using NL128x128 = LdsCfg<128, 128, 64, 2, 4, 4, true, false, 1, false, true>;

@@ -54,7 +54,7 @@ struct LdsKernelInfo {
   int ragged_mn;          // 1: tf_bgemm_persist_ragged_kernel, for ragged tiles or a batch that is no multiple of eight (and only for those)
   int k_tail;             // 1: instance for a K that is no multiple of bk (and only for that)
   int lines;              // 1: such an instance that stages rows in whole 128-byte lines (no K tiles dealt to the slices, rows of 256 bytes and more)
-  int appended;           // 1: its variants follow all others of a family
+  int appended;           // its variants follow all others of a family: 1, and behind those 2
   const void* func;       // kernel symbol, for hipFuncGetAttributes / occupancy queries
   void (*launch)(const GemmParams&, dim3 grid, hipStream_t);
 };

@@ -21,3 +21,26 @@ def test_the_counter_area_is_that_of_the_other_variants(M, N, K, trans_b):
     others = [area(tiles(v)) for v in sliced if (v.bm, v.bn) != (64, 128) and v.kind != tf.TF_KIND_MFMA_KSHARE]
     others += [area(-(-M // v.bm) * -(-N // v.bn)) for v in streamk + [v for v in sliced if v.kind == tf.TF_KIND_MFMA_KSHARE]]
     assert others and {v.workspace_bytes - v.split_k * M * N * 4 for v in sliced} == {max(others) + 256}
+
+
+def ragged(v, bm, stages):
+    return v.kind == tf.TF_KIND_MFMA_LDS and v.direct_to_lds >= 2 and v.bm == bm and v.bn == 128 and v.stages == stages
+
+
+def launch(v):
+    return v.split_k, v.fused_reduce, v.xcd_swizzle, v.grid, v.workspace_bytes, v.trans_b
+
+
+@pytest.mark.parametrize("M,N,K,trans_b,bms", [(1160, 3080, 1864, 0, {128}), (1160, 3080, 1864, 1, {128}), (551, 2880, 1128, 0, {64, 128}), (1172, 928, 2120, 1, {64, 128}),
+                                               (128, 256, 11528, 1, {64, 128}), (1000, 2000, 520, 0, set())])
+def test_rows_in_whole_lines_are_offered_beside_the_other_instances(M, N, K, trans_b, bms):
+    """Every launch in whole lines has its counterpart with three buffers, and follows all other variants; it is the one the
+    static model puts ahead."""
+    with tf.Problem(M, N, K, trans_b=trans_b) as p:
+        vs = p.variants()
+        us = [tf.predict_us(p.desc, tf.hw_nominal(), v) for v in vs]
+    lined = [v for v in vs if ragged(v, 64, 4) or ragged(v, 128, 4)]
+    assert {v.bm for v in lined} == bms and [v.id for v in lined] == list(range(len(vs) - len(lined), len(vs)))
+    for v in lined:
+        other = [u for u in vs if ragged(u, v.bm, 3) and launch(u) == launch(v)]
+        assert len(other) == 1 and us[v.id] < us[other[0].id]
