@@ -51,9 +51,11 @@ struct LdsCfg {
   // same cycles per flop and the same fragment bytes per wave, but the second reads and writes half as many accumulators
   // per flop, and under load this board's clock is what its power limit leaves: register-only loops on random operands
   // sustain 1775 TFLOP/s (1.84 GHz) with the first and 2010 (2.05 GHz) with the second, 2060 in the serpentine order below
-  // (on zeros both 2440, 2.4 GHz). It is used where the matrix pipes set the pace, in wave tiles of 64 rows and more;
-  // smaller ones wait for operands and keep the first, which needs half as many instructions.
-  static constexpr int MB = DIRECT_ && !ABYPASS_ && !TRANSA_ && WK_ == 1 && BK_ >= 64 && WM_ * WN_ > 1 && BM_ / WM_ >= 64 ? 16 : 32;
+  // (on zeros both 2440, 2.4 GHz). It is used where the matrix pipes set the pace, in the eight-wave tiles with wave tiles of 64
+  // rows and more; smaller ones wait for operands and keep the first, which needs half as many instructions, and so do
+  // tiles of four waves, one to a SIMD, where nothing fills the pipe while its wave issues or waits (with the second, over 28 to 92
+  // problems, 128 x 256 tiles took 12 % longer, 256 x 128 7 %, 128 x 128 13 % with three buffers and 2 % with two).
+  static constexpr int MB = DIRECT_ && !ABYPASS_ && !TRANSA_ && WK_ == 1 && BK_ >= 64 && WM_ * WN_ >= 8 && BM_ / WM_ >= 64 ? 16 : 32;
   static constexpr int KMF = MB == 16 ? 32 : 16;
   static constexpr int QN = MB / 16 * (MB / 16);           // runs of four accumulators a lane holds of a block
   static constexpr int KSTEPS = BK / KMF;                  // MFMA steps per K tile
