@@ -66,6 +66,10 @@ struct LdsCfg {
   // fragment reads that a finer split of the tile along m or n costs.
   static constexpr int WK = WK_, KS = KSTEPS / WK_;        // MFMA steps per wave per K step
   static_assert(KS >= 2 && KS % 2 == 0, "the pipeline alternates two fragment sets per MFMA step");
+  // ORDERED: a step's blocks in serpentine order, its MFMAs pinned to it (see the main loops). Not where a wave has two MFMA
+  // steps of 32 x 32 blocks in a K tile: there the compiler's own order is the faster (128 x 128 tiles with two k groups 2.3 %
+  // over 95 problems, 256 x 256 tiles with a K tile of 32 1.6 % over 16).
+  static constexpr bool ORDERED = MB == 16 || KS > 2;
   static constexpr bool DIRECT = DIRECT_;
   // ABYPASS: the A operand never enters LDS. Each wave loads its own A fragments from memory
   // straight into registers (WN must be 1, so no two waves need the same A rows) and only B is
@@ -890,7 +894,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     for (int i = 0; i < C::TM; ++i)
 #pragma unroll
       for (int u = 0; u < C::TN; ++u) {
-        const int t = i & 1 ? C::TN - 1 - u : u;
+        const int t = C::ORDERED && (i & 1) ? C::TN - 1 - u : u;
         acc[i][t] = mma(bfr[set][t], af[set][i], acc[i][t]);
       }
   };
@@ -905,8 +909,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one DS read
     });
-    if constexpr (R > N) __builtin_amdgcn_sched_group_barrier(0x100, R - N, 0);
-    if constexpr (N > R) __builtin_amdgcn_sched_group_barrier(0x008, N - R, 0);
+    if constexpr (C::ORDERED && R > N) __builtin_amdgcn_sched_group_barrier(0x100, R - N, 0);
+    if constexpr (C::ORDERED && N > R) __builtin_amdgcn_sched_group_barrier(0x008, N - R, 0);
   };
   auto interleave_hint = [&]() { spread(EpiTag<N_DS>{}, EpiTag<N_MFMA>{}); };
 
@@ -1154,7 +1158,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
         for (int i = 0; i < C::TM; ++i)
 #pragma unroll
           for (int u = 0; u < C::TN; ++u) {
-            const int t = i & 1 ? C::TN - 1 - u : u;
+            const int t = C::ORDERED && (i & 1) ? C::TN - 1 - u : u;
             acc[i][t] = mma(b[kk][t], a[kk][i], acc[i][t]);
           }
     };
@@ -1183,7 +1187,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
         read_tile(nstage, na, nb);
         mfma_tile(ca, cb);
         if constexpr (C::MB == 16) spread(EpiTag<C::KS * N_DS>{}, EpiTag<C::KS * N_MFMA>{});
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (C::ORDERED) __builtin_amdgcn_sched_barrier(0);
         stage = nstage;
       };
       int kt = 0;
@@ -1377,7 +1381,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
           mfma_step(kk & 1);
           interleave_hint();
         }
-        __builtin_amdgcn_sched_barrier(0);   // (the MFMAs above stay above)
+        if constexpr (C::ORDERED) __builtin_amdgcn_sched_barrier(0);   // (the MFMAs above stay above)
         if (FETCH || last_b) wait_vmcnt<(D - 1) * PER_TILE>();    // tile kt+1 has landed
         else wait_vmcnt<0>();
         barrier_lds();                       // ... for every wave, and every wave is done reading tile kt
