@@ -1244,17 +1244,18 @@ extern "C" tf_status tf_hw_measure(int32_t device, void* hip_stream, double* mfm
   if (hipMalloc(&sink, 256) != hipSuccess) { cleanup(); return fail(TF_E_NOMEM, "cannot allocate the sink"); }
   float ms = 0.f;
   if (mfma_tflops) {
-    // two waves per SIMD, about 3 ms per launch: long enough for the clock to settle
-    const int wgs = hw.cus * 2, iters = 20000;
+    // two waves per SIMD, about 3 ms per launch: long enough for the clock to settle. With either instruction of the tile
+    // kernels, and the faster counts.
+    const int wgs = hw.cus * 2;
     double best = 0.0;
-    for (int rep = 0; rep < 3; ++rep) {
-      if (hipEventRecord(e0, stream) != hipSuccess) { cleanup(); return fail(TF_E_LAUNCH, "hipEventRecord failed"); }
-      tf::launch_calib_mfma((float*)sink, wgs, iters, stream);
-      if (hipEventRecord(e1, stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-          hipEventElapsedTime(&ms, e0, e1) != hipSuccess) { cleanup(); return fail(TF_E_LAUNCH, "MFMA calibration launch failed"); }
-      const double flops = (double)wgs * 4.0 * iters * 4.0 * 32768.0;
-      if (rep > 0) best = std::max(best, flops / (ms * 1e-3) * 1e-12);    // the first launch warms the clock up
-    }
+    for (int block : {32, 16})
+      for (int rep = 0; rep < 3; ++rep) {
+        if (hipEventRecord(e0, stream) != hipSuccess) { cleanup(); return fail(TF_E_LAUNCH, "hipEventRecord failed"); }
+        const double flops = tf::launch_calib_mfma((float*)sink, block, wgs, block == 32 ? 20000 : 10000, stream);
+        if (hipEventRecord(e1, stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+            hipEventElapsedTime(&ms, e0, e1) != hipSuccess) { cleanup(); return fail(TF_E_LAUNCH, "MFMA calibration launch failed"); }
+        if (rep > 0) best = std::max(best, flops / (ms * 1e-3) * 1e-12);    // the first launch warms the clock up
+      }
     *mfma_tflops = best;
   }
   if (hbm_read_gbs) {

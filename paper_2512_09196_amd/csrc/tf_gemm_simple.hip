@@ -62,31 +62,67 @@ __global__ void __launch_bounds__(64) tf_gemm_mfma_direct_kernel(const GemmParam
 }
 
 // What the chip sustains, measured rather than quoted: an MFMA loop on registers only, with
-// operands that look like data (random bf16 mantissas: the clock the chip holds under MFMA load
+// operands that look like data (bf16 values about normal, sigma 0.014: the clock the chip holds under MFMA load
 // depends on what the multipliers toggle), and a streaming read of a large buffer.
+// BLOCK: outputs per side of the matrix instruction, 32 (over 16 of k) or 16 (over 32), the two the tile kernels use; 4 x 4
+// blocks in serpentine order (every instruction shares an operand with the one before) or, at 32, 2 x 2. TFLOP/s on two
+// boards: 1845 and 1860 at 32, 2060 and 2080 at 16.
+template <int BLOCK>
 __global__ void __launch_bounds__(256) tf_calib_mfma_kernel(float* sink, int iters, unsigned seed) {
+  constexpr int T = BLOCK == 16 ? 4 : 2;
+  typedef float Acc __attribute__((ext_vector_type(BLOCK * BLOCK / 64)));
   unsigned h = (threadIdx.x + blockIdx.x * 256u + 1u) * 2654435761u ^ seed;
   auto next = [&]() { h ^= h << 13; h ^= h >> 17; h ^= h << 5; return h; };
-  // bf16 pairs with random sign and mantissa, exponents near 2^-7: sums stay far from overflow
-  u32x4 ra, rb;
+  auto value = [&]() {             // (the sum of six uniform numbers; its upper half is the bf16)
+    float v = 0.0f;
+    for (int i = 0; i < 6; ++i) v += (float)(next() >> 8) * (1.0f / 16777216.0f) - 0.5f;
+    return __builtin_bit_cast(unsigned, 0.02f * v);
+  };
+  auto operand = [&]() {
+    u32x4 r;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    ra[i] = (next() & 0x807f807fu) | 0x3c003c00u;
-    rb[i] = (next() & 0x807f807fu) | 0x3c003c00u;
+    for (int i = 0; i < 4; ++i) {
+      const unsigned lo = value(), hi = value();
+      r[i] = (lo >> 16) | (hi & 0xffff0000u);
+    }
+    return __builtin_bit_cast(bf16x8, r);
+  };
+  bf16x8 a[T], b[T];
+#pragma unroll
+  for (int x = 0; x < T; ++x) {
+    a[x] = operand();
+    b[x] = operand();
   }
-  const bf16x8 a = __builtin_bit_cast(bf16x8, ra), b = __builtin_bit_cast(bf16x8, rb);
-  f32x16 c0, c1, c2, c3;
+  Acc c[T][T];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) { c0[i] = 0.0f; c1[i] = 0.0f; c2[i] = 0.0f; c3[i] = 0.0f; }
+  for (int x = 0; x < T; ++x)
+#pragma unroll
+    for (int y = 0; y < T; ++y)
+#pragma unroll
+      for (int i = 0; i < BLOCK * BLOCK / 64; ++i) c[x][y][i] = 0.0f;
+  // (the small blocks in asm: of the builtin the compiler makes a loop with up to four register moves an instruction, 1260 to 1490
+  // TFLOP/s. What it cannot see then it cannot space either: an accumulator comes round every 16 instructions, far beyond
+  // what a chain of them needs, and the waits on either side of the loop cover the operands and the sums.)
+  asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll 1
   for (int it = 0; it < iters; ++it) {
-    c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c0, 0, 0, 0);
-    c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c1, 0, 0, 0);
-    c2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, a, c2, 0, 0, 0);
-    c3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, b, c3, 0, 0, 0);
+#pragma unroll
+    for (int x = 0; x < T; ++x)
+#pragma unroll
+      for (int u = 0; u < T; ++u) {
+        const int y = x & 1 ? T - 1 - u : u;
+        if constexpr (BLOCK == 16) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c[x][y]) : "v"(b[y]), "v"(a[x]));
+        else c[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[y], a[x], c[x][y], 0, 0, 0);
+      }
   }
+  asm volatile("s_nop 15\n\ts_nop 15");
   float s = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) s += c0[i] + c1[i] + c2[i] + c3[i];
+  for (int x = 0; x < T; ++x)
+#pragma unroll
+    for (int y = 0; y < T; ++y)
+#pragma unroll
+      for (int i = 0; i < BLOCK * BLOCK / 64; ++i) s += c[x][y][i];
   if (s == 1.2345e-30f) sink[0] = s;      // keeps the loop alive; never true
 }
 
@@ -110,8 +146,10 @@ __global__ void __launch_bounds__(256) tf_calib_read_kernel(const u32x4* src, si
   if ((acc[0] ^ acc[1] ^ acc[2] ^ acc[3]) == 0x12345678u) sink[0] = 1u;   // never true for the buffer the host fills
 }
 
-void launch_calib_mfma(float* sink, int wgs, int iters, hipStream_t s) {
-  hipLaunchKernelGGL(tf_calib_mfma_kernel, dim3((unsigned)wgs), dim3(256), 0, s, sink, iters, 0x9e3779b9u);
+double launch_calib_mfma(float* sink, int block, int wgs, int iters, hipStream_t s) {
+  if (block == 16) hipLaunchKernelGGL(tf_calib_mfma_kernel<16>, dim3((unsigned)wgs), dim3(256), 0, s, sink, iters, 0x9e3779b9u);
+  else hipLaunchKernelGGL(tf_calib_mfma_kernel<32>, dim3((unsigned)wgs), dim3(256), 0, s, sink, iters, 0x9e3779b9u);
+  return (double)wgs * 4.0 * iters * (block == 16 ? 16.0 * 16384.0 : 4.0 * 32768.0);
 }
 void launch_calib_read(const void* src, size_t bytes, unsigned* sink, int /*wgs*/, hipStream_t s) {
   const size_t n16 = bytes / 16, waves = (n16 + 511) / 512;

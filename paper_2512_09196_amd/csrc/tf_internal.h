@@ -138,7 +138,7 @@ void launch_xcc_probe(unsigned* out, int wgs, hipStream_t);                // ou
 // its elements are elem_stride apart; out[o * n_inner + i]
 void launch_norms(const uint16_t* X, long n_outer, long outer_stride, long n_inner, long inner_stride, long len, long elem_stride,
                   float* out, hipStream_t);
-void launch_calib_mfma(float* sink, int wgs, int iters, hipStream_t);                       // 4 * iters MFMA 32x32x16 per wave, 4 waves per work-group
+double launch_calib_mfma(float* sink, int block, int wgs, int iters, hipStream_t);            // MFMA of block x block outputs (32 or 16), 4 waves per work-group; returns the flops
 void launch_calib_read(const void* src, size_t bytes, unsigned* sink, int wgs, hipStream_t);  // reads every byte once
 void launch_splitk_reduce(const GemmParams&, hipStream_t);   // sums ws slices in order, bias + epilogue -> Y
 const void* splitk_reduce_func();
