@@ -157,7 +157,9 @@ typedef struct {
                               1 = the last slice to arrive reduces inside the GEMM kernel (one launch,
                               arrival counters); 0 = a second kernel sums the slices and applies the epilogue */
   int32_t direct_to_lds;   /* 1: global_load_lds staging; 2: the same in a kernel for a K that is no multiple of bk (its
-                              last K tile overlaps the one before); 0: via registers (zero-fills a ragged K tail) */
+                              last K tile overlaps the one before); 3: such a kernel that stages rows contiguous along k
+                              in whole 128-byte lines, wherever they start in one; 0: via registers (zero-fills a
+                              ragged K tail) */
   int32_t a_bypass_lds;    /* 1: A fragments are loaded from memory straight into MFMA operand registers, only B is
                               staged in LDS (one wave column per work-group) */
   int32_t trans_a;         /* TF_OP_BATCHED_GEMM_TN, tile kernels: 1 = the A tile is staged as it lies in memory

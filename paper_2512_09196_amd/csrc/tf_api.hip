@@ -497,7 +497,7 @@ void build_family(tf_problem* p) {
         v.k_rotate = kr;
         v.kind = TF_KIND_MFMA_LDS; v.bm = k.bm; v.bn = k.bn; v.bk = k.bk; v.waves_m = k.waves_m; v.waves_n = k.waves_n; v.waves_k = k.waves_k;
         v.stages = k.stages; v.split_k = s; v.fused_reduce = (s > 1) ? fused : 0;
-        v.direct_to_lds = k.k_tail ? 2 : k.direct_to_lds; v.a_bypass_lds = k.a_bypass_lds; v.xcd_swizzle = xs;
+        v.direct_to_lds = k.lines ? 3 : k.k_tail ? 2 : k.direct_to_lds; v.a_bypass_lds = k.a_bypass_lds; v.xcd_swizzle = xs;
         v.trans_b = k.trans_b;
         v.group_m = (int32_t)std::min<long>(tm, 8);
         v.threads = k.threads; v.lds_bytes = k.lds_bytes;
@@ -1374,7 +1374,7 @@ extern "C" int32_t tf_variant_kernel_name(const tf_variant_desc* v, char* buf, i
                v->waves_n, v->stages, b(v->direct_to_lds), b(v->a_bypass_lds), v->waves_k, b(v->trans_a), b(v->trans_b), v->bn);
       n = snprintf(buf, cap, "%s%s", v->bn_tail ? "tf_gemm_mixed_kernel<"
                                      : v->persistent ? (v->xcd_swizzle ? "tf_bgemm_persist_kernel<" : "tf_bgemm_persist_ragged_kernel<")
-                                     : v->direct_to_lds == 2 ? "tf_gemm_lds_ktail_kernel<"
+                                     : v->direct_to_lds >= 2 ? "tf_gemm_lds_ktail_kernel<"
                                      : v->stream_k ? "tf_gemm_lds_kernel<tf::StreamKCfg<" : "tf_gemm_lds_kernel<", cfg);
       break;
     case TF_KIND_MFMA_STREAM:

@@ -387,7 +387,7 @@ double tf::base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_
 //    [N][K] 47.4 against 50.8 us, 1559 x 4096 x 3328 42.8 / 47.7, 487 x 10200 x 1688 26.2 / 28.8);
 //  * 64 x 64 tiles where K is short (845 x 5568 x 256 8.8 against 10.0 us, 101 x 7552 x 832 6.9 / 7.8);
 //  * sixteen slices behind a second kernel (300 x 448 x 14016 in 128 x 128 tiles 19.1 us, with eight in 64 x 128 16.4).
-//  * the instances that stage rows in whole lines (the ones with four buffers), against the others for a ragged K.
+//  * the instances that stage rows in whole lines, against the others for a ragged K.
 // Over 236 problems the picks were 2.1 % behind the fastest variant without these factors, 1.3 % with them. They are not in
 // what decides which problems are small (base_predict_us).
 extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
@@ -396,7 +396,7 @@ extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, cons
   if (v->bm == 128 && v->bn == 256 && v->waves_m * v->waves_n == 8) us *= 0.95;
   if (v->bm == 64 && v->bn == 64) us *= 1.0 - 0.2 * exp(-(pr->K / 64.0) / 12.0);
   if (v->split_k >= 16 && !v->fused_reduce) us *= 1.08;
-  if (v->direct_to_lds == 2 && v->bm >= 64 && v->stages == 4) us *= v->trans_b ? 0.88 : 0.95;
+  if (v->direct_to_lds == 3) us *= v->trans_b ? 0.88 : 0.95;
   return us;
 }
 

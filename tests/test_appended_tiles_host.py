@@ -23,10 +23,6 @@ def test_the_counter_area_is_that_of_the_other_variants(M, N, K, trans_b):
     assert others and {v.workspace_bytes - v.split_k * M * N * 4 for v in sliced} == {max(others) + 256}
 
 
-def ragged(v, bm, stages):
-    return v.kind == tf.TF_KIND_MFMA_LDS and v.direct_to_lds >= 2 and v.bm == bm and v.bn == 128 and v.stages == stages
-
-
 def launch(v):
     return v.split_k, v.fused_reduce, v.xcd_swizzle, v.grid, v.workspace_bytes, v.trans_b
 
@@ -39,8 +35,18 @@ def test_rows_in_whole_lines_are_offered_beside_the_other_instances(M, N, K, tra
     with tf.Problem(M, N, K, trans_b=trans_b) as p:
         vs = p.variants()
         us = [tf.predict_us(p.desc, tf.hw_nominal(), v) for v in vs]
-    lined = [v for v in vs if ragged(v, 64, 4) or ragged(v, 128, 4)]
+    lined = [v for v in vs if v.direct_to_lds == 3]
     assert {v.bm for v in lined} == bms and [v.id for v in lined] == list(range(len(vs) - len(lined), len(vs)))
     for v in lined:
-        other = [u for u in vs if ragged(u, v.bm, 3) and launch(u) == launch(v)]
+        other = [u for u in vs if (u.kind, u.direct_to_lds, u.bm, u.bn, u.stages) == (v.kind, 2, v.bm, v.bn, 3) and launch(u) == launch(v)]
         assert len(other) == 1 and us[v.id] < us[other[0].id]
+
+
+def test_the_model_takes_no_other_ragged_instance_for_one_in_whole_lines():
+    """The descriptor says which they are: one more buffer alone makes no difference to a problem that three keep fed."""
+    with tf.Problem(1160, 3080, 1864) as p:
+        v = [v for v in p.variants() if v.name == b"lds_128x128x64_w2x4_s3_direct_sk1"][0]
+        us = []
+        for v.stages in (3, 4, 5):
+            us.append(tf.predict_us(p.desc, tf.hw_nominal(), v))
+    assert us[0] == us[1] == us[2]

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 def lined(v):
-    return v.kind == tf.TF_KIND_MFMA_LDS and v.direct_to_lds == 2 and v.bm >= 64 and v.stages == 4
+    return v.kind == tf.TF_KIND_MFMA_LDS and v.direct_to_lds == 3
 
 
 def rows_from(bits, ld, skip):
