@@ -273,7 +273,8 @@ double tf::base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_
   //  * the clock under MFMA load with every CU busy is about 1650 MHz, whatever the nominal figure says (the board
   //    is power limited); with fewer work-groups than CUs it is higher, by about 0.38 of the idle share; all
   //    cycle counts below are at that clock;
-  //  * an MFMA 32x32x16 costs 36.5 cycles of its pipe, not 32;
+  //  * an MFMA 32x32x16 costs 36.5 cycles of its pipe, not 32 (every tile kernel ran it then; the eight-wave tiles with rows of 64
+  //    and more per wave have since gone over to 16x16x32, on which the board holds about a tenth more clock: tf_predict_us);
   //  * tiles enter LDS at about 167 B/clk, fragments leave it at about 203 B/clk; reads and writes take turns;
   //  * a CU receives A tiles (short row pieces) at 82 B/clk and B tiles (long ones) at 52 B/clk when all CUs
   //    ask at once; 0.38 of that time is not hidden behind the matrix pipes;
@@ -382,21 +383,30 @@ double tf::base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_
   return fmax(us * rot, (hbm_us + ws_us) / (0.75 * inflight) * spread) + 3.6 + reduce_us + fused_tail_us + pretrans_us;
 }
 
-// What the tile kernels have gained since the constants above were fitted they have gained nearly alike (7 to 15 %), but for:
-//  * eight-wave 128 x 256 tiles, which lead those of 256 x 128, rows of 512 bytes instead of 256 (1500 x 4096 x 4096 with B as
-//    [N][K] 47.4 against 50.8 us, 1559 x 4096 x 3328 42.8 / 47.7, 487 x 10200 x 1688 26.2 / 28.8);
-//  * 64 x 64 tiles where K is short (845 x 5568 x 256 8.8 against 10.0 us, 101 x 7552 x 832 6.9 / 7.8);
-//  * sixteen slices behind a second kernel (300 x 448 x 14016 in 128 x 128 tiles 19.1 us, with eight in 64 x 128 16.4).
-//  * the instances that stage rows in whole lines, against the others for a ragged K.
-// Over 236 problems the picks were 2.1 % behind the fastest variant without these factors, 1.3 % with them. They are not in
-// what decides which problems are small (base_predict_us).
+// What ranks the tile kernels beside the constants above. Those were fitted when every tile kernel ran 32x32x16 MFMAs and fetched
+// whole K tiles ahead; what the kernels have gained since differs by kind (128 x 128 tiles of 2 x 4 waves 0 to 2 %, 256 x 128
+// and 128 x 256 ones 2 to 5, 192 x 256 ones with a ragged K 11, the others 0), and so did what the constants were off before.
+//  * Eight-wave 128 x 256 tiles, also in slices, lead those of 256 x 128: rows of 512 bytes instead of 256 (1500 x 4096 x 4096 with
+//    B as [N][K] 47.4 against 50.8 us, 1559 x 4096 x 3328 42.8 / 47.7, 487 x 10200 x 1688 26.2 / 28.8).
+//  * 64 x 64 tiles where K is short (845 x 5568 x 256 8.8 against 10.0 us, 101 x 7552 x 832 6.9 / 7.8). The whole K counts, a slice's
+//    would pick alike in 716 problems; so would leaving out the register-staged and the pre-transposed ones.
+//  * Sixteen slices behind a second kernel, whose partial tiles cost more than predicted (300 x 448 x 14016 in 128 x 128 tiles
+//    19.1 us, with eight in 64 x 128 16.4).
+//  * Rows staged in whole lines, against three buffers: 5 % ([N][K] 12 %) from 16 K tiles a slice on; with fewer the two are level
+//    (12 to 15 tiles: 1.01 over 58 launches, [N][K] 0.98 over 43; from 48 on 0.91 and 0.78).
+// Over 451 drawn problems (M above 32) the picks are 1.6 % behind the fastest variant, 4.3 % without the four factors; without the
+// first 2.0, the second 2.0, the third 2.1, the fourth 2.9. They are not in what decides which problems are small
+// (base_predict_us).
 extern "C" double tf_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
   double us = tf::base_predict_us(pr, hw, v);
   if (v->kind != TF_KIND_MFMA_LDS || pr->op != TF_OP_GEMM_EPILOGUE) return us;
   if (v->bm == 128 && v->bn == 256 && v->waves_m * v->waves_n == 8) us *= 0.95;
   if (v->bm == 64 && v->bn == 64) us *= 1.0 - 0.2 * exp(-(pr->K / 64.0) / 12.0);
   if (v->split_k >= 16 && !v->fused_reduce) us *= 1.08;
-  if (v->direct_to_lds == 3) us *= v->trans_b ? 0.88 : 0.95;
+  if (v->direct_to_lds == 3) {
+    const bool few = cdiv(cdiv(pr->K, 64), v->split_k) < 16;
+    us *= v->trans_b ? (few ? 0.97 : 0.88) : few ? 1.0 : 0.95;
+  }
   return us;
 }
 

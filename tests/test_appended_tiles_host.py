@@ -28,10 +28,10 @@ def launch(v):
 
 
 @pytest.mark.parametrize("M,N,K,trans_b,bms", [(1160, 3080, 1864, 0, {128}), (1160, 3080, 1864, 1, {128}), (551, 2880, 1128, 0, {64, 128}), (1172, 928, 2120, 1, {64, 128}),
-                                               (128, 256, 11528, 1, {64, 128}), (1000, 2000, 520, 0, set())])
+                                               (128, 256, 11528, 1, {64, 128}), (1000, 2000, 520, 0, set()), (3219, 936, 880, 0, {128})])
 def test_rows_in_whole_lines_are_offered_beside_the_other_instances(M, N, K, trans_b, bms):
-    """Every launch in whole lines has its counterpart with three buffers, and follows all other variants; it is the one the
-    static model puts ahead."""
+    """Every launch in whole lines has its counterpart with three buffers, and follows all other variants; the static model puts
+    it ahead of that one, but for a [K][N] B and fewer than 16 K tiles a slice, where the two were measured level."""
     with tf.Problem(M, N, K, trans_b=trans_b) as p:
         vs = p.variants()
         us = [tf.predict_us(p.desc, tf.hw_nominal(), v) for v in vs]
@@ -39,7 +39,8 @@ def test_rows_in_whole_lines_are_offered_beside_the_other_instances(M, N, K, tra
     assert {v.bm for v in lined} == bms and [v.id for v in lined] == list(range(len(vs) - len(lined), len(vs)))
     for v in lined:
         other = [u for u in vs if (u.kind, u.direct_to_lds, u.bm, u.bn, u.stages) == (v.kind, 2, v.bm, v.bn, 3) and launch(u) == launch(v)]
-        assert len(other) == 1 and us[v.id] < us[other[0].id]
+        level = not trans_b and -(-(-(-K // 64)) // v.split_k) < 16
+        assert len(other) == 1 and (us[v.id] == us[other[0].id] if level else us[v.id] < us[other[0].id])
 
 
 def test_the_model_takes_no_other_ragged_instance_for_one_in_whole_lines():
@@ -50,3 +51,14 @@ def test_the_model_takes_no_other_ragged_instance_for_one_in_whole_lines():
         for v.stages in (3, 4, 5):
             us.append(tf.predict_us(p.desc, tf.hw_nominal(), v))
     assert us[0] == us[1] == us[2]
+
+
+# (us, the pick in whole lines / the one expected: 12.6 / 10.0, 11.0 / 9.1, 12.9 / 10.8, 12.9 / 11.0, 13.0 / 12.3)
+@pytest.mark.parametrize("M,N,K,trans_b,name", [(396, 3000, 944, 1, b"lds_64x128x64_w2x4_s3_direct_bnk_sk1"), (114, 10032, 824, 1, b"lds_64x128x64_w2x4_s3_direct_bnk_sk1"),
+                                                (1107, 1616, 872, 1, b"lds_64x128x64_w2x4_s3_direct_bnk_sk1"), (504, 3680, 936, 1, b"lds_64x128x64_w2x4_s3_direct_bnk_sk1"),
+                                                (3219, 936, 880, 0, b"lds_128x128x64_w2x4_s3_direct_sk1")])
+def test_static_picks_at_few_k_tiles_keep_off_whole_lines(M, N, K, trans_b, name):
+    hw = tf.hw_nominal()
+    with tf.Problem(M, N, K, trans_b=trans_b, epi=tf.TF_EPI_BIAS) as p:
+        vs = p.variants()
+        assert vs[tf.proposal(p.desc, hw, vs, [v.id == 0 for v in vs], 0, tf.TF_BN_UNKNOWN)].name == name
