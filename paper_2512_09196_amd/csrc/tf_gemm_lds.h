@@ -49,9 +49,9 @@ struct LdsCfg {
   static constexpr int K_ROW_BYTES = BK * 2, K_CHUNKS = BK / 8, K_ROWS_PER_LINE = 16 / K_CHUNKS, K_ROWS_PER_INSTR = 64 / K_CHUNKS;
   // The matrix instruction: blocks of MB x MB outputs over KMF of k, 32 x 32 over 16 or 16 x 16 over 32. Both take the
   // same cycles per flop and the same fragment bytes per wave, but the second reads and writes half as many accumulators
-  // per flop, and under load this board's clock is what its power limit leaves: register-only loops on random operands
-  // sustain 1775 TFLOP/s (1.84 GHz) with the first and 2010 (2.05 GHz) with the second, 2060 in the serpentine order below
-  // (on zeros both 2440, 2.4 GHz). It is used where the matrix pipes set the pace, in the eight-wave tiles with wave tiles of 64
+  // per flop, and under load this board's clock is what its power limit leaves: register-only loops on operands
+  // about normal sustain 1810 to 1860 TFLOP/s with the first and 2020 to 2040 with the second, 2050 to 2080 in the serpentine order
+  // below (on zeros both 2400 to 2490). It is used where the matrix pipes set the pace, in the eight-wave tiles with wave tiles of 64
   // rows and more; smaller ones wait for operands and keep the first, which needs half as many instructions, and so do
   // tiles of four waves, one to a SIMD, where nothing fills the pipe while its wave issues or waits (with the second, over 28 to 92
   // problems, 128 x 256 tiles took 12 % longer, 256 x 128 7 %, 128 x 128 13 % with three buffers and 2 % with two).
