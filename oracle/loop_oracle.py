@@ -107,7 +107,7 @@ def moves_in_direction(hint, base, v, fill_base, fill_v):
     if hint == MFMA:
         return area_v >= area_b and fill_v >= fill_base - 1e-9
     if hint == LDS_CONFLICT:
-        return v["direct_to_lds"] != base["direct_to_lds"] or v["bn"] != base["bn"]
+        return bool(v["direct_to_lds"]) != bool(base["direct_to_lds"]) or v["bn"] != base["bn"]
     if hint == OCCUPANCY:
         return area_v < area_b or (area_v == area_b and v["lds_bytes"] < base["lds_bytes"])
     if hint == LATENCY:

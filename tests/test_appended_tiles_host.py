@@ -62,3 +62,21 @@ def test_static_picks_at_few_k_tiles_keep_off_whole_lines(M, N, K, trans_b, name
     with tf.Problem(M, N, K, trans_b=trans_b, epi=tf.TF_EPI_BIAS) as p:
         vs = p.variants()
         assert vs[tf.proposal(p.desc, hw, vs, [v.id == 0 for v in vs], 0, tf.TF_BN_UNKNOWN)].name == name
+
+
+def test_whole_lines_are_no_other_staging_path_to_a_hint():
+    """A bank-conflict diagnosis asks for another staging path or tile: the same tile in whole lines is neither, for the library
+    and for the oracle."""
+    from oracle import loop_oracle as orc
+    fields = ("kind", "bm", "bn", "bk", "stages", "split_k", "direct_to_lds", "lds_bytes", "grid")
+    hw = tf.hw_nominal()
+    with tf.Problem(1160, 3080, 1864) as p:
+        vs = p.variants()
+        base, lined = ([v for v in vs if v.name == name][0] for name in (b"lds_128x128x64_w2x4_s3_direct_sk1", b"lds_128x128x64_w2x4_s4_direct_sk1"))
+        assert (base.direct_to_lds, lined.direct_to_lds) == (2, 3)
+        other = [v for v in vs if v.kind == base.kind and v.bn != base.bn and tf.predict_us(p.desc, hw, v) > tf.predict_us(p.desc, hw, lined)][0]
+        tried = [v.id not in (lined.id, other.id) for v in vs]
+        assert tf.proposal(p.desc, hw, vs, tried, base.id, tf.TF_BN_LDS_CONFLICT) == other.id
+    as_dict = lambda v: {f: getattr(v, f) for f in fields}
+    fill = [tf.grid_fill(hw, v) for v in (base, lined)]
+    assert not orc.moves_in_direction(orc.LDS_CONFLICT, as_dict(base), as_dict(lined), *fill)
