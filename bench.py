@@ -45,7 +45,7 @@ GEMM_WORKLOADS = ["C1", "C2", "C3", "C4", "C5"]
 FETCH_SCALE, WRITE_SCALE = 262144.0 / 131084.9, 1.0
 TRAFFIC_SOURCE = "recorded: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command, see profiles/"
 HBM_TRAFFIC_KIB = {
-    ("C3", "lds_256x256x64_w2x4_s2_direct_tail192_sk1x"): (305629.5, 89554.4),
+    ("C3", "lds_256x256x64_w2x4_s2_direct_tail192_sk1x"): (305622.5, 89441.8),
     # the same compiled kernel with the plain K order, and the 4 x 2 wave arrangement
     ("C3", "lds_256x256x64_w2x4_s2_direct_tail192_sk1"): (305630.1, 89564.6),
     ("C3", "lds_256x256x64_w4x2_s2_direct_tail192_sk1x"): (305651.4, 89323.0),
