@@ -1607,7 +1607,7 @@ __global__ void __launch_bounds__(C::THREADS) tf_gemm_lds_kernel(const GemmParam
 
 // The same kernel for a K that is no multiple of its K tile (1160 x 3080 x 1864: 34.0 us on the register-staged
 // kernels, 22.7 us on the direct ones). An instance of its own, since it takes no rotated order of K: what it does beside costs where K
-// is whole tiles no more than 1 % (us, the ordinary kernel / this: 4096 x 11008 x 4096 in tiles of 256 x 256 290.7 / 291.8, 192 x 256
+// is whole tiles about 1 % or nothing (us, the ordinary kernel / this: 4096 x 11008 x 4096 in tiles of 256 x 256 290.7 / 291.8, 192 x 256
 // 308.5 / 312.1, 256 x 128 331.8 / 331.1; 4096^3 101.6 / 101.7; 3000 x 3000 x 2048 with B as [N][K] in 192 x 256 39.4 / 39.5; 2048^3 20.0 /
 // 20.4; 64 x 64 tiles 1418 x 1152 x 1856 13.8 / 13.5, 700 x 1024^2 [N][K] 7.4 / 7.1). It was 1 to 3 % while the ragged tile was zeroed last.
 template <class Base>
