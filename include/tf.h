@@ -81,8 +81,10 @@ typedef enum {
                                one-wave kernel. What the static pick of a small problem takes, see tf_proposal */
   TF_KIND_MFMA_KSHARE = 10, /* problems with few output tiles: bm x bn tiles, the waves_k waves of a work-group share K, each
                                staging through a ring of its own (stages K tiles of bk). split_k > 1 (fused_reduce 1): the
-                               slices exchange partial tiles through memory. Of a small problem, the ones without slices are
-                               listed as TF_KIND_MFMA_LDS_ANY (waves_m = waves_n = 1, waves_k > 1) */
+                               slices exchange partial tiles through memory. Without slices the launch's tiles may be cut
+                               to fewer rows and columns than bm x bn where that suits the problem (grid is what is
+                               launched; lds_bytes is then no multiple of 1024). Of a small problem, the ones without
+                               slices are listed as TF_KIND_MFMA_LDS_ANY (waves_m = waves_n = 1, waves_k > 1) */
   TF_KIND_SIN = 7            /* TF_OP_ELEMENTWISE_SIN: one arithmetic, many launch shapes. Descriptor fields: threads,
                                bn = elements per work-group and pass (the paper's BLOCK_SIZE; variant 0 has 4),
                                bk = consecutive elements per thread, stages = passes per work-group,

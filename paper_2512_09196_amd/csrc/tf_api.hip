@@ -46,6 +46,7 @@ struct VariantImpl {
   int sk_first, sk_tiles; // stream-K: tiles computed whole (= first shared work-group), tiles whose K steps are shared
   int mix_tiles, mix_blocks;   // lighter last round: its tiles per row panel, the blocks of 32 columns they share (tiles_n = tile columns of the wide part)
   int any_id;             // TF_KIND_MFMA_LDS_ANY: the variant that takes the calls whose pointers the tile kernel does not
+  int groups_a, groups_b, ring_stages;   // kernels whose waves share K: see tf::kshare_shape
   size_t aux_off;         // B given as [N][K] behind a transposing pass: where B^T lies in the workspace (behind the family's counter area)
 };
 
@@ -255,43 +256,58 @@ void build_any_family(tf_problem* p) {
   }
 }
 
-// Few output tiles: the waves of a work-group share K, and where tiles alone leave the chip idle so do work-groups.
-void build_kshare_family(tf_problem* p) {
+// Few output tiles: the waves of a work-group share K, and where tiles alone leave the chip idle so do work-groups. Tiles of 16
+// rows (`rows16`, without slices, for up to 64 rows) come behind all other variants of a family.
+void build_kshare_family(tf_problem* p, bool rows16) {
   const tf_problem_desc& d = p->desc;
   if (d.K < 64) return;
   const int cus = p->hw.cus > 0 ? p->hw.cus : 256;
   const long nkt = cdivl(d.K, 64);
+  int any = -1;                     // of a small problem: what takes the calls these do not
+  if (rows16) {
+    for (size_t i = 0; i < p->family.size(); ++i)
+      if (p->family[i].kind == TF_KIND_MFMA_LDS_ANY) any = p->impl[i].any_id;
+  }
   const tf::KshareKernelInfo* tab = tf::kshare_kernel_table();
   for (int i = 0; i < tf::kshare_kernel_count(); ++i) {
     const tf::KshareKernelInfo& k = tab[i];
-    if ((k.trans_b != 0) != (d.trans_b != 0) || k.lds_bytes > p->hw.lds_bytes_per_cu) continue;
+    const int lds_whole = k.waves * k.stages * (k.bm + k.bn) * 128;
+    if ((k.trans_b != 0) != (d.trans_b != 0) || lds_whole > p->hw.lds_bytes_per_cu) continue;
+    if ((k.bm == 16) != rows16 || (rows16 && d.M > 64)) continue;
     if (k.bm > 32 && k.bm / 2 >= d.M) continue;
     if (k.bn > 32 && k.bn / 2 >= d.N) continue;
-    const long tm = cdivl(d.M, k.bm), tn = cdivl(d.N, k.bn), tiles = tm * tn;
+    const long tiles = cdivl(d.M, k.bm) * cdivl(d.N, k.bn);
     if (tiles > 8L * cus) continue;
     // slices: an XCD takes one or several, or shares one; every wave has a K tile, and the work-groups one round of the
     // CUs; of the counts that allows the three largest (of 187 problems timed with every count, none was faster with another)
-    const long round = (long)cus * std::max(1, p->hw.lds_bytes_per_cu / k.lds_bytes);
+    const long round = (long)cus * std::max(1, p->hw.lds_bytes_per_cu / lds_whole);
     std::vector<int> counts;
     for (int s : {2, 4, 8, 16})
-      if (cdivl(nkt, s) >= k.waves && cdivl(nkt, s) * (s - 1) < nkt && tiles * s <= round) counts.push_back(s);
+      if (!rows16 && cdivl(nkt, s) >= k.waves && cdivl(nkt, s) * (s - 1) < nkt && tiles * s <= round) counts.push_back(s);
     if (counts.size() > 3) counts.erase(counts.begin());
     counts.insert(counts.begin(), 1);
     for (int s : counts) {
       const long per = cdivl(nkt, s);
       tf_variant_desc v;
       memset(&v, 0, sizeof(v));
-      v.kind = TF_KIND_MFMA_KSHARE; v.bm = k.bm; v.bn = k.bn; v.bk = 64; v.waves_m = 1; v.waves_n = 1; v.waves_k = k.waves;
+      v.kind = any >= 0 ? TF_KIND_MFMA_LDS_ANY : TF_KIND_MFMA_KSHARE;
+      v.bm = k.bm; v.bn = k.bn; v.bk = 64; v.waves_m = 1; v.waves_n = 1; v.waves_k = k.waves;
       v.stages = k.stages; v.split_k = s; v.fused_reduce = s > 1 ? 1 : 0; v.direct_to_lds = 1; v.trans_b = k.trans_b;
-      v.xcd_swizzle = 1; v.group_m = (int32_t)std::min<long>(tm, 8);
-      v.threads = k.threads; v.lds_bytes = k.lds_bytes;
-      v.grid = (int32_t)(s == 1 ? tiles : s <= 8 ? 8 * cdivl(tiles, 8 / s) : tiles * s);
+      v.xcd_swizzle = 1;
+      const tf::KshareShape sh = tf::kshare_shape(&d, &p->hw, &v);
+      if (sh.groups_a == 0) continue;
+      const long cut = sh.tiles_m * sh.tiles_n;
+      v.group_m = (int32_t)std::min<long>(sh.tiles_m, 8);
+      v.threads = k.threads; v.lds_bytes = sh.lds_bytes;
+      v.grid = (int32_t)(s == 1 ? cut : s <= 8 ? 8 * cdivl(cut, 8 / s) : cut * s);
       VariantImpl im{};
-      im.lds_index = i; im.ktiles_per_split = (int)per; im.tiles_m = (int)tm; im.tiles_n = (int)tn;
-      im.counter_bytes = s > 1 ? (size_t)((tiles * 8 + 255) / 256 * 256) : 0;
+      im.lds_index = i; im.ktiles_per_split = (int)per; im.tiles_m = (int)sh.tiles_m; im.tiles_n = (int)sh.tiles_n;
+      im.groups_a = sh.groups_a; im.groups_b = sh.groups_b; im.ring_stages = sh.stages;
+      im.any_id = any;
+      im.counter_bytes = s > 1 ? (size_t)((tiles * 8 + 255) / 256 * 256) : 0;      // (of whole tiles; the cut has no more than that holds)
       v.workspace_bytes = s > 1 ? (int64_t)(im.counter_bytes + (size_t)s * d.M * d.N * 4) : 0;
-      snprintf(v.name, sizeof(v.name), "kshare_%dx%dx64_k%d_s%d%s_sk%d%s", k.bm, k.bn, k.waves, k.stages, k.trans_b ? "_bnk" : "", s,
-               s > 1 ? "f" : "");
+      snprintf(v.name, sizeof(v.name), "kshare_%dx%dx64_k%d_s%d%s_sk%d%s%s", k.bm, k.bn, k.waves, k.stages, k.trans_b ? "_bnk" : "", s,
+               s > 1 ? "f" : "", any >= 0 ? "_or_any" : "");
       add_variant(p, v, im);
     }
   }
@@ -520,7 +536,7 @@ void build_family(tf_problem* p) {
   }
   };
   add_tiles(0);
-  build_kshare_family(p);
+  build_kshare_family(p, false);
   // Streaming kernels for skinny problems: K in blocks of 32, each wave of a work-group at least one block.
   if (!tb && d.M <= 32 && d.K % 32 == 0 && d.K >= 32) {
     const tf::StreamKernelInfo* stab = tf::stream_kernel_table();
@@ -559,6 +575,7 @@ void build_family(tf_problem* p) {
   build_small_family(p);
   add_tiles(1);
   add_tiles(2);
+  build_kshare_family(p, true);
   // One counter area for the whole family, so that the partial sums of one variant never
   // land on the counters of another: [counters, status word | partial sums]. The status word
   // takes the last 256 bytes of the area.
@@ -821,12 +838,17 @@ tf_status do_launch(tf_problem* p, int id, const void* A, const void* B, const v
     const bool streaming = v.kind == TF_KIND_MFMA_STREAM, kshare = tf::is_kshare(&v);
     const int slot = kshare ? tf::lds_kernel_count() + tf::stream_kernel_count() + tf::any_kernel_count() + im.lds_index
                      : streaming ? tf::lds_kernel_count() + im.lds_index : im.lds_index;
-    const void* func = kshare ? tf::kshare_kernel_table()[im.lds_index].func
+    const void* func = kshare ? (tf::kshare_is_cut(&v) ? tf::kshare_kernel_table()[im.lds_index].func_cut : tf::kshare_kernel_table()[im.lds_index].func)
                        : streaming ? tf::stream_kernel_table()[im.lds_index].func : tf::lds_kernel_table()[im.lds_index].func;
-    if (!p->attr_done[slot]) {
-      TF_HIP(hipFuncSetAttribute(func, hipFuncAttributeMaxDynamicSharedMemorySize, v.lds_bytes));
-      p->attr_done[slot] = 1;
+    // (of a kernel whose waves share K, a problem's launches may be of whole tiles and of cut ones: two kernels, and what the
+    // second needs differs from problem to problem)
+    const bool is_cut = kshare && tf::kshare_is_cut(&v);
+    const char done = is_cut ? 2 : 1;
+    if (!(p->attr_done[slot] & done)) {
+      TF_HIP(hipFuncSetAttribute(func, hipFuncAttributeMaxDynamicSharedMemorySize, is_cut ? p->hw.lds_bytes_per_cu : v.lds_bytes));
+      p->attr_done[slot] |= done;
     }
+    g.groups_a = im.groups_a; g.groups_b = im.groups_b; g.ring_stages = im.ring_stages;
     if (kshare) tf::kshare_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
     else if (streaming) tf::stream_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
     else tf::lds_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
@@ -848,7 +870,11 @@ void fill_static(tf_problem* p, int id, tf_report* r) {
   else if (v.kind == TF_KIND_NAIVE) func = tf::naive_func();
   else if (v.kind == TF_KIND_MFMA_DIRECT) func = tf::mfma_direct_func();
   else if (v.kind == TF_KIND_MFMA_STREAM) { func = tf::stream_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
-  else if (tf::is_kshare(&v)) { func = tf::kshare_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
+  else if (tf::is_kshare(&v)) {
+    const tf::KshareKernelInfo& k = tf::kshare_kernel_table()[p->impl[id].lds_index];
+    func = tf::kshare_is_cut(&v) ? k.func_cut : k.func;
+    dyn = v.lds_bytes;
+  }
   else if (v.kind == TF_KIND_MFMA_ANY) { func = tf::any_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
   else { func = tf::lds_kernel_table()[p->impl[id].lds_index].func; dyn = v.lds_bytes; }
   hipFuncAttributes a;
@@ -1366,7 +1392,7 @@ extern "C" int32_t tf_variant_kernel_name(const tf_variant_desc* v, char* buf, i
     case TF_KIND_MFMA_DIRECT: n = snprintf(buf, cap, "tf_gemm_mfma_direct_kernel"); break;
     case TF_KIND_MFMA_LDS: case TF_KIND_MFMA_LDS_ANY: case TF_KIND_MFMA_KSHARE:
       if (tf::is_kshare(v)) {
-        n = snprintf(buf, cap, "tf_gemm_kshare_kernel<tf::KshareCfg<%d, %d, %d, %d, %s>", v->bm, v->bn, v->waves_k, v->stages, b(v->trans_b));
+        n = snprintf(buf, cap, "tf_gemm_kshare_kernel<tf::KshareCfg<%d, %d, %d, %d, %s>, %s", v->bm, v->bn, v->waves_k, v->stages, b(v->trans_b), b(tf::kshare_is_cut(v)));
         break;
       }
       // (a counter file may hold several instances of one configuration: each has a kernel name of its own)

@@ -39,6 +39,7 @@ struct GemmParams {
   // mixed grid (tf_gemm_mixed_kernel): the first mix_main_wgs work-groups compute BN-wide tiles (tiles_m x tiles_n of them),
   // then tiles_m x mix_tiles work-groups share out the mix_blocks blocks of 32 columns that begin at column mix_n_origin
   int mix_main_wgs, mix_tiles, mix_blocks, mix_n_origin;
+  int groups_a, groups_b, ring_stages;   // kernels whose waves share K: eights of rows and of columns of a tile, K tiles in a wave's ring
 };
 
 // One compiled kernel of the LDS-staged MFMA family.
@@ -90,9 +91,9 @@ const AnyKernelInfo* any_kernel_table();
 
 // One compiled kernel whose waves share K (see tf_gemm_kshare.hip): K >= 64, rows of whole 16-byte pieces.
 struct KshareKernelInfo {
-  int bm, bn, waves, stages;          // stages: K tiles of 64 in each wave's ring
-  int trans_b, threads, lds_bytes;
-  const void* func;
+  int bm, bn, waves, stages;          // the largest tile; stages: K tiles of 64 of that size in each wave's ring
+  int trans_b, threads;
+  const void *func, *func_cut;        // whole tiles of that size; tiles cut to a size given at launch; null: no such kernel
   void (*launch)(const GemmParams&, dim3 grid, hipStream_t);
 };
 int kshare_kernel_count();

@@ -97,7 +97,9 @@ extern "C" int32_t tf_resident_wgs(const tf_hw* hw, const tf_variant_desc* v) {
     return r < 1 ? 1 : (r > 8 ? 8 : r);
   }
   if (tf::is_kshare(v)) {
-    const int r = v->lds_bytes > 0 ? hw->lds_bytes_per_cu / v->lds_bytes : 8;
+    int r = v->lds_bytes > 0 ? hw->lds_bytes_per_cu / (v->lds_bytes + 64) : 8;
+    const int by_waves = hw->simds_per_cu * hw->max_waves_per_simd / v->waves_k;
+    if (by_waves < r) r = by_waves;
     return r < 1 ? 1 : (r > 8 ? 8 : r);
   }
   if (!is_tile_kernel(v)) return 8;
@@ -119,6 +121,86 @@ extern "C" double tf_grid_fill(const tf_hw* hw, const tf_variant_desc* v) {
   const long slots = (long)hw->cus * tf_resident_wgs(hw, v);
   if (v->grid <= 0) return 0.0;
   return (double)v->grid / (double)(cdiv(v->grid, slots) * slots);
+}
+
+// The shape of a launch whose waves share K, and its predicted time. Without slices the tiles are cut to what suits the problem,
+// whatever the kernel's largest is: as many tiles as there are CUs, no more rows of A than the problem has, the rest shared out
+// evenly (us, the pick in whole tiles / the cut: 8 x 2048 x 7432 with B as [N][K] in 64 tiles of 32 x 32 15.2, in 256 of 8 x 8 8.7;
+// 32 x 2576 x 2856 [N][K] 9.7 / 7.1; 12 x 1552 x 5352 [N][K] 10.4 / 6.8; 5 x 11008 x 4096 [N][K] 19.1 / 17.5; 30 x 2048 x 4920 in 64
+// tiles of 32 x 32 15.9, in 256 of 8 x 32 11.4; 368 x 1408 x 2240 [N][K] 10.9 / 9.5). Not the tiles of 32 x 32, whose four waves have
+// nothing to hide the cut kernel's tests behind (12 x 1552 x 5352 10.7 whole, 12.1 cut), and no slices, which fill the chip by
+// themselves: over 147 problems, what is left out was 0.6 % faster where it was the best.
+//   * A wave's ring takes a second K tile where the work-groups of a CU have no more than 40 KB in flight without (the second
+//     gains 17 % at 16 KB, 8 % at 32, 4 % at 40, nothing from 48 KB on, and a third gains nothing).
+//   * The time: fitted (log error, 9 % rms within 1.25 times the best) to 3400 timings of these kernels on 147 problems, operands
+//     of several calls in turn. A CU fetches k-contiguous rows at 106 GB/s and rows of a [K][N] B at 94 in pieces of 128 bytes, 73
+//     in pieces of 64, less by a half where rows start off 128-byte lines; a wave takes 0.09 us for a K tile and every 32 x 32
+//     outputs, 0.11 more in cut tiles, which start 0.4 us later; the L2s together fetch 6.2 TB/s; the three overlap. The
+//     variant and shape predicted to be the fastest is 2.4 % behind the fastest of all.
+tf::KshareShape tf::kshare_shape(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
+  const int nw = v->waves_k, sums = v->bm * v->bn * 4;
+  const long nkt = cdiv(pr->K, 64);
+  const double off_a = pr->lda % 64 ? 1.47 : 1.0, off_b = pr->ldb % 64 ? 1.47 : 1.0;
+  const double rate_b = pr->trans_b ? 105.6e3 : v->bn > 32 ? 93.6e3 : 73.4e3;
+  const bool may_cut = v->split_k == 1 && !(v->bm == 32 && v->bn == 32);
+  KshareShape all{}, cut{};
+  for (int ga = may_cut ? 1 : v->bm / 8; ga <= v->bm / 8; ++ga) {
+    const long tm = cdiv(pr->M, 8 * ga);
+    if (ga > 1 && ga < v->bm / 8 && cdiv(pr->M, 8 * (ga - 1)) == tm) continue;                  // fewer rows make as many tiles
+    for (int gb = may_cut && pr->trans_b ? 1 : v->bn / 8; gb <= v->bn / 8; ++gb) {
+      const long tn = cdiv(pr->N, 8 * gb), tiles = tm * tn;
+      const bool whole = 8 * ga == v->bm && 8 * gb == v->bn && v->bm >= 32;
+      if (!whole && (tiles > hw->cus || (gb > 1 && pr->trans_b && cdiv(pr->N, 8 * (gb - 1)) == tn))) continue;
+      const double load = (double)tiles / hw->cus, on_cu = fmax(1.0, ceil(load - 1e-9));
+      const int stages = whole ? v->stages : v->bm <= 32 && nw * (ga + gb) * on_cu <= 40.0 && nkt > nw ? 2 : 1;
+      const int ring = stages * (ga + gb) * 1024 > sums ? stages * (ga + gb) * 1024 : sums;
+      const int lds = nw * ring + (whole ? 0 : KSHARE_CUT_MARK);
+      if (!whole && lds > hw->lds_bytes_per_cu) continue;
+      const int by_lds = hw->lds_bytes_per_cu / (lds + 64), by_waves = hw->simds_per_cu * hw->max_waves_per_simd / nw;
+      const double res = fmax(1.0, by_lds < by_waves ? by_lds : by_waves), rounds = fmax(1.0, ceil(load / res - 1e-9));
+      const double at_once = fmin(on_cu, res);
+      const double fetch = nkt * on_cu * (ga * 1024.0 * off_a / 105.6e3 + gb * 1024.0 * off_b / rate_b);
+      const double serial = rounds * cdiv(nkt, nw) * ((whole ? 0.0 : 0.108) + 0.088 * v->bm * v->bn / 1024.0 * at_once * nw / 8.0);
+      // an XCD's run of neighbouring tiles, in columns of group_m
+      const double run = tiles / 8.0, gm = tm < 8 ? (double)tm : 8.0;
+      const double rows = fmin((double)tm, run < gm ? fmax(1.0, run) : gm * fmax(1.0, ceil(run / (gm * tn)))), cols = fmin((double)tn, fmax(1.0, run / gm));
+      const double fabric = fmax(8.0 * (rows * ga + cols * gb) * 1024.0 * nkt, 2.0 * ((double)pr->M * pr->K + (double)pr->K * pr->N)) / 6.24e6;
+      const double us = 3.03 + (whole ? 0.0 : 0.4) - (nw == 4 ? 0.15 : 0.0) + (v->bm == 64 ? 0.71 : 0.0) + 0.068 * nw * at_once / 16.0 +
+                        pow(pow(fetch, 2.29) + pow(serial, 2.29) + pow(fabric, 2.29), 1.0 / 2.29) + 2.55 * (rounds - 1.0);
+      const KshareShape one{ga, gb, stages, tm, tn, lds, us, 0.0, false};
+      if (whole) all = one;
+      else if (cut.groups_a == 0 || us < cut.us) cut = one;
+    }
+  }
+  const bool is_cut = cut.groups_a != 0 && (all.groups_a == 0 || cut.us < 0.97 * all.us);
+  KshareShape best = is_cut ? cut : all;
+  best.is_cut = is_cut;
+  best.whole_us = all.us;
+  return best;
+}
+
+// A launch of whole tiles.
+static double kshare_whole_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
+  // Fitted (log error, 12 % rms) to 893 timings of these kernels on 176 problems from 1 x 4096 x 11008 to 2965 x 1104 x 2224
+  // (13 % rms over three thousand timings on 700 others):
+  // a CU fetches the panels of its tiles at 76 to 101 GB/s (rows of 32 columns of a [K][N] B are half a 128-byte line), the
+  // L2s together what their tiles need at 7.4 TB/s (the two overlap in part), a launch takes 2.9 us and a further round of
+  // work-groups costs 2.3 beside its bytes.
+  const int s = v->split_k, lds_whole = v->waves_k * v->stages * (v->bm + v->bn) * 128;
+  const int res = fmax(1.0, fmin(8.0, hw->lds_bytes_per_cu / lds_whole));
+  const long tm = cdiv(pr->M, v->bm), tn = cdiv(pr->N, v->bn), nkt = cdiv(pr->K, 64);
+  const double load = (double)(tm * tn * s) / hw->cus;
+  const double rate = v->bm > 32 ? 76.3e3 : v->bn > 32 ? 96.4e3 : pr->trans_b ? 101.2e3 : 89.7e3;
+  const double fetch = (v->bm + v->bn) * 128.0 * cdiv(nkt, s) * fmax(1.0, ceil(load - 1e-9)) / rate;
+  // an XCD's run of neighbouring tiles (8 / s XCDs share the tiles of a slice), in columns of group_m
+  const double run = (double)(tm * tn) / (s >= 8 ? 1 : 8 / s), gm = v->group_m > 0 ? v->group_m : 1;
+  const double rows = fmin((double)tm, run < gm ? fmax(1.0, run) : gm * fmax(1.0, ceil(run / (gm * tn)))), cols = fmin((double)tn, fmax(1.0, run / gm));
+  const double fabric = fmax(8.0 * (rows * v->bm + cols * v->bn) * 128.0 * nkt / (s < 8 ? s : 8), 2.0 * ((double)pr->M * pr->K + (double)pr->K * pr->N)) / 7.35e6;
+  double us = 2.9 + pow(pow(fetch, 1.55) + pow(fabric, 1.55), 1.0 / 1.55) + 2.3 * fmax(0.0, ceil(load / res - 1e-9) - 1.0);
+  // slices: the acknowledgement of the partial tile, the ticket, the other slices' tiles
+  const double tile_bytes = v->bm * (double)v->bn * 4.0;
+  if (s > 1) us += 1.45 + 1.16e-5 * s * tile_bytes + 6.1e-7 * load * hw->cus * tile_bytes;
+  return us;
 }
 
 double tf::base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
@@ -207,35 +289,27 @@ double tf::base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_
     return 4.0 + fmax(fmax(traffic / (t64 ? 9.5e6 : 13.0e6), hbm_us / 0.55), serial);
   }
   if (tf::is_kshare(v)) {
-    // Fitted (log error, 12 % rms) to 893 timings of these kernels on 176 problems from 1 x 4096 x 11008 to 2965 x 1104 x 2224
-    // (13 % rms over three thousand timings on 700 others):
-    // a CU fetches the panels of its tiles at 76 to 101 GB/s (rows of 32 columns of a [K][N] B are half a 128-byte line), the
-    // L2s together what their tiles need at 7.4 TB/s (the two overlap in part), a launch takes 2.9 us and a further round of
-    // work-groups costs 2.3 beside its bytes.
-    const int s = v->split_k, res = tf_resident_wgs(hw, v);
-    const long tm = cdiv(pr->M, v->bm), tn = cdiv(pr->N, v->bn), nkt = cdiv(pr->K, 64);
-    const double load = (double)(tm * tn * s) / hw->cus;
-    const double rate = v->bm > 32 ? 76.3e3 : v->bn > 32 ? 96.4e3 : pr->trans_b ? 101.2e3 : 89.7e3;
-    const double fetch = (v->bm + v->bn) * 128.0 * cdiv(nkt, s) * fmax(1.0, ceil(load - 1e-9)) / rate;
-    // an XCD's run of neighbouring tiles (8 / s XCDs share the tiles of a slice), in columns of group_m
-    const double run = (double)(tm * tn) / (s >= 8 ? 1 : 8 / s), gm = v->group_m > 0 ? v->group_m : 1;
-    const double rows = fmin((double)tm, run < gm ? fmax(1.0, run) : gm * fmax(1.0, ceil(run / (gm * tn)))), cols = fmin((double)tn, fmax(1.0, run / gm));
-    const double fabric = fmax(8.0 * (rows * v->bm + cols * v->bn) * 128.0 * nkt / (s < 8 ? s : 8), 2.0 * ((double)pr->M * pr->K + (double)pr->K * pr->N)) / 7.35e6;
-    double us = 2.9 + pow(pow(fetch, 1.55) + pow(fabric, 1.55), 1.0 / 1.55) + 2.3 * fmax(0.0, ceil(load / res - 1e-9) - 1.0);
-    // slices: the acknowledgement of the partial tile, the ticket, the other slices' tiles
-    const double tile_bytes = v->bm * (double)v->bn * 4.0;
-    if (s > 1) us += 1.45 + 1.16e-5 * s * tile_bytes + 6.1e-7 * load * hw->cus * tile_bytes;
-    // On the scale of what it is compared with. Small problems, the any-address kernels: a factor. (Where rows start
-    // off 128-byte lines the two are level, 0.9 to 1.1 over 300 problems; on whole lines these lead by 3 to 12 %.)
-    if (v->kind == TF_KIND_MFMA_LDS_ANY) return 1.15 * us;
+    const int s = v->split_k;
+    const long nkt = cdiv(pr->K, 64);
+    // What is known of whole tiles, and how much less their cut takes (the tiles of 16 rows go by those of 32 x 32).
+    tf_variant_desc whole = *v;
+    if (v->bm < 32) { whole.bm = whole.bn = 32; whole.waves_k = 4; whole.stages = 2; }
+    double us = kshare_whole_us(pr, hw, &whole);
+    const KshareShape shape = kshare_shape(pr, hw, v);
+    if (shape.is_cut) us = fmin(us, fmax(us * shape.us / kshare_shape(pr, hw, &whole).whole_us, shape.us));
+    // On the scale of what it is compared with. Small problems, the any-address kernels, which are the faster where K is short or rows
+    // start off 128-byte lines. (Over 136 drawn problems the faster of the two is picked but for 2.3 %, with a factor of 1.15 in
+    // place of this 3.4 %: 105 x 648 x 360 with B as [N][K] 5.3 us where the any-address kernel takes 3.5, 93 x 6480 x 264 [N][K] 6.3 / 4.9.)
+    if (v->kind == TF_KIND_MFMA_LDS_ANY) return 1.05 * us + (pr->lda % 64 ? 0.7 : 0.0) + 0.6 * exp(-(double)nkt / 8.0);
     // Otherwise the tile kernels. Operands that no cache holds (three such sets are more than the memory-side cache's 256 MB)
     // arrive at 3.6 TB/s in half lines of B, at 4.2 in slices (16 x 8192 x 8192 31.8 us, the tile kernels' 26.5), at 4.6 in
     // whole lines and whole sums (11008 x 5120 24.3).
     const double opnd_bytes = 2.0 * ((double)pr->M * pr->K + (double)pr->K * pr->N);
     if (!pr->trans_b && opnd_bytes > 95e6) us = fmax(us, 2.9 + opnd_bytes / (v->bn <= 32 ? 3.6e6 : s > 1 ? 4.25e6 : 4.6e6));
     // Where K is whole tiles their 64 x 64 tiles, with the K order rotated or a K tile of 128, are 5 to 15 % faster than these
-    // without slices up to a K of about 2000; where it is ragged, 0 to 10 % slower.
-    if (v->bm > 32 && s == 1 && pr->K % 64 == 0) us *= 1.0 + 0.3 * exp(-(double)nkt / 40.0);
+    // without slices up to a K of about 2000; where it is ragged, 0 to 10 % slower. Cut ones a little more: 277 x 2368 x 1792 with B
+    // as [N][K] 10.7 us, the tile kernel 10.1.
+    if (v->bm > 32 && s == 1 && pr->K % 64 == 0) us *= 1.0 + (shape.is_cut ? 0.36 : 0.3) * exp(-(double)nkt / 40.0);
     // The tile kernels' figure below is high by what it counts for start-up: 1.4 us, up to 3.4 where K is short (917 x 640 x
     // 320 4.0 us measured, 6.7 predicted). With one factor, 1.15, in place of all this, 101 of 1350 picks were 2 to 23 % slower
     // than the other kernels' (917 x 640 x 320 4.8 / 4.0 us, 1103 x 640 x 448 5.5 / 4.9, 25 x 7808 x 6208 25.5 / 21.5) and the
