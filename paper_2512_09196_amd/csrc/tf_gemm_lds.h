@@ -619,12 +619,11 @@ __device__ __forceinline__ void epilogue_staged(const typename C::Acc (&acc)[C::
       const int g = rs >> 5;                               // wave row and k group the staged row came from
       const int m = m0 + C::row_off(RB * i, g / C::WK) + (g % C::WK) * (C::WTM / 2) + (rs & 31);
       const u32x4 v = *(const u32x4*)(smem + rs * ROWB + cc * 16);
-      if (cc * 16 < ncols * ESZ) {
-        // the output is not read again by this launch: non-temporal; a partial tile is read back at once by the
-        // reduction: ordinary stores, so that it may stay in the caches on the way
-        if constexpr (PARTIAL) *(u32x4*)(dst + ((size_t)m * ld + n0) * ESZ + cc * 16) = v;
-        else __builtin_nontemporal_store(v, (u32x4*)(dst + ((size_t)m * ld + n0) * ESZ + cc * 16));
-      }
+      // not read again by this launch: non-temporal. A partial tile too: ordinary stores leave 4 MB of it in this XCD's L2 until the
+      // launch ends, and the lines that the reducing kernel of the call before has left in other L2s make them slower still (one
+      // workspace for call after call, us, with ordinary loads there too / both non-temporal: 512 x 768 x 8192 in eight slices
+      // 19.7 / 15.2, 288 x 1152 x 7360 18.9 / 15.0, 1912 x 488 x 3976 in four 20.0 / 18.3, 1024 x 1024 x 16384 42.9 / 40.0)
+      if (cc * 16 < ncols * ESZ) __builtin_nontemporal_store(v, (u32x4*)(dst + ((size_t)m * ld + n0) * ESZ + cc * 16));
     }
   }
 }

@@ -203,39 +203,52 @@ __global__ void tf_fill_u32_kernel(unsigned* p, size_t n, unsigned v) {
 }
 
 // Second kernel of the two-kernel split-K: Y = epilogue(sum_s ws[s] + bias), slices summed in
-// slice order. One thread per four consecutive n (N is a multiple of 8 for every tile kernel).
+// slice order. One thread per four consecutive n (N is a multiple of 8 for every tile kernel; the slices are tiles of one or two
+// rounds of the CUs, so the quads fit 32 bits). Bound by memory: all slices of a thread's quad are asked for at once, with
+// non-temporal loads, or the lines would stay in this XCD's L2 and slow down the next call's stores to them. (us a call, one 64-bit
+// division per thread, a loop over the slices and ordinary loads / this, the partial tiles written with ordinary stores: 478 x 768 x 7872
+// in eight slices 19.9 / 17.2 on one workspace, 17.2 / 15.7 on two in turn; 1024 x 1024 x 16384 42.9 / 41.0; 2048^3 in two 36.0 /
+// 34.2. Non-temporal stores there: 15.2, 15.2, 40.0, 34.6.)
+template <int S>
 __global__ void __launch_bounds__(256) tf_splitk_reduce_kernel(const GemmParams p) {
-  const size_t quads_per_row = (size_t)p.N / 4;
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (size_t)p.M * quads_per_row) return;
-  const size_t m = i / quads_per_row;
-  const int n = (int)(i % quads_per_row) * 4;
+  const unsigned quads_per_row = (unsigned)p.N / 4;
+  const unsigned i = blockIdx.x * 256u + threadIdx.x;
+  if (i >= (unsigned)p.M * quads_per_row) return;
+  const unsigned m = i / quads_per_row;
+  const int n = (int)(i - m * quads_per_row) * 4;
   const size_t slice = (size_t)p.M * p.N;
-  const float* src = p.ws + m * p.N + n;
-  f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
-  // the partial sums are read once and the output written once: neither needs to stay in the caches
-  for (int s = 0; s < p.split_k; ++s) sum += *(const f32x4*)(src + (size_t)s * slice);
+  const float* src = p.ws + (size_t)i * 4;
+  f32x4 v[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) v[s] = __builtin_nontemporal_load((const f32x4*)(src + (size_t)s * slice));
   const u32x2 braw = *(const u32x2*)(p.bias + n);
+  f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int s = 0; s < S; ++s) sum += v[s];
   const float z0 = sum[0] + __builtin_bit_cast(float, braw[0] << 16);
   const float z1 = sum[1] + __builtin_bit_cast(float, braw[0] & 0xffff0000u);
   const float z2 = sum[2] + __builtin_bit_cast(float, braw[1] << 16);
   const float z3 = sum[3] + __builtin_bit_cast(float, braw[1] & 0xffff0000u);
   if (p.epi == TF_EPI_NONE_F32) {
-    const f32x4 v = {z0, z1, z2, z3};
-    __builtin_nontemporal_store(v, (f32x4*)((float*)p.Y + m * p.ldy + n));
+    const f32x4 o = {z0, z1, z2, z3};
+    __builtin_nontemporal_store(o, (f32x4*)((float*)p.Y + (size_t)m * p.ldy + n));
   } else {
     u32x2 o;
     o[0] = pack_bf16x2(activate(z0, p.epi), activate(z1, p.epi));
     o[1] = pack_bf16x2(activate(z2, p.epi), activate(z3, p.epi));
-    __builtin_nontemporal_store(o, (u32x2*)((uint16_t*)p.Y + m * p.ldy + n));
+    __builtin_nontemporal_store(o, (u32x2*)((uint16_t*)p.Y + (size_t)m * p.ldy + n));
   }
 }
 
 void launch_splitk_reduce(const GemmParams& p, hipStream_t s) {
-  const size_t quads = (size_t)p.M * (p.N / 4);
-  hipLaunchKernelGGL(tf_splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, p);
+  const dim3 grid((unsigned)(((size_t)p.M * (p.N / 4) + 255) / 256));
+  if (p.split_k == 2) hipLaunchKernelGGL(tf_splitk_reduce_kernel<2>, grid, dim3(256), 0, s, p);
+  else if (p.split_k == 4) hipLaunchKernelGGL(tf_splitk_reduce_kernel<4>, grid, dim3(256), 0, s, p);
+  else if (p.split_k == 8) hipLaunchKernelGGL(tf_splitk_reduce_kernel<8>, grid, dim3(256), 0, s, p);
+  else if (p.split_k == 16) hipLaunchKernelGGL(tf_splitk_reduce_kernel<16>, grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL(tf_splitk_reduce_kernel<32>, grid, dim3(256), 0, s, p);
 }
-const void* splitk_reduce_func() { return (const void*)tf_splitk_reduce_kernel; }
+const void* splitk_reduce_func() { return (const void*)tf_splitk_reduce_kernel<2>; }
 
 void launch_naive(const GemmParams& p, hipStream_t s) {
   dim3 grid((p.N + 63) / 64, (p.M + 3) / 4);
