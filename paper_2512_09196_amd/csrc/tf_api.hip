@@ -257,7 +257,10 @@ void build_any_family(tf_problem* p) {
 }
 
 // Few output tiles: the waves of a work-group share K, and where tiles alone leave the chip idle so do work-groups. Tiles of 16
-// rows (`rows16`, without slices, for up to 64 rows) come behind all other variants of a family.
+// rows (`rows16`, without slices) come behind all other variants of a family. They are for up to 64 rows, and for small problems
+// of more, which have no slices to pick: sixteen waves to a long sum (us, four
+// waves / these: 79 x 256 x 11456 with B as [N][K] 17.4 / 9.4, 171 x 272 x 4640 [N][K] 11.4 / 7.3, 79 x 320 x 10272 24.6 / 17.5,
+// 75 x 384 x 8768 19.0 / 15.1; 0.87 of the time over 60 problems, the worst 71 x 896 x 3904 [N][K] 7.7 / 8.2).
 void build_kshare_family(tf_problem* p, bool rows16) {
   const tf_problem_desc& d = p->desc;
   if (d.K < 64) return;
@@ -267,13 +270,14 @@ void build_kshare_family(tf_problem* p, bool rows16) {
   if (rows16) {
     for (size_t i = 0; i < p->family.size(); ++i)
       if (p->family[i].kind == TF_KIND_MFMA_LDS_ANY) any = p->impl[i].any_id;
+    if (d.M > 64 && (any < 0 || p->family.back().direct_to_lds == 3)) return;      // (rows in whole lines: these end their family)
   }
   const tf::KshareKernelInfo* tab = tf::kshare_kernel_table();
   for (int i = 0; i < tf::kshare_kernel_count(); ++i) {
     const tf::KshareKernelInfo& k = tab[i];
     const int lds_whole = k.waves * k.stages * (k.bm + k.bn) * 128;
     if ((k.trans_b != 0) != (d.trans_b != 0) || lds_whole > p->hw.lds_bytes_per_cu) continue;
-    if ((k.bm == 16) != rows16 || (rows16 && d.M > 64)) continue;
+    if ((k.bm == 16) != rows16) continue;
     if (k.bm > 32 && k.bm / 2 >= d.M) continue;
     if (k.bn > 32 && k.bn / 2 >= d.N) continue;
     const long tiles = cdivl(d.M, k.bm) * cdivl(d.N, k.bn);

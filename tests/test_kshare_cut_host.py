@@ -8,7 +8,7 @@ WHOLE = {b"kshare_32x32x64_k4_s2": 65536, b"kshare_32x64x64_k8_s1": 98304, b"ksh
 
 def test_families_with_cut_tiles():
     rng = random.Random(2)
-    seen = set()
+    seen, rows_over_64 = set(), False
     for _ in range(300):
         M, N, K, nk = rng.choice([rng.randint(1, 64), rng.randint(65, 900)]), 8 * rng.randint(1, 900), 8 * rng.randint(8, 900), rng.randint(0, 1)
         with tf.Problem(M, N, K, trans_b=nk) as p:
@@ -25,8 +25,10 @@ def test_families_with_cut_tiles():
                 assert v.split_k > 1 or v.grid == -(-M // v.bm) * -(-N // v.bn)
                 assert tf.kernel_substr(v).endswith("false")
         rows16 = [i for i, v in enumerate(fam) if v.name.startswith(b"kshare_16x")]
-        assert rows16 == list(range(len(fam) - len(rows16), len(fam))) and (M <= 64 or not rows16)     # behind all others
+        assert rows16 == list(range(len(fam) - len(rows16), len(fam)))     # behind all others
         small = any(v.kind == tf.TF_KIND_MFMA_LDS_ANY for v in fam)
+        assert M <= 64 or not rows16 or small
+        rows_over_64 |= M > 64 and bool(rows16)
         assert all((fam[i].kind == tf.TF_KIND_MFMA_LDS_ANY) == small for i in rows16)
     assert {(k, c, s) for k, c, s in seen if k in WHOLE} >= {(k, False, True) for k in WHOLE} | {(k, True, False) for k in list(WHOLE)[1:]}
-    assert (b"kshare_32x32x64_k4_s2", True, False) not in seen
+    assert (b"kshare_32x32x64_k4_s2", True, False) not in seen and rows_over_64
