@@ -33,6 +33,7 @@ struct AnyCfg {
   static constexpr int WAVE_BYTES = 2 * OP_BYTES;       // a wave's LDS: its A and B tile, later its partial sums
   static_assert(TILE * TILE * 4 <= WAVE_BYTES, "the partial sums fit where the tiles were");
   static constexpr int LDS_BYTES = NW * WAVE_BYTES;
+  static constexpr int CPR = TILE / 4;                  // 16-byte chunks per row of the partial sums
   static constexpr int B_ROW_BYTES = TILE * 2, B_PIECES = B_ROW_BYTES / 64, B_CHUNKS = B_ROW_BYTES / 16;   // [k][n] tile
 };
 
@@ -151,6 +152,19 @@ __global__ void __launch_bounds__(C::THREADS, C::T == 1 ? 2 : 1) tf_gemm_any_ker
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   };
 
+  // This thread's bias values: all its chunks of the tile lie in the same four columns. Asked for with the first K tiles, so that the
+  // epilogue waits for no memory; with B as [N][K] behind the main loop, where registers are free (before it they cost a fourth
+  // wave per SIMD: 719 x 865 x 81 3.8 / 4.0 us). Asked for chunk by chunk behind the barrier / so (us): 509 x 1021 x 763 with fp32 result
+  // 7.04 / 6.95, 170 x 455 x 493 4.65 / 4.37, 789 x 145 x 431 4.53 / 4.20; [N][K] 45 x 1879 x 355 4.33 / 4.12. (A third K tile in
+  // flight: 4 to 11 % slower where K has four to a wave.)
+  static_assert(C::THREADS % C::CPR == 0, "one column group per thread");
+  uint16_t b16[4];
+  auto load_bias = [&]() {
+    const int n = n0 + 4 * (tid % C::CPR);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b16[e] = p.bias[n + e < p.N ? n + e : p.N - 1];
+  };
+  if constexpr (!C::TB) load_bias();
   {
     Regs r0, r1;
     if (wave < nkt) load(r0, wave);
@@ -161,9 +175,11 @@ __global__ void __launch_bounds__(C::THREADS, C::T == 1 ? 2 : 1) tf_gemm_any_ker
     }
   }
 
+  if constexpr (C::TB) load_bias();
+
   // ---- partial sums to this wave's LDS: [row][4-column chunk ^ swizzle], 16 bytes each. Lane l, register e of a
   // 32 x 32 block: m = l & 31, n = 8 (e / 4) + 4 (l / 32) + e % 4
-  constexpr int CPR = C::TILE / 4;                       // 16-byte chunks per row of the tile
+  constexpr int CPR = C::CPR;
 #pragma unroll
   for (int i = 0; i < C::T; ++i) {
     const int m = 32 * i + fr;
@@ -178,6 +194,9 @@ __global__ void __launch_bounds__(C::THREADS, C::T == 1 ? 2 : 1) tf_gemm_any_ker
   }
   __syncthreads();
   const int n_end = n_own + C::TILE < p.N ? n_own + C::TILE : p.N;
+  float b[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) b[e] = bf16_bits_to_f32(b16[e]);
 #pragma unroll
   for (int x = tid; x < C::TILE * CPR; x += C::THREADS) {
     const int r = x / CPR, c = x % CPR;
@@ -189,9 +208,6 @@ __global__ void __launch_bounds__(C::THREADS, C::T == 1 ? 2 : 1) tf_gemm_any_ker
     if (m >= p.M) continue;
     const size_t at = (size_t)m * p.ldy + n;
     const bool whole = n >= n_own && n + 4 <= n_end;
-    float b[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) b[e] = bf16_bits_to_f32(p.bias[n + e < p.N ? n + e : p.N - 1]);
     if (p.epi == TF_EPI_NONE_F32) {
       float* y = (float*)p.Y + at;
       if (whole) {
