@@ -3,8 +3,10 @@
 //  * naive: the baseline kernel K of the variant loop. One thread per output element, a
 //    scalar fp32 FMA loop over K, no MFMA, no LDS; accepts any shape, stride and alignment.
 //  * mfma_direct: one wave per 32x32 output tile; MFMA operands are gathered straight from
-//    memory, element by element, with guards, so it also accepts any shape. It exists to pin
-//    the MFMA operand and accumulator lane layouts with nothing else in the way.
+//    memory, element by element, so it also accepts any shape. It pins the MFMA operand and accumulator
+//    lane layouts with nothing else in the way, and is the quickest where K is below 64 and rows are odd.
+#include <type_traits>
+
 #include "tf_device.h"
 
 namespace tf {
@@ -31,33 +33,63 @@ __global__ void __launch_bounds__(64) tf_gemm_mfma_direct_kernel(const GemmParam
   const int r = lane & 31, g = lane >> 5;
   // v_mfma_f32_32x32x16_bf16 operand layout: lane l supplies row (A) / column (B) l % 32
   // and the eight k values 8 (l / 32) .. 8 (l / 32) + 7 of the 16-wide k step.
-  const int am = m0 + r, bn = n0 + r;
+  // Bound by trips to memory: the operands of 64 of K are all asked for before the first is used (element by element behind a
+  // guard each, a step of 16 was a trip of its own, and the activations a chain of sixteen; us, so / now: 365 x 87 x 53 with fp32 result 6.2 / 4.2,
+  // 36 x 253 x 59 6.9 / 4.4, 491 x 379 x 33 with GELU 6.1 / 4.6, 202 x 43 x 51 with B as [N][K] and GELU 6.5 / 5.0).
+  // Rows and k outside the operands repeat their last ones; what such rows give is not stored, such k are zeroed in both operands.
+  const int am = m0 + r < p.M ? m0 + r : p.M - 1, bn = n0 + r < p.N ? n0 + r : p.N - 1;
+  const uint16_t* const a_row = p.A + (size_t)am * p.lda;
+  const uint16_t* const b_col = p.B + (p.trans_b ? (size_t)bn * p.ldb : (size_t)bn);
+  const size_t b_step = p.trans_b ? 1 : (size_t)p.ldb;
+  const float bias = bf16_bits_to_f32(p.bias[bn]);
   f32x16 acc;
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-  for (int k0 = 0; k0 < p.K; k0 += 16) {
-    s16x8 av, bv;
+  for (int k0 = 0; k0 < p.K; k0 += 64) {
+    uint16_t a[4][8], b[4][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = k0 + 8 * g + e;
-      const bool kin = k < p.K;
-      av[e] = (kin && am < p.M) ? (short)p.A[(size_t)am * p.lda + k] : (short)0;
-      bv[e] = (kin && bn < p.N) ? (short)p.B[p.trans_b ? (size_t)bn * p.ldb + k : (size_t)k * p.ldb + bn] : (short)0;
-    }
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
+    for (int s = 0; s < 4; ++s)
+      if (k0 + 16 * s < p.K) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int ke = k0 + 16 * s + 8 * g + e, k = ke < p.K ? ke : p.K - 1;
+          a[s][e] = a_row[k];
+          b[s][e] = b_col[(size_t)k * b_step];
+        }
+      }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (k0 + 16 * s < p.K) {
+        s16x8 av, bv;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const bool kin = k0 + 16 * s + 8 * g + e < p.K;
+          av[e] = kin ? (short)a[s][e] : (short)0;
+          bv[e] = kin ? (short)b[s][e] : (short)0;
+        }
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
+      }
   }
   // accumulator layout: register i of lane l is row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32
   const int n = n0 + r;
   if (n >= p.N) return;
-  const float bias = bf16_bits_to_f32(p.bias[n]);
+  auto finish = [&](auto epi) {            // (one branch on the epilogue, so that the sixteen activations overlap)
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int m = m0 + 8 * (i >> 2) + 4 * g + (i & 3);
-    if (m < p.M) {
-      const float z = acc[i] + bias;
-      if (p.epi == TF_EPI_NONE_F32) ((float*)p.Y)[(size_t)m * p.ldy + n] = z;
-      else ((uint16_t*)p.Y)[(size_t)m * p.ldy + n] = f32_to_bf16_bits(activate(z, p.epi));
+    for (int i = 0; i < 16; ++i) acc[i] = activate<decltype(epi)::value>(acc[i] + bias);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int m = m0 + 8 * (i >> 2) + 4 * g + (i & 3);
+      if (m < p.M) {
+        if (decltype(epi)::value == TF_EPI_NONE_F32) ((float*)p.Y)[(size_t)m * p.ldy + n] = acc[i];
+        else ((uint16_t*)p.Y)[(size_t)m * p.ldy + n] = f32_to_bf16_bits(acc[i]);
+      }
     }
+  };
+  switch (p.epi) {
+    case TF_EPI_NONE_F32: finish(std::integral_constant<int, TF_EPI_NONE_F32>{}); break;
+    case TF_EPI_BIAS_GELU_ERF: finish(std::integral_constant<int, TF_EPI_BIAS_GELU_ERF>{}); break;
+    case TF_EPI_BIAS_GELU_TANH: finish(std::integral_constant<int, TF_EPI_BIAS_GELU_TANH>{}); break;
+    default: finish(std::integral_constant<int, TF_EPI_BIAS>{}); break;
   }
 }
 
