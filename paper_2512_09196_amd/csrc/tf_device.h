@@ -82,6 +82,13 @@ __device__ __forceinline__ float activate(float z, int epi) {
   if (epi == TF_EPI_BIAS_GELU_TANH) return gelu_tanh(z);
   return z;
 }
+// One branch for four values, so that their chains overlap: behind a branch each they ran one after another (449 x 328 x 1568 with
+// tanh-GELU 7.03 / 6.81 us, 428 x 416 x 600 4.34 / 4.13; 0.99 of the time over 100 small products with a GELU).
+__device__ __forceinline__ f32x4 activate(f32x4 z, int epi) {
+  if (epi == TF_EPI_BIAS_GELU_ERF) z = f32x4{gelu_erf(z[0]), gelu_erf(z[1]), gelu_erf(z[2]), gelu_erf(z[3])};
+  else if (epi == TF_EPI_BIAS_GELU_TANH) z = f32x4{gelu_tanh(z[0]), gelu_tanh(z[1]), gelu_tanh(z[2]), gelu_tanh(z[3])};
+  return z;
+}
 
 // Work-group id -> position in the tile order.
 //  * The hardware deals consecutive work-group ids round-robin over the 8 XCDs, each with

@@ -221,8 +221,9 @@ __global__ void __launch_bounds__(C::THREADS, C::T == 1 ? 2 : 1) tf_gemm_any_ker
     } else {
       uint16_t* y = (uint16_t*)p.Y + at;
       u32x2 o;
-      o[0] = pack_bf16x2(activate(z[0] + b[0], p.epi), activate(z[1] + b[1], p.epi));
-      o[1] = pack_bf16x2(activate(z[2] + b[2], p.epi), activate(z[3] + b[3], p.epi));
+      const f32x4 v = activate(f32x4{z[0] + b[0], z[1] + b[1], z[2] + b[2], z[3] + b[3]}, p.epi);
+      o[0] = pack_bf16x2(v[0], v[1]);
+      o[1] = pack_bf16x2(v[2], v[3]);
       if (whole) {
         *(u32x2_any*)y = o;
       } else {

@@ -266,8 +266,9 @@ __global__ void __launch_bounds__(256) tf_splitk_reduce_kernel(const GemmParams 
     __builtin_nontemporal_store(o, (f32x4*)((float*)p.Y + (size_t)m * p.ldy + n));
   } else {
     u32x2 o;
-    o[0] = pack_bf16x2(activate(z0, p.epi), activate(z1, p.epi));
-    o[1] = pack_bf16x2(activate(z2, p.epi), activate(z3, p.epi));
+    const f32x4 a = activate(f32x4{z0, z1, z2, z3}, p.epi);
+    o[0] = pack_bf16x2(a[0], a[1]);
+    o[1] = pack_bf16x2(a[2], a[3]);
     __builtin_nontemporal_store(o, (u32x2*)((uint16_t*)p.Y + (size_t)m * p.ldy + n));
   }
 }
