@@ -49,15 +49,12 @@ struct KshareCfg : LdsCfg<(BM_ < 32 ? 32 : BM_), BN_, 64, 1, 1, S_, true, false,
   static_assert(CHUNKS % WG_THREADS == 0 || CHUNKS < WG_THREADS, "the pieces divide over the threads");
 };
 
-// Partial tiles, written and read by work-groups of different XCDs: past this XCD's L2, and not kept there, or the next call's stores to
-// the same workspace are slowed down by the lines (us, two 8-byte atomic loads and stores without `nt` / 16 bytes of either with it:
-// 371 x 312 x 12632 in eight slices of 64 x 64 tiles 17.0 / 15.9, 120 x 576 x 11648 with B as [N][K] 13.4 / 12.4, 264 x 560 x 4088 in four
-// 11.8 / 11.0; 0.94 of the time with eight slices of 64 x 64, 0.98 to 1.00 with others, over 91 launches). `at`: bytes into the slice, whose tiles fit 32 bits by far.
-__device__ __forceinline__ f32x4 load_device(__amdgpu_buffer_rsrc_t slice, unsigned at) {
-  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(slice, at, 0, 16 | 2));    // sc1 nt
-}
-__device__ __forceinline__ void store_device(float* ptr, const f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1 nt" :: "v"(ptr), "v"(v) : "memory");
+// 16 bytes past this XCD's L2, written by work-groups of other XCDs
+__device__ __forceinline__ f32x4 load_device(const float* src) {
+  typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+  const u64x2 w = {__hip_atomic_load((unsigned long long*)src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                   __hip_atomic_load((unsigned long long*)src + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
+  return __builtin_bit_cast(f32x4, w);
 }
 
 template <class C, bool CUT>
@@ -238,7 +235,7 @@ __global__ void __launch_bounds__(C::WG_THREADS) tf_gemm_kshare_kernel(const Gem
     for (int y = 0; y < C::PER_THREAD; ++y) {
       const int x = tid + y * C::WG_THREADS, r = x / C::CPR;
       ok[y] = m0 + r < m_end && n_ok;
-      if (ok[y]) store_device(corner + ks * slice + (size_t)r * p.N, z[y]);
+      if (ok[y]) store_through_f32x4(corner + ks * slice + (size_t)r * p.N, z[y]);
     }
     // every store of this wave has been acknowledged before the wave reaches the barrier, so the ticket taken behind
     // it is ordered behind the whole work-group's sums
@@ -259,10 +256,9 @@ __global__ void __launch_bounds__(C::WG_THREADS) tf_gemm_kshare_kernel(const Gem
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const int s = s0 + g < p.split_k ? s0 + g : p.split_k - 1;
-        const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(p.ws + s * slice, 0, (int)(slice * 4), 0x00027000);
 #pragma unroll
         for (int y = 0; y < C::PER_THREAD; ++y)      // (a piece outside Y reads the workspace's first 16 bytes and is not stored)
-          v[g][y] = load_device(part, ok[y] ? 4u * ((unsigned)(m0 + (tid + y * C::WG_THREADS) / C::CPR) * (unsigned)p.N + (unsigned)n) : 0u);
+          v[g][y] = load_device(ok[y] ? corner + s * slice + (size_t)((tid + y * C::WG_THREADS) / C::CPR) * p.N : p.ws);
       }
 #pragma unroll
       for (int g = 0; g < G; ++g)
