@@ -118,3 +118,17 @@ def run_variant(prob, vid, dA, dB, dbias, out: OutBuf, **kw):
     out.reset()
     prob.run(vid, dA, dB, dbias, out.ptr, **kw)
     return out.host()
+
+
+def arbitrated(log, theta):
+    """The report of a loop's log that the oracle's Arbiter ends on: log[0] is the baseline's, then one per round. A candidate
+    is left for a gain below later_accept_gain, and one of any speed for a failed run or gate or a spread above robust_spread."""
+    from oracle import loop_oracle as lo
+    as_dict = lambda r: {k: getattr(r, k) for k in ("status", "parity_ok", "t_med_us", "t_min_us")}
+    th = {k: getattr(theta, k) for k in lo.DEFAULT_THETA}
+    best, stall = log[0], 0
+    for rnd, r in enumerate(log[1:], 1):
+        dec = lo.arbiter(as_dict(r), as_dict(best), th, best is log[0], stall, rnd)
+        best, stall = (r, 0) if dec == lo.ACCEPT else (best, stall + 1)
+        assert dec != lo.FINISH or r is log[-1], "the log goes on after the Arbiter has finished"
+    return best

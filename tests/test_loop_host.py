@@ -10,6 +10,8 @@ import pytest
 from oracle import loop_oracle as lo
 from paper_2512_09196_amd import tf
 
+import gpu_util as gu
+
 GOLDEN = os.path.join(os.path.dirname(__file__), "golden", "case_study3_rounds.txt")
 REPORT_KEYS = ["status", "parity_ok", "t_med_us", "t_min_us", "grid_fill", "arithmetic_intensity", "pct_mfma_peak",
                "pct_hbm_peak", "occupancy_pct", "have_counters", "mfma_busy_pct", "hbm_read_gbs", "hbm_write_gbs",
@@ -117,6 +119,26 @@ def test_tune_replay_matches_oracle_loop():
         assert [r.variant_id for r in clog] == [r["variant_id"] for r in log]
         assert [r.bottleneck for r in clog] == [r["bottleneck"] for r in log]
         assert len(clog) <= 9
+
+
+def test_a_log_tells_which_candidate_the_loop_ends_on():
+    """What the loop's test on the GPU asserts of a log: here with candidates that are the fastest and too unsteady to take, as in a
+    run of 256^3 whose result was 3.380 us beside a candidate of 3.306."""
+    rng = random.Random(14)
+    hw, th = tf.hw_nominal(), tf.theta_default()
+    desc = tf.ProblemDesc(256, 256, 256, 256, 256, 256, 0, 0)
+    left = 0
+    for _ in range(100):
+        fam = [c_variant(rand_variant(rng, kind=0), 0)] + [c_variant(rand_variant(rng), i) for i in range(1, 9)]
+        reps = [rand_report(rng) for _ in fam]
+        for r, t in zip(reps, [30.0] + [rng.uniform(3.2, 3.6) for _ in fam]):
+            r.update(status=0, parity_ok=1, t_med_us=t, t_min_us=t * rng.choice([0.97, 0.97, 0.88]))
+        bv, best, log = tf.tune_replay(desc, hw, fam, [c_report(r) for r in reps], th)
+        assert gu.arbitrated(log, th).variant_id == bv and gu.arbitrated(log, th).t_med_us == best.t_med_us
+        steady = [r.t_med_us for r in log if (r.t_med_us - r.t_min_us) / r.t_med_us <= th.robust_spread]
+        assert bv == 0 or best.t_med_us <= min(steady) * th.later_accept_gain
+        left += bv != 0 and best.t_med_us > 1.02 * min(r.t_med_us for r in log)
+    assert left >= 5
 
 
 def test_case_study3_replay_through_the_library():
