@@ -85,6 +85,7 @@ extern "C" int32_t tf_refine_hint(const tf_report* prev, const tf_report* cand, 
 
 // ------------------------------------------------------------------ static cost model
 static inline long cdiv(long a, long b) { return (a + b - 1) / b; }
+static inline int at_least(int least, int x) { return x < least ? least : x; }      // (a caller's descriptor may hold anything)
 static inline bool is_tile_kernel(const tf_variant_desc* v) { return v->kind == TF_KIND_MFMA_LDS || (v->kind == TF_KIND_MFMA_LDS_ANY && !tf::is_kshare(v)); }
 
 extern "C" int32_t tf_resident_wgs(const tf_hw* hw, const tf_variant_desc* v) {
@@ -98,7 +99,7 @@ extern "C" int32_t tf_resident_wgs(const tf_hw* hw, const tf_variant_desc* v) {
   }
   if (tf::is_kshare(v)) {
     int r = v->lds_bytes > 0 ? hw->lds_bytes_per_cu / (v->lds_bytes + 64) : 8;
-    const int by_waves = hw->simds_per_cu * hw->max_waves_per_simd / v->waves_k;
+    const int by_waves = hw->simds_per_cu * hw->max_waves_per_simd / at_least(1, v->waves_k);
     if (by_waves < r) r = by_waves;
     return r < 1 ? 1 : (r > 8 ? 8 : r);
   }
@@ -138,16 +139,16 @@ extern "C" double tf_grid_fill(const tf_hw* hw, const tf_variant_desc* v) {
 //     outputs, 0.11 more in cut tiles, which start 0.4 us later; the L2s together fetch 6.2 TB/s; the three overlap. The
 //     variant and shape predicted to be the fastest is 2.4 % behind the fastest of all.
 tf::KshareShape tf::kshare_shape(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
-  const int nw = v->waves_k, sums = v->bm * v->bn * 4;
+  const int nw = at_least(1, v->waves_k), max_a = at_least(1, v->bm / 8), max_b = at_least(1, v->bn / 8), sums = v->bm * v->bn * 4;
   const long nkt = cdiv(pr->K, 64);
   const double off_a = pr->lda % 64 ? 1.47 : 1.0, off_b = pr->ldb % 64 ? 1.47 : 1.0;
   const double rate_b = pr->trans_b ? 105.6e3 : v->bn > 32 ? 93.6e3 : 73.4e3;
   const bool may_cut = v->split_k == 1 && !(v->bm == 32 && v->bn == 32);
   KshareShape all{}, cut{};
-  for (int ga = may_cut ? 1 : v->bm / 8; ga <= v->bm / 8; ++ga) {
+  for (int ga = may_cut ? 1 : max_a; ga <= max_a; ++ga) {
     const long tm = cdiv(pr->M, 8 * ga);
-    if (ga > 1 && ga < v->bm / 8 && cdiv(pr->M, 8 * (ga - 1)) == tm) continue;                  // fewer rows make as many tiles
-    for (int gb = may_cut && pr->trans_b ? 1 : v->bn / 8; gb <= v->bn / 8; ++gb) {
+    if (ga > 1 && ga < max_a && cdiv(pr->M, 8 * (ga - 1)) == tm) continue;                  // fewer rows make as many tiles
+    for (int gb = may_cut && pr->trans_b ? 1 : max_b; gb <= max_b; ++gb) {
       const long tn = cdiv(pr->N, 8 * gb), tiles = tm * tn;
       const bool whole = 8 * ga == v->bm && 8 * gb == v->bn && v->bm >= 32;
       if (!whole && (tiles > hw->cus || (gb > 1 && pr->trans_b && cdiv(pr->N, 8 * (gb - 1)) == tn))) continue;
@@ -186,9 +187,9 @@ static double kshare_whole_us(const tf_problem_desc* pr, const tf_hw* hw, const 
   // a CU fetches the panels of its tiles at 76 to 101 GB/s (rows of 32 columns of a [K][N] B are half a 128-byte line), the
   // L2s together what their tiles need at 7.4 TB/s (the two overlap in part), a launch takes 2.9 us and a further round of
   // work-groups costs 2.3 beside its bytes.
-  const int s = v->split_k, lds_whole = v->waves_k * v->stages * (v->bm + v->bn) * 128;
-  const int res = fmax(1.0, fmin(8.0, hw->lds_bytes_per_cu / lds_whole));
-  const long tm = cdiv(pr->M, v->bm), tn = cdiv(pr->N, v->bn), nkt = cdiv(pr->K, 64);
+  const int s = at_least(1, v->split_k), lds_whole = v->waves_k * v->stages * (v->bm + v->bn) * 128;
+  const int res = fmax(1.0, fmin(8.0, hw->lds_bytes_per_cu / at_least(1, lds_whole)));
+  const long tm = cdiv(pr->M, at_least(1, v->bm)), tn = cdiv(pr->N, at_least(1, v->bn)), nkt = cdiv(pr->K, 64);
   const double load = (double)(tm * tn * s) / hw->cus;
   const double rate = v->bm > 32 ? 76.3e3 : v->bn > 32 ? 96.4e3 : pr->trans_b ? 101.2e3 : 89.7e3;
   const double fetch = (v->bm + v->bn) * 128.0 * cdiv(nkt, s) * fmax(1.0, ceil(load - 1e-9)) / rate;

@@ -1,5 +1,8 @@
 """Cut tiles of the kernels whose waves share K, on the CPU: what a family promises whatever the cut."""
+import os
 import random
+import subprocess
+import sys
 
 from paper_2512_09196_amd import tf
 
@@ -32,3 +35,24 @@ def test_families_with_cut_tiles():
         assert all((fam[i].kind == tf.TF_KIND_MFMA_LDS_ANY) == small for i in rows16)
     assert {(k, c, s) for k, c, s in seen if k in WHOLE} >= {(k, False, True) for k in WHOLE} | {(k, True, False) for k in list(WHOLE)[1:]}
     assert (b"kshare_32x32x64_k4_s2", True, False) not in seen and rows_over_64
+
+
+def test_a_descriptor_with_empty_fields_is_priced():
+    """A caller's descriptor may leave out what the model divides by (in a process of its own, which a division by zero would end)."""
+    code = """
+import math
+from paper_2512_09196_amd import tf
+hw = tf.hw_nominal()
+for M, N, K in ((16, 4096, 4096), (256, 256, 256)):
+    with tf.Problem(M, N, K) as p:
+        for at in [v.id for v in p.variants() if v.name.startswith(b"kshare_")]:
+            for fields in (["waves_k"], ["stages"], ["bm"], ["bn"], ["split_k"], ["lds_bytes"], ["bm", "bn", "waves_k", "stages", "split_k", "lds_bytes"]):
+                v = p.variants()[at]
+                for f in fields:
+                    setattr(v, f, 0)
+                if v.waves_k > 1 or v.kind == tf.TF_KIND_MFMA_KSHARE:
+                    assert math.isfinite(tf.predict_us(p.desc, hw, v)) and 1 <= tf.resident_wgs(hw, v) <= 8 and tf.grid_fill(hw, v) > 0, fields
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True)
+    assert r.returncode == 0, (r.returncode, r.stderr)
