@@ -257,10 +257,11 @@ void build_any_family(tf_problem* p) {
 }
 
 // Few output tiles: the waves of a work-group share K, and where tiles alone leave the chip idle so do work-groups. Tiles of 16
-// rows (`rows16`, without slices) come behind all other variants of a family. They are for up to 64 rows, and for small problems
-// of more, which have no slices to pick: sixteen waves to a long sum (us, four
+// rows (`rows16`, without slices) come behind all other variants of a family but, above 64 rows, the ones in whole lines, which end
+// theirs. They are for up to 64 rows, and for small problems of more, which have no slices to pick: sixteen waves to a long sum (us, four
 // waves / these: 79 x 256 x 11456 with B as [N][K] 17.4 / 9.4, 171 x 272 x 4640 [N][K] 11.4 / 7.3, 79 x 320 x 10272 24.6 / 17.5,
-// 75 x 384 x 8768 19.0 / 15.1; 0.87 of the time over 60 problems, the worst 71 x 896 x 3904 [N][K] 7.7 / 8.2).
+// 75 x 384 x 8768 19.0 / 15.1; 0.87 of the time over 60 problems, the worst 71 x 896 x 3904 [N][K] 7.7 / 8.2; where K is no
+// multiple of 64 0.86 over 60 more whose pick moves, the best 141 x 184 x 11760 [N][K] 15.2 / 10.7, the worst 161 x 512 x 2288 5.6 / 6.4).
 void build_kshare_family(tf_problem* p, bool rows16) {
   const tf_problem_desc& d = p->desc;
   if (d.K < 64) return;
@@ -270,7 +271,7 @@ void build_kshare_family(tf_problem* p, bool rows16) {
   if (rows16) {
     for (size_t i = 0; i < p->family.size(); ++i)
       if (p->family[i].kind == TF_KIND_MFMA_LDS_ANY) any = p->impl[i].any_id;
-    if (d.M > 64 && (any < 0 || p->family.back().direct_to_lds == 3)) return;      // (rows in whole lines: these end their family)
+    if (d.M > 64 && any < 0) return;
   }
   const tf::KshareKernelInfo* tab = tf::kshare_kernel_table();
   for (int i = 0; i < tf::kshare_kernel_count(); ++i) {
@@ -578,8 +579,9 @@ void build_family(tf_problem* p) {
   }
   build_small_family(p);
   add_tiles(1);
+  if (d.M > 64) build_kshare_family(p, true);
   add_tiles(2);
-  build_kshare_family(p, true);
+  if (d.M <= 64) build_kshare_family(p, true);
   // One counter area for the whole family, so that the partial sums of one variant never
   // land on the counters of another: [counters, status word | partial sums]. The status word
   // takes the last 256 bytes of the area.

@@ -28,13 +28,39 @@ def test_families_with_cut_tiles():
                 assert v.split_k > 1 or v.grid == -(-M // v.bm) * -(-N // v.bn)
                 assert tf.kernel_substr(v).endswith("false")
         rows16 = [i for i, v in enumerate(fam) if v.name.startswith(b"kshare_16x")]
-        assert rows16 == list(range(len(fam) - len(rows16), len(fam)))     # behind all others
+        lined = [i for i, v in enumerate(fam) if v.direct_to_lds == 3] if M > 64 else []
+        last = len(fam) - len(lined)
+        assert rows16 == list(range(last - len(rows16), last)) and lined == list(range(last, len(fam)))     # behind all others, but for rows in whole lines
         small = any(v.kind == tf.TF_KIND_MFMA_LDS_ANY for v in fam)
         assert M <= 64 or not rows16 or small
         rows_over_64 |= M > 64 and bool(rows16)
         assert all((fam[i].kind == tf.TF_KIND_MFMA_LDS_ANY) == small for i in rows16)
     assert {(k, c, s) for k, c, s in seen if k in WHOLE} >= {(k, False, True) for k in WHOLE} | {(k, True, False) for k in list(WHOLE)[1:]}
     assert (b"kshare_32x32x64_k4_s2", True, False) not in seen and rows_over_64
+
+
+def test_rows_of_16_go_by_size_and_not_by_what_else_the_family_has():
+    """A K of whole tiles and its neighbours, whose families end in instances that stage rows in whole lines (us in tiles of 32 rows /
+    of 16: 141 x 184 x 11760 with B as [N][K] 15.2 / 10.7, 87 x 336 x 7704 21.2 / 15.3)."""
+    hw, lined = tf.hw_nominal(), 0
+    for M, N, Ks, nk in ((79, 256, (11448, 11456, 11464), 1), (79, 320, (10272, 10280), 0), (141, 184, (11760,), 1), (87, 336, (7680, 7704), 0)):
+        for K in Ks:
+            with tf.Problem(M, N, K, trans_b=nk) as p:
+                fam = p.variants()
+            pick = fam[tf.proposal(p.desc, hw, fam, [v.id == 0 for v in fam], 0, tf.TF_BN_UNKNOWN)]
+            assert pick.bm == 16 and pick.kind == tf.TF_KIND_MFMA_LDS_ANY, (M, N, K)
+            lined += any(v.direct_to_lds == 3 for v in fam)
+    assert lined >= 5
+    rng = random.Random(5)
+    for _ in range(100):
+        M, N, K, nk = rng.randint(65, 400), 8 * rng.randint(8, 60), 64 * rng.randint(32, 128), rng.randint(0, 1)
+        offers = []
+        for k in (K - 8, K, K + 8):
+            with tf.Problem(M, N, k, trans_b=nk) as p:
+                fam = p.variants()
+            if any(v.kind == tf.TF_KIND_MFMA_LDS_ANY for v in fam):
+                offers.append({v.name for v in fam if v.bm == 16 and v.name.startswith(b"kshare_")})
+        assert all(o == offers[0] for o in offers), (M, N, K, nk)
 
 
 def test_a_descriptor_with_empty_fields_is_priced():
