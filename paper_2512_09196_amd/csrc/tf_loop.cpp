@@ -138,39 +138,68 @@ extern "C" double tf_grid_fill(const tf_hw* hw, const tf_variant_desc* v) {
 //     in pieces of 64, less by a half where rows start off 128-byte lines; a wave takes 0.09 us for a K tile and every 32 x 32
 //     outputs, 0.11 more in cut tiles, which start 0.4 us later; the L2s together fetch 6.2 TB/s; the three overlap. The
 //     variant and shape predicted to be the fastest is 2.4 % behind the fastest of all.
+//   * Shapes that cannot be the fastest are left before the overlap is worked out, and what has no cut is priced once: 64 shapes of four
+//     powers each, twice for every variant, took half of a small problem's proposal (79 x 256 x 11448 with B as [N][K] 24 us, now 13; 32 x 2576 x 2856
+//     [N][K] 10 and 7; without any cuts 8 and 5).
+struct KsharePricer {
+  const tf_problem_desc* pr;
+  const tf_hw* hw;
+  const tf_variant_desc* v;
+  int nw, max_a, max_b, sums;
+  long nkt;
+  double off_a, off_b, rate_b;
+  KsharePricer(const tf_problem_desc* pr_, const tf_hw* hw_, const tf_variant_desc* v_) : pr(pr_), hw(hw_), v(v_) {
+    nw = at_least(1, v->waves_k); max_a = at_least(1, v->bm / 8); max_b = at_least(1, v->bn / 8); sums = v->bm * v->bn * 4;
+    nkt = cdiv(pr->K, 64);
+    off_a = pr->lda % 64 ? 1.47 : 1.0; off_b = pr->ldb % 64 ? 1.47 : 1.0;
+    rate_b = pr->trans_b ? 105.6e3 : v->bn > 32 ? 93.6e3 : 73.4e3;
+  }
+  // The launch in tiles of ga x gb eights, or groups_a = 0 if there is none or it takes `bound` or longer.
+  tf::KshareShape price(int ga, int gb, bool whole, double bound) const {
+    const long tm = cdiv(pr->M, 8 * ga), tn = cdiv(pr->N, 8 * gb), tiles = tm * tn;
+    const double load = (double)tiles / hw->cus, on_cu = fmax(1.0, ceil(load - 1e-9));
+    const int stages = whole ? v->stages : v->bm <= 32 && nw * (ga + gb) * on_cu <= 40.0 && nkt > nw ? 2 : 1;
+    const int ring = stages * (ga + gb) * 1024 > sums ? stages * (ga + gb) * 1024 : sums;
+    const int lds = nw * ring + (whole ? 0 : tf::KSHARE_CUT_MARK);
+    if (!whole && lds > hw->lds_bytes_per_cu) return {};
+    const int by_lds = hw->lds_bytes_per_cu / (lds + 64), by_waves = hw->simds_per_cu * hw->max_waves_per_simd / nw;
+    const double res = fmax(1.0, by_lds < by_waves ? by_lds : by_waves), rounds = fmax(1.0, ceil(load / res - 1e-9));
+    const double at_once = fmin(on_cu, res);
+    const double fetch = nkt * on_cu * (ga * 1024.0 * off_a / 105.6e3 + gb * 1024.0 * off_b / rate_b);
+    const double serial = rounds * cdiv(nkt, nw) * ((whole ? 0.0 : 0.108) + 0.088 * v->bm * v->bn / 1024.0 * at_once * nw / 8.0);
+    // an XCD's run of neighbouring tiles, in columns of group_m
+    const double run = tiles / 8.0, gm = tm < 8 ? (double)tm : 8.0;
+    const double rows = fmin((double)tm, run < gm ? fmax(1.0, run) : gm * fmax(1.0, ceil(run / (gm * tn)))), cols = fmin((double)tn, fmax(1.0, run / gm));
+    const double fabric = fmax(8.0 * (rows * ga + cols * gb) * 1024.0 * nkt, 2.0 * ((double)pr->M * pr->K + (double)pr->K * pr->N)) / 6.24e6;
+    const double start = 3.03 + (whole ? 0.0 : 0.4) - (nw == 4 ? 0.15 : 0.0) + (v->bm == 64 ? 0.71 : 0.0) + 0.068 * nw * at_once / 16.0;
+    // (the three overlap to no less than the longest)
+    if (start + fmax(fmax(fetch, serial), fabric) + 2.55 * (rounds - 1.0) > bound * (1.0 + 1e-9)) return {};
+    const double us = start + pow(pow(fetch, 2.29) + pow(serial, 2.29) + pow(fabric, 2.29), 1.0 / 2.29) + 2.55 * (rounds - 1.0);
+    if (bound != INFINITY && !(us < bound)) return {};
+    return tf::KshareShape{ga, gb, stages, tm, tn, lds, us, 0.0, false};
+  }
+  // Tiles of the kernel's own size, if it has them.
+  tf::KshareShape whole() const {
+    return 8 * max_a == v->bm && 8 * max_b == v->bn && v->bm >= 32 ? price(max_a, max_b, true, INFINITY) : tf::KshareShape{};
+  }
+};
+
 tf::KshareShape tf::kshare_shape(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
-  const int nw = at_least(1, v->waves_k), max_a = at_least(1, v->bm / 8), max_b = at_least(1, v->bn / 8), sums = v->bm * v->bn * 4;
-  const long nkt = cdiv(pr->K, 64);
-  const double off_a = pr->lda % 64 ? 1.47 : 1.0, off_b = pr->ldb % 64 ? 1.47 : 1.0;
-  const double rate_b = pr->trans_b ? 105.6e3 : v->bn > 32 ? 93.6e3 : 73.4e3;
-  const bool may_cut = v->split_k == 1 && !(v->bm == 32 && v->bn == 32);
-  KshareShape all{}, cut{};
-  for (int ga = may_cut ? 1 : max_a; ga <= max_a; ++ga) {
-    const long tm = cdiv(pr->M, 8 * ga);
-    if (ga > 1 && ga < max_a && cdiv(pr->M, 8 * (ga - 1)) == tm) continue;                  // fewer rows make as many tiles
-    for (int gb = may_cut && pr->trans_b ? 1 : max_b; gb <= max_b; ++gb) {
-      const long tn = cdiv(pr->N, 8 * gb), tiles = tm * tn;
-      const bool whole = 8 * ga == v->bm && 8 * gb == v->bn && v->bm >= 32;
-      if (!whole && (tiles > hw->cus || (gb > 1 && pr->trans_b && cdiv(pr->N, 8 * (gb - 1)) == tn))) continue;
-      const double load = (double)tiles / hw->cus, on_cu = fmax(1.0, ceil(load - 1e-9));
-      const int stages = whole ? v->stages : v->bm <= 32 && nw * (ga + gb) * on_cu <= 40.0 && nkt > nw ? 2 : 1;
-      const int ring = stages * (ga + gb) * 1024 > sums ? stages * (ga + gb) * 1024 : sums;
-      const int lds = nw * ring + (whole ? 0 : KSHARE_CUT_MARK);
-      if (!whole && lds > hw->lds_bytes_per_cu) continue;
-      const int by_lds = hw->lds_bytes_per_cu / (lds + 64), by_waves = hw->simds_per_cu * hw->max_waves_per_simd / nw;
-      const double res = fmax(1.0, by_lds < by_waves ? by_lds : by_waves), rounds = fmax(1.0, ceil(load / res - 1e-9));
-      const double at_once = fmin(on_cu, res);
-      const double fetch = nkt * on_cu * (ga * 1024.0 * off_a / 105.6e3 + gb * 1024.0 * off_b / rate_b);
-      const double serial = rounds * cdiv(nkt, nw) * ((whole ? 0.0 : 0.108) + 0.088 * v->bm * v->bn / 1024.0 * at_once * nw / 8.0);
-      // an XCD's run of neighbouring tiles, in columns of group_m
-      const double run = tiles / 8.0, gm = tm < 8 ? (double)tm : 8.0;
-      const double rows = fmin((double)tm, run < gm ? fmax(1.0, run) : gm * fmax(1.0, ceil(run / (gm * tn)))), cols = fmin((double)tn, fmax(1.0, run / gm));
-      const double fabric = fmax(8.0 * (rows * ga + cols * gb) * 1024.0 * nkt, 2.0 * ((double)pr->M * pr->K + (double)pr->K * pr->N)) / 6.24e6;
-      const double us = 3.03 + (whole ? 0.0 : 0.4) - (nw == 4 ? 0.15 : 0.0) + (v->bm == 64 ? 0.71 : 0.0) + 0.068 * nw * at_once / 16.0 +
-                        pow(pow(fetch, 2.29) + pow(serial, 2.29) + pow(fabric, 2.29), 1.0 / 2.29) + 2.55 * (rounds - 1.0);
-      const KshareShape one{ga, gb, stages, tm, tn, lds, us, 0.0, false};
-      if (whole) all = one;
-      else if (cut.groups_a == 0 || us < cut.us) cut = one;
+  const KsharePricer k(pr, hw, v);
+  const KshareShape all = k.whole();
+  KshareShape cut{};
+  if (v->split_k == 1 && !(v->bm == 32 && v->bn == 32)) {
+    double bound = INFINITY;
+    for (int ga = 1; ga <= k.max_a; ++ga) {
+      const long tm = cdiv(pr->M, 8 * ga);
+      if (ga > 1 && ga < k.max_a && cdiv(pr->M, 8 * (ga - 1)) == tm) continue;                  // fewer rows make as many tiles
+      for (int gb = pr->trans_b ? 1 : k.max_b; gb <= k.max_b; ++gb) {
+        const long tn = cdiv(pr->N, 8 * gb);
+        if (tm * tn > hw->cus || (gb > 1 && pr->trans_b && cdiv(pr->N, 8 * (gb - 1)) == tn)) continue;
+        if (all.groups_a == ga && all.groups_b == gb) continue;
+        const KshareShape one = k.price(ga, gb, false, bound);
+        if (one.groups_a != 0) { cut = one; bound = one.us; }
+      }
     }
   }
   const bool is_cut = cut.groups_a != 0 && (all.groups_a == 0 || cut.us < 0.97 * all.us);
@@ -296,8 +325,8 @@ double tf::base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_
     tf_variant_desc whole = *v;
     if (v->bm < 32) { whole.bm = whole.bn = 32; whole.waves_k = 4; whole.stages = 2; }
     double us = kshare_whole_us(pr, hw, &whole);
-    const KshareShape shape = kshare_shape(pr, hw, v);
-    if (shape.is_cut) us = fmin(us, fmax(us * shape.us / kshare_shape(pr, hw, &whole).whole_us, shape.us));
+    const KshareShape shape = s == 1 ? kshare_shape(pr, hw, v) : KshareShape{};        // (slices are of whole tiles)
+    if (shape.is_cut) us = fmin(us, fmax(us * shape.us / (v->bm < 32 ? KsharePricer(pr, hw, &whole).whole().us : shape.whole_us), shape.us));
     // On the scale of what it is compared with. Small problems, the any-address kernels, which are the faster where K is short or rows
     // start off 128-byte lines. (Over 136 drawn problems the faster of the two is picked but for 2.3 %, with a factor of 1.15 in
     // place of this 3.4 %: 105 x 648 x 360 with B as [N][K] 5.3 us where the any-address kernel takes 3.5, 93 x 6480 x 264 [N][K] 6.3 / 4.9.)

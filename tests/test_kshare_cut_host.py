@@ -1,8 +1,10 @@
 """Cut tiles of the kernels whose waves share K, on the CPU: what a family promises whatever the cut."""
+import ctypes as C
 import os
 import random
 import subprocess
 import sys
+import time
 
 from paper_2512_09196_amd import tf
 
@@ -82,3 +84,20 @@ for M, N, K in ((16, 4096, 4096), (256, 256, 256)):
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True)
     assert r.returncode == 0, (r.returncode, r.stderr)
+
+
+def test_pricing_a_cut_costs_little_more_than_pricing_whole_tiles():
+    """A proposal prices every variant. Pricing all 64 cuts of a 64 x 64 tile in full took 12 times what a kernel without cuts does;
+    with those left out that cannot be the fastest, 3.6. (The fastest of many runs of each, taken in turn.)"""
+    hw, f = tf.hw_nominal(), tf.lib().tf_predict_us
+    with tf.Problem(128, 256, 11528, trans_b=1) as p:
+        whole, cut = ([v for v in p.variants() if v.name.startswith(name)][0] for name in (b"kshare_32x32x64_k4_s2_bnk_sk1", b"kshare_64x64x64_k8_s1_bnk_sk1"))
+        least = {id(v): float("inf") for v in (whole, cut)}
+        for _ in range(40):
+            for v in (whole, cut):
+                args = C.byref(p.desc), C.byref(hw), C.byref(v)
+                start = time.perf_counter()
+                for _ in range(100):
+                    f(*args)
+                least[id(v)] = min(least[id(v)], time.perf_counter() - start)
+    assert least[id(cut)] < 7 * least[id(whole)]
