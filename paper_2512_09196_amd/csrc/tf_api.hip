@@ -764,6 +764,8 @@ tf_status do_launch(tf_problem* p, int id, const void* A, const void* B, const v
     g.tiles_m = im.tiles_m; g.tiles_n = im.tiles_n; g.ktiles_per_split = im.ktiles_per_split;
     k.launch(g, dim3((unsigned)v.grid), stream);
   } else {
+    const bool reduces = v.split_k > 1 && !v.fused_reduce;       // a second kernel sums the slices
+    if (reduces && !tf::splitk_reduce_takes(v.split_k)) return fail(TF_E_UNSUPPORTED, "variant %s: no kernel sums %d slices", v.name, v.split_k);
     g.tiles_m = im.tiles_m; g.tiles_n = im.tiles_n; g.ktiles_per_split = im.ktiles_per_split;
     if (d.trans_b && v.kind == TF_KIND_MFMA_LDS && !v.trans_b) {
       // B arrives as [N][K] and this kernel reads [K][N]: a separate pass writes B^T into the workspace first
@@ -858,7 +860,7 @@ tf_status do_launch(tf_problem* p, int id, const void* A, const void* B, const v
     if (kshare) tf::kshare_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
     else if (streaming) tf::stream_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
     else tf::lds_kernel_table()[im.lds_index].launch(g, dim3((unsigned)v.grid), stream);
-    if (v.split_k > 1 && !v.fused_reduce) tf::launch_splitk_reduce(g, stream);
+    if (reduces) tf::launch_splitk_reduce(g, stream);
   }
   TF_HIP(hipGetLastError());
   return TF_OK;

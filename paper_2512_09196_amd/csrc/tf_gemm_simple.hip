@@ -273,15 +273,22 @@ __global__ void __launch_bounds__(256) tf_splitk_reduce_kernel(const GemmParams 
   }
 }
 
+// (an instance for each number of slices: one of another number would read past the workspace, or leave slices out)
+static auto splitk_reduce_kernel(int slices) -> void (*)(const GemmParams) {
+  switch (slices) {
+    case 2: return tf_splitk_reduce_kernel<2>;
+    case 4: return tf_splitk_reduce_kernel<4>;
+    case 8: return tf_splitk_reduce_kernel<8>;
+    case 16: return tf_splitk_reduce_kernel<16>;
+    case 32: return tf_splitk_reduce_kernel<32>;
+    default: return nullptr;
+  }
+}
+bool splitk_reduce_takes(int slices) { return splitk_reduce_kernel(slices) != nullptr; }
 void launch_splitk_reduce(const GemmParams& p, hipStream_t s) {
   const dim3 grid((unsigned)(((size_t)p.M * (p.N / 4) + 255) / 256));
-  if (p.split_k == 2) hipLaunchKernelGGL(tf_splitk_reduce_kernel<2>, grid, dim3(256), 0, s, p);
-  else if (p.split_k == 4) hipLaunchKernelGGL(tf_splitk_reduce_kernel<4>, grid, dim3(256), 0, s, p);
-  else if (p.split_k == 8) hipLaunchKernelGGL(tf_splitk_reduce_kernel<8>, grid, dim3(256), 0, s, p);
-  else if (p.split_k == 16) hipLaunchKernelGGL(tf_splitk_reduce_kernel<16>, grid, dim3(256), 0, s, p);
-  else hipLaunchKernelGGL(tf_splitk_reduce_kernel<32>, grid, dim3(256), 0, s, p);
+  hipLaunchKernelGGL(splitk_reduce_kernel(p.split_k), grid, dim3(256), 0, s, p);
 }
-const void* splitk_reduce_func() { return (const void*)tf_splitk_reduce_kernel<2>; }
 
 void launch_naive(const GemmParams& p, hipStream_t s) {
   dim3 grid((p.N + 63) / 64, (p.M + 3) / 4);

@@ -141,7 +141,7 @@ void launch_norms(const uint16_t* X, long n_outer, long outer_stride, long n_inn
                   float* out, hipStream_t);
 double launch_calib_mfma(float* sink, int block, int wgs, int iters, hipStream_t);            // MFMA of block x block outputs (32 or 16), 4 waves per work-group; returns the flops
 void launch_calib_read(const void* src, size_t bytes, unsigned* sink, int wgs, hipStream_t);  // reads every byte once
+bool splitk_reduce_takes(int slices);                        // whether there is a kernel for so many
 void launch_splitk_reduce(const GemmParams&, hipStream_t);   // sums ws slices in order, bias + epilogue -> Y
-const void* splitk_reduce_func();
 
 }  // namespace tf
