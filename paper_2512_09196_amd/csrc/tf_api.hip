@@ -764,6 +764,8 @@ tf_status do_launch(tf_problem* p, int id, const void* A, const void* B, const v
     g.tiles_m = im.tiles_m; g.tiles_n = im.tiles_n; g.ktiles_per_split = im.ktiles_per_split;
     k.launch(g, dim3((unsigned)v.grid), stream);
   } else {
+    if (tf::is_kshare(&v) && !tf::kshare_takes(im.lds_index, im.groups_a, im.groups_b, im.ring_stages))
+      return fail(TF_E_UNSUPPORTED, "variant %s: no kernel for tiles of %d x %d with %d K tiles in a ring", v.name, 8 * im.groups_a, 8 * im.groups_b, im.ring_stages);
     const bool reduces = v.split_k > 1 && !v.fused_reduce;       // a second kernel sums the slices
     if (reduces && !tf::splitk_reduce_takes(v.split_k)) return fail(TF_E_UNSUPPORTED, "variant %s: no kernel sums %d slices", v.name, v.split_k);
     g.tiles_m = im.tiles_m; g.tiles_n = im.tiles_n; g.ktiles_per_split = im.ktiles_per_split;

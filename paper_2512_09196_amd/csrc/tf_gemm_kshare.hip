@@ -40,8 +40,14 @@ struct KshareCfg : LdsCfg<(BM_ < 32 ? 32 : BM_), BN_, 64, 1, 1, S_, true, false,
   // blocks of 16 x 16 over 32 of K: a wave has a K tile's fragments in half as many dependent MFMAs, of half the latency
   static constexpr int MB = 16, KMF = 32, TM = BM_ / 16, TN = BN_ / 16;
   static constexpr bool HAS_WHOLE = BM_ >= 32, HAS_CUT = !(BM_ == 32 && BN_ == 32);      // which kernels there are, see tf::kshare_shape
-  // transfers of a K tile, at most, where a cut's ring holds two (kshare_shape: 40 KB in a work-group's rings otherwise)
-  static constexpr int MAX_FLYING = BM_ > 32 || !HAS_CUT ? 0 : 40 / NW_ < BM_ / 8 + BN_ / 8 ? 40 / NW_ : BM_ / 8 + BN_ / 8;
+  // transfers of a K tile, at most, where a cut's ring holds two
+  static constexpr int MAX_FLYING = BM_ > 32 || !HAS_CUT ? 0 : KSHARE_TWO_TILES_KB / NW_ < BM_ / 8 + BN_ / 8 ? KSHARE_TWO_TILES_KB / NW_ : BM_ / 8 + BN_ / 8;
+  // what a launch may ask for: whole tiles, or a cut that the kernel has a main loop for
+  static bool takes(int groups_a, int groups_b, int stages) {
+    if (HAS_WHOLE && groups_a == BM_ / 8 && groups_b == BN_ / 8) return stages == S_;
+    const bool cut = groups_a >= 1 && groups_a <= BM_ / 8 && groups_b <= BN_ / 8 && (TB_ ? groups_b >= 1 : groups_b == BN_ / 8);
+    return HAS_CUT && cut && (stages == 1 || (stages == 2 && groups_a + groups_b <= MAX_FLYING));
+  }
   static constexpr int SUMS = BM_ * BN_ * 4;                  // bytes of a wave's partial sums, where its ring was
   static constexpr int CPR = BN_ / 4, CHUNKS = BM_ * CPR;     // 16-byte pieces of fp32 sums: per row, per tile
   static constexpr int PER_THREAD = CHUNKS < WG_THREADS ? 1 : CHUNKS / WG_THREADS;
@@ -202,7 +208,7 @@ __global__ void __launch_bounds__(C::WG_THREADS) tf_gemm_kshare_kernel(const Gem
       case 0: main_loop(EpiTag<0>{}); break;
       case 1: if constexpr (C::MAX_FLYING >= 2) main_loop(EpiTag<2>{}); break;
       case 2: if constexpr (C::MAX_FLYING >= 4) main_loop(EpiTag<4>{}); break;
-      default: break;
+      default: break;                              // (the host launches none: KshareCfg::takes)
     }
   }
 
@@ -305,6 +311,7 @@ static KshareKernelInfo make_kshare_info() {
   k.func = k.func_cut = nullptr;
   if constexpr (C::HAS_WHOLE) k.func = (const void*)tf_gemm_kshare_kernel<C, false>;
   if constexpr (C::HAS_CUT) k.func_cut = (const void*)tf_gemm_kshare_kernel<C, true>;
+  k.takes = C::takes;
   k.launch = launch_kshare<C>;
   return k;
 }
@@ -317,5 +324,6 @@ static const KshareKernelInfo g_kshare_table[] = {
 };
 int kshare_kernel_count() { return (int)(sizeof(g_kshare_table) / sizeof(g_kshare_table[0])); }
 const KshareKernelInfo* kshare_kernel_table() { return g_kshare_table; }
+bool kshare_takes(int kernel, int groups_a, int groups_b, int stages) { return g_kshare_table[kernel].takes(groups_a, groups_b, stages); }
 
 }  // namespace tf

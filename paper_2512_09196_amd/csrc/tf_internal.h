@@ -94,10 +94,12 @@ struct KshareKernelInfo {
   int bm, bn, waves, stages;          // the largest tile; stages: K tiles of 64 of that size in each wave's ring
   int trans_b, threads;
   const void *func, *func_cut;        // whole tiles of that size; tiles cut to a size given at launch; null: no such kernel
+  bool (*takes)(int groups_a, int groups_b, int stages);
   void (*launch)(const GemmParams&, dim3 grid, hipStream_t);
 };
 int kshare_kernel_count();
 const KshareKernelInfo* kshare_kernel_table();
+bool kshare_takes(int kernel, int groups_a, int groups_b, int stages);      // whether there is a kernel for tiles of that size, with so many K tiles in a ring
 
 // One compiled kernel of the streaming family of the batched vector-matrix product.
 // GemmParams: A [M][lda], B [M][N][ldb] (k contiguous), Y fp32 [M][ldy]; group_m unused.

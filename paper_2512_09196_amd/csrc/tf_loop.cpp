@@ -158,7 +158,7 @@ struct KsharePricer {
   tf::KshareShape price(int ga, int gb, bool whole, double bound) const {
     const long tm = cdiv(pr->M, 8 * ga), tn = cdiv(pr->N, 8 * gb), tiles = tm * tn;
     const double load = (double)tiles / hw->cus, on_cu = fmax(1.0, ceil(load - 1e-9));
-    const int stages = whole ? v->stages : v->bm <= 32 && nw * (ga + gb) * on_cu <= 40.0 && nkt > nw ? 2 : 1;
+    const int stages = whole ? v->stages : v->bm <= 32 && nw * (ga + gb) * on_cu <= tf::KSHARE_TWO_TILES_KB && nkt > nw ? 2 : 1;
     const int ring = stages * (ga + gb) * 1024 > sums ? stages * (ga + gb) * 1024 : sums;
     const int lds = nw * ring + (whole ? 0 : tf::KSHARE_CUT_MARK);
     if (!whole && lds > hw->lds_bytes_per_cu) return {};

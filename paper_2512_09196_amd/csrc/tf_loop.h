@@ -4,6 +4,7 @@
 #include "tf.h"
 
 namespace tf {
+constexpr int KSHARE_TWO_TILES_KB = 40;    // two K tiles in a ring of a cut where the rings of a CU have no more in flight without the second
 constexpr int KSHARE_CUT_MARK = 64;    // what a launch of cut tiles asks for beyond its rings: a descriptor tells by it which of two kernels it means
 // A variant of the kernels whose waves share K: of a small problem, the ones without slices are listed as
 // TF_KIND_MFMA_LDS_ANY (no other tile kernel has a single wave per k group and several groups).

@@ -101,3 +101,46 @@ def test_pricing_a_cut_costs_little_more_than_pricing_whole_tiles():
                     f(*args)
                 least[id(v)] = min(least[id(v)], time.perf_counter() - start)
     assert least[id(cut)] < 7 * least[id(whole)]
+
+
+class Shape(C.Structure):
+    """tf::KshareShape"""
+    _fields_ = [("groups_a", C.c_int), ("groups_b", C.c_int), ("stages", C.c_int), ("tiles_m", C.c_long), ("tiles_n", C.c_long), ("lds_bytes", C.c_int),
+                ("us", C.c_double), ("whole_us", C.c_double), ("is_cut", C.c_bool)]
+
+
+KERNELS = [(32, 32, 4, 0), (32, 64, 8, 0), (64, 64, 8, 0), (32, 32, 4, 1), (32, 64, 8, 1), (64, 64, 8, 1), (16, 32, 8, 0), (16, 32, 16, 0), (16, 32, 8, 1), (16, 32, 16, 1)]
+
+
+def takes(kernel, groups_a, groups_b, stages):
+    f = tf.lib()["_ZN2tf12kshare_takesEiiii"]           # bool tf::kshare_takes(int, int, int, int), what a launch asks before it starts anything
+    f.argtypes, f.restype = [C.c_int] * 4, C.c_bool
+    return f(kernel, groups_a, groups_b, stages)
+
+
+def test_a_cut_without_a_main_loop_is_told_from_the_others():
+    """A kernel has a main loop for two K tiles in a ring up to 40 KB in flight in a work-group's rings; another launch would store the bias alone."""
+    for i, (bm, bn, waves, nk) in enumerate(KERNELS):
+        for ga in range(0, 11):
+            for gb in range(0, 11):
+                whole = bm >= 32 and (8 * ga, 8 * gb) == (bm, bn)
+                cut = not whole and (bm, bn) != (32, 32) and 1 <= ga <= bm // 8 and (1 <= gb <= bn // 8 if nk else gb == bn // 8)
+                two = bm <= 32 and waves * (ga + gb) <= 40
+                for stages in range(0, 4):
+                    want = stages == (2 if bn == 32 else 1) if whole else cut and (stages == 1 or stages == 2 and two)
+                    assert takes(i, ga, gb, stages) == want, (bm, bn, waves, nk, ga, gb, stages)
+
+
+def test_the_model_cuts_to_no_other():
+    rng, hw, seen = random.Random(4), tf.hw_nominal(), set()
+    f = tf.lib()["_ZN2tf12kshare_shapeEPK15tf_problem_descPK5tf_hwPK15tf_variant_desc"]
+    f.argtypes, f.restype = [C.POINTER(tf.ProblemDesc), C.POINTER(tf.Hw), C.POINTER(tf.VariantDesc)], Shape
+    for _ in range(400):
+        M, N, K, nk = rng.choice([rng.randint(1, 64), rng.randint(65, 900)]), 8 * rng.randint(1, 900), 8 * rng.randint(8, 900), rng.randint(0, 1)
+        with tf.Problem(M, N, K, trans_b=nk) as p:
+            for v in [v for v in p.variants() if v.name.startswith(b"kshare_")]:
+                s = f(C.byref(p.desc), C.byref(hw), C.byref(v))
+                assert takes(KERNELS.index((v.bm, v.bn, v.waves_k, nk)), s.groups_a, s.groups_b, s.stages), (M, N, K, nk, v.name)
+                assert s.lds_bytes == v.lds_bytes and (v.split_k > 1 or s.tiles_m * s.tiles_n == v.grid)
+                seen.add((s.is_cut, s.stages))
+    assert seen == {(False, 1), (False, 2), (True, 1), (True, 2)}
