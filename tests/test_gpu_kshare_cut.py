@@ -1,5 +1,6 @@
 """Kernels whose waves share K, in tiles cut to the problem: the numbers of rows and columns that a cut can end on, one and two
-K tiles in a wave's ring, a ragged last K tile, against the oracle and, bit for bit, against whole tiles of the same waves."""
+K tiles in a wave's ring, a ragged last K tile, against the oracle and, where eight waves share K, bit for bit against whole tiles
+of the same waves (sixteen have no whole tiles: the oracle's bound is all that holds them)."""
 import numpy as np
 import pytest
 
@@ -14,6 +15,24 @@ pytestmark = pytest.mark.gpu
 
 def is_cut(v):
     return v.name.startswith(b"kshare_") and v.lds_bytes % 1024 == 64
+
+
+def whole_tiles(M, N, K, A, B, bias, b_as_nk):
+    """The product by every kernel of whole tiles whose eight waves share K: its rows and columns over and over, until the tiles
+    are more than the CUs and so are not cut."""
+    N2 = max(N, 1032)
+    M2 = max(M, 64 * -(-257 // -(-N2 // 64)))
+    A2, B2, bias2 = A[np.arange(M2) % M], np.ascontiguousarray(B[:, np.arange(N2) % N]), bias[np.arange(N2) % N]
+    if b_as_nk:
+        B2 = np.ascontiguousarray(B2.T)
+    out = gu.OutBuf(M2, N2, f32=True)
+    with tf.Problem(M2, N2, K, epi=tf.TF_EPI_NONE_F32, trans_b=b_as_nk) as prob:
+        dA, dB, dbias = gu.to_dev(A2), gu.to_dev(B2), gu.to_dev(bias2)
+        for v in [v for v in prob.variants() if v.name.startswith(b"kshare_") and v.waves_k == 8 and v.split_k == 1 and not is_cut(v)]:
+            print("whole", (M2, N2, K, b_as_nk), "variant", v.name.decode(), v.grid, flush=True)
+            got, intact, _ = gu.run_variant(prob, v.id, dA, dB, dbias, out)
+            assert intact
+            yield got[:M, :N]
 
 
 # one row; eights of rows that the last tile has none, one or seven of; columns shared out unevenly; K of one round of the waves and of
@@ -31,7 +50,9 @@ def test_cut_tiles(M, N, K, b_as_nk, pad):
     with tf.Problem(M, N, K, lda=K + pad, ldb=Bd.shape[1] + pad, ldy=N + pad, epi=tf.TF_EPI_NONE_F32, trans_b=b_as_nk) as prob:
         cut = [v for v in prob.variants() if is_cut(v)]
         assert cut and all(v.split_k == 1 and v.grid <= 256 for v in cut)
-        same = {}
+        whole = list(whole_tiles(M, N, K, A, B, bias, b_as_nk))
+        assert whole and all(np.array_equal(w, whole[0]) for w in whole)
+        same = {8: whole[0]}
         for v in cut:
             print("case", (M, N, K, b_as_nk, pad), "variant", v.name.decode(), v.grid, v.lds_bytes, flush=True)
             got, intact, _ = gu.run_variant(prob, v.id, dA, dB, dbias, out)
