@@ -823,6 +823,7 @@ tf_status do_launch(tf_problem* p, int id, const void* A, const void* B, const v
       g.status = (unsigned*)((char*)ws + im.counter_bytes - kStatusBytes);
       g.ws = (float*)((char*)ws + im.counter_bytes);
       g.ws_vec16 = ((uintptr_t)g.ws % 16 == 0) && (d.N % 4 == 0);
+      g.ws_past_l2 = tf::splitk_past_l2(d.M, d.N, v.split_k);
       if (v.fused_reduce == 2) {
         // the L2-local reduction: only on a device whose work-group placement has been confirmed
         const int dev = d.device >= 0 && d.device < 64 ? d.device : 0;

@@ -622,8 +622,19 @@ __device__ __forceinline__ void epilogue_staged(const typename C::Acc (&acc)[C::
       // not read again by this launch: non-temporal. A partial tile too: ordinary stores leave 4 MB of it in this XCD's L2 until the
       // launch ends, and the lines that the reducing kernel of the call before has left in other L2s make them slower still (one
       // workspace for call after call, us, with ordinary loads there too / both non-temporal: 512 x 768 x 8192 in eight slices
-      // 19.7 / 15.2, 288 x 1152 x 7360 18.9 / 15.0, 1912 x 488 x 3976 in four 20.0 / 18.3, 1024 x 1024 x 16384 42.9 / 40.0)
-      if (cc * 16 < ncols * ESZ) __builtin_nontemporal_store(v, (u32x4*)(dst + ((size_t)m * ld + n0) * ESZ + cc * 16));
+      // 19.7 / 15.2, 288 x 1152 x 7360 18.9 / 15.0, 1912 x 488 x 3976 in four 20.0 / 18.3, 1024 x 1024 x 16384 42.9 / 40.0).
+      // Not where many rows start off 128-byte lines, whose ends would go out in halves: p.ws_past_l2.
+      if (cc * 16 < ncols * ESZ) {
+        u32x4* const to = (u32x4*)(dst + ((size_t)m * ld + n0) * ESZ + cc * 16);
+        if (PARTIAL && !p.ws_past_l2) {
+          // (two stores to one place, of which the compiler would make one, an ordinary one, if the branches began or ended alike)
+          asm volatile("" ::: "memory");
+          *to = v;
+          asm volatile("" ::: "memory");
+        } else {
+          __builtin_nontemporal_store(v, to);
+        }
+      }
     }
   }
 }

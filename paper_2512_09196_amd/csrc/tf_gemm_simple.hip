@@ -240,8 +240,10 @@ __global__ void tf_fill_u32_kernel(unsigned* p, size_t n, unsigned v) {
 // non-temporal loads, or the lines would stay in this XCD's L2 and slow down the next call's stores to them. (us a call, one 64-bit
 // division per thread, a loop over the slices and ordinary loads / this, the partial tiles written with ordinary stores: 478 x 768 x 7872
 // in eight slices 19.9 / 17.2 on one workspace, 17.2 / 15.7 on two in turn; 1024 x 1024 x 16384 42.9 / 41.0; 2048^3 in two 36.0 /
-// 34.2. Non-temporal stores there: 15.2, 15.2, 40.0, 34.6.)
-template <int S>
+// 34.2. Non-temporal stores there: 15.2, 15.2, 40.0, 34.6.) The loads at once apart from their kind: one slice after another, non-temporal
+// too, takes 1.11 of the time of the whole call over 58 launches in 2 to 32 slices (1.58 at the most, 100 x 512 x 16384 in sixteen 10.5 / 16.6), four
+// at a time 1.01 (11.7).
+template <int S, bool PAST_L2>
 __global__ void __launch_bounds__(256) tf_splitk_reduce_kernel(const GemmParams p) {
   const unsigned quads_per_row = (unsigned)p.N / 4;
   const unsigned i = blockIdx.x * 256u + threadIdx.x;
@@ -252,7 +254,10 @@ __global__ void __launch_bounds__(256) tf_splitk_reduce_kernel(const GemmParams 
   const float* src = p.ws + (size_t)i * 4;
   f32x4 v[S];
 #pragma unroll
-  for (int s = 0; s < S; ++s) v[s] = __builtin_nontemporal_load((const f32x4*)(src + (size_t)s * slice));
+  for (int s = 0; s < S; ++s) {
+    if constexpr (PAST_L2) v[s] = __builtin_nontemporal_load((const f32x4*)(src + (size_t)s * slice));
+    else v[s] = *(const f32x4*)(src + (size_t)s * slice);
+  }
   const u32x2 braw = *(const u32x2*)(p.bias + n);
   f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -274,20 +279,26 @@ __global__ void __launch_bounds__(256) tf_splitk_reduce_kernel(const GemmParams 
 }
 
 // (an instance for each number of slices: one of another number would read past the workspace, or leave slices out)
-static auto splitk_reduce_kernel(int slices) -> void (*)(const GemmParams) {
+static auto splitk_reduce_kernel(int slices, bool past_l2) -> void (*)(const GemmParams) {
   switch (slices) {
-    case 2: return tf_splitk_reduce_kernel<2>;
-    case 4: return tf_splitk_reduce_kernel<4>;
-    case 8: return tf_splitk_reduce_kernel<8>;
-    case 16: return tf_splitk_reduce_kernel<16>;
-    case 32: return tf_splitk_reduce_kernel<32>;
+    case 2: return past_l2 ? tf_splitk_reduce_kernel<2, true> : tf_splitk_reduce_kernel<2, false>;
+    case 4: return past_l2 ? tf_splitk_reduce_kernel<4, true> : tf_splitk_reduce_kernel<4, false>;
+    case 8: return past_l2 ? tf_splitk_reduce_kernel<8, true> : tf_splitk_reduce_kernel<8, false>;
+    case 16: return past_l2 ? tf_splitk_reduce_kernel<16, true> : tf_splitk_reduce_kernel<16, false>;
+    case 32: return past_l2 ? tf_splitk_reduce_kernel<32, true> : tf_splitk_reduce_kernel<32, false>;
     default: return nullptr;
   }
 }
-bool splitk_reduce_takes(int slices) { return splitk_reduce_kernel(slices) != nullptr; }
+bool splitk_reduce_takes(int slices) { return splitk_reduce_kernel(slices, true) != nullptr; }
+// Partial tiles pass the L2s by (epilogue_staged has what that gives) but where much of them lies in rows off 128-byte lines: a
+// line that two tiles share goes out in halves, and the memory-side cache no longer makes up for it. Time against ordinary stores
+// and loads: rows of whole lines 0.89 over 29 launches up to 16 MB of slices, 0.98 over 91 above 25 (worst 1.035); others 0.90 over 119
+// up to 20 MB (none loses 2 %), 1.00 over 44 above (928 x 2072 x 11776 with B as [N][K] in eight slices, 62 MB, 72.6 / 80.3 us; 838 x
+// 2040 x 6320 [N][K] in four, 27 MB, 33.7 / 36.2; 804 x 2184 x 8416 [N][K] in four, 28 MB, 41.6 / 42.8), and with this line 0.99.
+bool splitk_past_l2(int M, int N, int slices) { return N % 32 == 0 || 4.0 * slices * M * N <= 20e6; }
 void launch_splitk_reduce(const GemmParams& p, hipStream_t s) {
   const dim3 grid((unsigned)(((size_t)p.M * (p.N / 4) + 255) / 256));
-  hipLaunchKernelGGL(splitk_reduce_kernel(p.split_k), grid, dim3(256), 0, s, p);
+  hipLaunchKernelGGL(splitk_reduce_kernel(p.split_k, p.ws_past_l2), grid, dim3(256), 0, s, p);
 }
 
 void launch_naive(const GemmParams& p, hipStream_t s) {

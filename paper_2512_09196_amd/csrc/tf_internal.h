@@ -39,6 +39,7 @@ struct GemmParams {
   // mixed grid (tf_gemm_mixed_kernel): the first mix_main_wgs work-groups compute BN-wide tiles (tiles_m x tiles_n of them),
   // then tiles_m x mix_tiles work-groups share out the mix_blocks blocks of 32 columns that begin at column mix_n_origin
   int mix_main_wgs, mix_tiles, mix_blocks, mix_n_origin;
+  int ws_past_l2;         // a second kernel sums the slices: partial tiles written and read past the L2s (splitk_past_l2)
   int groups_a, groups_b, ring_stages;   // kernels whose waves share K: eights of rows and of columns of a tile, K tiles in a wave's ring
 };
 
@@ -144,6 +145,7 @@ void launch_norms(const uint16_t* X, long n_outer, long outer_stride, long n_inn
 double launch_calib_mfma(float* sink, int block, int wgs, int iters, hipStream_t);            // MFMA of block x block outputs (32 or 16), 4 waves per work-group; returns the flops
 void launch_calib_read(const void* src, size_t bytes, unsigned* sink, int wgs, hipStream_t);  // reads every byte once
 bool splitk_reduce_takes(int slices);                        // whether there is a kernel for so many
+bool splitk_past_l2(int M, int N, int slices);               // whether partial tiles go past the L2s on their way there
 void launch_splitk_reduce(const GemmParams&, hipStream_t);   // sums ws slices in order, bias + epilogue -> Y
 
 }  // namespace tf

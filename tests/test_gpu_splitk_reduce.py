@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,N,K,epi,slices", [(1, 8, 1024, tf.TF_EPI_NONE_F32, {2}), (7, 72, 8192, tf.TF_EPI_BIAS_GELU_ERF, {2, 4, 8, 16, 32}),
                                               (32, 1032, 4096, tf.TF_EPI_NONE_F32, {2, 4, 8, 16}), (65, 136, 4096, tf.TF_EPI_BIAS, {2, 4, 8, 16}),
-                                              (130, 264, 4160, tf.TF_EPI_NONE_F32, {2, 4, 8})])
+                                              (130, 264, 4160, tf.TF_EPI_NONE_F32, {2, 4, 8}),
+                                              (640, 1048, 2048, tf.TF_EPI_NONE_F32, {2, 4, 8}), (625, 1000, 2048, tf.TF_EPI_BIAS, {2, 4, 8})])   # (eight: 21 MB, not past the L2s; 20 MB)
 def test_reducing_kernel(M, N, K, epi, slices):
     A, B, bias = wl.make_custom(M, N, K, seed=M + N)
     _, z, s = orc.gemm_bias_gelu(A, B, bias)
