@@ -326,7 +326,13 @@ double tf::base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_
     if (v->bm < 32) { whole.bm = whole.bn = 32; whole.waves_k = 4; whole.stages = 2; }
     double us = kshare_whole_us(pr, hw, &whole);
     const KshareShape shape = s == 1 ? kshare_shape(pr, hw, v) : KshareShape{};        // (slices are of whole tiles)
-    if (shape.is_cut) us = fmin(us, fmax(us * shape.us / (v->bm < 32 ? KsharePricer(pr, hw, &whole).whole().us : shape.whole_us), shape.us));
+    if (shape.is_cut) {
+      const double cut = fmax(us * shape.us / (v->bm < 32 ? KsharePricer(pr, hw, &whole).whole().us : shape.whole_us), shape.us);
+      // Where the two fits leave the tiles of 16 rows level with those of 32 x 32, which come first in a family, they are ahead by a hair if each of
+      // eight waves has more than one K tile: a chain half as long (over 200 such problems, us, 32 x 32 / eight waves to 16 rows, 0.85 of the
+      // time, 1.01 at the worst: 2 x 32 x 11120 14.6 / 8.8, 3 x 104 x 5824 8.9 / 6.0, 164 x 96 x 7312 18.2 / 12.3; with no more than one 0.99, 1.05).
+      us = cut < us ? cut : v->bm < 32 && nkt > 8 ? 0.999 * us : us;
+    }
     // On the scale of what it is compared with. Small problems, the any-address kernels, which are the faster where K is short or rows
     // start off 128-byte lines. (Over 136 drawn problems the faster of the two is picked but for 2.3 %, with a factor of 1.15 in
     // place of this 3.4 %: 105 x 648 x 360 with B as [N][K] 5.3 us where the any-address kernel takes 3.5, 93 x 6480 x 264 [N][K] 6.3 / 4.9.)

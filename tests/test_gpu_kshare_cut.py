@@ -40,7 +40,7 @@ def whole_tiles(M, N, K, A, B, bias, b_as_nk):
 @pytest.mark.parametrize("M,N,K,b_as_nk,pad", [(1, 2048, 1024, 1, 0), (8, 1032, 4104, 1, 8), (9, 520, 4152, 1, 0), (16, 2064, 2048, 1, 0), (17, 1104, 2056, 0, 8),
                                                (31, 2576, 1416, 1, 0), (40, 328, 4104, 0, 0), (64, 336, 3000, 1, 16), (83, 536, 4616, 1, 0),
                                                (130, 640, 2120, 0, 0), (368, 1400, 1096, 1, 0),
-                                               (71, 328, 4608, 1, 0), (190, 264, 2048, 0, 8), (79, 264, 4616, 1, 0), (150, 328, 2056, 0, 8)])       # (small problems of more than 64 rows)
+                                               (71, 328, 4608, 1, 0), (190, 264, 2048, 0, 8), (79, 264, 4616, 1, 0), (150, 328, 2056, 0, 8), (3, 8, 2064, 0, 8), (47, 24, 1096, 0, 0), (25, 8, 1032, 1, 0)])       # (small problems of more than 64 rows)
 def test_cut_tiles(M, N, K, b_as_nk, pad):
     A, B, bias = wl.make_custom(M, N, K, seed=7 * M + N + K)
     Bd = np.ascontiguousarray(B.T) if b_as_nk else B

@@ -6,6 +6,8 @@ import subprocess
 import sys
 import time
 
+import pytest
+
 from paper_2512_09196_amd import tf
 
 WHOLE = {b"kshare_32x32x64_k4_s2": 65536, b"kshare_32x64x64_k8_s1": 98304, b"kshare_64x64x64_k8_s1": 131072}
@@ -63,6 +65,18 @@ def test_rows_of_16_go_by_size_and_not_by_what_else_the_family_has():
             if any(v.kind == tf.TF_KIND_MFMA_LDS_ANY for v in fam):
                 offers.append({v.name for v in fam if v.bm == 16 and v.name.startswith(b"kshare_")})
         assert all(o == offers[0] for o in offers), (M, N, K, nk)
+
+
+@pytest.mark.parametrize("M,N,K,name", [(3, 48, 8000, b"kshare_16x32x64_k8_s1_sk1_or_any"), (349, 8, 11136, b"kshare_16x32x64_k8_s1_sk1_or_any"),
+                                        (2, 32, 11120, b"kshare_16x32x64_k8_s1_sk1_or_any"), (3, 104, 5824, b"kshare_16x32x64_k8_s1_sk1_or_any"),
+                                        (1, 24, 304, b"kshare_32x32x64_k4_s2_sk1_or_any"), (92, 72, 296, b"kshare_32x32x64_k4_s2_sk1_or_any")])
+def test_few_tiles_and_a_long_sum_go_to_the_shorter_chain(M, N, K, name):
+    """The model has the two level; by their order in the family they went to tiles of 32 x 32 and four waves, which lost up to 7 % there with the
+    instruction they run since (us, then / since / eight waves: 2 x 32 x 11120 13.7 / 14.6 / 8.8, 3 x 104 x 5824 8.2 / 8.9 / 6.0)."""
+    hw = tf.hw_nominal()
+    with tf.Problem(M, N, K) as p:
+        fam = p.variants()
+        assert fam[tf.proposal(p.desc, hw, fam, [v.id == 0 for v in fam], 0, tf.TF_BN_UNKNOWN)].name == name
 
 
 def test_a_descriptor_with_empty_fields_is_priced():
