@@ -390,7 +390,12 @@ int32_t tf_refine_hint(const tf_report* prev, const tf_report* cand, const tf_hw
  * pick, which needs no measurement. The static pick of a small problem (its family has a variant of
  * kind TF_KIND_MFMA_LDS_ANY) takes operands at any element address and no workspace, so it may run from
  * several streams at once and be captured on its first call; any other static pick may need
- * 16-byte aligned pointers and a workspace, see its descriptor. */
+ * 16-byte aligned pointers and a workspace, see its descriptor. It is the variant with the smallest
+ * predicted time, except that one with K slices gives way to slices summed by a second kernel where
+ * tf_predict_us, which does not know all that these have gained, still leaves them far ahead. Their
+ * workspace is the larger, two to eight times that of the variant with the smallest predicted time,
+ * up to tf_static_scratch_bytes(): a caller that brings a buffer of its own sizes it by the
+ * descriptor of the pick, not by an earlier version's. */
 int32_t tf_proposal(const tf_problem_desc* prob, const tf_hw* hw, const tf_variant_desc* family,
                     int32_t n, const uint8_t* tried, int32_t base_id, int32_t bottleneck);
 
@@ -403,7 +408,9 @@ int32_t tf_proposal_from(const tf_hw* hw, const tf_variant_desc* family, const d
                          int32_t n, const uint8_t* tried, int32_t base_id, int32_t bottleneck);
 
 /* Static cost model behind tf_proposal: predicted time in microseconds of variant v on the
- * problem, from tile shape, wave quantisation and the measured LDS / load-path rates. */
+ * problem, from tile shape, wave quantisation and the measured LDS / load-path rates. (High by 4 us and
+ * more for slices that a second kernel sums: the static pick of tf_proposal makes up for it, later rounds
+ * of the loop go by this figure and measure.) */
 double tf_predict_us(const tf_problem_desc* prob, const tf_hw* hw, const tf_variant_desc* v);
 /* Work-groups of v that fit on one compute unit (registers and LDS), 1..8. */
 int32_t tf_resident_wgs(const tf_hw* hw, const tf_variant_desc* v);

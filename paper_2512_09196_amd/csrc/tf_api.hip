@@ -325,10 +325,10 @@ void build_kshare_family(tf_problem* p, bool rows16) {
 // any-address kernels, and kernels without K slices that hand the calls they cannot take to them: one tile kernel, and
 // those whose waves share K. (The line is
 // a promise kept to those programs, not an optimum.) Measured, us, one-wave kernel / best with K slices / the pick: 256^3
-// 16.3 / none / 3.1, 5 x 11008 x 4096 with B as [N][K] 187 / 19.6 / 16.9, 9 x 2304 x 3776 263 / 8.5 / 10.0, 16 x 576 x 4544 with B
-// as [N][K] 166 / 6.2 / 7.2. Long sums over few columns lose: a CU fetches 60 to 66 GB/s and there are fewer tiles than CUs
-// (7 x 968 x 10752 717 / 9.2 / 22.9; 64 x 256 x 16384 1080 / 9.3 / 34.9; more waves per tile do not help the any-address
-// kernel: 8, 12 and 16 measured). The loop goes on to K slices where they are faster.
+// 9.0 / none / 3.6, 5 x 11008 x 4096 with B as [N][K] 156 / 18.2 / 15.5, 9 x 2304 x 3776 86 / 8.0 / 8.6, 16 x 576 x 4544 with B
+// as [N][K] 123 / 5.9 / 5.3. Long sums over few columns lose: there are fewer tiles than CUs
+// (7 x 968 x 10752 239 / 8.7 / 21.8; 64 x 256 x 16384 385 / 8.7 / 25.3; more waves per tile do not help the any-address
+// kernel, where a CU fetches 60 to 66 GB/s: 8, 12 and 16 measured). The loop goes on to K slices where they are faster.
 void build_small_family(tf_problem* p) {
   const tf_problem_desc& d = p->desc;
   const double flops = 2.0 * d.M * (double)d.N * d.K;

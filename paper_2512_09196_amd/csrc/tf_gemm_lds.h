@@ -1521,8 +1521,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& p_in) {
     const size_t slice = (size_t)p.M * p.N;
     float* wsk = p.ws + (size_t)tc.ks * slice;
     if (!C::FUSED_OK || !p.fused_reduce) {
-      // two-kernel split-K: plain stores; a reduce kernel launched behind this one sums the
-      // slices in slice order and applies the epilogue (the kernel boundary orders the two)
+      // two-kernel split-K: a reduce kernel launched behind this one sums the slices in slice order and applies the
+      // epilogue (the kernel boundary orders the two). Whole tiles go out staged, past the L2s where p.ws_past_l2 says so;
+      // ragged ones, and those of kernels that cannot stage floats (stage_ok), in ordinary stores
       if (C::stage_ok(4) && full && p.ws_vec16) {
         if constexpr (C::stage_ok(4))
           epilogue_staged<C, TF_EPI_NONE_F32, true>(acc, p, smem, m0, n0, tid_out, wave_m, wave_n, wave_k, lane_m, lane_g, (char*)wsk, (size_t)p.N);

@@ -212,8 +212,9 @@ tf::KshareShape tf::kshare_shape(const tf_problem_desc* pr, const tf_hw* hw, con
 // A launch of whole tiles.
 static double kshare_whole_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* v) {
   // Fitted (log error, 12 % rms) to 893 timings of these kernels on 176 problems from 1 x 4096 x 11008 to 2965 x 1104 x 2224
-  // (13 % rms over three thousand timings on 700 others):
-  // a CU fetches the panels of its tiles at 76 to 101 GB/s (rows of 32 columns of a [K][N] B are half a 128-byte line), the
+  // (13 % rms over three thousand timings on 700 others), when these kernels ran MFMAs of 32 x 32 x 16. (With those of 16 x 16 x 32 they take 0.98
+  // of the time in the mean. On 130 problems of any size 292 launches in slices are within 11 % rms; 211 without are predicted 12 % low, 19 % rms.)
+  // A CU fetches the panels of its tiles at 76 to 101 GB/s (rows of 32 columns of a [K][N] B are half a 128-byte line), the
   // L2s together what their tiles need at 7.4 TB/s (the two overlap in part), a launch takes 2.9 us and a further round of
   // work-groups costs 2.3 beside its bytes.
   const int s = at_least(1, v->split_k), lds_whole = v->waves_k * v->stages * (v->bm + v->bn) * 128;
@@ -304,8 +305,10 @@ double tf::base_predict_us(const tf_problem_desc* pr, const tf_hw* hw, const tf_
     return fmax(floor_us / (0.72 * feed), serial_us) + 3.0;
   }
   if (v->kind == TF_KIND_NAIVE) return fmax(flops / (0.004 * hw->bf16_tflops_peak * 1e6), hbm_us) + 2.0;
-  // one wave per tile that gathers element by element: each 16 of K are a dependent trip to memory, about 0.75 us,
-  // however few tiles there are (256^3 16.7 us, 6 x 3008 x 1856 98.6 us, 5 x 11008 x 4096 170 us, 19 x 2432 x 3392 225 us)
+  // one wave per tile that gathers element by element: a chain of trips to memory, 1.2 to 2.3 us for 64 of K, however few tiles there are
+  // (256^3 9.0 us, 6 x 3008 x 1856 43.6, 5 x 11008 x 4096 101 and with B as [N][K] 156, 19 x 2432 x 3392 78.9). The figure below, 3 us, is of the
+  // time when 16 of K were a trip (16.7, 98.6, 170, 225). Nothing hangs on it: where another kernel but the naive one takes the problem and K is 64
+  // or more, it is 1.5 to 8 times as fast as this one is now (18 drawn problems).
   if (v->kind == TF_KIND_MFMA_DIRECT) return fmax(fmax(flops / (0.02 * hw->bf16_tflops_peak * 1e6), hbm_us), 0.75 * (pr->K / 16.0)) + 2.0;
   if (v->kind == TF_KIND_MFMA_ANY) {
     // every tile fetches its row and column panel (mostly from L2): 13 TB/s in tiles of 32, 9.5 in tiles of 64 (two
@@ -581,9 +584,13 @@ static bool second_kernel(const tf_variant_desc* v) {
 // slices, 13 % more at up to 32 rows (fitted to the fastest of 900 drawn problems). Whether there are slices at all, and so a workspace
 // that calls side by side must not share, is left as it was. What has slices anyhow moves where the second kernel is predicted 5 % faster
 // than another tile or streaming kernel, 16 % than one whose waves share K, whose predictions are within 10 % for large tiles
-// and off by up to 20 for small ones; and where its workspace is no larger than the first choice's or the library's own buffer.
+// and off by up to 20 for small ones; and where its workspace is no larger than the first choice's or the library's own buffer
+// (it is two to eight times the first choice's: tf.h says so to callers with a buffer of their own).
 // us, before / after: 170 x 648 x 14936 23.4 / 15.6, 322 x 504 x 7528 with B as [N][K] 17.9 / 12.3, 72 x 1576 x 7032 18.2 / 11.2. Of 900 drawn
-// problems whose pick has slices 107 move, 14 % faster on average; one loses more than 3 (69 x 616 x 16176 [N][K] 3.3).
+// problems whose pick has slices 107 move, 14 % faster on average; one loses more than 3 (69 x 616 x 16176 [N][K] 3.3). That fit was
+// made while partial tiles inside a launch went out non-temporal, which they no longer do (up to 6 % faster, and wrong once in a run of all tests);
+// with both kinds of kernel as they are now 60 other moves take 0.83 of the time, one loses more than 3 % (38 x 1568 x 8192 11.3 / 12.2).
+// It stands here and not in tf_predict_us because what the loop tries after its first round goes by that, and is measured.
 static int with_second_kernel(const tf_problem_desc* pr, const tf_hw* hw, const tf_variant_desc* family, int n, const double* pred,
                               const uint8_t* out, int first) {
   if (pr->op != TF_OP_GEMM_EPILOGUE || family[first].split_k <= 1) return first;
