@@ -39,8 +39,8 @@ struct GemmParams {
   // mixed grid (tf_gemm_mixed_kernel): the first mix_main_wgs work-groups compute BN-wide tiles (tiles_m x tiles_n of them),
   // then tiles_m x mix_tiles work-groups share out the mix_blocks blocks of 32 columns that begin at column mix_n_origin
   int mix_main_wgs, mix_tiles, mix_blocks, mix_n_origin;
-  int ws_past_l2;         // a second kernel sums the slices: partial tiles written and read past the L2s (splitk_past_l2)
   int groups_a, groups_b, ring_stages;   // kernels whose waves share K: eights of rows and of columns of a tile, K tiles in a wave's ring
+  int ws_past_l2;         // a second kernel sums the slices: partial tiles written and read past the L2s (splitk_past_l2)
 };
 
 // One compiled kernel of the LDS-staged MFMA family.
